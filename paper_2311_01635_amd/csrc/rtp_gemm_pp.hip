@@ -22,7 +22,8 @@ hipError_t launch_gemm_pp_tn_f16(const PpGroup &g, unsigned blocks, hipStream_t 
 
 bool gemm_bf16_pp_supported(int layout, const GemmArgs &a)
 {
-    if (a.K < 32 || (a.K & 31)) return false;
+    // a partial last sub-tile is read as zeros past K; fp16 layers are defined on whole sub-tiles only
+    if (a.K <= 0 || (a.elem != ELEM_BF16 && (a.K & 31))) return false;
     if (layout == LAY_TN && a.M < 8) return false;
     if (layout != LAY_NT && a.N < 8) return false;
     // the kernel addresses each operand through a buffer descriptor with 32-bit byte offsets
@@ -83,7 +84,7 @@ static double epilogue_steps(int epi, int c_is_f32)
 static double tile_cost(const GemmArgs &a, int bm, int ksplit, double frac = 1.0, double area = 1.0)
 {
     const double handicap = bm == 256 ? 1.0 : bm == 192 ? 1.04 : 1.12;
-    const int kt = a.K / 32, each = (kt + ksplit - 1) / ksplit;
+    const int kt = (a.K + 31) / 32, each = (kt + ksplit - 1) / ksplit;
     // (an edge tile still fetches whole sub-tiles and passes every barrier: a floor under its loop time)
     const double loop = each * std::max(frac, 0.35);
     return handicap * (bm / 256.0) * (loop + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32));
@@ -123,7 +124,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
     double end = 0.0;
     for (int i = 0; i < count; ++i) {
         const int q = order[i];
-        const int kt = a[q].K / 32, each = (kt + ks[q] - 1) / ks[q], chunks = (kt + each - 1) / each;
+        const int kt = (a[q].K + 31) / 32, each = (kt + ks[q] - 1) / ks[q], chunks = (kt + each - 1) / each;
         const long tm = (a[q].M + bm[q] - 1) / bm[q], tn = tiles_n_of(a[q]);
         const long tiles = tm * tn * chunks;
         const long mine = (tiles + 7) / 8;
@@ -197,7 +198,7 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
         for (int h = 0; h < 3; ++h) {
             if ((forced == 256 || forced == 192 || forced == 128) && forced != heights[h]) continue;
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
-                if (splits[k] > 1 && a[q].K / 32 / splits[k] < 4) break; // keep at least four sub-tiles per chunk
+                if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < 4) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
@@ -284,7 +285,7 @@ hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a_in, int count
         p.tiles_n = tiles_n_of(a[q]);
         p.vec_epilogue = gemm_epilogue_vec_ok(a[q]) ? 1 : 0;
         // as many chunks as are not empty
-        const int kt = a[q].K / 32, each = (kt + pl.ks[q] - 1) / pl.ks[q];
+        const int kt = (a[q].K + 31) / 32, each = (kt + pl.ks[q] - 1) / pl.ks[q];
         p.ksplit = (kt + each - 1) / each;
         if (p.ksplit > 1) p.a.epi = EPI_ACC_ATOMIC;
         per_xcd += (unsigned)(((long)p.tiles_m * p.tiles_n * p.ksplit + 7) / 8);

@@ -59,7 +59,7 @@ constexpr int SYNC_ROWS = 64;
 hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStream_t s);
 // alignment and minimum sizes every bf16 kernel needs (M, N > 0 assumed)
 bool gemm_bf16_args_ok(int layout, const GemmArgs &a);
-// the ping-pong kernel (rtp_gemm_pp.h): needs K % 32 == 0; bm_override 0 = pick the tile height
+// the ping-pong kernel (rtp_gemm_pp.h): any K for bf16, K % 32 == 0 for fp16; bm_override 0 = pick the tile height
 bool gemm_bf16_pp_supported(int layout, const GemmArgs &a);
 hipError_t launch_gemm_bf16_pp(int layout, const GemmArgs &a, int bm_override, hipStream_t s);
 // up to PP_MAX_GROUP independent GEMMs of one layout in a single launch; tile heights, and for an
