@@ -488,33 +488,76 @@ hipError_t launch_scatter_rows(void *out, const void *in, const int *perm, int r
 }
 
 // ---- bias gradient: column sums --------------------------------------------------------------
-// One workgroup per 64 columns: 4 row groups of 64 lanes walk the rows (coalesced 128- or 256-byte
-// row segments), the four partial sums meet in LDS.  Deterministic order; the matrices this runs
-// on ([tokens, shard width]) are small next to the GEMMs of the same step.
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T *Y, int64_t ld, int rows, int cols, const float *in, float *out)
+// out[c] = in[c] + sum over rows of Y[r, c].  Bound: memory latency (the matrix is [tokens, shard width], a few
+// megabytes, and a shard is only some hundred columns wide).  A workgroup of 1024 threads owns 32 columns: VEC
+// columns per thread (16 bytes of a 16-bit matrix where the rows allow it), 32 / VEC threads across, the rest down the
+// rows with four loads in flight each; the row groups' sums meet in LDS in a fixed order, so the result does not
+// depend on timing.  1024 tokens x 384 columns, fp16: 53 us with one 2-byte load in flight per thread and 256 threads
+// on 64 columns; the training step of the unit they belong to went from 1.96 to 1.15 ms.
+constexpr int COLSUM_COLS = 32, COLSUM_THREADS = 1024;
+
+template <typename T, int VEC>
+__global__ __launch_bounds__(COLSUM_THREADS) void colsum_kernel(const T *Y, int64_t ld, int rows, int cols, const float *in, float *out)
 {
-    __shared__ float part[4][64];
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
-    float s = 0.0f;
-    if (c < cols)
-        for (int r = g; r < rows; r += 4) s += (float)Y[(int64_t)r * ld + c];
-    part[g][threadIdx.x & 63] = s;
+    constexpr int TX = COLSUM_COLS / VEC, GROUPS = COLSUM_THREADS / TX, UNROLL = 4;
+    typedef __attribute__((ext_vector_type(VEC))) T vec;
+    __shared__ float part[GROUPS * COLSUM_COLS]; // [group][column]
+    __shared__ float part2[32][COLSUM_COLS];
+    const int tid = threadIdx.x, x = tid % TX, g = tid / TX;
+    const int c = blockIdx.x * COLSUM_COLS + x * VEC;
+    float s[VEC] = {};
+    if (c < cols) { // (VEC > 1: cols is a multiple of VEC)
+        const T *p = Y + c;
+        int r = g;
+        for (; r + (UNROLL - 1) * GROUPS < rows; r += UNROLL * GROUPS) {
+            vec v[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) v[u] = *(const vec *)(p + (int64_t)(r + u * GROUPS) * ld);
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) s[i] += (float)v[u][i];
+        }
+        for (; r < rows; r += GROUPS) {
+            const vec v = *(const vec *)(p + (int64_t)r * ld);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) s[i] += (float)v[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) part[g * COLSUM_COLS + x * VEC + i] = s[i];
     __syncthreads();
-    if (g == 0 && c < cols) out[c] = in[c] + ((part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]));
+    // 32 sums per column, then one
+    const int col = tid & 31, q = tid >> 5;
+    float t = 0.0f;
+    for (int i = q; i < GROUPS; i += 32) t += part[i * COLSUM_COLS + col];
+    part2[q][col] = t;
+    __syncthreads();
+    if (q == 0 && blockIdx.x * COLSUM_COLS + col < cols) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) sum += part2[i][col];
+        const int cc = blockIdx.x * COLSUM_COLS + col;
+        out[cc] = in[cc] + sum;
+    }
 }
 
 hipError_t launch_colsum(int elem, const void *Y, int64_t ld, int rows, int cols, const float *in, float *out, hipStream_t s)
 {
     if (cols <= 0) return hipSuccess;
     if (rows < 0 || !in || !out || (rows > 0 && !Y)) return hipErrorInvalidValue;
-    const dim3 grid((cols + 63) / 64), block(256);
-    if (elem == ELEM_BF16)
-        hipLaunchKernelGGL(colsum_kernel<__bf16>, grid, block, 0, s, (const __bf16 *)Y, ld, rows, cols, in, out);
+    const dim3 grid((cols + COLSUM_COLS - 1) / COLSUM_COLS), block(COLSUM_THREADS);
+    const bool wide = (ld & 7) == 0 && (cols & 7) == 0 && ((uintptr_t)Y & 15) == 0;
+    if (elem == ELEM_BF16 && wide)
+        hipLaunchKernelGGL((colsum_kernel<__bf16, 8>), grid, block, 0, s, (const __bf16 *)Y, ld, rows, cols, in, out);
+    else if (elem == ELEM_BF16)
+        hipLaunchKernelGGL((colsum_kernel<__bf16, 1>), grid, block, 0, s, (const __bf16 *)Y, ld, rows, cols, in, out);
+    else if (elem == ELEM_F16 && wide)
+        hipLaunchKernelGGL((colsum_kernel<_Float16, 8>), grid, block, 0, s, (const _Float16 *)Y, ld, rows, cols, in, out);
     else if (elem == ELEM_F16)
-        hipLaunchKernelGGL(colsum_kernel<_Float16>, grid, block, 0, s, (const _Float16 *)Y, ld, rows, cols, in, out);
+        hipLaunchKernelGGL((colsum_kernel<_Float16, 1>), grid, block, 0, s, (const _Float16 *)Y, ld, rows, cols, in, out);
     else
-        hipLaunchKernelGGL(colsum_kernel<float>, grid, block, 0, s, (const float *)Y, ld, rows, cols, in, out);
+        hipLaunchKernelGGL((colsum_kernel<float, 1>), grid, block, 0, s, (const float *)Y, ld, rows, cols, in, out);
     return hipGetLastError();
 }
 
