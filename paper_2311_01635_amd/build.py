@@ -22,7 +22,7 @@ def _newer(dst, srcs):
 
 def build(force: bool = True, verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    kernel_headers = [os.path.join(CSRC, h) for h in ("rtp_kernels.h", "rtp_gemm_epilogue.h", "rtp_gemm_pp.h")]
+    kernel_headers = [os.path.join(CSRC, h) for h in ("rtp_kernels.h", "rtp_gemm_epilogue.h", "rtp_gemm_pp.h", "rtp_gemm_small.h")]
     host_headers = [os.path.join(CSRC, "rtp_kernels.h"), os.path.join(HERE, "..", "include", "rtp.h")]
 
     def compile_one(src):

@@ -302,8 +302,9 @@ static const Variant kVariants[] = {
     {256, 256, 2, 4, {"gemm_pp_kernel<0, __bf16>", "gemm_pp_kernel<1, __bf16>", "gemm_pp_kernel<2, __bf16>"}},
     {192, 256, 2, 4, {"gemm_pp_kernel<0, __bf16>", "gemm_pp_kernel<1, __bf16>", "gemm_pp_kernel<2, __bf16>"}},
     {128, 256, 2, 4, {"gemm_pp_kernel<0, __bf16>", "gemm_pp_kernel<1, __bf16>", "gemm_pp_kernel<2, __bf16>"}},
+    {64, 128, 2, 2, {"gemm_pp_kernel<0, __bf16>", "gemm_pp_kernel<1, __bf16>", "gemm_pp_kernel<2, __bf16>"}},
 };
-constexpr int kNumVariants = 7;
+constexpr int kNumVariants = 8;
 
 const char *gemm_bf16_kernel_name(int layout, int variant)
 {
@@ -314,9 +315,9 @@ const char *gemm_bf16_kernel_name(int layout, int variant)
 static int pick_variant(int layout, const GemmArgs &a)
 {
     if (a.elem != ELEM_BF16) return 4; // fp16 inputs: only the tiled kernel is built
-    // the ping-pong kernel whenever its shape rules hold and there is at least a tile's worth of work
-    if (gemm_bf16_pp_supported(layout, a) && a.M >= 64 && a.N >= 64) return 4;
-    // the large tile when it yields at least ~one workgroup per CU, else the small one
+    // the ping-pong kernel whenever its operands are within reach of its 32-bit offsets
+    if (gemm_bf16_pp_supported(layout, a)) return 4;
+    // else the large tile when it yields at least ~one workgroup per CU, else the small one
     const int ncols = a.epi == EPI_SWIGLU_FWD ? a.half : a.N;
     const int bn = a.epi == EPI_SWIGLU_FWD ? 128 : 256;
     const long big = (long)((a.M + 255) / 256) * ((ncols + bn - 1) / bn);
@@ -365,10 +366,10 @@ hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStrea
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_bf16_args_ok(layout, a)) return hipErrorInvalidValue;
     if (variant == 0) variant = pick_variant(layout, a);
-    if (a.elem != ELEM_BF16 && (variant < 4 || variant > 7)) return hipErrorInvalidValue; // fp16: tiled kernel only
-    if (variant >= 4 && variant <= 7) {
+    if (a.elem != ELEM_BF16 && (variant < 4 || variant > 8)) return hipErrorInvalidValue; // fp16: tiled kernel only
+    if (variant >= 4 && variant <= 8) {
         if (!gemm_bf16_pp_supported(layout, a)) return hipErrorInvalidValue;
-        const int bm[4] = {0, 256, 192, 128};
+        const int bm[5] = {0, 256, 192, 128, 64};
         return launch_gemm_bf16_pp(layout, a, bm[variant - 4], s);
     }
     switch (variant) {

@@ -79,7 +79,7 @@ constexpr int BUFFER_RSRC_FLAGS = 0x00020000;
 // One GEMM of a group launch and the whole group (a kernel argument, passed by value).
 struct PpProblem {
     GemmArgs a;
-    int bm;               // tile height: 256, 192 or 128
+    int bm;               // tile height: 256, 192 or 128 (tiles 256 wide), or 64 (128 wide, rtp_gemm_small.h)
     int tiles_m, tiles_n;
     int vec_epilogue;
     int ksplit;           // > 1: the K loop is cut into this many chunks, one workgroup each, whose partial
@@ -113,6 +113,11 @@ template <typename V8, int KS, int ROWB> __device__ __forceinline__ V8 frag_mc_r
     u.h[1] = ds_read_tr16_b64<KS * 16 * ROWB + 4 * ROWB>(addr);
     return u.v;
 }
+
+} // namespace rtp
+#include "rtp_gemm_small.h"
+namespace rtp {
+static_assert(pps::RING_BYTES <= pp::SMEM_BYTES && pps::EPI_BYTES + 4 * pps::SUM_BYTES_PER_WAVE <= pp::SMEM_BYTES, "the small tile fits the workgroup's LDS");
 
 // One BM x 256 tile over the K sub-tiles [kt_begin, kt_begin + kt_count): `pid` is the tile's index inside its
 // problem, `smem` the workgroup's LDS.
@@ -476,7 +481,8 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
     const int per_chunk = P.tiles_m * P.tiles_n;
     const int chunk = pid / per_chunk;
     pid -= chunk * per_chunk;
-    const int kt_total = (P.a.K + pp::BK - 1) / pp::BK;
+    const int bk = P.bm == 64 ? pps::BK : pp::BK;
+    const int kt_total = (P.a.K + bk - 1) / bk;
     const int kt_each = (kt_total + P.ksplit - 1) / P.ksplit;
     const int kt_begin = chunk * kt_each;
     const int kt_count = min(kt_each, kt_total - kt_begin);
@@ -484,6 +490,7 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
     switch (P.bm) {
     case 256: pp_tile<LAY, 256, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
     case 192: pp_tile<LAY, 192, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    case 64: pp_small_tile<LAY, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
     default: pp_tile<LAY, 128, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
     }
 }

@@ -48,14 +48,27 @@ static int compute_units()
     return cus;
 }
 
-static int tiles_n_of(const GemmArgs &a)
+// output columns of a tile of height bm (of each half for the paired epilogue)
+static int tile_width(const GemmArgs &a, int bm)
 {
-    const int ncols = a.epi == EPI_SWIGLU_FWD ? a.half : a.N;
-    const int bn = a.epi == EPI_SWIGLU_FWD ? 128 : 256;
+    const int bn = bm == 64 ? pps::BN : pp::BN;
+    return a.epi == EPI_SWIGLU_FWD ? bn / 2 : bn;
+}
+static int tiles_n_of(const GemmArgs &a, int bm)
+{
+    const int ncols = a.epi == EPI_SWIGLU_FWD ? a.half : a.N, bn = tile_width(a, bm);
     return (ncols + bn - 1) / bn;
 }
+// K chunks that are not empty when the K loop of a tile of height bm is cut in `ksplit`; *each: sub-tiles of a chunk
+static int k_chunks(const GemmArgs &a, int bm, int ksplit, int *each)
+{
+    const int bk = bm == 64 ? pps::BK : pp::BK;
+    const int kt = (a.K + bk - 1) / bk;
+    *each = (kt + ksplit - 1) / ksplit;
+    return (kt + *each - 1) / *each;
+}
 
-int gemm_bf16_pp_tiles_n(const GemmArgs &a) { return tiles_n_of(a); }
+int gemm_bf16_pp_tiles_n(const GemmArgs &a) { return tiles_n_of(a, 128); } // (a producer never takes the small tile)
 
 // ---- run-time estimate of a launch ------------------------------------------------------
 // Unit: one K sub-tile (32) of a 256 x 256 tile.  A tile costs its K loop plus its epilogue,
@@ -79,12 +92,20 @@ static double epilogue_steps(int epi, int c_is_f32)
     }
 }
 
+// The small tile: a fixed part (prologue, the K halves' meeting) and a part per 64 K.  Measured one round of it takes
+// 4.5 us + 0.33 us per sub-tile, the 128-high tile 2 us + 0.76 us per 64 K (K = 2048: 13.4 against 26 us while one
+// round holds all tiles, 45 against 32 us for 8192 x 768, where the small tile needs three).
+constexpr double SMALL_FIXED = 3.0, SMALL_STEP = 0.5;
+
 // frac: the share of the K loop's MFMA time an edge tile still needs (1 for an interior tile), area: the share
 // of the tile that exists (scales the epilogue's traffic)
 static double tile_cost(const GemmArgs &a, int bm, int ksplit, double frac = 1.0, double area = 1.0)
 {
+    int each;
+    (void)k_chunks(a, bm, ksplit, &each);
+    if (bm == 64) // 64 x 128, sub-tiles of 64
+        return SMALL_FIXED + SMALL_STEP * each * std::max(frac, 0.7) + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32) / 8.0;
     const double handicap = bm == 256 ? 1.0 : bm == 192 ? 1.04 : 1.12;
-    const int kt = (a.K + 31) / 32, each = (kt + ksplit - 1) / ksplit;
     // (an edge tile still fetches whole sub-tiles and passes every barrier: a floor under its loop time)
     const double loop = each * std::max(frac, 0.35);
     return handicap * (bm / 256.0) * (loop + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32));
@@ -97,12 +118,12 @@ static void edge_shares(const GemmArgs &a, int bm, double *frac_m, double *area_
 {
     const int tm = (a.M + bm - 1) / bm, vr = a.M - (tm - 1) * bm; // valid rows of the last tile row
     const int fm = bm / 64;
-    *frac_m = vr >= bm / 2 ? 1.0 : (double)((vr + 31) / 32) / fm;
+    *frac_m = vr >= bm / 2 || bm == 64 ? 1.0 : (double)((vr + 31) / 32) / fm; // (the small tile skips nothing)
     *area_m = (double)vr / bm;
     const bool paired = a.epi == EPI_SWIGLU_FWD;
-    const int ncols = paired ? a.half : a.N, bn = paired ? 128 : 256;
+    const int ncols = paired ? a.half : a.N, bn = tile_width(a, bm);
     const int tn = (ncols + bn - 1) / bn, vc = ncols - (tn - 1) * bn;
-    *frac_n = paired || vc > 128 ? 1.0 : 0.5;
+    *frac_n = paired || vc > 128 || bm == 64 ? 1.0 : 0.5;
     *area_n = (double)vc / bn;
 }
 
@@ -124,8 +145,9 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
     double end = 0.0;
     for (int i = 0; i < count; ++i) {
         const int q = order[i];
-        const int kt = (a[q].K + 31) / 32, each = (kt + ks[q] - 1) / ks[q], chunks = (kt + each - 1) / each;
-        const long tm = (a[q].M + bm[q] - 1) / bm[q], tn = tiles_n_of(a[q]);
+        int each;
+        const int chunks = k_chunks(a[q], bm[q], ks[q], &each);
+        const long tm = (a[q].M + bm[q] - 1) / bm[q], tn = tiles_n_of(a[q], bm[q]);
         const long tiles = tm * tn * chunks;
         const long mine = (tiles + 7) / 8;
         // interior tiles, then the last tile column, the last tile row and the corner, each with its own cost
@@ -156,7 +178,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
 }
 
 // Heights, K splits and launch order (longest tiles first) of a group.  Every combination is tried
-// (3 heights, and up to 6 split factors for a problem that may be split and is short of tiles);
+// (4 tiles, and up to 6 split factors for a problem that may be split and is short of tiles);
 // the estimate above picks.  Plans are remembered per shape.
 struct PlanKey {
     int layout, count, cu_share;
@@ -184,21 +206,22 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
         auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
-    const int heights[3] = {256, 192, 128};
+    const int heights[4] = {256, 192, 128, 64};
     const int splits[6] = {1, 2, 4, 8, 16, 32};
     const int cus = std::max(8, compute_units() / std::max(1, cu_share));
     const int cus_per_xcd = std::max(1, cus / 8);
     // options per problem
-    int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][18], oks[PP_MAX_GROUP][18];
+    int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][24], oks[PP_MAX_GROUP][24];
     for (int q = 0; q < count; ++q) {
         nopt[q] = 0;
         const int forced = bm_override ? bm_override[q] : 0;
-        const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q]);
+        const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
         const bool split_ok = may_split_k(a[q]) && tiles128 < cus;
-        for (int h = 0; h < 3; ++h) {
-            if ((forced == 256 || forced == 192 || forced == 128) && forced != heights[h]) continue;
+        for (int h = 0; h < 4; ++h) {
+            if (forced != 0 && forced != heights[h]) continue;
+            if (heights[h] == 64 && a[q].sync) continue; // the counters are the tall tiles'
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
-                if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < 4) break; // keep at least four sub-tiles per chunk
+                if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (heights[h] == 64 ? 8 : 4)) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
@@ -282,11 +305,11 @@ hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a_in, int count
         p.a = a[q];
         p.bm = bm[q];
         p.tiles_m = (a[q].M + bm[q] - 1) / bm[q];
-        p.tiles_n = tiles_n_of(a[q]);
+        p.tiles_n = tiles_n_of(a[q], bm[q]);
         p.vec_epilogue = gemm_epilogue_vec_ok(a[q]) ? 1 : 0;
         // as many chunks as are not empty
-        const int kt = (a[q].K + 31) / 32, each = (kt + pl.ks[q] - 1) / pl.ks[q];
-        p.ksplit = (kt + each - 1) / each;
+        int each;
+        p.ksplit = k_chunks(a[q], bm[q], pl.ks[q], &each);
         if (p.ksplit > 1) p.a.epi = EPI_ACC_ATOMIC;
         per_xcd += (unsigned)(((long)p.tiles_m * p.tiles_n * p.ksplit + 7) / 8);
     }

@@ -55,7 +55,7 @@ constexpr int SYNC_ROWS = 64;
 
 // bf16 inputs, fp32 MFMA accumulation.  variant: 0 = pick by shape; 1, 2, 3 = register-staged
 // tiles (256x256/8 waves, 128x128/4 waves, 256x256/4 waves); 4 = the ping-pong kernel with the
-// tile height picked by shape; 5, 6, 7 = the ping-pong kernel with tile height 256, 192, 128.
+// tile height picked by shape; 5, 6, 7, 8 = the ping-pong kernel with tile height 256, 192, 128 (256 wide), 64 (128 wide).
 hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStream_t s);
 // alignment and minimum sizes every bf16 kernel needs (M, N > 0 assumed)
 bool gemm_bf16_args_ok(int layout, const GemmArgs &a);
