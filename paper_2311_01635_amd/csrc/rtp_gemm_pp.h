@@ -1,5 +1,5 @@
 // bf16 / fp16 partition GEMM for gfx950, "ping-pong" form: the kernel the rotated
-// linear layer uses for every shape with a tile's worth of rows and columns.
+// linear layer uses for every shape whose operands its 32-bit offsets reach.
 // (Template; instantiated per operand layout in rtp_gemm_pp_<layout>.hip.)
 //
 // One workgroup of 8 waves owns a BM x 256 tile of C, BM = 256, 192 or 128
@@ -48,11 +48,12 @@
 // handled by clamping the fetched row/column (the clamped results are never
 // stored).  A K that is not a multiple of 32 (a batch of 1990 tokens in a weight
 // gradient, a shard of 688 units in a down projection) leaves one partial
-// sub-tile: it is fetched FIRST, in the prologue, where its lanes past K can be
-// given an offset beyond the operand's descriptor (the load then writes zeros to
-// LDS) without a single instruction added to the loop.  Llama-shaped unit over 16
-// workers, 1990 tokens, training step: 5.66 ms with the register-staged kernel on
-// the four ragged GEMMs of a step, 4.02 ms this way.
+// sub-tile: the prologue fetches it into a stage of its own behind the ring, its
+// lanes past K with an offset beyond the operand's descriptor (the load then
+// writes zeros to LDS), and it is multiplied behind the loop, which holds no
+// instruction for it.  It stays the last one: every tile height, and the
+// register-staged kernel, add up the products of an element in the order of K and
+// give the same bits.
 #pragma once
 #include "rtp_gemm_epilogue.h"
 #include <type_traits>
@@ -66,7 +67,8 @@ constexpr int WM = 2, WN = 4, NTHR = 512;
 constexpr int FN = BN / (WN * 32);   // 2 fragments of 32 columns per wave
 constexpr int B_BYTES = BN * BK * 2; // 16 KB of B per stage
 constexpr int STAGES = 4; // deeper rings (5 or 6 stages fit the 160 KB LDS) measured no faster
-constexpr int RING_BYTES = STAGES * (256 * BK * 2 + B_BYTES); // the tallest tile's ring: 128 KB
+// the tallest tile's ring (128 KB), and a stage behind it for a partial last sub-tile
+constexpr int RING_BYTES = (STAGES + 1) * (256 * BK * 2 + B_BYTES);
 // the epilogue reuses the ring: per wave, one parked fragment row and the landing area of its fp32 reads (136 KB)
 constexpr int EPI_BYTES = NTHR / 64 * (EPI_LDS_BYTES_PER_WAVE + EPI_LAND_BYTES_PER_WAVE);
 constexpr int SMEM_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
@@ -137,7 +139,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
     constexpr int A_PW = (A_PIECES + 7) / 8; // ... per wave (the second one only on waves 0-3 when BM = 192)
     constexpr int A_CPR = BM / 8;            // 16-byte chunks per K-row of an M-contiguous A stage
     constexpr int A_ROWB = BM * 2;           // bytes per K-row of an M-contiguous A stage
-    static_assert(STAGES * STAGE <= SMEM_BYTES, "ring fits the workgroup's LDS");
+    static_assert((STAGES + 1) * STAGE <= SMEM_BYTES, "ring and partial sub-tile fit the workgroup's LDS");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -240,15 +242,14 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)p.B, 0, b_bytes, BUFFER_RSRC_FLAGS);
     const int stepA = A_KC ? BK * 2 : (int)(BK * p.lda * 2);
     const int stepB = B_KC ? BK * 2 : (int)(BK * p.ldb * 2);
-    const int KT = kt_count;
-    // 1 when the last sub-tile of this chunk is cut short by K: it then comes first, the others follow in order
+    // 1 when the last sub-tile of this chunk is cut short by K: the loop runs over the KT whole ones
     // (read through readfirstlane: the sub-tile index feeds the loads' scalar offsets)
-    const int tail = __builtin_amdgcn_readfirstlane((kt_begin + KT) * BK > K ? 1 : 0);
-    const int kt_first = kt_begin - tail;
+    const int tail = __builtin_amdgcn_readfirstlane((kt_begin + kt_count) * BK > K ? 1 : 0);
+    const int KT = kt_count - tail;
 
     auto issue = [&](int kt) {
-        const int kk = max(kt_first + min(kt, KT - 1), 0); // past the end: refetch a sub-tile into a stage nobody reads
-        char *st = smem + (kt % STAGES) * STAGE;
+        const int kk = max(kt_begin + min(kt, KT - 1), 0); // past the end: refetch a sub-tile into a stage nobody reads
+        char *st = smem + ((unsigned)kt % STAGES) * STAGE;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + wave * 1024), 16, oa[0], kk * stepA, 0, 0);
         if (A_PW == 2 && a_pieces_mine == 2)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + (wave + 8) * 1024), 16, oa[A_PW - 1], kk * stepA, 0, 0);
@@ -256,30 +257,29 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
         for (int i = 0; i < 2; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_vp)(st + A_BYTES + (2 * wave + i) * 1024), 16, ob[i], kk * stepB, 0, 0);
     };
-    // the partial sub-tile into stage 0: chunks (K-contiguous operand) or K-rows past K read as zero
+    // the partial sub-tile into the stage behind the ring: chunks (K-contiguous operand) or K-rows past K read as zero
     auto issue_tail = [&]() {
-        const int kk = kt_begin + KT - 1, k0 = kk * BK;
+        const int kk = kt_begin + KT, k0 = kk * BK;
         constexpr unsigned PAST = 0x80000000u; // beyond every operand's byte range
-        auto kc_chunk = [&](int j) { const int row = 16 * j + (lane >> 2); return (lane & 3) ^ ((row >> 2) & 3); };
+        const int kc_k = ((lane & 3) ^ ((lane >> 4) & 3)) * 8; // K index of this lane's chunk: (row >> 2) & 3 == (lane >> 4) & 3
+        char *st = smem + STAGES * STAGE;
         unsigned ta[A_PW], tb[2];
 #pragma unroll
         for (int i = 0; i < A_PW; ++i) {
-            const int j = min(wave + 8 * i, A_PIECES - 1);
-            const int k = k0 + (A_KC ? kc_chunk(j) * 8 : (64 * j + lane) / A_CPR);
+            const int k = k0 + (A_KC ? kc_k : (64 * min(wave + 8 * i, A_PIECES - 1) + lane) / A_CPR);
             ta[i] = k < K ? oa[i] + (unsigned)(kk * stepA) : PAST;
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int j = 2 * wave + i;
-            const int k = k0 + (B_KC ? kc_chunk(j) * 8 : 2 * j + (lane >> 5));
+            const int k = k0 + (B_KC ? kc_k : 2 * (2 * wave + i) + (lane >> 5));
             tb[i] = k < K ? ob[i] + (unsigned)(kk * stepB) : PAST;
         }
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(smem + wave * 1024), 16, ta[0], 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + wave * 1024), 16, ta[0], 0, 0, 0);
         if (A_PW == 2 && a_pieces_mine == 2)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(smem + (wave + 8) * 1024), 16, ta[A_PW - 1], 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + (wave + 8) * 1024), 16, ta[A_PW - 1], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_vp)(smem + A_BYTES + (2 * wave + i) * 1024), 16, tb[i], 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_vp)(st + A_BYTES + (2 * wave + i) * 1024), 16, tb[i], 0, 0, 0);
     };
     // ends a slot: all but this wave's PF-1 newest sub-tiles of direct loads have landed, its LDS
     // reads have returned, and everybody is here
@@ -342,12 +342,9 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
                 acc[i][j][v] = 0.0f;
 
     // ---- prologue: PF sub-tiles in flight, the first one landed -------------------------
-    if (tail)
-        issue_tail();
-    else
-        issue(0);
+    if (tail) issue_tail();
 #pragma unroll
-    for (int i = 1; i < PF; ++i) issue(i);
+    for (int i = 0; i < PF; ++i) issue(i);
     end_slot_after_loads();
     if (group == 1) asm volatile("s_barrier" ::: "memory"); // start one slot late
 
@@ -372,9 +369,8 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
 #pragma unroll
             for (int f = 0; f < FN; ++f) bf[0][f] = bf[1][f] = frag8{};
         }
-        for (int kt = 0; kt < KT; ++kt) {
+        auto step = [&](const unsigned stage_off, const int kt, auto issues) __attribute__((always_inline)) {
             // ---- memory slot ------------------------------------------------------------------
-            const unsigned stage_off = (unsigned)((kt % STAGES) * STAGE);
             const char *sa = smem + stage_off;
             const char *sb = sa + A_BYTES;
 #pragma unroll
@@ -399,7 +395,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
                     bf[1][f] = frag_mc_read<frag8, 1, 512>(b_tr[f] + stage_off);
                 }
             }
-            issue(kt + PF);
+            if constexpr (decltype(issues)::value) issue(kt + PF);
             // own loads of sub-tile kt+1 have landed, fragments are in registers
             end_slot_after_loads();
             __builtin_amdgcn_sched_barrier(0); // nothing may drift across a slot boundary
@@ -429,7 +425,9 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_barrier" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-        }
+        };
+        for (int kt = 0; kt < KT; ++kt) step(((unsigned)kt % STAGES) * STAGE, kt, std::true_type{});
+        if (tail) step(STAGES * STAGE, 0, std::false_type{}); // the partial sub-tile, last in the order of K
     };
     if (interior)
         k_loop(std::true_type{});
