@@ -119,7 +119,7 @@ template <typename V8, int KS, int ROWB> __device__ __forceinline__ V8 frag_mc_r
 } // namespace rtp
 #include "rtp_gemm_small.h"
 namespace rtp {
-static_assert(pps::RING_BYTES <= pp::SMEM_BYTES && pps::EPI_BYTES + 4 * pps::SUM_BYTES_PER_WAVE <= pp::SMEM_BYTES, "the small tile fits the workgroup's LDS");
+static_assert(pps::RING_BYTES <= pp::SMEM_BYTES && pps::EPI_BYTES <= pp::SMEM_BYTES, "the small tile fits the workgroup's LDS");
 
 // One BM x 256 tile over the K sub-tiles [kt_begin, kt_begin + kt_count): `pid` is the tile's index inside its
 // problem, `smem` the workgroup's LDS.

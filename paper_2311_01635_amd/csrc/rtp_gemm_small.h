@@ -6,10 +6,14 @@
 // L2 -> LDS path (24 KB per step for 256 cycles of MFMA).  Hence
 //  * sub-tiles of 64 K, five LDS stages (120 KB), four of them in flight: twice the bytes in flight per flop of the
 //    tall tile's ring;
-//  * the eight waves are a 2 x 2 grid of 32 x 64 wave tiles times TWO halves of every sub-tile's K: a wave keeps the
-//    tall tile's fragment shape (one LDS read feeds two MFMAs) and the epilogues apply unchanged; the halves' sums
-//    meet once, in LDS, in a fixed order;
+//  * waves 4-7 fetch, waves 0-3, one per SIMD, multiply: a 2 x 2 grid of 32 x 64 wave tiles with the tall tile's
+//    fragment shape (three LDS reads feed two MFMAs), to which the epilogues apply unchanged.  An element is summed
+//    by one wave in the order of K, so its bits are those of the tall tiles, whichever the planner picks;
 //  * fragments of sub-tile t + 1 are read while the MFMAs of sub-tile t run; one barrier per sub-tile.
+// us per launch, as a layer's step runs them: all eight waves fetching and multiplying, each one half of a sub-tile's K
+// (two sums per element, joined at the end), 200 x 768 x 2048 13.3, 512 x 2752 x 4096 23.5, 1024 x 384 x 768 8.1,
+// 2048 x 1792 x 8192 84.5; eight waves of one 32 x 32 fragment each 14.2, 24.9, 8.3, 91.9; this split 11.1, 21.0,
+// 7.2, 75.2.
 // LDS layout: K-contiguous operands as 128-byte rows with the 16-byte chunk index xor-ed with (row/2)%8, M- or
 // N-contiguous ones as K-rows of 128 (A) or 256 bytes (B) with the chunk index xor-ed with 4*((k/2)%2) or 4*(k%4):
 // every fragment read then touches each of the 64 banks once per half-wave.
@@ -17,6 +21,7 @@
 // and read as zeros without touching memory.
 #pragma once
 #include "rtp_gemm_epilogue.h"
+#include <type_traits>
 
 namespace rtp {
 
@@ -26,10 +31,8 @@ constexpr int WM = 2, WN = 2, FN = 2;
 constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
 constexpr int STAGES = 5;
 constexpr int RING_BYTES = STAGES * STAGE;
-constexpr int LOADS = 3; // direct loads per wave and sub-tile: 1 KB of A, 2 KB of B
-// after the ring: four waves' staged epilogue, then the other four waves' sums
-constexpr int EPI_BYTES = 4 * (EPI_LDS_BYTES_PER_WAVE + EPI_LAND_BYTES_PER_WAVE);
-constexpr int SUM_BYTES_PER_WAVE = 64 * 32 * 4;
+constexpr int LOADS = 6; // direct loads per fetching wave and sub-tile: 2 KB of A, 4 KB of B
+constexpr int EPI_BYTES = 4 * (EPI_LDS_BYTES_PER_WAVE + EPI_LAND_BYTES_PER_WAVE); // after the ring: four waves' staged epilogue
 } // namespace pps
 
 template <int LAY, typename E>
@@ -42,7 +45,7 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
     constexpr bool A_KC = (LAY != LAY_TN), B_KC = (LAY == LAY_NT);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1; // K half, place in the 2 x 2 grid
+    const int wm = (wave >> 1) & 1, wn = wave & 1; // place of a multiplying wave in the 2 x 2 grid
 
     constexpr int GROUP_M = 4; // 4-tall column strips, as the tall tiles
     const int group_sz = GROUP_M * tiles_n;
@@ -53,21 +56,26 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
     const int m0 = tm * BM, n0 = paired ? tn * (BN / 2) : tn * BN;
     const int M = p.M, N = p.N, K = p.K, half = p.half;
 
-    // ---- direct loads: this lane's byte offset in sub-tile 0 and its K index there ----------------
-    unsigned oa, ob[2];
-    int ka, kb[2];
-    if (A_KC) {
-        const int row = 8 * wave + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-        ka = c * 8;
-        oa = (unsigned)(((int64_t)min(m0 + row, M - 1) * p.lda + c * 8) * 2);
-    } else {
-        const int kr = 8 * wave + (lane >> 3), c = (lane & 7) ^ (4 * ((kr >> 1) & 1));
-        ka = kr;
-        oa = (unsigned)(((int64_t)kr * p.lda + min(m0 + c * 8, M - 8)) * 2);
-    }
+    // ---- direct loads (waves 4-7): this lane's byte offsets in sub-tile 0 and its K indices there ----------------
+    unsigned oa[2], ob[4];
+    int ka[2], kb[4];
+    const int lw = wave & 3;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int j = 2 * wave + i;
+        const int j = 2 * lw + i;
+        if (A_KC) {
+            const int row = 8 * j + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+            ka[i] = c * 8;
+            oa[i] = (unsigned)(((int64_t)min(m0 + row, M - 1) * p.lda + c * 8) * 2);
+        } else {
+            const int kr = 8 * j + (lane >> 3), c = (lane & 7) ^ (4 * ((kr >> 1) & 1));
+            ka[i] = kr;
+            oa[i] = (unsigned)(((int64_t)kr * p.lda + min(m0 + c * 8, M - 8)) * 2);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = 4 * lw + i;
         if (B_KC) {
             const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
             const int row = paired ? (r < BN / 2 ? min(n0 + r, half - 1) : half + min(n0 + r - BN / 2, half - 1)) : min(n0 + r, N - 1);
@@ -92,59 +100,62 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
     auto issue = [&](int kt, int stage) {
         const int kk = kt_begin + kt, k0 = kk * BK;
         char *st = smem + stage * STAGE;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + wave * 1024), 16, k0 + ka < k_end ? oa + kk * stepA : PAST, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_vp)(st + A_BYTES + (2 * wave + i) * 1024), 16,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_vp)(st + (2 * lw + i) * 1024), 16,
+                                                     k0 + ka[i] < k_end ? oa[i] + kk * stepA : PAST, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_vp)(st + A_BYTES + (4 * lw + i) * 1024), 16,
                                                      k0 + kb[i] < k_end ? ob[i] + kk * stepB : PAST, 0, 0, 0);
     };
 
-    // ---- fragment addresses (LDS byte addresses of stage 0; the wave's K half is folded in) ----------------
+    // ---- fragment addresses (LDS byte addresses of stage 0) ----------------
     const unsigned smem_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)smem;
     const int q = lane >> 4, i16 = lane & 15;
     unsigned fa, fb[FN];
     if (A_KC) {
         const int row = wm * 32 + (lane & 31);
         fa = row * 128 + (((lane >> 5) ^ ((row >> 1) & 7)) << 4);
-        fa ^= kh << 6;
     } else {
         const int col = wm * 32 + (q & 1) * 16 + (i16 & 3) * 4, kr = (q >> 1) * 8 + (i16 >> 2);
-        fa = kr * 128 + (((col >> 3) ^ (4 * ((kr >> 1) & 1))) << 4) + (col & 7) * 2 + kh * 32 * 128;
+        fa = kr * 128 + (((col >> 3) ^ (4 * ((kr >> 1) & 1))) << 4) + (col & 7) * 2;
     }
 #pragma unroll
-    for (int f = 0; f < FN; ++f) {
-        const int rbase = f * (WN * 32) + wn * 32;
+    for (int j = 0; j < FN; ++j) {
+        const int rbase = j * (WN * 32) + wn * 32;
         if (B_KC) {
             const int row = rbase + (lane & 31);
-            fb[f] = row * 128 + (((lane >> 5) ^ ((row >> 1) & 7)) << 4);
-            fb[f] ^= kh << 6;
+            fb[j] = row * 128 + (((lane >> 5) ^ ((row >> 1) & 7)) << 4);
         } else {
             const int col = rbase + (q & 1) * 16 + (i16 & 3) * 4, kr = (q >> 1) * 8 + (i16 >> 2);
-            fb[f] = kr * 256 + (((col >> 3) ^ (4 * (kr & 3))) << 4) + (col & 7) * 2 + kh * 32 * 256;
+            fb[j] = kr * 256 + (((col >> 3) ^ (4 * (kr & 3))) << 4) + (col & 7) * 2;
         }
     }
+    constexpr int KS = BK / 16; // MFMA steps of a sub-tile
     struct Frags {
-        frag8 a[2], b[2][FN];
+        frag8 a[KS], b[KS][FN];
     };
     auto read = [&](int stage, Frags &f) {
         const unsigned so = stage * STAGE;
-        if (A_KC) {
-            f.a[0] = *(const frag8 *)(smem + so + fa);
-            f.a[1] = *(const frag8 *)(smem + so + (fa ^ 32));
-        } else {
-            f.a[0] = frag_mc_read<frag8, 0, 128>(smem_lds + so + fa);
-            f.a[1] = frag_mc_read<frag8, 1, 128>(smem_lds + so + fa);
-        }
+        auto one = [&](auto ks_) {
+            constexpr int ks = decltype(ks_)::value;
+            if (A_KC)
+                f.a[ks] = *(const frag8 *)(smem + so + (fa ^ (ks << 5)));
+            else
+                f.a[ks] = frag_mc_read<frag8, ks, 128>(smem_lds + so + fa);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            if (B_KC) {
-                f.b[0][j] = *(const frag8 *)(smem + so + A_BYTES + fb[j]);
-                f.b[1][j] = *(const frag8 *)(smem + so + A_BYTES + (fb[j] ^ 32));
-            } else {
-                f.b[0][j] = frag_mc_read<frag8, 0, 256>(smem_lds + so + A_BYTES + fb[j]);
-                f.b[1][j] = frag_mc_read<frag8, 1, 256>(smem_lds + so + A_BYTES + fb[j]);
+            for (int j = 0; j < FN; ++j) {
+                if (B_KC)
+                    f.b[ks][j] = *(const frag8 *)(smem + so + A_BYTES + (fb[j] ^ (ks << 5)));
+                else
+                    f.b[ks][j] = frag_mc_read<frag8, ks, 256>(smem_lds + so + A_BYTES + fb[j]);
             }
-        }
+        };
+        one(std::integral_constant<int, 0>{});
+        one(std::integral_constant<int, 1>{});
+        one(std::integral_constant<int, 2>{});
+        one(std::integral_constant<int, 3>{});
     };
 
     f32x16 acc[1][FN];
@@ -154,66 +165,54 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
         for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.0f;
     auto multiply = [&](const Frags &f) {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[0][j] = mfma_32x32x16(f.a[ks], f.b[ks][j], acc[0][j]);
     };
 
-    // A step ends with this wave's reads in registers, so that behind the barrier the stage they came from may be
-    // overwritten; the barrier itself follows the landing of the sub-tile that is read next (LEFT newer ones may
-    // still be on their way).
-    static_assert((STAGES - 2) * LOADS < 64, "vmcnt is a 6-bit counter");
-    int st = 0; // stage of sub-tile kt
-    auto step = [&](int kt, const Frags &cur, Frags &nxt) {
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 2) * LOADS) : "memory"); // sub-tile kt + 1 has landed
+    // One barrier per step kt: before it the fetching waves have seen sub-tile kt + 1 land and the multiplying waves
+    // hold sub-tile kt in registers; behind it kt + 1 may be read and the stage of kt be overwritten.
+    static_assert((STAGES - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
+    const int steps = kt_count & ~1; // taken in pairs; an odd last sub-tile needs no barrier of its own
+    int st = 0;                      // stage of sub-tile kt
+    if (wave >= 4) {
+#pragma unroll
+        for (int i = 0; i < STAGES; ++i) issue(i, i);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LOADS) : "memory"); // sub-tile 0 has landed
+        for (int kt = 0; kt < steps; ++kt) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 2) * LOADS) : "memory");
+            issue(kt + STAGES, st);
+            st = st + 1 == STAGES ? 0 : st + 1;
+        }
+        // what was issued past the end lands before the epilogue takes the ring's LDS
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        return;
+    }
+    Frags f0, f1;
+    auto read_next = [&](Frags &nxt) {
+        asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        issue(kt + STAGES, st); // sub-tile kt was in registers before the barrier
-        st = st + 1 == STAGES ? 0 : st + 1;
         read(st, nxt);
-        multiply(cur);
+        st = st + 1 == STAGES ? 0 : st + 1;
+    };
+    auto in_registers = [&]() {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
-
-#pragma unroll
-    for (int i = 0; i < STAGES; ++i) issue(i, i);
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LOADS) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    Frags f0, f1;
-    read(0, f0);
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    int kt = 0;
-    for (; kt + 1 < kt_count; kt += 2) {
-        step(kt, f0, f1);
-        step(kt + 1, f1, f0);
+    read_next(f0);
+    in_registers();
+    for (int kt = 0; kt < steps; kt += 2) {
+        read_next(f1);
+        multiply(f0);
+        in_registers();
+        read_next(f0);
+        multiply(f1);
+        in_registers();
     }
-    if (kt < kt_count) multiply(f0);
-    // what was issued past the end lands before the ring is reused
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (kt_count & 1) multiply(f0);
+    asm volatile("s_barrier" ::: "memory");
 
-    // ---- the two K halves' sums meet: the second half's waves park theirs, the first half's add them ----------------
-    f32x4 *sums = (f32x4 *)(smem + EPI_BYTES + (wave & 3) * SUM_BYTES_PER_WAVE);
-    if (kh == 1)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                f32x4 t;
-                t.x = acc[0][j][4 * v]; t.y = acc[0][j][4 * v + 1]; t.z = acc[0][j][4 * v + 2]; t.w = acc[0][j][4 * v + 3];
-                sums[(j * 4 + v) * 64 + lane] = t;
-            }
-    __syncthreads();
-    if (kh == 1) return;
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const f32x4 t = sums[(j * 4 + v) * 64 + lane];
-            acc[0][j][4 * v] += t.x; acc[0][j][4 * v + 1] += t.y; acc[0][j][4 * v + 2] += t.z; acc[0][j][4 * v + 3] += t.w;
-        }
     if (vec_epilogue)
         gemm_epilogue_staged<E, 1, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * 32, n0, wn * 32, lane,
                                                 smem + 4 * EPI_LDS_BYTES_PER_WAVE + wave * EPI_LAND_BYTES_PER_WAVE);

@@ -39,17 +39,17 @@ def test_partial_sub_tile(layout, variant):
 
 @pytest.mark.parametrize("layout", [B.LAYOUT_NT, B.LAYOUT_NN, B.LAYOUT_TN])
 def test_every_tile_adds_up_in_the_order_of_k(layout):
-    """Which tile runs a problem is the planner's choice and must not show in the result: the tall tiles (5, 6, 7) give
-    the bits of the register-staged kernel (2), partial sub-tile or not."""
+    """Which tile runs a problem is the planner's choice and must not show in the result: the tall tiles (5, 6, 7)
+    and the 64 x 128 one (8) give the bits of the register-staged kernel (2), partial sub-tile or not."""
     for M, N, K in SHAPES + ODD[layout] + [(136, 264, 32), (136, 264, 72), (136, 264, 104), (136, 264, 136), (136, 264, 1992)]:
         g = torch.Generator(device=DEV).manual_seed(M + N + K)
         sa, sb = {B.LAYOUT_NT: ((M, K), (N, K)), B.LAYOUT_NN: ((M, K), (K, N)), B.LAYOUT_TN: ((K, M), (K, N))}[layout]
         a, b = (torch.randn(*s, generator=g, device=DEV).bfloat16() for s in (sa, sb))
         out = {}
-        for variant in (2, 5, 6, 7):
+        for variant in (2, 5, 6, 7, 8):
             print(f"gemm layout={layout} variant={variant} M={M} N={N} K={K}", flush=True)
             out[variant] = torch.empty(M, N, device=DEV, dtype=torch.float32)
             B.rtp_gemm(layout, B.RTP_BF16, B.RTP_F32, False, a, sa[1], b, sb[1], out[variant], N, M, N, K, variant)
             torch.cuda.synchronize()
-        for variant in (5, 6, 7):
+        for variant in (5, 6, 7, 8):
             assert torch.equal(out[variant], out[2]), (variant, M, N, K)

@@ -1,4 +1,4 @@
-"""The 64 x 128 tile (two K halves per workgroup) at the edges of its tiles and sub-tiles, against the oracle."""
+"""The 64 x 128 tile (four waves fetch, four multiply) at the edges of its tiles and sub-tiles, against the oracle."""
 import numpy as np
 import pytest
 import torch
