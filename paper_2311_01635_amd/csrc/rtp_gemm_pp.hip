@@ -129,10 +129,13 @@ static void edge_shares(const GemmArgs &a, int bm, double *frac_m, double *area_
 
 // A problem may have its K loop cut into chunks when its result is an fp32 sum onto an accumulator
 // (the chunks' partial sums are added atomically) and it is short of tiles: the weight-gradient
-// GEMM of a narrow shard contracts over all T tokens into an output of a few tiles.
+// GEMM of a narrow shard contracts over all T tokens into an output of a few tiles.  The order of those adds is not
+// fixed, so such a result does not repeat bit for bit.  Only whole sub-tiles and outputs of at least 64 x 64 are split:
+// a batch of any other number of tokens, and a narrower shard, give the same gradients on every run.
 static bool may_split_k(const GemmArgs &a)
 {
     if (a.sync) return false; // the counters count whole tiles
+    if ((a.K & 31) || a.M < 64 || a.N < 64) return false;
     return a.epi == EPI_ACC_ADD && a.c_is_f32 && a.C == (void *)a.ws && a.ldc == a.ldws;
 }
 
@@ -210,6 +213,14 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
     const int splits[6] = {1, 2, 4, 8, 16, 32};
     const int cus = std::max(8, compute_units() / std::max(1, cu_share));
     const int cus_per_xcd = std::max(1, cus / 8);
+    // A launch that shares the machine (cu_share > 1) seldom gets exactly its share: its partner on the other
+    // stream may be a GEMM of a hundred tiles, or done already.  The estimate is the mean of the two ends, its
+    // share of the compute units and all of them, which is what the in-situ sweeps of the tile heights favour
+    // (a 96-tile GEMM planned for half the machine kept its 256-high tiles and left compute units idle).
+    auto estimate = [&](const GemmArgs *p, const int *bm, const int *ks, const int *order, int n) {
+        const double t = makespan(p, bm, ks, order, n, cus_per_xcd);
+        return cu_share > 1 ? 0.5 * (t + makespan(p, bm, ks, order, n, std::max(1, compute_units() / 8))) : t;
+    };
     // options per problem
     int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][24], oks[PP_MAX_GROUP][24];
     for (int q = 0; q < count; ++q) {
@@ -217,14 +228,21 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
         const int forced = bm_override ? bm_override[q] : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
         const bool split_ok = may_split_k(a[q]) && tiles128 < cus;
+        bool tall_split = false; // the best plan of the tall tiles alone is a split one: only then may the small tile be split
+        double tall_best = 1e300;
         for (int h = 0; h < 4; ++h) {
             if (forced != 0 && forced != heights[h]) continue;
             if (heights[h] == 64 && a[q].sync) continue; // the counters are the tall tiles'
-            for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
+            for (int k = 0; k < (split_ok && (heights[h] != 64 || tall_split || forced == 64) ? 6 : 1); ++k) {
                 if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (heights[h] == 64 ? 8 : 4)) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
+                if (split_ok && heights[h] != 64) {
+                    const int zero = 0;
+                    const double t = estimate(a + q, heights + h, splits + k, &zero, 1);
+                    if (t < tall_best - 1e-9) tall_best = t, tall_split = splits[k] > 1;
+                }
             }
         }
     }
@@ -244,12 +262,7 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
         if (!ordered)
             std::stable_sort(order, order + count,
                              [&](int i, int j) { return tile_cost(a[i], bm[i], ks[i]) > tile_cost(a[j], bm[j], ks[j]); });
-        // A launch that shares the machine (cu_share > 1) seldom gets exactly its share: its partner on the other
-        // stream may be a GEMM of a hundred tiles, or done already.  The estimate is the mean of the two ends, its
-        // share of the compute units and all of them, which is what the in-situ sweeps of the tile heights favour
-        // (a 96-tile GEMM planned for half the machine kept its 256-high tiles and left compute units idle).
-        double t = makespan(a, bm, ks, order, count, cus_per_xcd);
-        if (cu_share > 1) t = 0.5 * (t + makespan(a, bm, ks, order, count, std::max(1, compute_units() / 8)));
+        const double t = estimate(a, bm, ks, order, count);
         if (t < best - 1e-9) {
             best = t;
             for (int q = 0; q < count; ++q) {

@@ -1,0 +1,40 @@
+"""The GEMM launcher behind the layers, which the C ABI does not expose: its argument block and two of its entry points,
+so that a test can ask which tile a shape gets and run an epilogue on a chosen kernel."""
+import ctypes as C
+
+from paper_2311_01635_amd import binding as B
+
+EPI_STORE, EPI_ACC_FIRST, EPI_ACC_ADD, EPI_ACC_LAST = 0, 1, 2, 3
+EPI_GELU_ERF_FWD, EPI_GELU_TANH_FWD, EPI_SWIGLU_FWD = 4, 5, 6
+EPI_GELU_ERF_BWD, EPI_GELU_TANH_BWD, EPI_SWIGLU_BWD = 7, 8, 9
+ELEM = {"bf16": 0, "f16": 1}
+
+
+class GemmArgs(C.Structure):
+    _fields_ = [("A", C.c_void_p), ("B", C.c_void_p), ("lda", C.c_int64), ("ldb", C.c_int64), ("M", C.c_int), ("N", C.c_int),
+                ("K", C.c_int), ("epi", C.c_int), ("C", C.c_void_p), ("ldc", C.c_int64), ("ws", C.c_void_p), ("ldws", C.c_int64),
+                ("aux", C.c_void_p), ("ldaux", C.c_int64), ("bias", C.c_void_p), ("half", C.c_int), ("c_is_f32", C.c_int),
+                ("elem", C.c_int), ("cu_share", C.c_int), ("sync", C.c_void_p), ("sync_signal", C.c_int), ("sync_wait", C.c_int)]
+
+
+_plan = getattr(B.lib, "_ZN3rtp17gemm_bf16_pp_planEiPKNS_8GemmArgsEiPKiPiS5_")
+_plan.restype = None
+_plan.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+_launch = getattr(B.lib, "_ZN3rtp16launch_gemm_bf16EiRKNS_8GemmArgsEiP12ihipStream_t")
+_launch.restype = C.c_int
+_launch.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.c_void_p]
+
+
+def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_share=1, force=0):
+    """(tile height, K split) the launcher picks for one GEMM.  Needs no GPU: an fp32 sum lives at a made-up address."""
+    a = GemmArgs(M=M, N=N, K=K, epi=epi, half=half, c_is_f32=int(f32), elem=ELEM[dtype], cu_share=cu_share, C=0x1000, ldc=N)
+    if epi in (EPI_ACC_FIRST, EPI_ACC_ADD):
+        a.ws, a.ldws, a.c_is_f32 = 0x1000, N, 1
+    bm, ks = C.c_int(0), C.c_int(0)
+    _plan(layout, C.byref(a), 1, C.byref(C.c_int(force)), C.byref(bm), C.byref(ks))
+    return bm.value, ks.value
+
+
+def launch(layout, args, variant, stream=None):
+    """launch_gemm_bf16 with the given arguments on kernel `variant`; the HIP status."""
+    return _launch(layout, C.byref(args), variant, stream)

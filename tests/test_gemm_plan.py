@@ -1,0 +1,21 @@
+"""Which tile, and how many chunks of K, the launcher picks for a shape (needs no GPU)."""
+import pytest
+
+import gemm_internal as G
+from paper_2311_01635_amd import binding as B
+
+
+@pytest.mark.parametrize("cu_share", [1, 2])
+def test_gradients_of_a_ragged_batch_or_a_narrow_shard_are_not_split(cu_share):
+    """The chunks of a split sum meet through atomic adds and do not repeat bit for bit: only sums over whole sub-tiles
+    into outputs of at least 64 x 64 may be split, and only where the tall tiles alone would be."""
+    for K in (200, 301, 1000, 1990, 5000):
+        assert K % 32
+        for M, N in ((384, 768), (128, 264), (688, 4096), (64, 64), (32, 768)):
+            assert G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=cu_share)[1] == 1, (M, N, K)
+    for M, N in ((16, 768), (56, 4096), (768, 16), (768, 56)):
+        for K in (256, 1024, 8192):
+            assert G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=cu_share)[1] == 1, (M, N, K)
+    for M, N, K in ((64, 1376, 1024), (96, 1376, 1024), (128, 1376, 512)):
+        assert G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=cu_share)[1] == 1, (M, N, K)
+    assert G.plan(B.LAYOUT_TN, 384, 768, 8192, G.EPI_ACC_ADD, cu_share=cu_share)[1] > 1, "a narrow shard's long sum is"

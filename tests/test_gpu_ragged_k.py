@@ -53,3 +53,19 @@ def test_every_tile_adds_up_in_the_order_of_k(layout):
             torch.cuda.synchronize()
         for variant in (5, 6, 7, 8):
             assert torch.equal(out[variant], out[2]), (variant, M, N, K)
+
+
+def test_gradients_of_a_ragged_batch_repeat():
+    """fp32 `C += A B` over 1990 tokens into few tiles: the same bits on every run (and those of the unsplit tiles)."""
+    M, N, K = 384, 768, 1990
+    g = torch.Generator(device=DEV).manual_seed(3)
+    a, b = (torch.randn(*s, generator=g, device=DEV).bfloat16() for s in ((K, M), (K, N)))
+    c0 = torch.randn(M, N, generator=g, device=DEV)
+    runs = []
+    for variant in (2, 4, 4, 4):
+        c = c0.clone()
+        print(f"gemm TN variant={variant} M={M} N={N} K={K} accumulate", flush=True)
+        B.rtp_gemm(B.LAYOUT_TN, B.RTP_BF16, B.RTP_F32, True, a, M, b, N, c, N, M, N, K, variant)
+        torch.cuda.synchronize()
+        runs.append(c)
+    assert all(torch.equal(c, runs[0]) for c in runs)
