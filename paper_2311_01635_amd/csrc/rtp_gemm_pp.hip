@@ -92,10 +92,15 @@ static double epilogue_steps(int epi, int c_is_f32)
     }
 }
 
-// The small tile: a fixed part (prologue, the K halves' meeting) and a part per 64 K.  Measured one round of it takes
-// 4.5 us + 0.33 us per sub-tile, the 128-high tile 2 us + 0.76 us per 64 K (K = 2048: 13.4 against 26 us while one
-// round holds all tiles, 45 against 32 us for 8192 x 768, where the small tile needs three).
-constexpr double SMALL_FIXED = 3.0, SMALL_STEP = 0.5;
+// The small tile: a fixed part and a part per 64 K.  Launches alone (us, launch included): one round 512 x 2752 x 4096
+// 21.0, two rounds 2048 x 1792 x 8192 75 and 992 x 4096 x 14336 139, three rounds 8192 x 768 x 2048 37.3 and
+// 8192 x 768 x 384 16.6 (the 128-high tile: 50.4, 91, 168, 31.6, 11.6) give 1.5 and 0.44.  Beside another GEMM both are
+// larger, as it fetches twice the bytes per flop: with 1.5 and 0.44 there too the ragged Llama-shaped step took 3.80 ms
+// and the expert layer's 17.15, with 3.0 and 0.5 3.73 and 17.00.
+struct SmallCost {
+    double fixed, step;
+};
+constexpr SmallCost SMALL_ALONE = {1.5, 0.44}, SMALL_SHARED = {3.0, 0.5};
 
 // frac: the share of the K loop's MFMA time an edge tile still needs (1 for an interior tile), area: the share
 // of the tile that exists (scales the epilogue's traffic)
@@ -103,8 +108,9 @@ static double tile_cost(const GemmArgs &a, int bm, int ksplit, double frac = 1.0
 {
     int each;
     (void)k_chunks(a, bm, ksplit, &each);
+    const SmallCost small = a.cu_share > 1 ? SMALL_SHARED : SMALL_ALONE;
     if (bm == 64) // 64 x 128, sub-tiles of 64
-        return SMALL_FIXED + SMALL_STEP * each * std::max(frac, 0.7) + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32) / 8.0;
+        return small.fixed + small.step * each + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32) / 8.0;
     const double handicap = bm == 256 ? 1.0 : bm == 192 ? 1.04 : 1.12;
     // (an edge tile still fetches whole sub-tiles and passes every barrier: a floor under its loop time)
     const double loop = each * std::max(frac, 0.35);
@@ -141,7 +147,7 @@ static bool may_split_k(const GemmArgs &a)
 
 // Greedy list schedule of one XCD's share (an eighth of each problem, rounded up) over its
 // compute units, problems in the order given: the finishing time of the last tile.
-static double makespan(const GemmArgs *a, const int *bm, const int *ks, const int *order, int count, int cus_per_xcd)
+static double makespan(const GemmArgs *a, const int *bm, const int *ks, const int *order, int count, int cus_per_xcd, bool whole_tile = true)
 {
     std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
     for (int i = 0; i < cus_per_xcd; ++i) free_at.push(0.0);
@@ -166,6 +172,11 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
             left -= cnt[c];
         }
         cnt[0] = left;
+        // No launch ends before one whole tile has: that share may leave out every class but the cheapest (a single tile
+        // per XCD is always the corner), and the fragments an edge tile skips shorten a busy machine's work, not its own
+        // K loop (768 x 2048 at height 192: 28 us for 8 rows as for 200).  Priced by the corner alone, those launches
+        // went to tall tiles; the small tile takes 10.4 and 10.8 us.
+        if (whole_tile) end = std::max(end, free_at.top() + cost[0]);
         // cheap tiles first: the grid hands tiles out in index order, not longest first, so the tile that starts a
         // further round is as likely a full one as not; an estimate that kept the cheap ones for last favoured plans
         // whose last round never comes out that short (a K split that spilled 8 tiles into a second round)
@@ -217,9 +228,23 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
     // stream may be a GEMM of a hundred tiles, or done already.  The estimate is the mean of the two ends, its
     // share of the compute units and all of them, which is what the in-situ sweeps of the tile heights favour
     // (a 96-tile GEMM planned for half the machine kept its 256-high tiles and left compute units idle).
-    auto estimate = [&](const GemmArgs *p, const int *bm, const int *ks, const int *order, int n) {
-        const double t = makespan(p, bm, ks, order, n, cus_per_xcd);
-        return cu_share > 1 ? 0.5 * (t + makespan(p, bm, ks, order, n, std::max(1, compute_units() / 8))) : t;
+    auto estimate = [&](const GemmArgs *p, const int *bm, const int *ks, const int *order, int n, bool whole_tile = true) {
+        const double t = makespan(p, bm, ks, order, n, cus_per_xcd, whole_tile);
+        return cu_share > 1 ? 0.5 * (t + makespan(p, bm, ks, order, n, std::max(1, compute_units() / 8), whole_tile)) : t;
+    };
+    // Whether a sum is split at all: only where a tall tile's split beats every tall tile, the unsplit ones priced by
+    // one XCD's share alone.  That is cheap where an XCD gets a tile or two, and errs towards gradients that repeat.
+    auto worth_splitting = [&](const GemmArgs &p) {
+        const int heights[3] = {256, 192, 128}, splits[6] = {1, 2, 4, 8, 16, 32}, zero = 0;
+        double best = 1e300;
+        bool split = false;
+        for (int h : heights)
+            for (int k : splits) {
+                if (k > 1 && p.K / 32 / k < 4) break;
+                const double t = estimate(&p, &h, &k, &zero, 1, false);
+                if (t < best - 1e-9) best = t, split = k > 1;
+            }
+        return split;
     };
     // options per problem
     int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][24], oks[PP_MAX_GROUP][24];
@@ -227,22 +252,15 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
         nopt[q] = 0;
         const int forced = bm_override ? bm_override[q] : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
-        const bool split_ok = may_split_k(a[q]) && tiles128 < cus;
-        bool tall_split = false; // the best plan of the tall tiles alone is a split one: only then may the small tile be split
-        double tall_best = 1e300;
+        const bool split_ok = may_split_k(a[q]) && tiles128 < cus && worth_splitting(a[q]);
         for (int h = 0; h < 4; ++h) {
             if (forced != 0 && forced != heights[h]) continue;
             if (heights[h] == 64 && a[q].sync) continue; // the counters are the tall tiles'
-            for (int k = 0; k < (split_ok && (heights[h] != 64 || tall_split || forced == 64) ? 6 : 1); ++k) {
+            for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
                 if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (heights[h] == 64 ? 8 : 4)) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
-                if (split_ok && heights[h] != 64) {
-                    const int zero = 0;
-                    const double t = estimate(a + q, heights + h, splits + k, &zero, 1);
-                    if (t < tall_best - 1e-9) tall_best = t, tall_split = splits[k] > 1;
-                }
             }
         }
     }

@@ -19,3 +19,15 @@ def test_gradients_of_a_ragged_batch_or_a_narrow_shard_are_not_split(cu_share):
     for M, N, K in ((64, 1376, 1024), (96, 1376, 1024), (128, 1376, 512)):
         assert G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=cu_share)[1] == 1, (M, N, K)
     assert G.plan(B.LAYOUT_TN, 384, 768, 8192, G.EPI_ACC_ADD, cu_share=cu_share)[1] > 1, "a narrow shard's long sum is"
+
+
+@pytest.mark.parametrize("N,K", [(256, 2048), (384, 768), (768, 384), (768, 2048), (1376, 4096)])
+def test_a_prompt_runs_on_the_small_tile_whatever_its_length(N, K):
+    """Few rows: the small tile is the fastest at every one of them, one row into a tall tile or eight past one."""
+    for M in (8, 32, 56, 64, 72, 96, 128, 130, 136, 192, 200, 224, 256, 264, 270, 400, 512):
+        assert G.plan(B.LAYOUT_NT, M, N, K) == (64, 1), M
+
+
+def test_a_machine_full_of_tall_tiles_keeps_them():
+    assert G.plan(B.LAYOUT_NT, 8192, 768, 2048)[0] == 128 and G.plan(B.LAYOUT_NT, 8192, 768, 384)[0] == 128
+    assert G.plan(B.LAYOUT_NN, 4096, 4096, 2752)[0] == 256
