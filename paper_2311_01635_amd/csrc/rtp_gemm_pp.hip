@@ -203,6 +203,13 @@ struct Plan {
     int bm[PP_MAX_GROUP], ks[PP_MAX_GROUP], order[PP_MAX_GROUP];
 };
 
+// the height a caller asks for; 0 (pick) also for one that is not built, or that the problem's counters cannot take
+static int forced_height(const GemmArgs &a, int asked)
+{
+    const bool built = asked == 256 || asked == 192 || asked == 128 || (asked == 64 && !a.sync);
+    return built ? asked : 0;
+}
+
 static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_override, int cu_share)
 {
     static std::map<PlanKey, Plan> cache;
@@ -211,7 +218,7 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
     memset(&key, 0, sizeof key);
     key.layout = layout; key.count = count; key.cu_share = cu_share;
     for (int q = 0; q < count; ++q) {
-        const int forced = bm_override ? bm_override[q] : 0;
+        const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
         const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi + (a[q].sync ? 64 : 0), forced, may_split_k(a[q]) ? 1 : 0};
         memcpy(key.dims[q], d, sizeof d);
     }
@@ -250,7 +257,7 @@ static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_o
     int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][24], oks[PP_MAX_GROUP][24];
     for (int q = 0; q < count; ++q) {
         nopt[q] = 0;
-        const int forced = bm_override ? bm_override[q] : 0;
+        const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
         const bool split_ok = may_split_k(a[q]) && tiles128 < cus && worth_splitting(a[q]);
         for (int h = 0; h < 4; ++h) {

@@ -25,11 +25,13 @@ _launch.restype = C.c_int
 _launch.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.c_void_p]
 
 
-def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_share=1, force=0):
+def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_share=1, force=0, sync=False):
     """(tile height, K split) the launcher picks for one GEMM.  Needs no GPU: an fp32 sum lives at a made-up address."""
     a = GemmArgs(M=M, N=N, K=K, epi=epi, half=half, c_is_f32=int(f32), elem=ELEM[dtype], cu_share=cu_share, C=0x1000, ldc=N)
     if epi in (EPI_ACC_FIRST, EPI_ACC_ADD):
         a.ws, a.ldws, a.c_is_f32 = 0x1000, N, 1
+    if sync:
+        a.sync = 0x2000
     bm, ks = C.c_int(0), C.c_int(0)
     _plan(layout, C.byref(a), 1, C.byref(C.c_int(force)), C.byref(bm), C.byref(ks))
     return bm.value, ks.value

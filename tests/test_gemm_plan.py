@@ -31,3 +31,14 @@ def test_a_prompt_runs_on_the_small_tile_whatever_its_length(N, K):
 def test_a_machine_full_of_tall_tiles_keeps_them():
     assert G.plan(B.LAYOUT_NT, 8192, 768, 2048)[0] == 128 and G.plan(B.LAYOUT_NT, 8192, 768, 384)[0] == 128
     assert G.plan(B.LAYOUT_NN, 4096, 4096, 2752)[0] == 256
+
+
+def test_a_height_that_is_not_built_is_picked():
+    shape = (B.LAYOUT_NT, 512, 768, 1024)
+    for force in (1, 32, 96, 160, 512, -1):
+        assert G.plan(*shape, force=force) == G.plan(*shape), force
+    # a producer or consumer of a fused step counts tall tiles' rows: the small tile is not for it, forced or not
+    assert G.plan(*shape, sync=True)[0] in (256, 192, 128)
+    assert G.plan(*shape, force=64, sync=True) == G.plan(*shape, sync=True)
+    for force in (256, 192, 128, 64):
+        assert G.plan(*shape, force=force)[0] == force
