@@ -574,7 +574,8 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
     for (rtp_linear *l : r->linears) l->next_step = 0;
     // The forward pass of a ring whose linears are all output-partitioned enqueues nothing on the auxiliary stream, so
     // its rotations and its end need not be ordered after that stream (a record and a wait each; such a pass is bound
-    // by how fast the host enqueues: 200 tokens, 2048 -> 6144 over 8 workers: 422 -> 407 us).  An input-partitioned
+    // by how fast the host enqueues: 200 tokens, 2048 -> 6144 over 8 workers, 290-369 us with them and 238-271 without,
+    // six runs of each; 64 tokens, 512 -> 1024 over 16, 530-691 and 440-470).  An input-partitioned
     // linear created while the pass is open says so when it uses the stream; the caller of a bare ring, a unit and a
     // backward pass may use it at any time.
     if (pass == RTP_PASS_FWD && !r->linears.empty() &&
