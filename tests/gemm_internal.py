@@ -1,4 +1,4 @@
-"""The GEMM launcher behind the layers, which the C ABI does not expose: its argument block and two of its entry points,
+"""The GEMM launcher behind the layers, which the C ABI does not expose: its argument block and entry points,
 so that a test can ask which tile a shape gets and run an epilogue on a chosen kernel."""
 import ctypes as C
 
@@ -40,3 +40,13 @@ def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_sha
 def launch(layout, args, variant, stream=None):
     """launch_gemm_bf16 with the given arguments on kernel `variant`; the HIP status."""
     return _launch(layout, C.byref(args), variant, stream)
+
+
+_colsum = getattr(B.lib, "_ZN3rtp13launch_colsumEiPKvliiPKfPfP12ihipStream_t")
+_colsum.restype = C.c_int
+_colsum.argtypes = [C.c_int, C.c_void_p, C.c_int64, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
+
+
+def colsum(elem, Y, ld, rows, cols, into, out, stream=None):
+    """out[c] = into[c] + sum over rows of Y[r, c]; elem -1: fp32.  Tensors must be on the GPU."""
+    return _colsum(elem, Y.data_ptr(), ld, rows, cols, into.data_ptr(), out.data_ptr(), stream)

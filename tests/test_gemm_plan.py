@@ -42,3 +42,14 @@ def test_a_height_that_is_not_built_is_picked():
     assert G.plan(*shape, force=64, sync=True) == G.plan(*shape, sync=True)
     for force in (256, 192, 128, 64):
         assert G.plan(*shape, force=force)[0] == force
+
+
+def test_the_unit_tests_reach_the_small_tile():
+    """The GEMMs of the units the GPU tests compare with the oracle (200 and 288 tokens) run on it, not only forced ones."""
+    for epi, half, N in ((G.EPI_GELU_ERF_FWD, 0, 136), (G.EPI_SWIGLU_FWD, 136, 272)):
+        assert G.plan(B.LAYOUT_NT, 200, N, 136, epi, half)[0] == 64
+    for dtype in ("bf16", "f16"):
+        assert G.plan(B.LAYOUT_NT, 288, 128, 160, G.EPI_GELU_TANH_FWD, dtype=dtype)[0] == 64
+        assert G.plan(B.LAYOUT_NT, 288, 256, 160, G.EPI_SWIGLU_FWD, 128, dtype=dtype)[0] == 64
+        assert G.plan(B.LAYOUT_NN, 288, 128, 96, G.EPI_GELU_TANH_BWD, dtype=dtype)[0] == 64
+        assert G.plan(B.LAYOUT_NN, 288, 128, 96, G.EPI_SWIGLU_BWD, 128, dtype=dtype)[0] == 64

@@ -89,20 +89,18 @@ GEMM_ODD = {B.LAYOUT_NT: [(301, 77, 72), (301, 77, 96)], B.LAYOUT_NN: [(301, 72,
 
 
 # variants 1-2: register-staged tiles; 4: the ping-pong kernel with the tile height picked by shape;
-# 5, 6, 7: ping-pong with tile height 256, 192, 128 (K must be a multiple of 32)
-@pytest.mark.parametrize("variant", [1, 2, 4, 5, 6, 7])
+# 5, 6, 7, 8: tile height 256, 192, 128, and the 64 x 128 tile
+@pytest.mark.parametrize("variant", [1, 2, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("layout", [B.LAYOUT_NT, B.LAYOUT_NN, B.LAYOUT_TN])
 def test_gemm_bf16_layouts_and_tails(layout, variant):
     for i, (M, N, K) in enumerate(GEMM_SHAPES + GEMM_ODD[layout]):
-        if variant >= 4 and K % 32:
-            continue
         for accumulate, out_f32 in ((False, True), (True, True), (False, False)):
             say(f"gemm layout={layout} variant={variant} M={M} N={N} K={K} acc={accumulate} f32out={out_f32}")
             err = _gemm_case(layout, M, N, K, variant, accumulate, out_f32, seed=100 * layout + i)
             assert err <= (TOL_F32 if out_f32 else TOL_BF16), (layout, variant, M, N, K, accumulate, out_f32, err)
 
 
-@pytest.mark.parametrize("variant", [4, 5, 6, 7])
+@pytest.mark.parametrize("variant", [4, 5, 6, 7, 8])
 @pytest.mark.parametrize("layout", [B.LAYOUT_NT, B.LAYOUT_NN, B.LAYOUT_TN])
 def test_gemm_fp16_layouts_and_tails(layout, variant):
     """fp16 inputs run on the tiled kernel (K a multiple of 32); same shapes, same oracle."""
