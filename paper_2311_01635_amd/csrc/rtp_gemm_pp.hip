@@ -210,10 +210,15 @@ static int forced_height(const GemmArgs &a, int asked)
     return built ? asked : 0;
 }
 
-static Plan plan_group(int layout, const GemmArgs *a, int count, const int *bm_override, int cu_share)
+static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share)
 {
     static std::map<PlanKey, Plan> cache;
     static std::mutex lock;
+    GemmArgs a[PP_MAX_GROUP]; // priced for the share the plan is remembered under, not for what each problem says
+    for (int q = 0; q < count; ++q) {
+        a[q] = given[q];
+        a[q].cu_share = cu_share;
+    }
     PlanKey key;
     memset(&key, 0, sizeof key);
     key.layout = layout; key.count = count; key.cu_share = cu_share;
