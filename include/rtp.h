@@ -237,7 +237,10 @@ rtp_status rtp_ring_seek_bwd_start(rtp_ring *ring);
  * for the previous step.  Enqueues on the stage stream: the held weights go
  * back to their home slot, the next shard's weights come into the staging
  * buffer; in a backward pass the gradient part follows each linear's dW
- * kernel (see rtp_linear_bwd).  Errors: RTP_ERR_STATE for a wrong direction,
+ * kernel (see rtp_linear_bwd).  Narrow shards: the pass runs on the compute
+ * stream alone, and these transfers are workgroups of the launch that the
+ * step's first linear call makes (of one of their own when the ring has no
+ * linear).  Errors: RTP_ERR_STATE for a wrong direction,
  * a step out of order or >= n-1, a linear lagging behind. */
 rtp_status rtp_rotate_step(rtp_ring *ring, int direction, int step);
 

@@ -7,9 +7,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librtp.so")
-SOURCES = ["rtp_gemm_bf16.hip", "rtp_gemm_pp.hip", "rtp_gemm_pp_nt.hip", "rtp_gemm_pp_nn.hip", "rtp_gemm_pp_tn.hip",
+# (the files that take longest to compile first)
+SOURCES = ["rtp_gemm_pp_nn_tn.hip", "rtp_gemm_pp_nn_tn_f16.hip",
+           "rtp_gemm_pp_nt.hip", "rtp_gemm_pp_nn.hip", "rtp_gemm_pp_tn.hip",
            "rtp_gemm_pp_nt_f16.hip", "rtp_gemm_pp_nn_f16.hip", "rtp_gemm_pp_tn_f16.hip",
-           "rtp_misc_kernels.hip", "rtp_host.cpp"]
+           "rtp_gemm_bf16.hip", "rtp_gemm_pp.hip", "rtp_misc_kernels.hip", "rtp_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops off: the compiler must not form packed fp32 arithmetic from scalar code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -22,7 +24,7 @@ def _newer(dst, srcs):
 
 def build(force: bool = True, verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    kernel_headers = [os.path.join(CSRC, h) for h in ("rtp_kernels.h", "rtp_gemm_epilogue.h", "rtp_gemm_pp.h", "rtp_gemm_small.h")]
+    kernel_headers = [os.path.join(CSRC, h) for h in ("rtp_kernels.h", "rtp_ride.h", "rtp_gemm_epilogue.h", "rtp_gemm_pp.h", "rtp_gemm_small.h")]
     host_headers = [os.path.join(CSRC, "rtp_kernels.h"), os.path.join(HERE, "..", "include", "rtp.h")]
 
     def compile_one(src):

@@ -56,6 +56,7 @@
 // give the same bits.
 #pragma once
 #include "rtp_gemm_epilogue.h"
+#include "rtp_ride.h"
 #include <type_traits>
 #include <hip/hip_ext.h>
 
@@ -86,11 +87,16 @@ struct PpProblem {
     int vec_epilogue;
     int ksplit;           // > 1: the K loop is cut into this many chunks, one workgroup each, whose partial
                           // sums meet in the fp32 accumulator through atomic adds (a.epi == EPI_ACC_ATOMIC)
+    int lay;              // operand layout, where the kernel holds more than one
 };
 struct PpGroup {
     int count;
+    unsigned tile_blocks; // workgroups from here on carry the transfers
     PpProblem p[PP_MAX_GROUP];
+    RideList ride;
 };
+// the kernel of a backward step: LAY_NN and LAY_TN problems in one launch
+constexpr int LAY_NN_TN = 3;
 
 // The transposing fragment read, issued as an instruction of our own.  Through the builtin the compiler puts a
 // wait for ALL outstanding direct loads in front of these reads (it cannot tell that the LDS stage being read is
@@ -453,6 +459,17 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
     }
 }
 
+template <int LAY, typename E>
+__device__ __forceinline__ void pp_any_tile(const PpProblem &P, const int pid, const int kt_begin, const int kt_count, char *smem)
+{
+    switch (P.bm) {
+    case 256: pp_tile<LAY, 256, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    case 192: pp_tile<LAY, 192, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    case 64: pp_small_tile<LAY, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    default: pp_tile<LAY, 128, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    }
+}
+
 // Workgroup ids are dealt round-robin to the 8 XCDs.  XCD x works through its own list: its
 // contiguous eighth of problem 0's tiles, then of problem 1's, ...; workgroup 8 l + x takes entry l
 // of that list (the host sizes the grid for the longest list; surplus workgroups leave at once).
@@ -460,6 +477,10 @@ template <int LAY, typename E>
 __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
 {
     __shared__ __attribute__((aligned(1024))) char smem[pp::SMEM_BYTES];
+    if (blockIdx.x >= g.tile_blocks) {
+        ride<pp::NTHR>(g.ride, blockIdx.x - g.tile_blocks);
+        return;
+    }
     const int xcd = blockIdx.x & 7;
     int l = blockIdx.x >> 3;
     int q = 0, pid = -1;
@@ -485,19 +506,20 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
     const int kt_begin = chunk * kt_each;
     const int kt_count = min(kt_each, kt_total - kt_begin);
     if (kt_count <= 0) return;
-    switch (P.bm) {
-    case 256: pp_tile<LAY, 256, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    case 192: pp_tile<LAY, 192, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    case 64: pp_small_tile<LAY, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    default: pp_tile<LAY, 128, E>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    }
+    if constexpr (LAY != LAY_NN_TN)
+        pp_any_tile<LAY, E>(P, pid, kt_begin, kt_count, smem);
+    else if (P.lay == LAY_NN)
+        pp_any_tile<LAY_NN, E>(P, pid, kt_begin, kt_count, smem);
+    else
+        pp_any_tile<LAY_TN, E>(P, pid, kt_begin, kt_count, smem);
 }
 
 // done: an event that completes with the kernel (its completion signal is the event's: no packet of its own in
 // the queue, which a separate record costs ~4 us of queue time between two dependent launches), or null.
 template <int LAY, typename E>
-static hipError_t launch_gemm_pp_layout(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done)
+static hipError_t launch_gemm_pp_layout(const PpGroup &g, hipStream_t s, hipEvent_t done)
 {
+    const unsigned blocks = g.tile_blocks + g.ride.blocks;
     if (done)
         hipExtLaunchKernelGGL((gemm_pp_kernel<LAY, E>), dim3(blocks), dim3(pp::NTHR), 0, s, nullptr, done, 0, g);
     else

@@ -13,12 +13,14 @@
 
 namespace rtp {
 
-hipError_t launch_gemm_pp_nt_bf16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
-hipError_t launch_gemm_pp_nn_bf16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
-hipError_t launch_gemm_pp_tn_bf16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
-hipError_t launch_gemm_pp_nt_f16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
-hipError_t launch_gemm_pp_nn_f16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
-hipError_t launch_gemm_pp_tn_f16(const PpGroup &g, unsigned blocks, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nt_bf16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nn_bf16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_tn_bf16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nt_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nn_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_tn_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nn_tn_bf16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_pp_nn_tn_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
 
 bool gemm_bf16_pp_supported(int layout, const GemmArgs &a)
 {
@@ -320,6 +322,47 @@ void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_o
     }
 }
 
+// the group's tiles in the order of its plan, behind them the transfers that ride along (may be null)
+static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a, int count, const Plan &pl, const Riders *riders,
+                               hipStream_t s, hipEvent_t done)
+{
+    const int *bm = pl.bm, *order = pl.order;
+    PpGroup g;
+    memset(&g, 0, sizeof g);
+    g.count = count;
+    unsigned per_xcd = 0;
+    long tiles = 0;
+    for (int i = 0; i < count; ++i) {
+        const int q = order[i];
+        PpProblem &p = g.p[i];
+        p.a = a[q];
+        p.lay = layouts ? layouts[q] : layout;
+        p.bm = bm[q];
+        p.tiles_m = (a[q].M + bm[q] - 1) / bm[q];
+        p.tiles_n = tiles_n_of(a[q], bm[q]);
+        p.vec_epilogue = gemm_epilogue_vec_ok(a[q]) ? 1 : 0;
+        // as many chunks as are not empty
+        int each;
+        p.ksplit = k_chunks(a[q], bm[q], pl.ks[q], &each);
+        if (p.ksplit > 1) p.a.epi = EPI_ACC_ATOMIC;
+        per_xcd += (unsigned)(((long)p.tiles_m * p.tiles_n * p.ksplit + 7) / 8);
+        tiles += (long)p.tiles_m * p.tiles_n * p.ksplit;
+    }
+    g.tile_blocks = per_xcd * 8;
+    if (riders) {
+        const hipError_t e = ride_list(*riders, std::max(64, compute_units() - (int)std::min<long>(tiles, 1 << 20)), &g.ride);
+        if (e != hipSuccess) return e;
+    }
+    const bool f16 = a[0].elem == ELEM_F16;
+    switch (layout) {
+    case LAY_NT: return f16 ? launch_gemm_pp_nt_f16(g, s, done) : launch_gemm_pp_nt_bf16(g, s, done);
+    case LAY_NN: return f16 ? launch_gemm_pp_nn_f16(g, s, done) : launch_gemm_pp_nn_bf16(g, s, done);
+    case LAY_TN: return f16 ? launch_gemm_pp_tn_f16(g, s, done) : launch_gemm_pp_tn_bf16(g, s, done);
+    case LAY_NN_TN: return f16 ? launch_gemm_pp_nn_tn_f16(g, s, done) : launch_gemm_pp_nn_tn_bf16(g, s, done);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a_in, int count_in, const int *bm_override, hipStream_t s,
                                      hipEvent_t done)
 {
@@ -336,34 +379,41 @@ hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a_in, int count
     }
     if (count == 0) return done ? hipEventRecord(done, s) : hipSuccess; // nothing to launch: the event still marks this point
     const Plan pl = plan_group(layout, a, count, forced, count == 1 ? a[0].cu_share : 1);
-    const int *bm = pl.bm, *order = pl.order;
+    return launch_group(layout, nullptr, a, count, pl, nullptr, s, done);
+}
 
-    PpGroup g;
-    memset(&g, 0, sizeof g);
-    g.count = count;
-    unsigned per_xcd = 0;
-    for (int i = 0; i < count; ++i) {
-        const int q = order[i];
-        PpProblem &p = g.p[i];
-        p.a = a[q];
-        p.bm = bm[q];
-        p.tiles_m = (a[q].M + bm[q] - 1) / bm[q];
-        p.tiles_n = tiles_n_of(a[q], bm[q]);
-        p.vec_epilogue = gemm_epilogue_vec_ok(a[q]) ? 1 : 0;
-        // as many chunks as are not empty
-        int each;
-        p.ksplit = k_chunks(a[q], bm[q], pl.ks[q], &each);
-        if (p.ksplit > 1) p.a.epi = EPI_ACC_ATOMIC;
-        per_xcd += (unsigned)(((long)p.tiles_m * p.tiles_n * p.ksplit + 7) / 8);
+// the layout code of a launch that holds problems of these layouts, -1 if no kernel does
+static int common_layout(const int *layouts, int count)
+{
+    int lay = layouts[0];
+    for (int q = 1; q < count; ++q)
+        if (layouts[q] != lay) lay = lay == LAY_NT || layouts[q] == LAY_NT ? -1 : LAY_NN_TN;
+    return lay;
+}
+
+void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out)
+{
+    if (count < 1 || count > PP_MAX_GROUP) return;
+    const Plan pl = plan_group(common_layout(layouts, count), a, count, nullptr, 1);
+    for (int q = 0; q < count; ++q) ksplit_out[q] = pl.ks[q];
+}
+
+hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_in, int count_in, const Riders &r, hipStream_t s)
+{
+    if (count_in < 0 || count_in > PP_MAX_GROUP) return hipErrorInvalidValue;
+    GemmArgs a[PP_MAX_GROUP];
+    int layouts[PP_MAX_GROUP], count = 0;
+    for (int q = 0; q < count_in; ++q) {
+        if (a_in[q].M <= 0 || a_in[q].N <= 0) continue;
+        if (!gemm_bf16_args_ok(layouts_in[q], a_in[q]) || !gemm_bf16_pp_supported(layouts_in[q], a_in[q])) return hipErrorInvalidValue;
+        if (count > 0 && a_in[q].elem != a[0].elem) return hipErrorInvalidValue;
+        layouts[count] = layouts_in[q];
+        a[count++] = a_in[q];
     }
-    const unsigned blocks = per_xcd * 8;
-    const bool f16 = a[0].elem == ELEM_F16;
-    switch (layout) {
-    case LAY_NT: return f16 ? launch_gemm_pp_nt_f16(g, blocks, s, done) : launch_gemm_pp_nt_bf16(g, blocks, s, done);
-    case LAY_NN: return f16 ? launch_gemm_pp_nn_f16(g, blocks, s, done) : launch_gemm_pp_nn_bf16(g, blocks, s, done);
-    case LAY_TN: return f16 ? launch_gemm_pp_tn_f16(g, blocks, s, done) : launch_gemm_pp_tn_bf16(g, blocks, s, done);
-    default: return hipErrorInvalidValue;
-    }
+    if (count == 0) return launch_riders(r, s);
+    const int lay = common_layout(layouts, count);
+    if (lay < 0) return hipErrorInvalidValue;
+    return launch_group(lay, layouts, a, count, plan_group(lay, a, count, nullptr, 1), &r, s, nullptr);
 }
 
 hipError_t launch_gemm_bf16_pp(int layout, const GemmArgs &a, int bm_override, hipStream_t s)

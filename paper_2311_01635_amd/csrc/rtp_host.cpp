@@ -246,6 +246,9 @@ struct rtp_ring {
     int base_idx = 0;    // weight buffer index at step 0 of the open pass
     int rotations = 0;   // rotate_step calls in the open pass
     int executed = 0;    // blocking mode: rotations already carried out
+    bool may_carry = true; // (a schedule that moves the shards itself on the other streams says no before it begins)
+    bool carry = false;  // the open pass runs on the compute stream alone, its transfers riding in the GEMM launches
+    Riders pend;         // transfers of the rotation that has been asked for: they go out with the step's first launch
     // test aid: a bounded spin kernel ahead of every transfer on the stage stream / every GEMM on the
     // auxiliary stream stretches the windows in which a missing cross-stream wait would show
     long long delay_stage_ticks = 0, delay_aux_ticks = 0, delay_compute_ticks = 0;
@@ -283,6 +286,7 @@ struct rtp_linear {
     int64_t o;        // shard width along the partitioned dimension
     size_t w_shard_bytes, g_shard_bytes;
     int next_step = 0;
+    bool unsent[2] = {false, false}; // riding transfers: gradient buffer i holds a sum of this layer that must still go home
     hipEvent_t ev_dw = nullptr, ev_g_in = nullptr;
 };
 
@@ -389,6 +393,56 @@ static rtp_status rotate_async(rtp_ring *r, void *out, const void *held, void *h
     return copy_batch_flush(r, b, s, done);
 }
 
+// ---- riding transfers ---------------------------------------------------------------------
+// Narrow shards: the whole pass runs on the compute stream.  The transfers of a step are extra workgroups of the step's
+// GEMM launches (rtp_ride.h), and the input and the weight gradients of a backward step go out as one launch where
+// nothing orders them, so a step is one or two launches and no event.  The buffers, the bytes and the order of the
+// transfers against the kernels are those of the two-stream schedules: a buffer is written by a launch behind the
+// last one that read it, and a launch reads what an earlier one brought in.
+static bool ring_carries(const rtp_ring *r, rtp_pass pass);
+
+// the transfers asked for so far as a launch of their own
+static rtp_status carry_flush(rtp_ring *r)
+{
+    if (r->pend.count == 0) return RTP_OK;
+    const Riders p = r->pend;
+    r->pend.count = 0;
+    HIP_TRY(launch_riders(p, r->cs()));
+    return RTP_OK;
+}
+
+// out <- buf <- in (out or in may be null), with the next launch
+static rtp_status carry_add(rtp_ring *r, void *out, void *buf, const void *in, size_t bytes)
+{
+    if (bytes == 0) return RTP_OK;
+    if (r->pend.count == RIDE_MAX_SEGS) RTP_TRY(carry_flush(r));
+    r->pend.seg[r->pend.count++] = RideSeg{out, buf, in, bytes};
+    return RTP_OK;
+}
+
+// Two gradient buffers: the next shard's part comes into the buffer that held the shard of the step before, whose sums
+// go home first where their kernel has not sent them (`kin` < 0: nothing comes in).
+static rtp_status carry_g_turnover(rtp_ring *r, int gdst, int kprev, int kin)
+{
+    bool any = false;
+    for (rtp_linear *l : r->linears) any = any || l->unsent[gdst];
+    if (!any) return kin < 0 ? RTP_OK : carry_add(r, nullptr, r->d.buf_g_dev[gdst], r->home_g(kin), r->d.g_bytes);
+    size_t at = 0; // the slot in order: what lies between the layers' parts only comes in
+    std::vector<rtp_linear *> parts(r->linears);
+    std::sort(parts.begin(), parts.end(), [](const rtp_linear *a, const rtp_linear *b) { return a->d.g_offset < b->d.g_offset; });
+    char *buf = (char *)r->d.buf_g_dev[gdst];
+    for (rtp_linear *l : parts) {
+        if (!l->unsent[gdst]) continue;
+        l->unsent[gdst] = false;
+        const size_t off = l->d.g_offset;
+        if (kin >= 0 && off > at) RTP_TRY(carry_add(r, nullptr, buf + at, r->home_g(kin) + at, off - at));
+        RTP_TRY(carry_add(r, r->home_g(kprev) + off, buf + off, kin >= 0 ? r->home_g(kin) + off : nullptr, l->g_shard_bytes));
+        at = off + l->g_shard_bytes;
+    }
+    if (kin >= 0 && at < r->d.g_bytes) RTP_TRY(carry_add(r, nullptr, buf + at, r->home_g(kin) + at, r->d.g_bytes - at));
+    return RTP_OK;
+}
+
 // make each stream wait for everything enqueued so far on the other
 static rtp_status cross_join(rtp_ring *r)
 {
@@ -407,12 +461,22 @@ static rtp_status cross_join(rtp_ring *r)
     return RTP_OK;
 }
 
+// Between passes, for work on the compute stream alone: nothing to wait for once the other streams have been joined.
+// They are ordered behind that work when a pass next uses them (begin_join).
+static rtp_status idle_join(rtp_ring *r)
+{
+    if (!r->joined) RTP_TRY(cross_join(r));
+    r->joined = true;
+    return RTP_OK;
+}
+
 // Start of a pass: the stage and auxiliary streams wait for everything the compute stream holds (the caller's
 // inputs were produced there); the other direction only if they may hold work the compute stream has not yet
 // waited for (rtp_ring_end joins them, and only passes enqueue on them).
 static rtp_status begin_join(rtp_ring *r)
 {
     if (r->dry) return RTP_OK;
+    if (r->carry) return idle_join(r); // nothing goes to the other streams
     if (!r->joined) return cross_join(r);
     r->joined = false;
     HIP_TRY(hipEventRecord(r->ev_join, r->cs()));
@@ -555,6 +619,28 @@ extern "C" rtp_status rtp_ring_set_ablation(rtp_ring *r, int rotate, int compute
     return set_ablation(r, rotate, compute);
 }
 
+// Whether a pass rides.  Against it stands that a riding workgroup takes a compute unit from the tiles once those fill the
+// machine, where a copy kernel on the stage stream runs beside them.  us a pass, two streams -> riding:
+//   forward, slots of 34 MB: 128 tokens 553 -> 394, 4096 tokens 1627 -> 1414, 8192 tokens 2627 -> 2617; of 88 MB, 512 to
+//   2048 tokens 2164 -> 2305, 2994 -> 2748, 3928 -> 4055;
+//   forward and backward, tokens x bytes of weights a slot, x 10^9: 24 (1024 tokens, 23 MB) 1756 -> 1735, 33 (4096 tokens,
+//   8 MB) 3106 -> 2983, 46 (4096 tokens, 11 MB) 4832 -> 4672, 69 (4096 tokens, 17 MB) 5358 -> 5568, 92 (4096 tokens,
+//   23 MB) 3270 -> 3506; gradients travel too: slots of 34 + 68 MB, 512 and 1024 tokens 1811 -> 1766, 2121 -> 2307.
+constexpr size_t CARRY_FWD_BYTES = (size_t)48 << 20, CARRY_BWD_BYTES = (size_t)72 << 20;
+constexpr double CARRY_BWD_WORK = 60e9;
+
+static bool ring_carries(const rtp_ring *r, rtp_pass pass)
+{
+    if (r->dry || r->d.n < 2 || !r->abl_rotate || r->d.mode == RTP_INPLACE_BLOCKING) return false;
+    if (r->d.flags & RTP_FLAG_STAGE_MEMCPY) return false;
+    // the test delays hold the other streams back: those passes run on them
+    if (r->delay_stage_ticks > 0 || r->delay_aux_ticks > 0 || r->delay_compute_ticks > 0) return false;
+    if (pass == RTP_PASS_FWD) return r->d.w_bytes <= CARRY_FWD_BYTES;
+    int64_t T = 0;
+    for (const rtp_linear *l : r->linears) T = std::max(T, l->d.T);
+    return r->d.w_bytes + r->d.g_bytes <= CARRY_BWD_BYTES && (double)T * (double)r->d.w_bytes <= CARRY_BWD_WORK;
+}
+
 extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
 {
     if (!r) return fail(RTP_ERR_INVALID, "rtp_ring_begin: null ring");
@@ -566,12 +652,18 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
                     (rank + 1) % n, r->resident);
     RTP_TRY(refuse_capture(r, "rtp_ring_begin"));
     RTP_TRY(ensure_events(r));
+    r->carry = r->may_carry && ring_carries(r, pass);
+    r->may_carry = true;
+    r->pend.count = 0;
     RTP_TRY(begin_join(r));
-    r->joined = false;
+    r->joined = r->carry;
     r->pass = pass;
     r->rotations = 0;
     r->executed = 0;
-    for (rtp_linear *l : r->linears) l->next_step = 0;
+    for (rtp_linear *l : r->linears) {
+        l->next_step = 0;
+        l->unsent[0] = l->unsent[1] = false;
+    }
     // The forward pass of a ring whose linears are all output-partitioned enqueues nothing on the auxiliary stream, so
     // its rotations and its end need not be ordered after that stream (a record and a wait each; such a pass is bound
     // by how fast the host enqueues: 200 tokens, 2048 -> 6144 over 8 workers, 290-369 us with them and 238-271 without,
@@ -600,8 +692,19 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
         // The gradient transfers of the pass's start run on the stage stream: only the weight-gradient kernels
         // (auxiliary stream, or the compute stream when there is none) wait for them, the first input-gradient
         // kernels do not.  cross_join above has ordered the stage stream after everything enqueued so far.
-        hipStream_t gs = r->ss();
-        if (r->d.g_bytes && r->res_g >= 0) {
+        hipStream_t gs = r->carry ? r->cs() : r->ss();
+        if (r->carry && r->d.g_bytes) {
+            // one launch: the two slots differ, and the buffers too or a thread moves its units out before it writes any
+            char *held = (char *)r->d.buf_g_dev[r->res_g_idx], *first = (char *)r->d.buf_g_dev[0];
+            if (r->res_g >= 0) r->rec(TR_G_OUT, -1, r->res_g, r->res_g_idx);
+            void *out = r->res_g >= 0 ? r->home_g(r->res_g) : nullptr;
+            if (out && held != first) {
+                RTP_TRY(carry_add(r, out, held, nullptr, r->d.g_bytes));
+                out = nullptr;
+            }
+            RTP_TRY(carry_add(r, out, first, r->home_g(r->resident), r->d.g_bytes));
+            RTP_TRY(carry_flush(r));
+        } else if (r->d.g_bytes && r->res_g >= 0) {
             // the gradient shard the previous backward pass ended on (the worker's own) is still in the
             // buffer: it goes back to its slot before the buffer takes the shard this pass starts with
             RTP_TRY(copy_async(r, r->home_g(r->res_g), r->d.buf_g_dev[r->res_g_idx], r->d.g_bytes, gs));
@@ -610,7 +713,7 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
         r->res_g_idx = 0;
         r->res_g = r->resident;
         if (r->d.g_bytes) {
-            RTP_TRY(copy_async(r, r->d.buf_g_dev[0], r->home_g(r->resident), r->d.g_bytes, gs));
+            if (!r->carry) RTP_TRY(copy_async(r, r->d.buf_g_dev[0], r->home_g(r->resident), r->d.g_bytes, gs));
             r->rec(TR_G_IN, -1, r->resident, 0);
             if (!r->dry && gs != r->cs()) {
                 HIP_TRY(hipEventRecord(r->ev_g0, gs));
@@ -627,7 +730,7 @@ extern "C" rtp_status rtp_ring_seek_bwd_start(rtp_ring *r)
     if (r->pass != RTP_PASS_IDLE) return fail(RTP_ERR_STATE, "rtp_ring_seek_bwd_start: a pass is open");
     RTP_TRY(refuse_capture(r, "rtp_ring_seek_bwd_start"));
     RTP_TRY(ensure_events(r));
-    RTP_TRY(cross_join(r));
+    RTP_TRY(idle_join(r));
     const int k = (r->d.rank + 1) % r->d.n;
     r->res_idx = 0;
     r->resident = k;
@@ -647,6 +750,17 @@ static rtp_status do_rotation(rtp_ring *r, int step)
     const int src = r->w_idx(step), dst = r->w_idx(step + 1);
     hipStream_t s = r->ss();
     const bool blocking = r->d.mode == RTP_INPLACE_BLOCKING;
+    if (r->carry) {
+        RTP_TRY(carry_add(r, nullptr, r->d.buf_w_dev[dst], r->home_w(kin), r->d.w_bytes));
+        RTP_TRY(carry_add(r, r->home_w(k), r->d.buf_w_dev[src], nullptr, r->d.w_bytes));
+        r->rec(TR_W_OUT, step, k, src);
+        r->rec(TR_W_IN, step, kin, dst);
+        if (bwd && r->d.g_bytes && r->d.mode == RTP_DOUBLE_BUFFER) {
+            RTP_TRY(carry_g_turnover(r, r->g_idx(step + 1), step > 0 ? r->shard_at(step - 1) : -1, kin));
+            r->rec(TR_G_IN, step, kin, r->g_idx(step + 1));
+        }
+        return r->linears.empty() ? carry_flush(r) : RTP_OK; // (a bare ring has no launch to ride in)
+    }
     if (!r->dry && !blocking) {
         // the staging buffer was resident one step ago: wait for its readers
         HIP_TRY(hipEventRecord(r->ev_free, r->cs()));
@@ -737,7 +851,7 @@ static rtp_status enter_step(rtp_ring *r, int next_step, int step, rtp_pass pass
                 RTP_TRY(do_rotation(r, r->executed));
                 r->executed++;
             }
-        } else if (step > 0 && !r->dry) {
+        } else if (step > 0 && !r->dry && !r->carry) {
             HIP_TRY(hipStreamWaitEvent(r->cs(), r->ev_w[step & 1], 0));
         }
         r->resident = r->shard_at(step);
@@ -772,10 +886,16 @@ extern "C" rtp_status rtp_ring_end(rtp_ring *r)
         r->resident = r->shard_at(r->d.n - 1);
         r->w_held = false;
     }
+    if (r->carry) {
+        // a sum of the last but one step that its kernel has not sent is still in the buffer the last step did not use
+        if (r->pass == RTP_PASS_BWD && r->d.mode == RTP_DOUBLE_BUFFER)
+            RTP_TRY(carry_g_turnover(r, r->g_idx(r->d.n - 2), r->shard_at(r->d.n - 2), -1));
+        RTP_TRY(carry_flush(r));
+    }
     r->pass = RTP_PASS_IDLE;
     // the pass is complete on the compute stream only once the stage stream's last transfers are:
     // a caller that waits on (or captures) the compute stream alone then sees the whole pass
-    if (!r->dry && r->events_ready) {
+    if (!r->dry && r->events_ready && !r->carry) {
         if (r->cs() != r->ss()) {
             HIP_TRY(hipEventRecord(r->ev_join, r->ss()));
             HIP_TRY(hipStreamWaitEvent(r->cs(), r->ev_join, 0));
@@ -798,6 +918,8 @@ extern "C" rtp_status rtp_ring_abort(rtp_ring *r)
     rtp_status st = (r->dry || !r->events_ready) ? RTP_OK : cross_join(r);
     r->pass = RTP_PASS_IDLE;
     r->joined = false;
+    r->carry = false;
+    r->pend.count = 0;
     r->pass_uses_as = true;
     r->resident = -1;
     r->w_held = false;
@@ -826,12 +948,15 @@ extern "C" rtp_status rtp_ring_flush(rtp_ring *r)
     if (r->resident < 0) return RTP_OK;
     RTP_TRY(refuse_capture(r, "rtp_ring_flush"));
     RTP_TRY(ensure_events(r));
-    RTP_TRY(cross_join(r));
-    RTP_TRY(copy_async(r, r->home_w(r->resident), r->d.buf_w_dev[r->res_idx], r->d.w_bytes, r->cs()));
+    RTP_TRY(idle_join(r));
+    CopyBatch b;
+    RTP_TRY(copy_batch_add(r, b, r->home_w(r->resident), r->d.buf_w_dev[r->res_idx], r->d.w_bytes, r->cs()));
     r->rec(TR_W_OUT, -1, r->resident, r->res_idx);
     r->w_held = false; // the store may be written from here on (an optimizer step): the next forward pass loads anew
-    if (r->d.g_bytes && r->res_g >= 0) {
-        RTP_TRY(copy_async(r, r->home_g(r->res_g), r->d.buf_g_dev[r->res_g_idx], r->d.g_bytes, r->cs()));
+    const bool held_g = r->d.g_bytes && r->res_g >= 0;
+    if (held_g) RTP_TRY(copy_batch_add(r, b, r->home_g(r->res_g), r->d.buf_g_dev[r->res_g_idx], r->d.g_bytes, r->cs()));
+    RTP_TRY(copy_batch_flush(r, b, r->cs()));
+    if (held_g) {
         r->rec(TR_G_OUT, -1, r->res_g, r->res_g_idx);
         r->res_g = -1; // the slot is current: the next backward pass has nothing to write back
     }
@@ -844,7 +969,7 @@ extern "C" rtp_status rtp_ring_zero_grads(rtp_ring *r)
     if (r->pass != RTP_PASS_IDLE) return fail(RTP_ERR_STATE, "rtp_ring_zero_grads: a pass is open");
     RTP_TRY(refuse_capture(r, "rtp_ring_zero_grads"));
     RTP_TRY(ensure_events(r));
-    RTP_TRY(cross_join(r));
+    RTP_TRY(idle_join(r));
     if (!r->dry && r->d.g_bytes) HIP_TRY(launch_fill_zero(r->d.home_g_dev, (size_t)r->d.n * r->d.g_bytes, r->cs()));
     r->res_g = -1; // the copy in the worker's buffer is dropped with the rest
     return RTP_OK;
@@ -1003,6 +1128,33 @@ static rtp_status gemm(rtp_linear *l, int layout, GemmArgs &a, hipStream_t st)
     return RTP_OK;
 }
 
+// The layer's GEMMs (layouts[i]; up to two that nothing orders) as one launch that carries the pending transfers.
+static rtp_status gemm_riding(rtp_linear *l, const int *layouts, GemmArgs *a, int count)
+{
+    rtp_ring *r = l->ring;
+    if (!r->abl_compute) return carry_flush(r);
+    const bool f32 = l->d.dtype == RTP_F32;
+    bool together = !g_prof_on; // (timed launches are one GEMM each)
+    for (int i = 0; i < count; ++i) {
+        a[i].elem = l->d.dtype == RTP_F16 ? ELEM_F16 : ELEM_BF16;
+        a[i].cu_share = 1;
+        together = together && (f32 || gemm_bf16_pp_supported(layouts[i], a[i]));
+    }
+    if (!together) {
+        RTP_TRY(carry_flush(r));
+        for (int i = 0; i < count; ++i) RTP_TRY(gemm(l, layouts[i], a[i], r->cs()));
+        return RTP_OK;
+    }
+    const Riders p = r->pend;
+    r->pend.count = 0;
+    if (f32)
+        HIP_TRY(launch_gemm_f32_riding(layouts, a, count, p, r->cs()));
+    else
+        HIP_TRY(launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()));
+    return RTP_OK;
+}
+static rtp_status gemm_riding(rtp_linear *l, int layout, GemmArgs &a) { return gemm_riding(l, &layout, &a, 1); }
+
 // whether the layer's steps meet in an fp32 accumulator (16-bit layer, more than one step)
 static bool needs_acc(const rtp_linear *l) { return l->d.dtype != RTP_F32 && l->ring->d.n > 1 && l->d.T > 0 && !l->ring->dry; }
 
@@ -1030,6 +1182,7 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
     // with an auxiliary stream and a second linear on the ring, two forward GEMMs share the machine
     const int fwd_share = (r->as() != r->cs() && r->linears.size() > 1) ? 2 : 1;
     a.cu_share = fwd_share;
+    auto launch = [&](hipStream_t st) { return r->carry ? gemm_riding(l, LAY_NT, a) : gemm(l, LAY_NT, a, st); };
     if (d.split == RTP_SPLIT_OUT) {
         a.A = X; a.lda = d.I;
         a.B = Wk; a.ldb = d.I;
@@ -1039,7 +1192,7 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
             a.N = (int)ov;
             a.epi = EPI_STORE;
             a.C = (char *)Y + (size_t)k * o * es; a.ldc = d.O;
-            RTP_TRY(gemm(l, LAY_NT, a, r->cs()));
+            RTP_TRY(launch(r->cs()));
         } else {
             const bool gated = d.act == RTP_ACT_SWIGLU;
             const int64_t ow = gated ? o / 2 : ov, Ow = gated ? d.O / 2 : d.O;   // (a gated layer is never padded)
@@ -1051,11 +1204,11 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
                 a.half = (int)(o / 2);
                 a.aux = pre; a.ldaux = d.O;
                 a.C = Yk; a.ldc = Ow;
-                RTP_TRY(gemm(l, LAY_NT, a, r->cs()));
+                RTP_TRY(launch(r->cs()));
             } else {
                 a.epi = EPI_STORE;
                 a.C = pre; a.ldc = d.O;
-                RTP_TRY(gemm(l, LAY_NT, a, r->cs()));
+                RTP_TRY(launch(r->cs()));
                 if (!r->dry && r->abl_compute)
                     HIP_TRY(launch_act_f32(fwd_act_epi(d.act), (const float *)pre, d.O, nullptr, 0, (float *)Yk, Ow,
                                            (int)d.T, (int)ow, (int)(o / 2), r->cs()));
@@ -1076,7 +1229,7 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
         // on the auxiliary stream beside the next step's output-partitioned GEMM.  It starts after
         // everything enqueued so far on the compute stream (its input may just have been produced
         // there) and after this step's shard has been staged.
-        hipStream_t fs = r->as();
+        hipStream_t fs = r->carry ? r->cs() : r->as();
         r->pass_uses_as = true;
         if (!r->dry && fs != r->cs()) {
             HIP_TRY(hipEventRecord(r->ev_aux, r->cs()));
@@ -1100,9 +1253,10 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
             else if (n == 1) a.bias = bk;
             else HIP_TRY(launch_bias_add(belem, bdst, d.O, (int)d.T, (int)pv, bk, fs));
         }
-        RTP_TRY(gemm(l, LAY_NT, a, fs));
+        RTP_TRY(launch(fs));
         if (after) HIP_TRY(launch_bias_add(belem, bdst, d.O, (int)d.T, (int)pv, bk, fs));
     }
+    if (r->carry) RTP_TRY(carry_flush(r)); // (a layer without tokens launches nothing)
     l->next_step = step + 1;
     return RTP_OK;
 }
@@ -1190,19 +1344,62 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
     // The weight-gradient kernel runs on the auxiliary stream when there is one, beside the
     // input-gradient kernels: shard GEMMs seldom fill the machine alone.  It starts after
     // everything enqueued so far on the compute stream (its dY may just have been produced there).
-    hipStream_t ws = r->as();
+    hipStream_t ws = r->carry ? r->cs() : r->as();
     const bool split = ws != r->cs();
     if (!r->dry && split) {
         HIP_TRY(hipEventRecord(r->ev_aux, r->cs()));
         HIP_TRY(hipStreamWaitEvent(ws, r->ev_aux, 0));
     }
     // the gradient shard this step adds onto must have arrived
-    if (!r->dry && r->abl_rotate && step > 0) {
+    if (!r->dry && r->abl_rotate && step > 0 && !r->carry) {
         if (r->d.mode == RTP_DOUBLE_BUFFER)
             HIP_TRY(hipStreamWaitEvent(ws, r->ev_g[step & 1], 0));
         else if (staged_g)
             HIP_TRY(hipStreamWaitEvent(ws, l->ev_g_in, 0));
     }
+
+    // the input gradient's GEMM; an fp32 layer applies an activation's derivative in a kernel of its own
+    auto dx_args = [&]() {
+        GemmArgs a;
+        memset(&a, 0, sizeof a);
+        a.c_is_f32 = f32;
+        a.A = dY; a.lda = d.O;
+        a.B = Wk;
+        a.M = (int)d.T;
+        if (d.split == RTP_SPLIT_OUT) {
+            a.A = (const char *)dY + (size_t)k * o * es;
+            a.ldb = d.I;
+            a.N = (int)d.I; a.K = (int)ov;
+            a.C = dX; a.ldc = d.I;
+            if (f32) {
+                a.epi = step == 0 ? EPI_STORE : EPI_ACC_ADD;
+            } else {
+                a.epi = acc_epi(step, n);
+                a.ws = d.acc_ws_dev; a.ldws = d.I;
+            }
+            return a;
+        }
+        const bool gated = d.act == RTP_ACT_SWIGLU;
+        const int64_t P = gated ? 2 * d.I : d.I, po = gated ? 2 * o : o;
+        a.ldb = o;
+        a.N = (int)ov; a.K = (int)d.O; // (a gated layer is never padded)
+        a.epi = EPI_STORE;
+        a.C = (char *)dX + (size_t)k * po * es; a.ldc = P;
+        if (d.act != RTP_ACT_NONE && !f32) {
+            a.epi = bwd_act_epi(d.act);
+            a.half = (int)o;
+            a.aux = (char *)d.preact_dev + (size_t)k * po * es; a.ldaux = P;
+        } else if (gated) {
+            a.C = (float *)a.C + o;
+        }
+        return a;
+    };
+    // Nothing orders the step's two GEMMs: one launch holds both.  (No auxiliary stream: a caller gets one after the other.)
+    const bool paired = r->carry && r->d.aux_stream && dX && d.T > 0 && !(f32 && d.act != RTP_ACT_NONE);
+    static const int pair_lay[2] = {LAY_NN, LAY_TN};
+    // (with other layers on the ring, one of them may not have issued the last but one step yet: rtp_ring_end sends then)
+    if (r->carry && step == n - 1 && r->d.mode == RTP_DOUBLE_BUFFER && r->linears.size() == 1)
+        RTP_TRY(carry_g_turnover(r, r->g_idx(n - 2), r->shard_at(n - 2), -1));
 
     GemmArgs a;
     // ---- weight gradient, fused into the travelling gradient shard -----------
@@ -1231,15 +1428,27 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
     if (fused_send && gemm_bf16_pp_supported(LAY_TN, a)) {
         // not when the launcher would cut this GEMM's K loop into chunks (few output tiles, long
         // contraction): their partial sums need the plain `+=` form
-        int ks = 1;
-        gemm_bf16_pp_plan(LAY_TN, &a, 1, nullptr, nullptr, &ks);
-        if (ks > 1) fused_send = false;
+        int ks[2] = {1, 1};
+        if (paired) {
+            const GemmArgs both[2] = {dx_args(), a};
+            gemm_bf16_pp_plan_riding(pair_lay, both, 2, ks);
+        } else if (r->carry) {
+            gemm_bf16_pp_plan_riding(pair_lay + 1, &a, 1, ks + 1);
+        } else {
+            gemm_bf16_pp_plan(LAY_TN, &a, 1, nullptr, nullptr, ks + 1);
+        }
+        if (ks[1] > 1) fused_send = false;
     }
     if (fused_send) {
         a.epi = EPI_ACC_LAST;
         a.C = r->home_g(k) + d.g_offset;
     }
-    if (d.T > 0) RTP_TRY(gemm(l, LAY_TN, a, ws));
+    if (paired) {
+        GemmArgs both[2] = {dx_args(), a};
+        RTP_TRY(gemm_riding(l, pair_lay, both, 2));
+    } else if (d.T > 0) {
+        RTP_TRY(r->carry ? gemm_riding(l, LAY_TN, a) : gemm(l, LAY_TN, a, ws));
+    }
     if (d.has_bias && !r->dry && r->abl_compute) {
         // bias gradient: column sums of this shard's slice of dY, onto the entries that follow the
         // matrix gradient in the travelling shard (and out to where it travels, like the matrix part)
@@ -1259,14 +1468,25 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
     // ---- hand the gradient part to the stage stream ---------------------------
     if (moves_on) {
         const int kin = rtp_bwd_shard(r->d.rank, step + 1, n);
-        if (!r->dry) {
+        if (!r->dry && !r->carry) {
             HIP_TRY(hipEventRecord(l->ev_dw, ws));
             HIP_TRY(hipStreamWaitEvent(r->ss(), l->ev_dw, 0));
         }
         char *part = (char *)r->d.buf_g_dev[gi] + d.g_offset;
-        if (!fused_send) RTP_TRY(copy_async(r, r->home_g(k) + d.g_offset, part, l->g_shard_bytes, r->ss()));
+        if (r->carry) {
+            // one buffer: the part is exchanged next, by the input-gradient launch or by one of its own (4096 tokens, 5.6 MB
+            // of weights a slot: the two GEMMs apart cost more than that launch); two: the next rotation moves it
+            if (staged_g)
+                RTP_TRY(carry_add(r, fused_send ? nullptr : r->home_g(k) + d.g_offset, part, r->home_g(kin) + d.g_offset, l->g_shard_bytes));
+            else
+                l->unsent[gi] = !fused_send;
+        } else if (!fused_send) {
+            RTP_TRY(copy_async(r, r->home_g(k) + d.g_offset, part, l->g_shard_bytes, r->ss()));
+        }
         r->rec(TR_G_OUT, step, k, gi);
-        if (staged_g) {
+        if (staged_g && r->carry) {
+            r->rec(TR_G_IN, step, kin, gi);
+        } else if (staged_g) {
             // in place: the next shard's part comes into the buffer the kernel has just finished with
             RTP_TRY(copy_async(r, part, r->home_g(kin) + d.g_offset, l->g_shard_bytes, r->ss(), l->ev_g_in));
             r->rec(TR_G_IN, step, kin, gi);
@@ -1274,57 +1494,20 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
     }
 
     // ---- input gradient ----------------------------------------------------------
-    if ((dX && d.T > 0) || r->dry) {
-        memset(&a, 0, sizeof a);
-        a.c_is_f32 = f32;
+    if (!paired && ((dX && d.T > 0) || r->dry)) {
+        a = dx_args();
         a.cu_share = split ? 2 : 1;
-        if (d.split == RTP_SPLIT_OUT) {
-            a.A = (const char *)dY + (size_t)k * o * es; a.lda = d.O;
-            a.B = Wk; a.ldb = d.I;
-            a.M = (int)d.T; a.N = (int)d.I; a.K = (int)ov;
-            a.C = dX; a.ldc = d.I;
-            if (f32) {
-                a.epi = step == 0 ? EPI_STORE : EPI_ACC_ADD;
-            } else {
-                a.epi = acc_epi(step, n);
-                a.ws = d.acc_ws_dev; a.ldws = d.I;
-            }
-            RTP_TRY(gemm(l, LAY_NN, a, r->cs()));
-        } else {
-            a.A = dY; a.lda = d.O;
-            a.B = Wk; a.ldb = o;
-            a.M = (int)d.T; a.N = (int)o; a.K = (int)d.O;
-            if (d.act == RTP_ACT_NONE) {
-                a.N = (int)ov;
-                a.epi = EPI_STORE;
-                a.C = (char *)dX + (size_t)k * o * es; a.ldc = d.I;
-                RTP_TRY(gemm(l, LAY_NN, a, r->cs()));
-            } else {
-                const bool gated = d.act == RTP_ACT_SWIGLU;
-                const int64_t P = gated ? 2 * d.I : d.I, po = gated ? 2 * o : o;
-                char *out = (char *)dX + (size_t)k * po * es;
-                const char *pre = (const char *)d.preact_dev + (size_t)k * po * es;
-                a.N = (int)ov;                                                   // (a gated layer is never padded)
-                if (!f32) {
-                    a.epi = bwd_act_epi(d.act);
-                    a.half = (int)o;
-                    a.aux = (void *)pre; a.ldaux = P;
-                    a.C = out; a.ldc = P;
-                    RTP_TRY(gemm(l, LAY_NN, a, r->cs()));
-                } else {
-                    // the plain product lands in the last o columns of the slice, then the
-                    // activation's derivative is applied elementwise, in place
-                    float *tmp = (float *)out + (gated ? o : 0);
-                    a.epi = EPI_STORE;
-                    a.C = tmp; a.ldc = P;
-                    RTP_TRY(gemm(l, LAY_NN, a, r->cs()));
-                    if (!r->dry && r->abl_compute)
-                        HIP_TRY(launch_act_f32(bwd_act_epi(d.act), (const float *)pre, P, tmp, P, (float *)out, P,
-                                               (int)d.T, (int)ov, (int)o, r->cs()));
-                }
-            }
+        RTP_TRY(r->carry ? gemm_riding(l, LAY_NN, a) : gemm(l, LAY_NN, a, r->cs()));
+        if (f32 && d.split == RTP_SPLIT_IN && d.act != RTP_ACT_NONE && !r->dry && r->abl_compute) {
+            // the plain product has landed in the last o columns of the slice; the activation's
+            // derivative is applied elementwise, in place
+            const bool gated = d.act == RTP_ACT_SWIGLU;
+            const int64_t P = gated ? 2 * d.I : d.I, po = gated ? 2 * o : o;
+            HIP_TRY(launch_act_f32(bwd_act_epi(d.act), (const float *)d.preact_dev + (size_t)k * po, P, (const float *)a.C, P,
+                                   (float *)dX + (size_t)k * po, P, (int)d.T, (int)ov, (int)o, r->cs()));
         }
     }
+    if (r->carry) RTP_TRY(carry_flush(r)); // (nothing was launched for the transfers to ride in)
     l->next_step = step + 1;
     return RTP_OK;
 }
@@ -1966,6 +2149,142 @@ static rtp_status mlp_bwd_two_stream(rtp_mlp *m, const void *X, const void *dY, 
     return rtp_ring_end(r);
 }
 
+// ---- riding schedule: narrow shards, everything on the compute stream ----------------------------
+// independent GEMMs of the unit and the pending transfers as one launch
+static rtp_status gemm_group_riding(rtp_ring *r, const int *layouts, const GemmArgs *a, int count)
+{
+    if (!r->abl_compute) return carry_flush(r);
+    if (g_prof_on) { // timed launches are one GEMM each
+        RTP_TRY(carry_flush(r));
+        for (int i = 0; i < count; ++i) RTP_TRY(gemm_group(r, layouts[i], a + i, 1, r->cs()));
+        return RTP_OK;
+    }
+    const Riders p = r->pend;
+    r->pend.count = 0;
+    HIP_TRY(launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()));
+    return RTP_OK;
+}
+
+// part [off, off + bytes) of the weight slot, with the next launch: shard k's from buffer `src` goes home, shard kin's comes into `dst`
+static rtp_status carry_w_part(rtp_ring *r, int step, int k, int kin, int src, int dst, size_t off, size_t bytes)
+{
+    RTP_TRY(carry_add(r, nullptr, (char *)r->d.buf_w_dev[dst] + off, r->home_w(kin) + off, bytes));
+    RTP_TRY(carry_add(r, r->home_w(k) + off, (char *)r->d.buf_w_dev[src] + off, nullptr, bytes));
+    r->rec(TR_W_OUT, step, k, src);
+    r->rec(TR_W_IN, step, kin, dst);
+    return RTP_OK;
+}
+
+// The launches of mlp_fwd_grouped; the shard parts that launch t's successor needs ride in launch t (their buffers were
+// last read by launch t - 1).
+static rtp_status mlp_fwd_riding(rtp_mlp *m, const void *X, void *Y)
+{
+    rtp_ring *r = m->ring;
+    const int n = r->d.n;
+    const MlpShapes h = mlp_shapes(m);
+    RTP_TRY(rtp_ring_begin(r, RTP_PASS_FWD));
+    const size_t w1_bytes = h.w_off2, w2_bytes = r->d.w_bytes - h.w_off2;
+    auto buf = [&](int step) { return (const char *)r->d.buf_w_dev[r->w_idx(step)]; };
+    for (int t = 0; t <= n; ++t) {
+        if (t >= 1 && t <= n - 1)
+            RTP_TRY(carry_w_part(r, t - 1, r->shard_at(t - 1), r->shard_at(t), r->w_idx(t - 1), r->w_idx(t), h.w_off2, w2_bytes));
+        if (t <= n - 2)
+            RTP_TRY(carry_w_part(r, t, r->shard_at(t), r->shard_at(t + 1), r->w_idx(t), r->w_idx(t + 1), 0, w1_bytes));
+        static const int lay[2] = {LAY_NT, LAY_NT};
+        GemmArgs g[2];
+        int cnt = 0;
+        if (t < n) {
+            r->rec(TR_FWD, t, r->shard_at(t), r->w_idx(t));
+            g[cnt++] = mlp_args_z(m, h, r->shard_at(t), X, buf(t));
+        }
+        if (t >= 1) g[cnt++] = mlp_args_down(m, h, r->shard_at(t - 1), t - 1, buf(t - 1), Y);
+        if (t >= 2) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(t - 1), buf(t - 1), r->cs()));
+        RTP_TRY(gemm_group_riding(r, lay, g, cnt));
+        if (t == 1) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(0), buf(0), r->cs())); // the sum exists from here on
+    }
+    mlp_close_pass(m);
+    return rtp_ring_end(r);
+}
+
+// Two launches a step: {dPre_s, dW2_s}, which need nothing of each other, then {dX_s, dW1_s}, which both need dPre_s.
+// The weights of shard s + 1 ride in the first (their buffer was last read by step s - 1).  Two gradient buffers: so does
+// the whole gradient shard s + 1.  One: its second part comes in under {dX_s, dW1_s}, behind dW2_s, its first under the
+// next step's {dPre, dW2}, behind dW1_s, each where the kernel that adds onto it is one launch away.
+static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void *dX)
+{
+    rtp_ring *r = m->ring;
+    const int n = r->d.n;
+    const MlpShapes h = mlp_shapes(m);
+    RTP_TRY(rtp_ring_begin(r, RTP_PASS_BWD));
+    const bool two_g = r->d.mode == RTP_DOUBLE_BUFFER;
+    const size_t g1_bytes = h.g_off2, g2_bytes = r->d.g_bytes - h.g_off2;
+    static const int lay[2] = {LAY_NN, LAY_TN};
+    auto wbuf = [&](int step) { return (const char *)r->d.buf_w_dev[r->w_idx(step)]; };
+    auto gbuf = [&](int step) { return (char *)r->d.buf_g_dev[r->g_idx(step)]; };
+    auto first = [&](int s, GemmArgs *g) { // {dPre_s, dW2_s}
+        g[0] = mlp_args_dh(m, h, r->shard_at(s), wbuf(s), dY);
+        g[1] = mlp_args_dw2(m, h, r->shard_at(s), gbuf(s), dY);
+    };
+    auto second = [&](int s, GemmArgs *g) { // {dX_s, dW1_s}
+        g[0] = mlp_args_dx(m, h, r->shard_at(s), s, wbuf(s), dX);
+        g[1] = mlp_args_dw1(m, h, r->shard_at(s), gbuf(s), X);
+    };
+    auto whole_k = [&](const GemmArgs *g) { // a sum whose K loop is split needs the plain `+=` form: its send is a copy
+        int ks[2] = {1, 1};
+        gemm_bf16_pp_plan_riding(lay, g, 2, ks);
+        return ks[1] == 1;
+    };
+    // the last step's shard is the worker's own: both parts straight into the own slot, or neither (mlp_bwd_two_stream)
+    bool own_to_slot = false;
+    if (r->abl_compute) {
+        GemmArgs g1[2], g2[2];
+        first(n - 1, g1);
+        second(n - 1, g2);
+        own_to_slot = whole_k(g1) && whole_k(g2);
+    }
+    auto send = [&](int s, GemmArgs *g, size_t off) { // the sum goes straight to where the gradient part travels to
+        const bool fused = r->abl_compute && (s <= n - 2 ? whole_k(g) : own_to_slot);
+        if (fused) {
+            g[1].epi = EPI_ACC_LAST;
+            g[1].C = r->home_g(r->shard_at(s)) + off;
+        }
+        return fused;
+    };
+    bool sent1 = false, sent2 = false;
+    for (int s = 0; s < n; ++s) {
+        const int k = r->shard_at(s), kin = s <= n - 2 ? r->shard_at(s + 1) : -1;
+        if (kin >= 0) RTP_TRY(carry_w_part(r, s, k, kin, r->w_idx(s), r->w_idx(s + 1), 0, r->d.w_bytes));
+        if (two_g) {
+            if (s > 0 || kin >= 0) RTP_TRY(carry_g_turnover(r, r->g_idx(s + 1), s > 0 ? r->shard_at(s - 1) : -1, kin));
+        } else if (s > 0) {
+            RTP_TRY(carry_add(r, sent1 ? nullptr : r->home_g(r->shard_at(s - 1)), gbuf(s), r->home_g(k), g1_bytes));
+        }
+        r->rec(TR_BWD, s, k, r->w_idx(s));
+        GemmArgs g[2];
+        first(s, g);
+        sent2 = send(s, g, h.g_off2);
+        RTP_TRY(gemm_group_riding(r, lay, g, 2));
+        RTP_TRY(mlp_bias_grads(m, h, k, gbuf(s), sent2 ? r->home_g(k) : nullptr, dY, false, true, r->cs()));
+        if (kin >= 0 && !two_g)
+            RTP_TRY(carry_add(r, sent2 ? nullptr : r->home_g(k) + h.g_off2, gbuf(s) + h.g_off2, r->home_g(kin) + h.g_off2, g2_bytes));
+        second(s, g);
+        sent1 = send(s, g, 0);
+        RTP_TRY(gemm_group_riding(r, lay, g, 2));
+        RTP_TRY(mlp_bias_grads(m, h, k, gbuf(s), sent1 ? r->home_g(k) : nullptr, dY, true, false, r->cs()));
+        if (kin >= 0) {
+            if (two_g) {
+                m->l1->unsent[r->g_idx(s)] = !sent1;
+                m->l2->unsent[r->g_idx(s)] = !sent2;
+            }
+            r->rec(TR_G_OUT, s, k, r->g_idx(s));
+            r->rec(TR_G_IN, s, kin, r->g_idx(s + 1));
+        }
+    }
+    mlp_close_pass(m);
+    if (own_to_slot) r->res_g = -1; // the slot is current
+    return rtp_ring_end(r);
+}
+
 // ---- fused step: the unit's dependent GEMMs of a rotation step as ONE launch ---------------------
 // Forward, Z_t = act(X W1_t^T) and down_t = H_t W2_t^T of the SAME step go out as one launch of the
 // tiled kernel: the tiles of down_t follow those of Z_t in the grid and each starts as soon as the Z
@@ -2254,11 +2573,18 @@ static rtp_status mlp_bwd_pipelined(rtp_mlp *m, const void *X, const void *dY, v
     return rtp_ring_end(r);
 }
 
+// a unit that was asked for a schedule gets that schedule
+constexpr unsigned MLP_SCHEDULE_FLAGS = RTP_FLAG_STEPWISE | RTP_FLAG_GROUPED | RTP_FLAG_PIPELINED | RTP_FLAG_FUSED_STEP;
+static bool mlp_rides(const rtp_mlp *m, rtp_pass pass) { return !(m->d.flags & MLP_SCHEDULE_FLAGS) && ring_carries(m->ring, pass); }
+
 static rtp_status mlp_fwd_pass(rtp_mlp *m, const void *X, void *Y)
 {
     const bool have_aux = m->ring->as() != m->ring->cs();
+    const bool grouped_ok = mlp_grouped_ok(m, X, Y, nullptr, nullptr);
+    if (grouped_ok && mlp_rides(m, RTP_PASS_FWD)) return mlp_fwd_riding(m, X, Y);
+    m->ring->may_carry = !(m->d.flags & MLP_SCHEDULE_FLAGS) && !grouped_ok; // the step-by-step calls below may
     if (mlp_fused_ok(m, X, Y, nullptr, nullptr)) return mlp_fwd_fused(m, X, Y);
-    if (mlp_grouped_ok(m, X, Y, nullptr, nullptr))
+    if (grouped_ok)
         return have_aux && (m->d.flags & RTP_FLAG_PIPELINED) ? mlp_fwd_pipelined(m, X, Y) : mlp_fwd_grouped(m, X, Y);
     const int n = m->d.n;
     RTP_TRY(rtp_ring_begin(m->ring, RTP_PASS_FWD));
@@ -2277,8 +2603,12 @@ static rtp_status mlp_bwd_pass(rtp_mlp *m, const void *X, const void *dY, void *
     // launches per step 3.4-3.5; without one the grouped launches win (3.5 against 3.7).  Whatever the schedule,
     // the kernels of a pass need the same time of a machine that is busy throughout.
     const bool have_aux = m->ring->as() != m->ring->cs();
+    const bool grouped_ok = dX && mlp_grouped_ok(m, X, nullptr, dY, dX);
+    // (without an auxiliary stream the unit's GEMMs run one layout after the other)
+    if (grouped_ok && have_aux && mlp_rides(m, RTP_PASS_BWD)) return mlp_bwd_riding(m, X, dY, dX);
+    m->ring->may_carry = !(m->d.flags & MLP_SCHEDULE_FLAGS) && !grouped_ok;
     if (dX && mlp_fused_ok(m, X, nullptr, dY, dX)) return mlp_bwd_fused(m, X, dY, dX);
-    if (dX && mlp_grouped_ok(m, X, nullptr, dY, dX)) {
+    if (grouped_ok) {
         if (have_aux && (m->d.flags & RTP_FLAG_PIPELINED)) return mlp_bwd_pipelined(m, X, dY, dX);
         if (!have_aux || (m->d.flags & RTP_FLAG_GROUPED)) return mlp_bwd_grouped(m, X, dY, dX);
         return mlp_bwd_two_stream(m, X, dY, dX);
@@ -2482,6 +2812,7 @@ static rtp_status moe_fwd_pass(rtp_moe *m, const void *X, const int32_t *route, 
     if (rows > cap) return fail(RTP_ERR_STATE, "rtp_moe_fwd: grouped rows exceed the workspace");
     HIP_TRY(launch_gather_rows(d.xp_dev, X, d.perm_dev, (int)rows, (size_t)d.I * es, cs));
 
+    r->may_carry = false;
     RTP_TRY(rtp_ring_begin(r, RTP_PASS_FWD));
     m->next_step = 0;
     for (int t = 0; t < n; ++t) {
@@ -2542,6 +2873,7 @@ static rtp_status moe_bwd_pass(rtp_moe *m, const void *dY, void *dX)
     // the gradient of the output, grouped like the tokens (into the buffer the expert outputs used)
     HIP_TRY(launch_gather_rows(d.yp_dev, dY, d.perm_dev, (int)rows, (size_t)d.O2 * es, cs));
 
+    r->may_carry = false;
     RTP_TRY(rtp_ring_begin(r, RTP_PASS_BWD));
     m->next_step = 0;
     bool own_to_slot = false;

@@ -76,8 +76,33 @@ void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_o
 int gemm_bf16_pp_tiles_n(const GemmArgs &a);
 const char *gemm_bf16_kernel_name(int layout, int variant);
 
+// ---- shard transfers that ride in a launch ------------------------------------------------
+// out <- what buf holds, then buf <- in; either of out and in may be null.  16-byte units, aligned; no two segments of a
+// launch share a byte that one of them writes.
+struct RideSeg {
+    void *out, *buf;
+    const void *in;
+    size_t bytes;
+};
+constexpr int RIDE_MAX_SEGS = 8;
+struct Riders {
+    int count = 0;
+    RideSeg seg[RIDE_MAX_SEGS];
+};
+// Up to PP_MAX_GROUP independent GEMMs and the transfers in one launch of the tiled kernel.  layouts[i]: all LAY_NT, or
+// LAY_NN and LAY_TN in any mix (the input and the weight gradients of a backward step).  Nothing to compute: the
+// transfers alone.  hipErrorInvalidValue as launch_gemm_bf16_pp_group, before anything is launched.
+hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
+// the K splits that launch would use
+void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);
+// the transfers as a launch of their own
+hipError_t launch_riders(const Riders &r, hipStream_t s);
+
 // fp32 inputs and outputs (epi: EPI_STORE, EPI_ACC_ADD with ws == C).
 hipError_t launch_gemm_f32(int layout, const GemmArgs &a, hipStream_t s);
+// up to F32_MAX_GROUP independent fp32 GEMMs and the transfers in one launch
+constexpr int F32_MAX_GROUP = 2;
+hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
 
 // elementwise pieces of the fp32 path (the bf16 path fuses them into the GEMMs)
 // kind: EPI_GELU_ERF_FWD / EPI_GELU_TANH_FWD / EPI_SWIGLU_FWD / *_BWD

@@ -1,6 +1,6 @@
 // fp32 path of the partition GEMM (the small fp32 configuration), the
 // elementwise activation kernels that path uses, and the shard-staging copy.
-#include "rtp_kernels.h"
+#include "rtp_ride.h"
 #include <hip/hip_ext.h>
 #include <cstring>
 #include <algorithm>
@@ -12,14 +12,22 @@ namespace rtp {
 // inner product reads both with unit stride.
 constexpr int FT = 64, FK = 16;
 
+struct F32Group {
+    int count;
+    unsigned tile_blocks;
+    struct {
+        GemmArgs a;
+        int lay;
+        unsigned tiles_n, first; // first workgroup
+    } p[F32_MAX_GROUP];
+    RideList ride;
+};
+
 template <int LAY>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs p)
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, const int m0, const int n0, float (&sA)[FK][FT + 4], float (&sB)[FK][FT + 4])
 {
-    __shared__ float sA[FK][FT + 4];
-    __shared__ float sB[FK][FT + 4];
     const float *A = (const float *)p.A, *B = (const float *)p.B;
     const int tid = threadIdx.x;
-    const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
     const int tx = tid & 15, ty = tid >> 4;
     float acc[4][4] = {};
     for (int k0 = 0; k0 < p.K; k0 += FK) {
@@ -80,19 +88,51 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs p)
     }
 }
 
-hipError_t launch_gemm_f32(int layout, const GemmArgs &a, hipStream_t s)
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Group g)
 {
-    if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    if (a.K <= 0 || (a.epi != EPI_STORE && a.epi != EPI_ACC_ADD)) return hipErrorInvalidValue;
-    const dim3 grid((a.N + FT - 1) / FT, (a.M + FT - 1) / FT), block(256);
-    switch (layout) {
-    case LAY_NT: hipLaunchKernelGGL(gemm_f32_kernel<LAY_NT>, grid, block, 0, s, a); break;
-    case LAY_NN: hipLaunchKernelGGL(gemm_f32_kernel<LAY_NN>, grid, block, 0, s, a); break;
-    case LAY_TN: hipLaunchKernelGGL(gemm_f32_kernel<LAY_TN>, grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
+    __shared__ float sA[FK][FT + 4];
+    __shared__ float sB[FK][FT + 4];
+    if (blockIdx.x >= g.tile_blocks) {
+        ride<256>(g.ride, blockIdx.x - g.tile_blocks);
+        return;
     }
+    const int q = g.count > 1 && blockIdx.x >= g.p[1].first ? 1 : 0;
+    const unsigned b = blockIdx.x - g.p[q].first;
+    const int m0 = (int)(b / g.p[q].tiles_n) * FT, n0 = (int)(b % g.p[q].tiles_n) * FT;
+    switch (g.p[q].lay) {
+    case LAY_NT: gemm_f32_tile<LAY_NT>(g.p[q].a, m0, n0, sA, sB); break;
+    case LAY_NN: gemm_f32_tile<LAY_NN>(g.p[q].a, m0, n0, sA, sB); break;
+    default: gemm_f32_tile<LAY_TN>(g.p[q].a, m0, n0, sA, sB); break;
+    }
+}
+
+hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s)
+{
+    if (count < 0 || count > F32_MAX_GROUP) return hipErrorInvalidValue;
+    F32Group g;
+    memset(&g, 0, sizeof g);
+    int64_t blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        if (a[i].M <= 0 || a[i].N <= 0) continue;
+        if (a[i].K <= 0 || (a[i].epi != EPI_STORE && a[i].epi != EPI_ACC_ADD)) return hipErrorInvalidValue;
+        if (layouts[i] < LAY_NT || layouts[i] > LAY_TN) return hipErrorInvalidValue;
+        auto &p = g.p[g.count++];
+        p.a = a[i];
+        p.lay = layouts[i];
+        p.tiles_n = (unsigned)((a[i].N + FT - 1) / FT);
+        p.first = (unsigned)blocks;
+        blocks += (int64_t)p.tiles_n * ((a[i].M + FT - 1) / FT);
+    }
+    if (g.count == 0) return launch_riders(r, s);
+    if (blocks >= (int64_t)1 << 30) return hipErrorInvalidValue;
+    g.tile_blocks = (unsigned)blocks;
+    const hipError_t e = ride_list(r, 256, &g.ride);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3(g.tile_blocks + g.ride.blocks), dim3(256), 0, s, g);
     return hipGetLastError();
 }
+
+hipError_t launch_gemm_f32(int layout, const GemmArgs &a, hipStream_t s) { return launch_gemm_f32_riding(&layout, &a, 1, Riders(), s); }
 
 // ---- elementwise activations for the fp32 path --------------------------------------
 __device__ __forceinline__ float act_gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
@@ -250,6 +290,44 @@ hipError_t launch_copy_multi(void *const *dst, const void *const *src, const siz
         hipExtLaunchKernelGGL(copy_multi_kernel, dim3(blocks), dim3(COPY_THREADS), 0, s, nullptr, done, 0, g);
     else
         hipLaunchKernelGGL(copy_multi_kernel, dim3(blocks), dim3(COPY_THREADS), 0, s, g);
+    return hipGetLastError();
+}
+
+// ---- transfers that ride in a launch, or go out as one of their own -------------------------
+hipError_t ride_list(const Riders &r, int idle, RideList *out)
+{
+    memset(out, 0, sizeof *out);
+    int64_t total = 0;
+    for (int i = 0; i < r.count; ++i) {
+        const RideSeg &q = r.seg[i];
+        if (((uintptr_t)q.out | (uintptr_t)q.buf | (uintptr_t)q.in | q.bytes) & 15) return hipErrorInvalidValue;
+        total += (int64_t)(q.bytes >> 4);
+    }
+    // pieces that fill the idle compute units once, of at least 16 KB (one round of reads in flight) and at most 64 KB
+    const int64_t per = std::min<int64_t>(4096, std::max<int64_t>(1024, (total / std::max(1, idle) + 1023) / 1024 * 1024));
+    out->per_block = (int)per;
+    for (int i = 0; i < r.count; ++i) {
+        const int64_t n16 = (int64_t)(r.seg[i].bytes >> 4);
+        if (n16 == 0 || (!r.seg[i].out && !r.seg[i].in)) continue;
+        auto &q = out->seg[out->count++];
+        q.out = (ride_u32x4 *)r.seg[i].out;
+        q.buf = (ride_u32x4 *)r.seg[i].buf;
+        q.in = (const ride_u32x4 *)r.seg[i].in;
+        q.n16 = n16;
+        q.first = out->blocks;
+        out->blocks += (unsigned)((n16 + per - 1) / per);
+    }
+    return hipSuccess;
+}
+
+__global__ __launch_bounds__(COPY_THREADS) void ride_kernel(const RideList g) { ride<COPY_THREADS>(g, blockIdx.x); }
+
+hipError_t launch_riders(const Riders &r, hipStream_t s)
+{
+    RideList g;
+    const hipError_t e = ride_list(r, 512, &g);
+    if (e != hipSuccess || g.blocks == 0) return e;
+    hipLaunchKernelGGL(ride_kernel, dim3(g.blocks), dim3(COPY_THREADS), 0, s, g);
     return hipGetLastError();
 }
 

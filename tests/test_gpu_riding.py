@@ -1,0 +1,209 @@
+"""Passes whose transfers ride in the GEMM launches (narrow shards) against the same passes on three streams: same
+outputs, same gradients, same store, bit for bit (no sum here is split along K).  A test delay on any stream, here one
+microsecond, keeps a pass on the streams."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2311_01635_amd import binding as B
+from paper_2311_01635_amd.layers import RtpLinear, RtpMlp
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TD = {B.RTP_BF16: torch.bfloat16, B.RTP_F16: torch.float16, B.RTP_F32: torch.float32}
+DB, IS = B.RTP_DOUBLE_BUFFER, B.RTP_INPLACE_STAGED
+
+
+def normal(seed, *shape, dtype=torch.float32):
+    return torch.randn(*shape, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV).to(dtype)
+
+
+def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb")):
+    """Several passes in a row, so that what a pass leaves in the buffers is picked up by the next; every output of each."""
+    scratch = torch.zeros(2, dtype=torch.int64, device=DEV)
+    B.check(B.lib.rtp_ring_set_test_delay_compute(ring, B._ptr(scratch), 1 if streams else 0), "delay")
+    out = []
+    for t in layer.buf_w + layer.buf_g:
+        if t is not None:
+            t.fill_(255)                       # nothing is legally read before it is written
+    for p in plan:
+        if "z" in p:
+            layer.zero_grads()
+        Y, dX = torch.empty_like(dY), torch.empty_like(X)
+        layer.forward(X, Y)
+        out.append(Y)
+        if "b" in p:
+            layer.backward(X, dY, dX)
+            out.append(dX)
+    layer.sync()
+    held = B.lib.rtp_ring_resident_grad(ring)
+    W, G = layer.gathered()
+    if linear:
+        W, G = (W,), (G,)
+    out += list(W) + list(G) + [layer.home_w.clone(), layer.home_g.clone()]
+    assert (scratch[0].item() > 0) == streams
+    return out, held
+
+
+def same(make, X, dY, linear):
+    runs = []
+    for streams in (False, True):
+        layer = make()
+        ring = layer.ring.handle if linear else B.lib.rtp_mlp_ring(layer.handle)
+        runs.append(passes(layer, ring, X, dY, linear, streams))
+        layer.close()
+    (a, held_a), (b, held_b) = runs
+    assert held_a == held_b
+    assert all(torch.isfinite(t.float()).all() for t in a[:-2])
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), i
+
+
+@pytest.mark.parametrize("aux", [True, False])
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("n,rank", [(2, 0), (2, 1), (3, 1), (8, 7)])
+@pytest.mark.parametrize("split", [B.RTP_SPLIT_OUT, B.RTP_SPLIT_IN])
+@pytest.mark.parametrize("dtype,bias", [(B.RTP_BF16, False), (B.RTP_BF16, True), (B.RTP_F16, True), (B.RTP_F32, False), (B.RTP_F32, True)])
+def test_linear_layer(dtype, bias, split, n, rank, mode, aux):
+    if not aux and n != 3:
+        pytest.skip("one partition without an auxiliary stream is enough")
+    td, u = TD[dtype], 32 if dtype == B.RTP_F16 else 8
+    T = {B.RTP_F16: 96, B.RTP_BF16: 75, B.RTP_F32: 33}[dtype]
+    part, other = n * u * 3, 136 if dtype != B.RTP_F16 else 160
+    O, I = (part, other) if split == B.RTP_SPLIT_OUT else (other, part)
+    X, dY, W = normal(1, T, I, dtype=td), normal(2, T, O, dtype=td), normal(3, O, I) * 0.1
+    g0, b = normal(4, O, I), normal(5, O) if bias else None
+    make = lambda: RtpLinear(W, T, n, rank, split, mode, dtype, G0=g0, bias=b, aux_stream=aux)
+    same(make, X, dY, True)
+
+
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("n,rank", [(2, 1), (3, 0), (8, 3)])
+@pytest.mark.parametrize("act,bias,dtype", [(B.RTP_ACT_GELU_ERF, False, B.RTP_BF16), (B.RTP_ACT_GELU_TANH, True, B.RTP_F16),
+                                            (B.RTP_ACT_SWIGLU, True, B.RTP_BF16), (B.RTP_ACT_SWIGLU, False, B.RTP_F32)])
+def test_mlp_unit(act, bias, dtype, n, rank, mode):
+    td, u = TD[dtype], 32 if dtype == B.RTP_F16 else 8
+    T, I, O, O2 = (96 if dtype == B.RTP_F16 else 77), 128, n * u * 3, 160
+    shapes = [(O, I)] * (2 if act == B.RTP_ACT_SWIGLU else 1) + [(O2, O)]
+    X, dY = normal(1, T, I, dtype=td), normal(2, T, O2, dtype=td)
+    ws, g0 = [normal(3 + i, *s) * 0.1 for i, s in enumerate(shapes)], [normal(13 + i, *s) for i, s in enumerate(shapes)]
+    bs = [normal(23 + i, s[0]) for i, s in enumerate(shapes)] if bias else None
+    make = lambda: RtpMlp(ws, T, n, rank, act, mode, dtype, G0=g0, biases=bs)
+    same(make, X, dY, False)
+
+
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("kind", ["linear", "mlp"])
+def test_gradients_whose_sum_is_split_along_k_travel_by_copy(kind, mode):
+    """A split sum is added onto the buffer and sent from there by the next launches: integers, so that any order of the
+    sum gives the same bits."""
+    T, n, rank = 4096, 4, 1
+    X, dY = [torch.randint(-2, 3, (T, 256), generator=torch.Generator().manual_seed(s)).to(DEV, torch.bfloat16) for s in (1, 2)]
+    W = torch.randint(-1, 2, (256, 256), generator=torch.Generator().manual_seed(3)).float()
+    if kind == "linear":
+        make = lambda: RtpLinear(W, T, n, rank, B.RTP_SPLIT_OUT, mode, G0=torch.ones(256, 256, device=DEV))
+        same(make, X, dY, True)
+        return
+    W1, W2 = W.repeat(2, 1), torch.zeros(256, 512)
+    W2[torch.arange(256), torch.arange(256) * 2] = 1.0
+    outs = []
+    for streams in (False, True):                # the activation's values are no integers: the sums agree to fp32 rounding
+        layer = RtpMlp([W1, W2], T, n, rank, B.RTP_ACT_GELU_ERF, mode)
+        outs.append(passes(layer, B.lib.rtp_mlp_ring(layer.handle), X, dY, False, streams, ("fb", "fb"))[0][:-2])
+        layer.close()
+    for x, y in zip(*outs):                      # 4 x sqrt(4096) roundings of 2^-24 of the sum's size
+        assert (x.double() - y.double()).norm() <= 2e-5 * y.double().norm()
+
+
+def test_two_layers_on_one_ring_and_a_bare_ring():
+    """Two layers share the ring's rotations: the transfers ride in the launch of the first; a ring without layers sends
+    them alone."""
+    T, I, O, n, rank = 64, 64, 96, 4, 2
+    for streams in (False, True):
+        wb, gb = 2 * (O // n) * I * 2, 2 * (O // n) * I * 4
+        home_w, home_g = normal(1, n, wb // 2, dtype=torch.bfloat16).view(torch.uint8), torch.zeros(n, gb, dtype=torch.uint8, device=DEV)
+        bufs = [torch.full((s,), 255, dtype=torch.uint8, device=DEV) for s in (wb, wb, gb, gb)]
+        cs, ss, aux = (torch.cuda.Stream() for _ in range(3))
+        ring = B.Ring(n, rank, DB, wb, gb, home_w, home_g, bufs[:2], bufs[2:], cs, ss, aux_stream=aux)
+        acc = [torch.empty(T, I, device=DEV) for _ in range(2)]
+        lins = [B.Linear(ring, T, I, O, B.RTP_SPLIT_OUT, B.RTP_BF16, B.RTP_ACT_NONE, i * wb // 2, i * gb // 2, None, acc[i]) for i in range(2)]
+        X, dY = normal(2, T, I, dtype=torch.bfloat16), normal(3, T, O, dtype=torch.bfloat16)
+        Y, dX = [torch.empty(T, O, device=DEV, dtype=torch.bfloat16) for _ in range(2)], [torch.empty_like(X) for _ in range(2)]
+        scratch = torch.zeros(2, dtype=torch.int64, device=DEV)
+        B.check(B.lib.rtp_ring_set_test_delay_compute(ring.handle, B._ptr(scratch), 1 if streams else 0), "delay")
+        torch.cuda.synchronize()
+        ring.begin(B.RTP_PASS_FWD)
+        for t in range(n):
+            if t < n - 1:
+                ring.rotate_step(B.RTP_CW, t)
+            for i in range(2):
+                lins[i].fwd(t, X, Y[i])
+        ring.end()
+        ring.begin(B.RTP_PASS_BWD)
+        for t in range(n):
+            if t < n - 1:
+                ring.rotate_step(B.RTP_CCW, t)
+            if t < n - 2:
+                for i in (1, 0):
+                    lins[i].bwd(t, X, dY, dX[i])
+        for i in range(2):                       # at the end of a pass one layer may run a step ahead of the other
+            for t in (n - 2, n - 1):
+                lins[i].bwd(t, X, dY, dX[i])
+        ring.end()
+        ring.flush()
+        ring.sync()
+        got = [t.clone() for t in Y + dX + [home_w, home_g]]
+        if streams:
+            for x, y in zip(got, want):
+                assert torch.equal(x, y)
+        want = got
+        for l in lins:
+            l.close()
+        ring.close()
+    W = normal(1, n, 256).view(torch.uint8)
+    bufs = [torch.full((1024,), 255, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    ring = B.Ring(n, rank, DB, 1024, 0, W, None, bufs, (None, None), cs, ss, aux_stream=aux)
+    keep = W.clone()
+    torch.cuda.synchronize()
+    ring.begin(B.RTP_PASS_FWD)
+    for t in range(n - 1):
+        ring.rotate_step(B.RTP_CW, t)
+    ring.end()
+    ring.sync()
+    assert torch.equal(W, keep) and torch.equal(bufs[(n - 1) & 1], W[(rank + 1) % n]) and torch.equal(bufs[n & 1], W[(rank + 2) % n])
+    ring.close()
+
+
+class Seg(C.Structure):
+    _fields_ = [("out", C.c_void_p), ("buf", C.c_void_p), ("src", C.c_void_p), ("bytes", C.c_size_t)]
+
+
+class Riders(C.Structure):
+    _fields_ = [("count", C.c_int), ("seg", Seg * 8)]
+
+
+def test_segments_of_every_kind_and_size():
+    """out <- buf <- in, with either end missing, from one unit to past a workgroup's 64 KB; nothing beyond them is touched."""
+    launch = getattr(B.lib, "_ZN3rtp13launch_ridersERKNS_6RidersEP12ihipStream_t")
+    launch.restype, launch.argtypes = C.c_int, [C.POINTER(Riders), C.c_void_p]
+    for units in (1, 255, 1023, 1024, 1025, 4095, 4096, 4097, 70001):
+        for count in (1, 3, 8):
+            r, state = Riders(), []
+            r.count = count
+            for i in range(count):
+                out, buf, src = (torch.randint(0, 2 ** 31, (units * 4 + 8,), dtype=torch.int32, device=DEV) for _ in range(3))
+                kind = i % 3
+                r.seg[i] = Seg(out.data_ptr() + 16 if kind != 1 else None, buf.data_ptr() + 16, src.data_ptr() + 16 if kind != 2 else None, units * 16)
+                state.append((kind, out, buf, src, out.clone(), buf.clone(), src.clone()))
+            torch.cuda.synchronize()
+            assert launch(C.byref(r), torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            for kind, out, buf, src, o0, b0, s0 in state:
+                if kind != 1:
+                    o0[4:-4] = b0[4:-4]
+                if kind != 2:
+                    b0[4:-4] = s0[4:-4]
+                assert torch.equal(out, o0) and torch.equal(buf, b0) and torch.equal(src, s0), (units, count, kind)
+    r.seg[0].bytes = 8                            # not whole units: refused
+    assert launch(C.byref(r), torch.cuda.current_stream().cuda_stream) != 0
