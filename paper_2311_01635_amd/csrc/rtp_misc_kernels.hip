@@ -7,6 +7,8 @@
 
 namespace rtp {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
 // ---- fp32 GEMM: 64x64 tile, 256 threads, 4x4 outputs per thread -------------------
 // LDS holds A as [BK][64] and B as [BK][64] whatever the HBM layout, so the
 // inner product reads both with unit stride.
@@ -24,7 +26,7 @@ struct F32Group {
 };
 
 template <int LAY>
-__device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, const int m0, const int n0, float (&sA)[FK][FT + 4], float (&sB)[FK][FT + 4])
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, const int m0, const int n0, float (*sA)[FT + 4], float (*sB)[FT + 4])
 {
     const float *A = (const float *)p.A, *B = (const float *)p.B;
     const int tid = threadIdx.x;
@@ -88,29 +90,153 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, const int m0, c
     }
 }
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Group g)
+// ---- the same for outputs of few tiles: 16x32, 128 threads, 2x2 outputs per thread -----------------
+// Bound: latency (a 64 x 128 output over K = 256 is 4 MFLOP).  64x64 tiles put it on two compute units, each waiting for
+// its operands once per 16 K: 27.6 us, here 8.1 (128 x 256 over K = 64 11.9 -> 5.3).  Here it is 16 workgroups; the chunk of 64 K behind the one being multiplied is
+// already on its way in registers, 16 bytes a load where rows and pointers allow, and the sums an `+=` adds onto are
+// fetched ahead of the loop.  LDS holds both operands along K, read four K at a time: rows of 68 floats put the 16
+// columns a wave reads on all 64 banks.  An element is the same chain of fused multiply-adds in the order of K, with
+// the same bits.  A 32x32 tile of 256 threads would be bound by its LDS reads (four waves to one LDS) at twice the time.
+constexpr int SM = 16, SN = 32, SK = 64, SPITCH = SK + 4, STHR = 128;
+
+// ROWS x SK of an operand into registers: thread t's share, ROWS * SK / STHR floats in groups of four
+template <bool KC, int ROWS>
+__device__ __forceinline__ void f32_fetch(f32x4 (&v)[ROWS * SK / STHR / 4], const float *p, const int64_t ld, const int r0, const int rows,
+                                          const int k0, const int K, const bool wide)
 {
-    __shared__ float sA[FK][FT + 4];
-    __shared__ float sB[FK][FT + 4];
+    constexpr int G = ROWS * SK / STHR / 4, PER = KC ? SK / 4 : ROWS / 4; // groups along the contiguous dimension
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int t = threadIdx.x + i * STHR;
+        const int k = k0 + (KC ? t % PER * 4 : t / PER), r = r0 + (KC ? t / PER : t % PER * 4);
+        const int left = KC ? K - k : rows - r; // elements of the group that exist
+        const bool on = KC ? r < rows : k < K;
+        const float *q = p + (KC ? (int64_t)r * ld + k : (int64_t)k * ld + r);
+        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (on && left >= 4 && wide) {
+            x = *(const f32x4 *)q;
+        } else if (on) {
+            if (left > 0) x.x = q[0];
+            if (left > 1) x.y = q[1];
+            if (left > 2) x.z = q[2];
+            if (left > 3) x.w = q[3];
+        }
+        v[i] = x;
+    }
+}
+template <bool KC, int ROWS>
+__device__ __forceinline__ void f32_park(float (*lds)[SPITCH], const f32x4 (&v)[ROWS * SK / STHR / 4])
+{
+    constexpr int G = ROWS * SK / STHR / 4, PER = KC ? SK / 4 : ROWS / 4;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int t = threadIdx.x + i * STHR;
+        if (KC) {
+            *(f32x4 *)&lds[t / PER][t % PER * 4] = v[i];
+        } else {
+            const int k = t / PER, r = t % PER * 4;
+            lds[r][k] = v[i].x; lds[r + 1][k] = v[i].y; lds[r + 2][k] = v[i].z; lds[r + 3][k] = v[i].w;
+        }
+    }
+}
+
+template <int LAY>
+__device__ __forceinline__ void gemm_f32_small_tile(const GemmArgs &p, const int m0, const int n0, float (*sA)[SPITCH], float (*sB)[SPITCH])
+{
+    constexpr bool A_KC = LAY != LAY_TN, B_KC = LAY == LAY_NT;
+    const float *A = (const float *)p.A, *B = (const float *)p.B;
+    const bool wa = (p.lda & 3) == 0 && ((uintptr_t)A & 15) == 0, wb = (p.ldb & 3) == 0 && ((uintptr_t)B & 15) == 0;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    float *C = (float *)p.C;
+    float acc[2][2] = {}, old[2][2] = {};
+    f32x4 va[SM * SK / STHR / 4], vb[SN * SK / STHR / 4];
+    f32_fetch<A_KC, SM>(va, A, p.lda, m0, p.M, 0, p.K, wa);
+    f32_fetch<B_KC, SN>(vb, B, p.ldb, n0, p.N, 0, p.K, wb);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = m0 + ty + 8 * i, col = n0 + tx + 16 * j;
+            if (p.epi == EPI_ACC_ADD && row < p.M && col < p.N) old[i][j] = C[(int64_t)row * p.ldc + col];
+        }
+    for (int k0 = 0; k0 < p.K; k0 += SK) {
+        f32_park<A_KC, SM>(sA, va);
+        f32_park<B_KC, SN>(sB, vb);
+        __syncthreads();
+        if (k0 + SK < p.K) {
+            f32_fetch<A_KC, SM>(va, A, p.lda, m0, p.M, k0 + SK, p.K, wa);
+            f32_fetch<B_KC, SN>(vb, B, p.ldb, n0, p.N, k0 + SK, p.K, wb);
+        }
+#pragma unroll
+        for (int k = 0; k < SK; k += 4) { // (K indices past the end hold zeros)
+            f32x4 a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = *(const f32x4 *)&sA[ty + 8 * i][k];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) b[j] = *(const f32x4 *)&sB[tx + 16 * j][k];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = fmaf(a[i][u], b[j][u], acc[i][j]);
+        }
+        __syncthreads();
+    }
+    const float *bias = (const float *)p.bias;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = m0 + ty + 8 * i, col = n0 + tx + 16 * j;
+            if (row >= p.M || col >= p.N) continue;
+            C[(int64_t)row * p.ldc + col] = p.epi == EPI_ACC_ADD ? old[i][j] + acc[i][j] : acc[i][j] + (bias ? bias[col] : 0.0f);
+        }
+}
+
+template <bool SMALL>
+__global__ __launch_bounds__(SMALL ? STHR : 256) void gemm_f32_kernel(const F32Group g)
+{
+    __shared__ __attribute__((aligned(16))) float lds[(SM + SN) * SPITCH];
+    static_assert(2 * FK * (FT + 4) <= (SM + SN) * SPITCH, "both tiles' LDS");
     if (blockIdx.x >= g.tile_blocks) {
-        ride<256>(g.ride, blockIdx.x - g.tile_blocks);
+        ride<SMALL ? STHR : 256>(g.ride, blockIdx.x - g.tile_blocks);
         return;
     }
     const int q = g.count > 1 && blockIdx.x >= g.p[1].first ? 1 : 0;
     const unsigned b = blockIdx.x - g.p[q].first;
-    const int m0 = (int)(b / g.p[q].tiles_n) * FT, n0 = (int)(b % g.p[q].tiles_n) * FT;
-    switch (g.p[q].lay) {
-    case LAY_NT: gemm_f32_tile<LAY_NT>(g.p[q].a, m0, n0, sA, sB); break;
-    case LAY_NN: gemm_f32_tile<LAY_NN>(g.p[q].a, m0, n0, sA, sB); break;
-    default: gemm_f32_tile<LAY_TN>(g.p[q].a, m0, n0, sA, sB); break;
+    const int m = (int)(b / g.p[q].tiles_n), n = (int)(b % g.p[q].tiles_n);
+    if constexpr (SMALL) {
+        float(*sA)[SPITCH] = (float(*)[SPITCH])lds, (*sB)[SPITCH] = sA + SM;
+        switch (g.p[q].lay) {
+        case LAY_NT: gemm_f32_small_tile<LAY_NT>(g.p[q].a, m * SM, n * SN, sA, sB); break;
+        case LAY_NN: gemm_f32_small_tile<LAY_NN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
+        default: gemm_f32_small_tile<LAY_TN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
+        }
+    } else {
+        float(*sA)[FT + 4] = (float(*)[FT + 4])lds, (*sB)[FT + 4] = sA + FK;
+        switch (g.p[q].lay) {
+        case LAY_NT: gemm_f32_tile<LAY_NT>(g.p[q].a, m * FT, n * FT, sA, sB); break;
+        case LAY_NN: gemm_f32_tile<LAY_NN>(g.p[q].a, m * FT, n * FT, sA, sB); break;
+        default: gemm_f32_tile<LAY_TN>(g.p[q].a, m * FT, n * FT, sA, sB); break;
+        }
     }
 }
+
+// Up to this many small tiles the small tile is the faster one.  us, K = 1024, 64x64 -> 16x32: 256 tiles (512 x 256) 93.9 -> 24.2,
+// 1024 93.7 -> 32.8, 4096 (2048 x 1024) 143 -> 103, 8192 170 -> 182, 16384 307 -> 338, 32768 506 -> 677.
+constexpr int64_t F32_SMALL_MAX = 4096;
 
 hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s)
 {
     if (count < 0 || count > F32_MAX_GROUP) return hipErrorInvalidValue;
     F32Group g;
     memset(&g, 0, sizeof g);
+    int64_t small_tiles = 0;
+    for (int i = 0; i < count; ++i)
+        if (a[i].M > 0 && a[i].N > 0) small_tiles += (int64_t)((a[i].N + SN - 1) / SN) * ((a[i].M + SM - 1) / SM);
+    const bool small = small_tiles <= F32_SMALL_MAX;
+    const int tm = small ? SM : FT, tn = small ? SN : FT;
     int64_t blocks = 0;
     for (int i = 0; i < count; ++i) {
         if (a[i].M <= 0 || a[i].N <= 0) continue;
@@ -119,16 +245,20 @@ hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int cou
         auto &p = g.p[g.count++];
         p.a = a[i];
         p.lay = layouts[i];
-        p.tiles_n = (unsigned)((a[i].N + FT - 1) / FT);
+        p.tiles_n = (unsigned)((a[i].N + tn - 1) / tn);
         p.first = (unsigned)blocks;
-        blocks += (int64_t)p.tiles_n * ((a[i].M + FT - 1) / FT);
+        blocks += (int64_t)p.tiles_n * ((a[i].M + tm - 1) / tm);
     }
     if (g.count == 0) return launch_riders(r, s);
     if (blocks >= (int64_t)1 << 30) return hipErrorInvalidValue;
     g.tile_blocks = (unsigned)blocks;
     const hipError_t e = ride_list(r, 256, &g.ride);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3(g.tile_blocks + g.ride.blocks), dim3(256), 0, s, g);
+    const dim3 grid(g.tile_blocks + g.ride.blocks);
+    if (small)
+        hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(STHR), 0, s, g);
+    else
+        hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, s, g);
     return hipGetLastError();
 }
 
