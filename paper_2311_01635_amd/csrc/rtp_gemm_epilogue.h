@@ -107,6 +107,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[F
     float *ws = p.ws;
     float bj[FN];
     gemm_epilogue_bias<E, FN, NSTRIDE>(p, n0 + cl, bj);
+    // the piece of a bias that an fp32 sum takes in (GemmArgs::bias)
+    auto piece = [&](int col, float old) {
+        return p.bias && col >= p.half && col < p.half + ldaux ? old + (float)((const E *)p.bias)[col - p.half] : old;
+    };
 
     if (p.epi == EPI_SWIGLU_FWD) {
         const int half = p.half;
@@ -153,20 +157,20 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[F
             each([&](int row, int col, float x) { Cb[(int64_t)row * ldc + col] = (E)x; });
         break;
     case EPI_ACC_FIRST:
-        each([&](int row, int col, float x) { ws[(int64_t)row * ldws + col] = x; });
+        each([&](int row, int col, float x) { ws[(int64_t)row * ldws + col] = piece(col, x); });
         break;
     case EPI_ACC_ADD:
-        each([&](int row, int col, float x) { ws[(int64_t)row * ldws + col] += x; });
+        each([&](int row, int col, float x) { ws[(int64_t)row * ldws + col] = piece(col, ws[(int64_t)row * ldws + col]) + x; });
         break;
     case EPI_ACC_ATOMIC:
         each([&](int row, int col, float x) { unsafeAtomicAdd(ws + (int64_t)row * ldws + col, x); });
         break;
     case EPI_ACC_LAST:
         if (p.c_is_f32)
-            each([&](int row, int col, float x) { Cf[(int64_t)row * ldc + col] = ws[(int64_t)row * ldws + col] + x; });
+            each([&](int row, int col, float x) { Cf[(int64_t)row * ldc + col] = piece(col, ws[(int64_t)row * ldws + col]) + x; });
         else
             each([&](int row, int col, float x) {
-                Cb[(int64_t)row * ldc + col] = (E)(ws[(int64_t)row * ldws + col] + x);
+                Cb[(int64_t)row * ldc + col] = (E)(piece(col, ws[(int64_t)row * ldws + col]) + x);
             });
         break;
     case EPI_GELU_ERF_FWD:
@@ -251,8 +255,81 @@ __host__ __device__ inline bool gemm_epilogue_vec_ok(const GemmArgs &p)
     auto al = [](const void *q, int a) { return ((uintptr_t)q & (uintptr_t)(a - 1)) == 0; };
     bool ok = (p.ldc & 3) == 0 && al(p.C, 16);
     if (p.epi == EPI_ACC_FIRST || p.epi == EPI_ACC_ADD || p.epi == EPI_ACC_LAST || p.epi == EPI_ACC_ATOMIC) ok = ok && (p.ldws & 3) == 0 && al(p.ws, 16);
+    if (p.bias && p.epi >= EPI_ACC_FIRST && p.epi <= EPI_ACC_LAST) ok = ok && ((p.half | (int)p.ldaux) & 3) == 0 && al(p.bias, 8);
     if (p.epi >= EPI_GELU_ERF_FWD && p.epi <= EPI_SWIGLU_BWD) ok = ok && (p.ldaux & 3) == 0 && al(p.aux, 8) && (p.half & 3) == 0;
     return ok && (p.N & 3) == 0;
+}
+
+// The staged epilogue for operands that four-wide accesses do not fit (a leading dimension or a pointer of odd
+// alignment): the parked fragment row is read back one float per lane, 32 consecutive columns of each fragment.
+template <typename E, int FM, int FN, int NSTRIDE>
+__device__ __forceinline__ void gemm_epilogue_staged_single(const GemmArgs &p, f32x16 (&acc)[FM][FN], float *wlds,
+                                                            int rbase_wave, int n0, int wn32, int lane)
+{
+    static_assert(FN == 2, "staging layout is written for two 32-column fragments per wave");
+    const int64_t ldc = p.ldc, ldws = p.ldws, ldaux = p.ldaux;
+    const int half = p.half, l32 = lane & 31, frag = lane >> 5;
+    E *Cb = (E *)p.C, *aux = (E *)p.aux;
+    float *Cf = (float *)p.C, *ws = p.ws;
+    float bj[FN];
+    gemm_epilogue_bias<E, FN, NSTRIDE>(p, n0 + wn32 + l32, bj);
+    const bool paired = p.epi == EPI_SWIGLU_FWD;
+    const int col = n0 + (paired ? 0 : frag * NSTRIDE) + wn32 + l32;
+    const bool in = paired ? frag == 0 && col < half : col < p.N; // (paired: the first half-wave takes both of a pair)
+    const bool pieced = p.bias && p.epi >= EPI_ACC_FIRST && p.epi <= EPI_ACC_LAST && col >= half && col < half + ldaux;
+    const float pv = pieced ? (float)((const E *)p.bias)[col - half] : 0.0f;
+    auto piece = [&](float old) { return pieced ? old + pv : old; };
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                wlds[(8 * (v >> 2) + 4 * frag + (v & 3)) * EPI_LDS_PITCH + j * 32 + l32] = acc[i][j][v] + bj[j];
+        __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): the wave's own writes have landed
+        __builtin_amdgcn_wave_barrier();
+        const int rows = min(32, p.M - (rbase_wave + i * 32));
+#pragma unroll 1
+        for (int r = 0; r < rows; ++r) {
+            const int64_t row = rbase_wave + i * 32 + r;
+            const float x = wlds[r * EPI_LDS_PITCH + lane], up = wlds[r * EPI_LDS_PITCH + 32 + l32];
+            if (!in) continue;
+            switch (p.epi) {
+            case EPI_STORE:
+                if (p.c_is_f32) Cf[row * ldc + col] = x;
+                else Cb[row * ldc + col] = (E)x;
+                break;
+            case EPI_ACC_FIRST: ws[row * ldws + col] = piece(x); break;
+            case EPI_ACC_ADD: ws[row * ldws + col] = piece(ws[row * ldws + col]) + x; break;
+            case EPI_ACC_ATOMIC: unsafeAtomicAdd(ws + row * ldws + col, x); break;
+            case EPI_ACC_LAST:
+                if (p.c_is_f32) Cf[row * ldc + col] = piece(ws[row * ldws + col]) + x;
+                else Cb[row * ldc + col] = (E)(piece(ws[row * ldws + col]) + x);
+                break;
+            case EPI_GELU_ERF_FWD:
+            case EPI_GELU_TANH_FWD:
+                aux[row * ldaux + col] = (E)x;
+                Cb[row * ldc + col] = (E)(p.epi == EPI_GELU_ERF_FWD ? gelu_erf(x) : gelu_tanh(x));
+                break;
+            case EPI_SWIGLU_FWD:
+                aux[row * ldaux + col] = (E)x;
+                aux[row * ldaux + half + col] = (E)up;
+                Cb[row * ldc + col] = (E)(silu(x) * up);
+                break;
+            case EPI_GELU_ERF_BWD: Cb[row * ldc + col] = (E)(x * gelu_erf_grad((float)aux[row * ldaux + col])); break;
+            case EPI_GELU_TANH_BWD: Cb[row * ldc + col] = (E)(x * gelu_tanh_grad((float)aux[row * ldaux + col])); break;
+            case EPI_SWIGLU_BWD: {
+                const float a = (float)aux[row * ldaux + col], b = (float)aux[row * ldaux + half + col];
+                Cb[row * ldc + col] = (E)(x * b * silu_grad(a));
+                Cb[row * ldc + half + col] = (E)(x * silu(a));
+                break;
+            }
+            default: break;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f); // the row has been read before the next is parked
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 template <typename E, int FM, int FN, int NSTRIDE>
@@ -271,6 +348,16 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
     const int wrow = 4 * (lane >> 5), wcol = lane & 31;
     float bj[FN];
     gemm_epilogue_bias<E, FN, NSTRIDE>(p, n0 + wn32 + wcol, bj);
+    // The piece of a bias that an fp32 sum takes in (GemmArgs::bias): a lane touches the same four columns of every row, so
+    // it holds their entries, zero outside the piece.
+    f32x4 pv = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bool pieced = p.bias && p.epi >= EPI_ACC_FIRST && p.epi <= EPI_ACC_LAST;
+    if (pieced) {
+        const int c4 = lane & 15, at = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4 - half;
+        if (at >= 0 && at < (int)ldaux) pv = from_elem4<E>(*(const out4 *)((const E *)p.bias + at));
+    }
+    auto piece = [&](f32x4 old) { return pieced ? old + pv : old; };
+    // (loops of their own for sums with a piece: a select in the others cost the units without a bias 0.5-1 %)
 
     // park fragment row i: rows 8*(v/4) + 4*(lane/32) + v%4, columns j*32 + lane%32
     auto park = [&](int i) {
@@ -403,14 +490,19 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
             each([&](int r, int c, f32x4 x) { *(out4 *)(Cb + (int64_t)r * ldc + c) = to_elem4<E>(x); });
         break;
     case EPI_ACC_FIRST:
-        each([&](int r, int c, f32x4 x) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = x; });
+        if (pieced)
+            each([&](int r, int c, f32x4 x) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = x + pv; });
+        else
+            each([&](int r, int c, f32x4 x) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = x; });
         break;
     case EPI_ACC_ADD:
-        if (landed)
+        if (landed && pieced)
+            each_rw_landed([&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = (old + pv) + x; });
+        else if (landed)
             each_rw_landed([&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = old + x; });
         else
             each_rw([&](int r, int c) { return *(const f32x4 *)(ws + (int64_t)r * ldws + c); },
-                    [&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = old + x; });
+                    [&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(ws + (int64_t)r * ldws + c) = piece(old) + x; });
         break;
     case EPI_ACC_ATOMIC:
         // one float per lane, 32 consecutive lanes on 32 consecutive columns: an atomic instruction
@@ -430,16 +522,18 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
         }
         break;
     case EPI_ACC_LAST:
-        if (landed && p.c_is_f32)
+        if (landed && p.c_is_f32 && !pieced)
             each_rw_landed([&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(Cf + (int64_t)r * ldc + c) = old + x; });
-        else if (landed)
+        else if (landed && !p.c_is_f32 && !pieced)
             each_rw_landed([&](int r, int c, f32x4 x, f32x4 old) { *(out4 *)(Cb + (int64_t)r * ldc + c) = to_elem4<E>(old + x); });
+        else if (landed && !p.c_is_f32)
+            each_rw_landed([&](int r, int c, f32x4 x, f32x4 old) { *(out4 *)(Cb + (int64_t)r * ldc + c) = to_elem4<E>((old + pv) + x); });
         else if (p.c_is_f32)
             each_rw([&](int r, int c) { return *(const f32x4 *)(ws + (int64_t)r * ldws + c); },
-                    [&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(Cf + (int64_t)r * ldc + c) = old + x; });
+                    [&](int r, int c, f32x4 x, f32x4 old) { *(f32x4 *)(Cf + (int64_t)r * ldc + c) = piece(old) + x; });
         else
             each_rw([&](int r, int c) { return *(const f32x4 *)(ws + (int64_t)r * ldws + c); },
-                    [&](int r, int c, f32x4 x, f32x4 old) { *(out4 *)(Cb + (int64_t)r * ldc + c) = to_elem4<E>(old + x); });
+                    [&](int r, int c, f32x4 x, f32x4 old) { *(out4 *)(Cb + (int64_t)r * ldc + c) = to_elem4<E>(piece(old) + x); });
         break;
     case EPI_GELU_ERF_FWD:
         each([&](int r, int c, f32x4 x) {

@@ -91,7 +91,9 @@ struct PpProblem {
 };
 struct PpGroup {
     int count;
-    unsigned tile_blocks; // workgroups from here on carry the transfers
+    // workgroups in the order of their index: the bias sums (a chain of reads each, so they start first; padded to whole
+    // rounds over the XCDs), the tiles, the transfers (they fill the tiles' last round)
+    unsigned sum_blocks, tile_blocks;
     PpProblem p[PP_MAX_GROUP];
     RideList ride;
 };
@@ -125,6 +127,7 @@ template <typename V8, int KS, int ROWB> __device__ __forceinline__ V8 frag_mc_r
 } // namespace rtp
 #include "rtp_gemm_small.h"
 namespace rtp {
+static_assert(COLSUM_LDS_FLOATS * 4 <= pp::SMEM_BYTES, "a bias sum fits the workgroup's LDS");
 static_assert(pps::RING_BYTES <= pp::SMEM_BYTES && pps::EPI_BYTES <= pp::SMEM_BYTES, "the small tile fits the workgroup's LDS");
 
 // One BM x 256 tile over the K sub-tiles [kt_begin, kt_begin + kt_count): `pid` is the tile's index inside its
@@ -448,7 +451,8 @@ __device__ __forceinline__ void pp_tile(const GemmArgs &p, const int tiles_m, co
                                               m0 + wm * (BM / WM), n0, wn * 32, lane,
                                               smem + (pp::NTHR / 64) * EPI_LDS_BYTES_PER_WAVE + wave * EPI_LAND_BYTES_PER_WAVE);
     else
-        gemm_epilogue<E, FM, FN, WN * 32>(p, acc, m0 + wm * (BM / WM) + 4 * (lane >> 5), n0, wn * 32 + (lane & 31));
+        gemm_epilogue_staged_single<E, FM, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * (BM / WM), n0,
+                                                        wn * 32, lane);
 
     // ---- producer: the tile's results are visible device-wide before the counters say so
     if (p.sync_signal) {
@@ -477,12 +481,17 @@ template <int LAY, typename E>
 __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
 {
     __shared__ __attribute__((aligned(1024))) char smem[pp::SMEM_BYTES];
-    if (blockIdx.x >= g.tile_blocks) {
-        ride<pp::NTHR>(g.ride, blockIdx.x - g.tile_blocks);
+    if (blockIdx.x < g.sum_blocks) {
+        if (blockIdx.x < g.ride.sum_blocks) ride_sum<E, pp::NTHR>(g.ride, blockIdx.x, (float *)smem);
         return;
     }
-    const int xcd = blockIdx.x & 7;
-    int l = blockIdx.x >> 3;
+    const unsigned tile_block = blockIdx.x - g.sum_blocks;
+    if (tile_block >= g.tile_blocks) {
+        ride<pp::NTHR>(g.ride, tile_block - g.tile_blocks);
+        return;
+    }
+    const int xcd = tile_block & 7;
+    int l = tile_block >> 3;
     int q = 0, pid = -1;
     for (; q < g.count; ++q) {
         const int tiles = g.p[q].tiles_m * g.p[q].tiles_n * g.p[q].ksplit;
@@ -519,7 +528,7 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
 template <int LAY, typename E>
 static hipError_t launch_gemm_pp_layout(const PpGroup &g, hipStream_t s, hipEvent_t done)
 {
-    const unsigned blocks = g.tile_blocks + g.ride.blocks;
+    const unsigned blocks = g.sum_blocks + g.tile_blocks + g.ride.blocks;
     if (done)
         hipExtLaunchKernelGGL((gemm_pp_kernel<LAY, E>), dim3(blocks), dim3(pp::NTHR), 0, s, nullptr, done, 0, g);
     else

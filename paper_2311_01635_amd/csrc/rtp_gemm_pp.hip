@@ -352,6 +352,9 @@ static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a
     if (riders) {
         const hipError_t e = ride_list(*riders, std::max(64, compute_units() - (int)std::min<long>(tiles, 1 << 20)), &g.ride);
         if (e != hipSuccess) return e;
+        g.sum_blocks = (g.ride.sum_blocks + 7) / 8 * 8;
+        for (int i = 0; i < riders->sums; ++i)
+            if (riders->sum[i].elem != a[0].elem) return hipErrorInvalidValue;
     }
     const bool f16 = a[0].elem == ELEM_F16;
     switch (layout) {

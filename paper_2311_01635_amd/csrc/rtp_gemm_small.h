@@ -217,7 +217,7 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
         gemm_epilogue_staged<E, 1, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * 32, n0, wn * 32, lane,
                                                 smem + 4 * EPI_LDS_BYTES_PER_WAVE + wave * EPI_LAND_BYTES_PER_WAVE);
     else
-        gemm_epilogue<E, 1, FN, WN * 32>(p, acc, m0 + wm * 32 + 4 * (lane >> 5), n0, wn * 32 + (lane & 31));
+        gemm_epilogue_staged_single<E, 1, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * 32, n0, wn * 32, lane);
 }
 
 } // namespace rtp

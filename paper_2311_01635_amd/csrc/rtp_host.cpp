@@ -404,9 +404,9 @@ static bool ring_carries(const rtp_ring *r, rtp_pass pass);
 // the transfers asked for so far as a launch of their own
 static rtp_status carry_flush(rtp_ring *r)
 {
-    if (r->pend.count == 0) return RTP_OK;
+    if (r->pend.count == 0 && r->pend.sums == 0) return RTP_OK;
     const Riders p = r->pend;
-    r->pend.count = 0;
+    r->pend.count = r->pend.sums = 0;
     HIP_TRY(launch_riders(p, r->cs()));
     return RTP_OK;
 }
@@ -417,6 +417,14 @@ static rtp_status carry_add(rtp_ring *r, void *out, void *buf, const void *in, s
     if (bytes == 0) return RTP_OK;
     if (r->pend.count == RIDE_MAX_SEGS) RTP_TRY(carry_flush(r));
     r->pend.seg[r->pend.count++] = RideSeg{out, buf, in, bytes};
+    return RTP_OK;
+}
+
+// a bias gradient with the next launch
+static rtp_status carry_sum(rtp_ring *r, const RideSum &sum)
+{
+    if (r->pend.sums == RIDE_MAX_SUMS) RTP_TRY(carry_flush(r));
+    r->pend.sum[r->pend.sums++] = sum;
     return RTP_OK;
 }
 
@@ -654,7 +662,7 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
     RTP_TRY(ensure_events(r));
     r->carry = r->may_carry && ring_carries(r, pass);
     r->may_carry = true;
-    r->pend.count = 0;
+    r->pend.count = r->pend.sums = 0;
     RTP_TRY(begin_join(r));
     r->joined = r->carry;
     r->pass = pass;
@@ -919,7 +927,7 @@ extern "C" rtp_status rtp_ring_abort(rtp_ring *r)
     r->pass = RTP_PASS_IDLE;
     r->joined = false;
     r->carry = false;
-    r->pend.count = 0;
+    r->pend.count = r->pend.sums = 0;
     r->pass_uses_as = true;
     r->resident = -1;
     r->w_held = false;
@@ -1146,7 +1154,7 @@ static rtp_status gemm_riding(rtp_linear *l, const int *layouts, GemmArgs *a, in
         return RTP_OK;
     }
     const Riders p = r->pend;
-    r->pend.count = 0;
+    r->pend.count = r->pend.sums = 0;
     if (f32)
         HIP_TRY(launch_gemm_f32_riding(layouts, a, count, p, r->cs()));
     else
@@ -1238,23 +1246,22 @@ static rtp_status linear_fwd_step(rtp_linear *l, int step, const void *X, void *
                 HIP_TRY(hipStreamWaitEvent(fs, r->ev_w[step & 1], 0));
         }
         // The bias of this layer is spread over the shards in pieces; shard k's piece, which follows
-        // its matrix in the slot, is added to its entries of every output row at shard k's step:
-        // onto the fp32 sum (after the kernel that starts it, before the kernel that rounds it),
-        // or inside the kernel when there is only one step.
+        // its matrix in the slot, is added to its entries of every output row at shard k's step, in the
+        // GEMM's epilogue: to the product when there is only one step, else to the fp32 sum.  (fp32
+        // layers: a kernel of its own behind the GEMM.)
         const int64_t pb = d.has_bias ? rtp_bias_piece_width(d.O, n, d.dtype) : 0;
         const int64_t pv = d.has_bias ? std::max<int64_t>(0, std::min<int64_t>(pb, d.O - (int64_t)k * pb)) : 0;
         const char *bk = Wk + (size_t)d.O * o * es;
-        const int belem = f32 ? -1 : d.dtype == RTP_F16 ? ELEM_F16 : ELEM_BF16;
-        const bool live = pv > 0 && !r->dry && r->abl_compute && d.T > 0;
-        float *bdst = (f32 ? (float *)Y : acc) + (size_t)k * pb;
-        bool after = false;
-        if (live) {
-            if (f32 || (n > 1 && step == 0)) after = true;
-            else if (n == 1) a.bias = bk;
-            else HIP_TRY(launch_bias_add(belem, bdst, d.O, (int)d.T, (int)pv, bk, fs));
+        if (pv > 0 && !f32) {
+            a.bias = bk;
+            if (n > 1) {
+                a.half = (int)(k * pb);
+                a.ldaux = pv;
+            }
         }
         RTP_TRY(launch(fs));
-        if (after) HIP_TRY(launch_bias_add(belem, bdst, d.O, (int)d.T, (int)pv, bk, fs));
+        if (pv > 0 && f32 && !r->dry && r->abl_compute && d.T > 0)
+            HIP_TRY(launch_bias_add((float *)Y + (size_t)k * pb, d.O, (int)d.T, (int)pv, (const float *)bk, fs));
     }
     if (r->carry) RTP_TRY(carry_flush(r)); // (a layer without tokens launches nothing)
     l->next_step = step + 1;
@@ -1443,12 +1450,6 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
         a.epi = EPI_ACC_LAST;
         a.C = r->home_g(k) + d.g_offset;
     }
-    if (paired) {
-        GemmArgs both[2] = {dx_args(), a};
-        RTP_TRY(gemm_riding(l, pair_lay, both, 2));
-    } else if (d.T > 0) {
-        RTP_TRY(r->carry ? gemm_riding(l, LAY_TN, a) : gemm(l, LAY_TN, a, ws));
-    }
     if (d.has_bias && !r->dry && r->abl_compute) {
         // bias gradient: column sums of this shard's slice of dY, onto the entries that follow the
         // matrix gradient in the travelling shard (and out to where it travels, like the matrix part)
@@ -1460,9 +1461,19 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
         const float *gb_in = (const float *)((const char *)Gk + boff);
         float *gb_out = fused_send ? (float *)(r->home_g(k) + d.g_offset + boff) : (float *)((char *)Gk + boff);
         const int elem = f32 ? -1 : d.dtype == RTP_F16 ? ELEM_F16 : ELEM_BF16;
-        HIP_TRY(launch_colsum(elem, (const char *)dY + (size_t)k * pb * es, d.O, (int)d.T, (int)pv, gb_in, gb_out, ws));
+        const RideSum q{elem, (const char *)dY + (size_t)k * pb * es, d.O, (int)d.T, (int)pv, gb_in, gb_out};
+        if (r->carry && !f32)
+            RTP_TRY(carry_sum(r, q)); // rides in the launch below
+        else
+            HIP_TRY(launch_colsum(q.elem, q.Y, q.ld, q.rows, q.cols, q.in, q.out, ws));
         // (padding entries of a partly filled shard are zero in the buffer and in the slot alike, and nobody
         // writes them)
+    }
+    if (paired) {
+        GemmArgs both[2] = {dx_args(), a};
+        RTP_TRY(gemm_riding(l, pair_lay, both, 2));
+    } else if (d.T > 0) {
+        RTP_TRY(r->carry ? gemm_riding(l, LAY_TN, a) : gemm(l, LAY_TN, a, ws));
     }
 
     // ---- hand the gradient part to the stage stream ---------------------------
@@ -1703,18 +1714,15 @@ static GemmArgs mlp_args_down(const rtp_mlp *m, const MlpShapes &h, int k, int s
     a.C = Y; a.ldc = h.O2;
     a.epi = acc_epi(step, m->d.n);
     a.ws = m->d.acc_y_dev; a.ldws = h.O2;
-    if (h.has_bias && h.n == 1) a.bias = Wslot + h.wb2(); // one step: the whole bias, inside the kernel
+    // piece k of this linear's bias joins the sum in the epilogue (one step: the whole bias, to the product)
+    if (h.has_bias && h.pv2(k) > 0) {
+        a.bias = Wslot + h.wb2();
+        if (h.n > 1) {
+            a.half = (int)(k * h.pb2);
+            a.ldaux = h.pv2(k);
+        }
+    }
     return a;
-}
-
-// Piece k of the second linear's bias onto the fp32 sum of the unit's output (n > 1): its place in the
-// stream is after the launch that starts the sum (step 0) and before the launch of any later step.
-static rtp_status mlp_bias2_add(rtp_mlp *m, const MlpShapes &h, int k, const char *Wslot, hipStream_t st)
-{
-    rtp_ring *r = m->ring;
-    if (!h.has_bias || h.n == 1 || h.pv2(k) <= 0 || r->dry || !r->abl_compute || h.T <= 0) return RTP_OK;
-    HIP_TRY(launch_bias_add(h.belem, m->d.acc_y_dev + (size_t)k * h.pb2, h.O2, (int)h.T, (int)h.pv2(k), Wslot + h.wb2(), st));
-    return RTP_OK;
 }
 
 // The two bias gradients of step s (shard k) onto the travelling gradient shard in `Gslot`: column sums of
@@ -1726,12 +1734,14 @@ static rtp_status mlp_bias_grads(rtp_mlp *m, const MlpShapes &h, int k, char *Gs
     rtp_ring *r = m->ring;
     if (!h.has_bias || r->dry || !r->abl_compute || h.T <= 0) return RTP_OK;
     char *dst = home ? home : Gslot;
-    if (first)
-        HIP_TRY(launch_colsum(h.belem, (const char *)m->d.dpre_dev + (size_t)k * h.o1 * h.es, h.P1, (int)h.T, (int)h.o1,
-                              (const float *)(Gslot + h.gb1()), (float *)(dst + h.gb1()), st));
-    if (second && h.pv2(k) > 0)
-        HIP_TRY(launch_colsum(h.belem, (const char *)dY + (size_t)k * h.pb2 * h.es, h.O2, (int)h.T, (int)h.pv2(k),
-                              (const float *)(Gslot + h.gb2()), (float *)(dst + h.gb2()), st));
+    auto emit = [&](const char *Y, int64_t ld, int64_t cols, size_t off) -> rtp_status {
+        const RideSum q{h.belem, Y, ld, (int)h.T, (int)cols, (const float *)(Gslot + off), (float *)(dst + off)};
+        if (r->carry) return carry_sum(r, q); // rides in the next launch
+        HIP_TRY(launch_colsum(q.elem, q.Y, q.ld, q.rows, q.cols, q.in, q.out, st));
+        return RTP_OK;
+    };
+    if (first) RTP_TRY(emit((const char *)m->d.dpre_dev + (size_t)k * h.o1 * h.es, h.P1, h.o1, h.gb1()));
+    if (second && h.pv2(k) > 0) RTP_TRY(emit((const char *)dY + (size_t)k * h.pb2 * h.es, h.O2, h.pv2(k), h.gb2()));
     return RTP_OK;
 }
 
@@ -1856,18 +1866,8 @@ static rtp_status stage_after_compute(rtp_ring *r)
     return RTP_OK;
 }
 
-// one part [off, off + bytes) of the weight slot: send shard k's from buffer `src`, receive
-// shard kin's into buffer `dst`
-static rtp_status rotate_w_part(rtp_ring *r, int step, int k, int kin, int src, int dst, size_t off, size_t bytes)
-{
-    RTP_TRY(rotate_async(r, r->home_w(k) + off, (char *)r->d.buf_w_dev[src] + off, (char *)r->d.buf_w_dev[dst] + off,
-                         r->home_w(kin) + off, bytes, r->ss()));
-    r->rec(TR_W_OUT, step, k, src);
-    r->rec(TR_W_IN, step, kin, dst);
-    return RTP_OK;
-}
-
-// the same into a batch (src != dst: the staged modes)
+// one part [off, off + bytes) of the weight slot into a batch: send shard k's from buffer `src`, receive
+// shard kin's into buffer `dst` (src != dst: the staged modes)
 static rtp_status rotate_w_part(rtp_ring *r, CopyBatch &b, int step, int k, int kin, int src, int dst, size_t off, size_t bytes)
 {
     RTP_TRY(copy_batch_add(r, b, (char *)r->d.buf_w_dev[dst] + off, r->home_w(kin) + off, bytes, r->ss()));
@@ -1930,11 +1930,7 @@ static rtp_status mlp_fwd_grouped(rtp_mlp *m, const void *X, void *Y)
             g[cnt++] = mlp_args_z(m, h, r->shard_at(t), X, buf(t));
         }
         if (t >= 1) g[cnt++] = mlp_args_down(m, h, r->shard_at(t - 1), t - 1, buf(t - 1), Y);
-        if (t >= 2) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(t - 1), buf(t - 1), r->cs()));
-        const bool bias_after = t == 1 && h.has_bias && h.n > 1;
-        RTP_TRY(gemm_group(r, LAY_NT, g, cnt, r->cs(), rot && !bias_after ? r->ev_free : nullptr));
-        if (t == 1) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(0), buf(0), r->cs())); // the sum exists from here on
-        if (rot && bias_after) HIP_TRY(hipEventRecord(r->ev_free, r->cs()));
+        RTP_TRY(gemm_group(r, LAY_NT, g, cnt, r->cs(), rot ? r->ev_free : nullptr));
     }
     mlp_close_pass(m);
     return rtp_ring_end(r);
@@ -2160,7 +2156,7 @@ static rtp_status gemm_group_riding(rtp_ring *r, const int *layouts, const GemmA
         return RTP_OK;
     }
     const Riders p = r->pend;
-    r->pend.count = 0;
+    r->pend.count = r->pend.sums = 0;
     HIP_TRY(launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()));
     return RTP_OK;
 }
@@ -2198,9 +2194,7 @@ static rtp_status mlp_fwd_riding(rtp_mlp *m, const void *X, void *Y)
             g[cnt++] = mlp_args_z(m, h, r->shard_at(t), X, buf(t));
         }
         if (t >= 1) g[cnt++] = mlp_args_down(m, h, r->shard_at(t - 1), t - 1, buf(t - 1), Y);
-        if (t >= 2) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(t - 1), buf(t - 1), r->cs()));
         RTP_TRY(gemm_group_riding(r, lay, g, cnt));
-        if (t == 1) RTP_TRY(mlp_bias2_add(m, h, r->shard_at(0), buf(0), r->cs())); // the sum exists from here on
     }
     mlp_close_pass(m);
     return rtp_ring_end(r);
@@ -2263,14 +2257,14 @@ static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void
         GemmArgs g[2];
         first(s, g);
         sent2 = send(s, g, h.g_off2);
-        RTP_TRY(gemm_group_riding(r, lay, g, 2));
         RTP_TRY(mlp_bias_grads(m, h, k, gbuf(s), sent2 ? r->home_g(k) : nullptr, dY, false, true, r->cs()));
+        RTP_TRY(gemm_group_riding(r, lay, g, 2));
         if (kin >= 0 && !two_g)
             RTP_TRY(carry_add(r, sent2 ? nullptr : r->home_g(k) + h.g_off2, gbuf(s) + h.g_off2, r->home_g(kin) + h.g_off2, g2_bytes));
         second(s, g);
         sent1 = send(s, g, 0);
-        RTP_TRY(gemm_group_riding(r, lay, g, 2));
         RTP_TRY(mlp_bias_grads(m, h, k, gbuf(s), sent1 ? r->home_g(k) : nullptr, dY, true, false, r->cs()));
+        RTP_TRY(gemm_group_riding(r, lay, g, 2));
         if (kin >= 0) {
             if (two_g) {
                 m->l1->unsent[r->g_idx(s)] = !sent1;
@@ -2348,9 +2342,7 @@ static rtp_status mlp_fwd_fused(rtp_mlp *m, const void *X, void *Y)
         g[0].sync = g[1].sync = (int *)m->d.step_sync_dev;
         g[0].sync_signal = 1;
         g[1].sync_wait = (t + 1) * gemm_bf16_pp_tiles_n(g[0]); // every Z tile of the rows, of this and the earlier steps
-        if (t >= 1) RTP_TRY(mlp_bias2_add(m, h, k, W, r->cs()));
         RTP_TRY(gemm_group(r, LAY_NT, g, 2, r->cs()));
-        if (t == 0) RTP_TRY(mlp_bias2_add(m, h, k, W, r->cs()));
         m->l1->next_step = m->l2->next_step = t + 1;
     }
     return rtp_ring_end(r);
@@ -2463,9 +2455,7 @@ static rtp_status mlp_fwd_pipelined(rtp_mlp *m, const void *X, void *Y)
         if (rot && t >= 1) HIP_TRY(hipStreamWaitEvent(as, r->ev_w2[t & 1], 0));
         a = mlp_args_down(m, h, k, t, buf(t), Y);
         a.cu_share = 2;
-        if (t >= 1) RTP_TRY(mlp_bias2_add(m, h, k, buf(t), as));
         RTP_TRY(gemm_group(r, LAY_NT, &a, 1, as));
-        if (t == 0) RTP_TRY(mlp_bias2_add(m, h, k, buf(t), as)); // the sum exists from here on
         if (rot) RTP_TRY(w_part_turnover(r, t, r->ev_free2, as, h.w_off2, w2_bytes, r->ev_w2[t & 1]));
     }
     mlp_close_pass(m);

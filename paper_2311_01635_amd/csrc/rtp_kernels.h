@@ -36,7 +36,9 @@ struct GemmArgs {
     void *aux;          // pre-activations, in the input dtype
     int64_t ldaux;
     const void *bias;   // optional, input dtype, one per column of B's rows (N of them, the (gate | up) order for
-                        // EPI_SWIGLU_FWD): added to the product before EPI_STORE / EPI_*_FWD act on it
+                        // EPI_SWIGLU_FWD): added to the product before EPI_STORE / EPI_*_FWD act on it.
+                        // EPI_ACC_FIRST / _ADD / _LAST: a piece, ldaux entries for the columns from `half` on (both
+                        // multiples of 4), that joins the fp32 sum ahead of the product (_FIRST: behind it)
     int half;           // EPI_SWIGLU_FWD: N/2 ; EPI_SWIGLU_BWD: N
     int c_is_f32;       // EPI_STORE / EPI_ACC_LAST write fp32 instead of the input dtype
     int elem;           // ELEM_BF16 or ELEM_F16 (the ping-pong kernel only; the register-staged one is bf16)
@@ -84,14 +86,24 @@ struct RideSeg {
     const void *in;
     size_t bytes;
 };
-constexpr int RIDE_MAX_SEGS = 8;
+// a bias gradient, as launch_colsum computes it, of a matrix that earlier launches have completed
+struct RideSum {
+    int elem;
+    const void *Y;
+    int64_t ld;
+    int rows, cols;
+    const float *in;
+    float *out;
+};
+constexpr int RIDE_MAX_SEGS = 8, RIDE_MAX_SUMS = 2;
 struct Riders {
-    int count = 0;
+    int count = 0, sums = 0;
     RideSeg seg[RIDE_MAX_SEGS];
+    RideSum sum[RIDE_MAX_SUMS];
 };
 // Up to PP_MAX_GROUP independent GEMMs and the transfers in one launch of the tiled kernel.  layouts[i]: all LAY_NT, or
-// LAY_NN and LAY_TN in any mix (the input and the weight gradients of a backward step).  Nothing to compute: the
-// transfers alone.  hipErrorInvalidValue as launch_gemm_bf16_pp_group, before anything is launched.
+// LAY_NN and LAY_TN in any mix (the input and the weight gradients of a backward step).  Sums are of the GEMMs' element
+// type.  Nothing to compute: the transfers alone.  hipErrorInvalidValue as launch_gemm_bf16_pp_group, before anything is launched.
 hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
 // the K splits that launch would use
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);
@@ -102,7 +114,7 @@ hipError_t launch_riders(const Riders &r, hipStream_t s);
 hipError_t launch_gemm_f32(int layout, const GemmArgs &a, hipStream_t s);
 // up to F32_MAX_GROUP independent fp32 GEMMs and the transfers in one launch
 constexpr int F32_MAX_GROUP = 2;
-hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
+hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s); // (no sums)
 
 // elementwise pieces of the fp32 path (the bf16 path fuses them into the GEMMs)
 // kind: EPI_GELU_ERF_FWD / EPI_GELU_TANH_FWD / EPI_SWIGLU_FWD / *_BWD
@@ -137,9 +149,8 @@ hipError_t launch_gather_rows(void *out, const void *in, const int *perm, int ro
 // out[perm[p], :] = in[p, :] where perm[p] >= 0
 hipError_t launch_scatter_rows(void *out, const void *in, const int *perm, int rows, size_t row_bytes, hipStream_t s);
 
-// dst[r, c] += bias[c] for r < rows, c < cols (dst fp32 with leading dimension ld; bias in the
-// element type: -1 fp32, ELEM_BF16, ELEM_F16)
-hipError_t launch_bias_add(int elem, float *dst, int64_t ld, int rows, int cols, const void *bias, hipStream_t s);
+// dst[r, c] += bias[c] for r < rows, c < cols (fp32, leading dimension ld)
+hipError_t launch_bias_add(float *dst, int64_t ld, int rows, int cols, const float *bias, hipStream_t s);
 
 // out[0] = wall-clock ticks, out[1] = shader cycles over a spin of wall_ticks
 hipError_t launch_clock_probe(long long *out, long long wall_ticks, hipStream_t s);

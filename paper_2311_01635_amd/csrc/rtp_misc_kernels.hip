@@ -229,7 +229,7 @@ constexpr int64_t F32_SMALL_MAX = 4096;
 
 hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s)
 {
-    if (count < 0 || count > F32_MAX_GROUP) return hipErrorInvalidValue;
+    if (count < 0 || count > F32_MAX_GROUP || r.sums != 0) return hipErrorInvalidValue;
     F32Group g;
     memset(&g, 0, sizeof g);
     int64_t small_tiles = 0;
@@ -447,6 +447,16 @@ hipError_t ride_list(const Riders &r, int idle, RideList *out)
         q.first = out->blocks;
         out->blocks += (unsigned)((n16 + per - 1) / per);
     }
+    for (int i = 0; i < r.sums; ++i) {
+        const RideSum &q = r.sum[i];
+        if (q.rows < 0 || !q.in || !q.out || (q.rows > 0 && !q.Y)) return hipErrorInvalidValue;
+        if (q.cols <= 0) continue;
+        auto &d = out->sum[out->sums++];
+        d.Y = q.Y; d.ld = q.ld; d.rows = q.rows; d.cols = q.cols; d.in = q.in; d.out = q.out;
+        d.wide = colsum_wide(q.Y, q.ld, q.cols);
+        d.first = out->sum_blocks;
+        out->sum_blocks += (unsigned)((q.cols + COLSUM_COLS - 1) / COLSUM_COLS);
+    }
     return hipSuccess;
 }
 
@@ -454,6 +464,11 @@ __global__ __launch_bounds__(COPY_THREADS) void ride_kernel(const RideList g) { 
 
 hipError_t launch_riders(const Riders &r, hipStream_t s)
 {
+    for (int i = 0; i < r.sums; ++i) {
+        const RideSum &q = r.sum[i];
+        const hipError_t e = launch_colsum(q.elem, q.Y, q.ld, q.rows, q.cols, q.in, q.out, s);
+        if (e != hipSuccess) return e;
+    }
     RideList g;
     const hipError_t e = ride_list(r, 512, &g);
     if (e != hipSuccess || g.blocks == 0) return e;
@@ -563,26 +578,20 @@ hipError_t launch_shard_layout(void *home, size_t slot_bytes, size_t off, int n,
                            : launch_shard_layout_units<uint32_t>(home, slot_bytes, off, n, cols, W, O, I, w, unpack, s);
 }
 
-// ---- bias piece of an input-partitioned layer, added onto a slice of the fp32 accumulator ----------
-template <typename T>
-__global__ __launch_bounds__(256) void bias_add_kernel(float *dst, int64_t ld, int rows, int cols, const T *bias)
+// ---- bias piece of an input-partitioned fp32 layer, added onto a slice of its output (16-bit layers: in the GEMM) ----
+__global__ __launch_bounds__(256) void bias_add_kernel(float *dst, int64_t ld, int rows, int cols, const float *bias)
 {
     const int c = blockIdx.x * 64 + (threadIdx.x & 63);
     if (c >= cols) return;
-    const float b = (float)bias[c];
+    const float b = bias[c];
     for (int r = blockIdx.y * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.y * 4) dst[(int64_t)r * ld + c] += b;
 }
 
-hipError_t launch_bias_add(int elem, float *dst, int64_t ld, int rows, int cols, const void *bias, hipStream_t s)
+hipError_t launch_bias_add(float *dst, int64_t ld, int rows, int cols, const float *bias, hipStream_t s)
 {
     if (rows <= 0 || cols <= 0) return hipSuccess;
     const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)std::min(1024, (rows + 3) / 4)), block(256);
-    if (elem == ELEM_BF16)
-        hipLaunchKernelGGL(bias_add_kernel<__bf16>, grid, block, 0, s, dst, ld, rows, cols, (const __bf16 *)bias);
-    else if (elem == ELEM_F16)
-        hipLaunchKernelGGL(bias_add_kernel<_Float16>, grid, block, 0, s, dst, ld, rows, cols, (const _Float16 *)bias);
-    else
-        hipLaunchKernelGGL(bias_add_kernel<float>, grid, block, 0, s, dst, ld, rows, cols, (const float *)bias);
+    hipLaunchKernelGGL(bias_add_kernel, grid, block, 0, s, dst, ld, rows, cols, bias);
     return hipGetLastError();
 }
 
@@ -696,58 +705,12 @@ hipError_t launch_scatter_rows(void *out, const void *in, const int *perm, int r
 }
 
 // ---- bias gradient: column sums --------------------------------------------------------------
-// out[c] = in[c] + sum over rows of Y[r, c].  Bound: memory latency (the matrix is [tokens, shard width], a few
-// megabytes, and a shard is only some hundred columns wide).  A workgroup of 1024 threads owns 32 columns: VEC
-// columns per thread (16 bytes of a 16-bit matrix where the rows allow it), 32 / VEC threads across, the rest down the
-// rows with four loads in flight each; the row groups' sums meet in LDS in a fixed order, so the result does not
-// depend on timing.  1024 tokens x 384 columns, fp16: 53 us with one 2-byte load in flight per thread and 256 threads
-// on 64 columns; the training step of the unit they belong to went from 1.96 to 1.15 ms.
-constexpr int COLSUM_COLS = 32, COLSUM_THREADS = 1024;
-
+// colsum_block (rtp_ride.h) as a launch of its own
 template <typename T, int VEC>
 __global__ __launch_bounds__(COLSUM_THREADS) void colsum_kernel(const T *Y, int64_t ld, int rows, int cols, const float *in, float *out)
 {
-    constexpr int TX = COLSUM_COLS / VEC, GROUPS = COLSUM_THREADS / TX, UNROLL = 4;
-    typedef __attribute__((ext_vector_type(VEC))) T vec;
-    __shared__ float part[GROUPS * COLSUM_COLS]; // [group][column]
-    __shared__ float part2[32][COLSUM_COLS];
-    const int tid = threadIdx.x, x = tid % TX, g = tid / TX;
-    const int c = blockIdx.x * COLSUM_COLS + x * VEC;
-    float s[VEC] = {};
-    if (c < cols) { // (VEC > 1: cols is a multiple of VEC)
-        const T *p = Y + c;
-        int r = g;
-        for (; r + (UNROLL - 1) * GROUPS < rows; r += UNROLL * GROUPS) {
-            vec v[UNROLL];
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) v[u] = *(const vec *)(p + (int64_t)(r + u * GROUPS) * ld);
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) s[i] += (float)v[u][i];
-        }
-        for (; r < rows; r += GROUPS) {
-            const vec v = *(const vec *)(p + (int64_t)r * ld);
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) s[i] += (float)v[i];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) part[g * COLSUM_COLS + x * VEC + i] = s[i];
-    __syncthreads();
-    // 32 sums per column, then one
-    const int col = tid & 31, q = tid >> 5;
-    float t = 0.0f;
-    for (int i = q; i < GROUPS; i += 32) t += part[i * COLSUM_COLS + col];
-    part2[q][col] = t;
-    __syncthreads();
-    if (q == 0 && blockIdx.x * COLSUM_COLS + col < cols) {
-        float sum = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 32; ++i) sum += part2[i][col];
-        const int cc = blockIdx.x * COLSUM_COLS + col;
-        out[cc] = in[cc] + sum;
-    }
+    __shared__ float lds[COLSUM_LDS_FLOATS];
+    colsum_block<T, VEC, COLSUM_THREADS>(Y, ld, rows, cols, in, out, blockIdx.x, lds);
 }
 
 hipError_t launch_colsum(int elem, const void *Y, int64_t ld, int rows, int cols, const float *in, float *out, hipStream_t s)
@@ -755,7 +718,7 @@ hipError_t launch_colsum(int elem, const void *Y, int64_t ld, int rows, int cols
     if (cols <= 0) return hipSuccess;
     if (rows < 0 || !in || !out || (rows > 0 && !Y)) return hipErrorInvalidValue;
     const dim3 grid((cols + COLSUM_COLS - 1) / COLSUM_COLS), block(COLSUM_THREADS);
-    const bool wide = (ld & 7) == 0 && (cols & 7) == 0 && ((uintptr_t)Y & 15) == 0;
+    const bool wide = colsum_wide(Y, ld, cols);
     if (elem == ELEM_BF16 && wide)
         hipLaunchKernelGGL((colsum_kernel<__bf16, 8>), grid, block, 0, s, (const __bf16 *)Y, ld, rows, cols, in, out);
     else if (elem == ELEM_BF16)

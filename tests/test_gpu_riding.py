@@ -80,11 +80,12 @@ def test_linear_layer(dtype, bias, split, n, rank, mode, aux):
 
 @pytest.mark.parametrize("mode", [DB, IS])
 @pytest.mark.parametrize("n,rank", [(2, 1), (3, 0), (8, 3)])
-@pytest.mark.parametrize("act,bias,dtype", [(B.RTP_ACT_GELU_ERF, False, B.RTP_BF16), (B.RTP_ACT_GELU_TANH, True, B.RTP_F16),
-                                            (B.RTP_ACT_SWIGLU, True, B.RTP_BF16), (B.RTP_ACT_SWIGLU, False, B.RTP_F32)])
-def test_mlp_unit(act, bias, dtype, n, rank, mode):
+@pytest.mark.parametrize("act,bias,dtype,T", [(B.RTP_ACT_GELU_ERF, False, B.RTP_BF16, 77), (B.RTP_ACT_GELU_TANH, True, B.RTP_F16, 96),
+                                              (B.RTP_ACT_SWIGLU, True, B.RTP_BF16, 77), (B.RTP_ACT_SWIGLU, False, B.RTP_F32, 77),
+                                              (B.RTP_ACT_SWIGLU, True, B.RTP_BF16, 1990)])  # (the bias sums' main loop: 1024 rows a trip)
+def test_mlp_unit(act, bias, dtype, T, n, rank, mode):
     td, u = TD[dtype], 32 if dtype == B.RTP_F16 else 8
-    T, I, O, O2 = (96 if dtype == B.RTP_F16 else 77), 128, n * u * 3, 160
+    I, O, O2 = 128, n * u * 3, 160
     shapes = [(O, I)] * (2 if act == B.RTP_ACT_SWIGLU else 1) + [(O2, O)]
     X, dY = normal(1, T, I, dtype=td), normal(2, T, O2, dtype=td)
     ws, g0 = [normal(3 + i, *s) * 0.1 for i, s in enumerate(shapes)], [normal(13 + i, *s) for i, s in enumerate(shapes)]
@@ -180,7 +181,7 @@ class Seg(C.Structure):
 
 
 class Riders(C.Structure):
-    _fields_ = [("count", C.c_int), ("seg", Seg * 8)]
+    _fields_ = [("count", C.c_int), ("sums", C.c_int), ("seg", Seg * 8), ("sum", C.c_uint64 * 12)]
 
 
 def test_segments_of_every_kind_and_size():
