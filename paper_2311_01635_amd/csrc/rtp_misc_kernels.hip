@@ -323,26 +323,37 @@ hipError_t launch_act_f32(int kind, const float *pre, int64_t ldpre, const float
 // ---- staging copy ---------------------------------------------------------------------
 // Each workgroup moves one 64 KB piece with 16-byte accesses and exits, so the
 // copy slips into whatever wave slots the GEMM running beside it leaves free
-// instead of holding compute units for the whole transfer.
+// instead of holding compute units for the whole transfer.  A whole piece is moved without a bounds test per unit:
+// behind one, the compiler waits ahead of every store for all stores before it (Llama-shaped unit's training step
+// against one reference on one box: 1.004 -> 1.027 x as fast).
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 constexpr int COPY_THREADS = 256;
 constexpr int COPY_PER_THREAD = 16; // x 16 bytes
+
+// the units of a thread from `base` on
+__device__ __forceinline__ void copy_units(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, const int64_t base, const int64_t n16)
+{
+    u32x4 v[COPY_PER_THREAD];
+    if (base - threadIdx.x + COPY_THREADS * COPY_PER_THREAD <= n16) {
+#pragma unroll
+        for (int i = 0; i < COPY_PER_THREAD; ++i) v[i] = __builtin_nontemporal_load(src + base + i * COPY_THREADS);
+#pragma unroll
+        for (int i = 0; i < COPY_PER_THREAD; ++i) __builtin_nontemporal_store(v[i], dst + base + i * COPY_THREADS);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < COPY_PER_THREAD; ++i)
+        if (base + i * COPY_THREADS < n16) v[i] = __builtin_nontemporal_load(src + base + i * COPY_THREADS);
+#pragma unroll
+    for (int i = 0; i < COPY_PER_THREAD; ++i)
+        if (base + i * COPY_THREADS < n16) __builtin_nontemporal_store(v[i], dst + base + i * COPY_THREADS);
+}
 
 __global__ __launch_bounds__(COPY_THREADS) void copy_kernel(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src,
                                                             int64_t n16)
 {
     const int64_t base = (int64_t)blockIdx.x * (COPY_THREADS * COPY_PER_THREAD) + threadIdx.x;
-    u32x4 v[COPY_PER_THREAD];
-#pragma unroll
-    for (int i = 0; i < COPY_PER_THREAD; ++i) {
-        const int64_t e = base + (int64_t)i * COPY_THREADS;
-        if (e < n16) v[i] = __builtin_nontemporal_load(src + e);
-    }
-#pragma unroll
-    for (int i = 0; i < COPY_PER_THREAD; ++i) {
-        const int64_t e = base + (int64_t)i * COPY_THREADS;
-        if (e < n16) __builtin_nontemporal_store(v[i], dst + e);
-    }
+    copy_units(dst, src, base, n16);
 }
 
 // done: an event that completes with the copy (the kernel's completion signal is the event's: no record packet of
@@ -381,17 +392,7 @@ __global__ __launch_bounds__(COPY_THREADS) void copy_multi_kernel(const CopySegs
     u32x4 *__restrict__ dst = g.dst[i];
     const int64_t n16 = g.n16[i];
     const int64_t base = (int64_t)(blockIdx.x - g.first[i]) * (COPY_THREADS * COPY_PER_THREAD) + threadIdx.x;
-    u32x4 v[COPY_PER_THREAD];
-#pragma unroll
-    for (int j = 0; j < COPY_PER_THREAD; ++j) {
-        const int64_t e = base + (int64_t)j * COPY_THREADS;
-        if (e < n16) v[j] = __builtin_nontemporal_load(src + e);
-    }
-#pragma unroll
-    for (int j = 0; j < COPY_PER_THREAD; ++j) {
-        const int64_t e = base + (int64_t)j * COPY_THREADS;
-        if (e < n16) __builtin_nontemporal_store(v[j], dst + e);
-    }
+    copy_units(dst, src, base, n16);
 }
 
 hipError_t launch_copy_multi(void *const *dst, const void *const *src, const size_t *bytes, int count, hipStream_t s,
@@ -501,16 +502,19 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s)
 // Bound: HBM (every element read once and written once).  The kernel moves units of type T: 16 bytes
 // where rows, shard width, slot and pointers are whole numbers of 16-byte units, else single elements.
 // A workgroup takes LAYOUT_PER_THREAD x 256 consecutive units of one shard, all reads of a thread in
-// flight before its first store.  A row block is one contiguous run of W and needs no row
-// arithmetic; a column block divides by the shard width once per unit.  One 2- or 4-byte element per
-// thread with 64-bit divisions took 105-121 us per [11008, 4096] matrix (1.7-3 TB/s); three matrices' weights and
-// gradients out and weights in, whole exchange: 958 -> 707 us.
+// flight before its first store.  That needs the workgroup whole inside the matrix: with a bounds test per
+// unit the compiler kept all eight in one block of 240 registers and waited for each read before it issued the
+// next.  The workgroups at a shard's end go unit by unit.  A row block is one contiguous run of W and needs no
+// row arithmetic; a column block divides by the shard width once per thread and counts from there.  Weights and
+// gradients of three [11008, 4096] matrices out and weights in, whole exchange: 958 us with an element per
+// thread, 707 with tests and divisions per unit, 396 so.
 typedef __attribute__((ext_vector_type(4))) unsigned int layout_u32x4;
 constexpr int LAYOUT_PER_THREAD = 8;
 
 template <typename T, bool COLS, bool UNPACK>
 __global__ __launch_bounds__(256) void shard_layout_kernel(char *home, size_t slot_bytes, size_t off, T *W, int64_t O,
-                                                           int64_t I, int64_t w, unsigned blocks_per_shard)
+                                                           int64_t I, int64_t w, unsigned blocks_per_shard,
+                                                           int64_t step_rows, int64_t step_cols)
 {
     const int64_t k = blockIdx.x / blocks_per_shard;
     T *slot = (T *)(home + (size_t)k * slot_bytes + off);
@@ -518,33 +522,53 @@ __global__ __launch_bounds__(256) void shard_layout_kernel(char *home, size_t sl
     // a row block's units inside the matrix, a column block's columns inside it
     const int64_t rows_in = min(w, max((int64_t)0, O - k * w)), cols_in = min(w, max((int64_t)0, I - k * w));
     T *Wk = W + (COLS ? k * w : k * w * I);
-    const int64_t base = (int64_t)(blockIdx.x % blocks_per_shard) * (256 * LAYOUT_PER_THREAD) + threadIdx.x;
-    const bool small = per >> 32 == 0; // 32-bit division reaches
-    T v[LAYOUT_PER_THREAD];
-    T *at[LAYOUT_PER_THREAD];
-    bool in[LAYOUT_PER_THREAD];
-#pragma unroll
-    for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
-        const int64_t e = base + u * 256;
-        if (COLS) {
-            const int64_t row = small ? (int64_t)((unsigned)e / (unsigned)w) : e / w, col = e - row * w;
-            in[u] = e < per && col < cols_in;
-            at[u] = Wk + row * I + col;
-        } else {
-            in[u] = e < rows_in * I;
-            at[u] = Wk + e;
-        }
-        v[u] = T{};
-        if (in[u]) v[u] = UNPACK ? __builtin_nontemporal_load(slot + e) : __builtin_nontemporal_load(at[u]);
+    const int64_t first = (int64_t)(blockIdx.x % blocks_per_shard) * (256 * LAYOUT_PER_THREAD), base = first + threadIdx.x;
+    int64_t row = 0, col = 0; // of the thread's next unit in a column block
+    if (COLS) {
+        row = per >> 32 == 0 ? (int64_t)((unsigned)base / (unsigned)w) : base / w; // (32-bit division where it reaches)
+        col = base - row * w;
     }
+    auto step = [&]() {
+        row += step_rows;
+        col += step_cols;
+        if (col >= w) {
+            col -= w;
+            ++row;
+        }
+    };
+    const int64_t end = first + 256 * LAYOUT_PER_THREAD;
+    if (COLS ? end <= per && cols_in == w : end <= rows_in * I) { // the workgroup's units all lie inside the matrix
+        T v[LAYOUT_PER_THREAD];
+        T *at[LAYOUT_PER_THREAD];
 #pragma unroll
+        for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
+            at[u] = Wk + (COLS ? row * I + col : base + u * 256);
+            if (COLS) step();
+            v[u] = UNPACK ? __builtin_nontemporal_load(slot + base + u * 256) : __builtin_nontemporal_load(at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
+            if (UNPACK)
+                __builtin_nontemporal_store(v[u], at[u]);
+            else
+                __builtin_nontemporal_store(v[u], slot + base + u * 256);
+        }
+        return;
+    }
+#pragma unroll 1
     for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
         const int64_t e = base + u * 256;
+        if (e >= per) break;
+        T *at = Wk + (COLS ? row * I + col : e);
+        const bool in = COLS ? col < cols_in : e < rows_in * I;
         if (UNPACK) {
-            if (in[u]) __builtin_nontemporal_store(v[u], at[u]);
+            if (in) __builtin_nontemporal_store(__builtin_nontemporal_load(slot + e), at);
         } else {
-            if (e < per) __builtin_nontemporal_store(v[u], slot + e);
+            T v = {};
+            if (in) v = __builtin_nontemporal_load(at);
+            __builtin_nontemporal_store(v, slot + e);
         }
+        if (COLS) step();
     }
 }
 
@@ -557,7 +581,7 @@ static hipError_t launch_shard_layout_units(void *home, size_t slot_bytes, size_
     if (blocks * n >= (int64_t)1 << 31) return hipErrorInvalidValue;
 #define RTP_SHARD_LAYOUT(C, U)                                                                                          \
     hipLaunchKernelGGL((shard_layout_kernel<T, C, U>), dim3((unsigned)(blocks * n)), dim3(256), 0, s, (char *)home, slot_bytes, \
-                       off, (T *)W, O, I, w, (unsigned)blocks)
+                       off, (T *)W, O, I, w, (unsigned)blocks, 256 / w, 256 % w)
     if (cols) { if (unpack) RTP_SHARD_LAYOUT(true, true); else RTP_SHARD_LAYOUT(true, false); }
     else { if (unpack) RTP_SHARD_LAYOUT(false, true); else RTP_SHARD_LAYOUT(false, false); }
 #undef RTP_SHARD_LAYOUT

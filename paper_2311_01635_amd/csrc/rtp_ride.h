@@ -62,8 +62,9 @@ __device__ __forceinline__ void colsum_block(const T *Y, int64_t ld, int rows, i
             for (int h = 0; h < PER; ++h)
 #pragma unroll
                 for (int u = 0; u < UNROLL; ++u) {
-                    const int r = r0 + h * (GROUPS / PER) + u * GROUPS;
-                    if (r < rows) v[h][u] = *(const vec *)(Y + (int64_t)r * ld + c);
+                    // (past the end the last row, which is not added: a test per read would put a wait behind each)
+                    const int r = min(r0 + h * (GROUPS / PER) + u * GROUPS, rows - 1);
+                    v[h][u] = *(const vec *)(Y + (int64_t)r * ld + c);
                 }
 #pragma unroll
             for (int h = 0; h < PER; ++h)
@@ -113,35 +114,64 @@ __device__ __forceinline__ void ride_sum(const RideList &g, const unsigned block
 hipError_t ride_list(const Riders &r, int idle, RideList *out);
 
 // Bound: memory latency (a few megabytes a launch), hence eight 16-byte reads in flight per thread and direction.
-// A thread reads its units of `buf` and `in` before it writes any, so a segment may send what `buf` holds and
+// The units go in runs of 8, 4 and 2 a thread without a bounds test: behind a test per unit the compiler waited for each
+// read before it issued the next (512-token pass of the Llama-shaped unit 450 -> 437).
+// A thread reads its units of `buf` and `in` before it writes them, so a segment may send what `buf` holds and
 // receive into it in one go; no two segments touch the same bytes.  What the next launch reads is stored the plain way,
 // what nobody reads soon past the caches: a 512-token pass of the Llama-shaped unit 505 -> 461 us, the query/key/value
 // training step 1041 -> 1029.
+// DEPTH units of a thread, NTHR apart, from `e` on: all reads, then all writes.  TAIL: units from `end` on do not exist (their
+// reads go to the last one that does).
+template <int NTHR, int DEPTH, bool OUT, bool IN, bool TAIL>
+__device__ __forceinline__ void ride_units(ride_u32x4 *out, ride_u32x4 *buf, const ride_u32x4 *in, const int64_t e, const int64_t end)
+{
+    ride_u32x4 held[DEPTH], next[DEPTH];
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) {
+        const int64_t q = TAIL ? min(e + j * NTHR, end - 1) : e + j * NTHR;
+        if (OUT) held[j] = __builtin_nontemporal_load(buf + q);
+        if (IN) next[j] = __builtin_nontemporal_load(in + q);
+    }
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) {
+        const int64_t q = e + j * NTHR;
+        if (TAIL && q >= end) continue;
+        if (OUT) __builtin_nontemporal_store(held[j], out + q);
+        if (IN) buf[q] = next[j]; // the next launch reads it
+    }
+}
+
+template <int NTHR, bool OUT, bool IN>
+__device__ __forceinline__ void ride_run(ride_u32x4 *out, ride_u32x4 *buf, const ride_u32x4 *in, int64_t begin, const int64_t end)
+{
+    const int t = threadIdx.x;
+    for (; begin + 8 * NTHR <= end; begin += 8 * NTHR) ride_units<NTHR, 8, OUT, IN, false>(out, buf, in, begin + t, end);
+    if (begin + 4 * NTHR <= end) {
+        ride_units<NTHR, 4, OUT, IN, false>(out, buf, in, begin + t, end);
+        begin += 4 * NTHR;
+    }
+    if (begin + 2 * NTHR <= end) {
+        ride_units<NTHR, 2, OUT, IN, false>(out, buf, in, begin + t, end);
+        begin += 2 * NTHR;
+    }
+    if (begin < end) ride_units<NTHR, 2, OUT, IN, true>(out, buf, in, begin + t, end);
+}
+
 template <int NTHR>
 __device__ __forceinline__ void ride(const RideList &g, const unsigned block)
 {
-    constexpr int DEPTH = 8;
     int i = 0;
     while (i + 1 < g.count && block >= g.seg[i + 1].first) ++i;
     ride_u32x4 *const out = g.seg[i].out, *const buf = g.seg[i].buf;
     const ride_u32x4 *const in = g.seg[i].in;
     const int64_t begin = (int64_t)(block - g.seg[i].first) * g.per_block;
     const int64_t end = min(begin + g.per_block, g.seg[i].n16);
-    for (int64_t e0 = begin + threadIdx.x; e0 < end; e0 += NTHR * DEPTH) {
-        ride_u32x4 held[DEPTH], next[DEPTH];
-#pragma unroll
-        for (int j = 0; j < DEPTH; ++j) {
-            const int64_t e = e0 + j * NTHR;
-            if (e < end && out) held[j] = __builtin_nontemporal_load(buf + e);
-            if (e < end && in) next[j] = __builtin_nontemporal_load(in + e);
-        }
-#pragma unroll
-        for (int j = 0; j < DEPTH; ++j) {
-            const int64_t e = e0 + j * NTHR;
-            if (e < end && out) __builtin_nontemporal_store(held[j], out + e);
-            if (e < end && in) buf[e] = next[j]; // the next launch reads it
-        }
-    }
+    if (out && in)
+        ride_run<NTHR, true, true>(out, buf, in, begin, end);
+    else if (out)
+        ride_run<NTHR, true, false>(out, buf, in, begin, end);
+    else if (in)
+        ride_run<NTHR, false, true>(out, buf, in, begin, end);
 }
 
 } // namespace rtp

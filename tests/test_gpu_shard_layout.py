@@ -57,6 +57,17 @@ def test_pack_matches_the_oracles_split_and_unpack_inverts_it(O, I, n, split, dt
     assert np.array_equal(_bits(back), _bits(W))
 
 
+@pytest.mark.parametrize("dtype", [B.RTP_BF16, B.RTP_F32])
+@pytest.mark.parametrize("split", [B.RTP_SPLIT_OUT, B.RTP_SPLIT_IN])
+@pytest.mark.parametrize("O,I,n", [(2048, 96, 4),      # column blocks a few units wide: a thread's next unit is many rows on
+                                   (700, 4800, 2),     # wider than the 256 units a workgroup takes at a time
+                                   (520, 6168, 3), (600, 1000, 7),   # one unit more than those; a padded last shard
+                                   (1024, 517, 4)])    # rows that are no whole 16-byte units
+def test_shards_of_many_workgroups(O, I, n, split, dtype):
+    """Workgroups whose units all lie inside the matrix, beside those at a shard's end."""
+    test_pack_matches_the_oracles_split_and_unpack_inverts_it(O, I, n, split, dtype)
+
+
 def test_linear_layer_store_is_the_oracles_partition():
     """RtpLinear builds its stores through the library: weights [W_k | bias entries], gradients the same in fp32,
     for both partitions, with a partition that needs padding."""
