@@ -652,6 +652,8 @@ static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
 {
     if (!r) return fail(RTP_ERR_INVALID, "rtp_ring_begin: null ring");
+    const bool may_carry = r->may_carry; // (said for this call, also where it fails)
+    r->may_carry = true;
     if (pass != RTP_PASS_FWD && pass != RTP_PASS_BWD) return fail(RTP_ERR_INVALID, "rtp_ring_begin: bad pass");
     if (r->pass != RTP_PASS_IDLE) return fail(RTP_ERR_STATE, "rtp_ring_begin: a pass is already open");
     const int n = r->d.n, rank = r->d.rank;
@@ -660,8 +662,7 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
                     (rank + 1) % n, r->resident);
     RTP_TRY(refuse_capture(r, "rtp_ring_begin"));
     RTP_TRY(ensure_events(r));
-    r->carry = r->may_carry && ring_carries(r, pass);
-    r->may_carry = true;
+    r->carry = may_carry && ring_carries(r, pass);
     r->pend.count = r->pend.sums = 0;
     RTP_TRY(begin_join(r));
     r->joined = r->carry;
