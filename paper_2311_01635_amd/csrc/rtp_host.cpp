@@ -628,14 +628,16 @@ extern "C" rtp_status rtp_ring_set_ablation(rtp_ring *r, int rotate, int compute
 }
 
 // Whether a pass rides.  Against it stands that a riding workgroup takes a compute unit from the tiles once those fill the
-// machine, where a copy kernel on the stage stream runs beside them.  us a pass, two streams -> riding:
-//   forward, slots of 34 MB: 128 tokens 553 -> 394, 4096 tokens 1627 -> 1414, 8192 tokens 2627 -> 2617; of 88 MB, 512 to
-//   2048 tokens 2164 -> 2305, 2994 -> 2748, 3928 -> 4055;
-//   forward and backward, tokens x bytes of weights a slot, x 10^9: 24 (1024 tokens, 23 MB) 1756 -> 1735, 33 (4096 tokens,
-//   8 MB) 3106 -> 2983, 46 (4096 tokens, 11 MB) 4832 -> 4672, 69 (4096 tokens, 17 MB) 5358 -> 5568, 92 (4096 tokens,
-//   23 MB) 3270 -> 3506; gradients travel too: slots of 34 + 68 MB, 512 and 1024 tokens 1811 -> 1766, 2121 -> 2307.
-constexpr size_t CARRY_FWD_BYTES = (size_t)48 << 20, CARRY_BWD_BYTES = (size_t)72 << 20;
-constexpr double CARRY_BWD_WORK = 60e9;
+// machine, and that a backward step's GEMMs follow one another where the streams run two of them at a time.
+// us a pass, streams -> riding:
+//   forward, slots of 56 MB: 512 tokens 1559 -> 1234, 4096 tokens 5252 -> 4967; of 86 MB, 512 to 8192 tokens 488 -> 416,
+//   839 -> 772, 2478 -> 2403; of 128 MB 377 -> 347; of 192 MB, 4096 tokens 3751 -> 3747; of 224 MB, 256 tokens 1069 -> 1008;
+//   forward and backward, tokens x bytes of weights a slot, x 10^9: 69 (2048 tokens, 32 MB) 2686 -> 2631, 71 (4096 tokens,
+//   17 MB) 2765 -> 2486, 86 (8192 tokens, 10 MB) 2845 -> 2737, 104 (3072 tokens, 32 MB) 3219 -> 3330, 129 (8192 tokens, 15 MB)
+//   3909 -> 3833, 138 (8192 tokens, 16 MB) 3162 -> 3175, 139 (4096 tokens, 32 MB) 4014 -> 4341; gradients travel too: slots of
+//   32 + 64 MB, 512 tokens 1557 -> 1465; of 56 + 112 MB, 1024 tokens 6192 -> 6254 though the forward pass gains 300.
+constexpr size_t CARRY_FWD_BYTES = (size_t)256 << 20, CARRY_BWD_BYTES = (size_t)128 << 20;
+constexpr double CARRY_BWD_WORK = 90e9;
 
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 {
