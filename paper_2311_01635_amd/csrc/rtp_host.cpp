@@ -401,13 +401,22 @@ static rtp_status rotate_async(rtp_ring *r, void *out, const void *held, void *h
 // last one that read it, and a launch reads what an earlier one brought in.
 static bool ring_carries(const rtp_ring *r, rtp_pass pass);
 
+// A launch that takes the pending transfers along (`launch`).  Where it fails the transfers stay asked for, so that the
+// call can be made again; its own bias gradients do not, which that call asks for anew.
+template <class F>
+static hipError_t carry_launch(rtp_ring *r, F launch)
+{
+    const hipError_t e = launch(r->pend);
+    r->pend.sums = 0;
+    if (e == hipSuccess) r->pend.count = 0;
+    return e;
+}
+
 // the transfers asked for so far as a launch of their own
 static rtp_status carry_flush(rtp_ring *r)
 {
     if (r->pend.count == 0 && r->pend.sums == 0) return RTP_OK;
-    const Riders p = r->pend;
-    r->pend.count = r->pend.sums = 0;
-    HIP_TRY(launch_riders(p, r->cs()));
+    HIP_TRY(carry_launch(r, [&](const Riders &p) { return launch_riders(p, r->cs()); }));
     return RTP_OK;
 }
 
@@ -1152,16 +1161,19 @@ static rtp_status gemm_riding(rtp_linear *l, const int *layouts, GemmArgs *a, in
         together = together && (f32 || gemm_bf16_pp_supported(layouts[i], a[i]));
     }
     if (!together) {
+        // an operand that a launcher would refuse is refused before the first of the launches
+        for (int i = 0; i < count && !f32; ++i)
+            if (a[i].M > 0 && a[i].N > 0 && !gemm_bf16_args_ok(layouts[i], a[i])) {
+                r->pend.sums = 0;
+                return fail(RTP_ERR_HIP, "a GEMM of the step: %s", hipGetErrorString(hipErrorInvalidValue));
+            }
         RTP_TRY(carry_flush(r));
         for (int i = 0; i < count; ++i) RTP_TRY(gemm(l, layouts[i], a[i], r->cs()));
         return RTP_OK;
     }
-    const Riders p = r->pend;
-    r->pend.count = r->pend.sums = 0;
-    if (f32)
-        HIP_TRY(launch_gemm_f32_riding(layouts, a, count, p, r->cs()));
-    else
-        HIP_TRY(launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()));
+    HIP_TRY(carry_launch(r, [&](const Riders &p) {
+        return f32 ? launch_gemm_f32_riding(layouts, a, count, p, r->cs()) : launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs());
+    }));
     return RTP_OK;
 }
 static rtp_status gemm_riding(rtp_linear *l, int layout, GemmArgs &a) { return gemm_riding(l, &layout, &a, 1); }
@@ -2158,9 +2170,7 @@ static rtp_status gemm_group_riding(rtp_ring *r, const int *layouts, const GemmA
         for (int i = 0; i < count; ++i) RTP_TRY(gemm_group(r, layouts[i], a + i, 1, r->cs()));
         return RTP_OK;
     }
-    const Riders p = r->pend;
-    r->pend.count = r->pend.sums = 0;
-    HIP_TRY(launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()));
+    HIP_TRY(carry_launch(r, [&](const Riders &p) { return launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()); }));
     return RTP_OK;
 }
 

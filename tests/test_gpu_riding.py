@@ -176,6 +176,65 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
     ring.close()
 
 
+def off_by_one(t):
+    """The same matrix two bytes past a 16-byte boundary, where no GEMM takes an operand."""
+    flat = torch.empty(t.numel() + 8, device=DEV, dtype=t.dtype)[1:1 + t.numel()]
+    return flat.copy_(t.flatten()).view(t.shape)
+
+
+@pytest.mark.parametrize("timed", [False, True])
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("split,T,n,bias", [(B.RTP_SPLIT_OUT, 75, 3, True), (B.RTP_SPLIT_IN, 75, 4, True),
+                                            (B.RTP_SPLIT_OUT, 4096, 4, False)])   # (the last: sums split along K, sent by copy)
+def test_a_refused_call_can_be_made_again(split, T, n, bias, mode, timed):
+    """A call that is refused for an operand's alignment leaves the step's transfers to the call that follows it."""
+    g = torch.Generator().manual_seed(1)
+    draw = lambda *s: torch.randint(-2, 3, s, generator=g).to(DEV, torch.bfloat16)   # any order of a sum gives the same bits
+    I = O = 256 if T > 75 else 48 * n
+    X, dY, W, g0 = draw(T, I), draw(T, O), draw(O, I).float(), draw(O, I).float()
+    b = draw(O).float() if bias else None
+    bad_X, bad_dY = off_by_one(X), off_by_one(dY)
+    runs = []
+    for disturb in (False, True):
+        layer = RtpLinear(W, T, n, 1, split, mode, G0=g0, bias=b)
+        for t in layer.buf_w + layer.buf_g:
+            if t is not None:
+                t.fill_(255)
+        Y, dX = torch.empty_like(dY), torch.empty_like(X)
+        torch.cuda.synchronize()
+        if timed:
+            B.rtp_prof_begin()
+
+        def call(f, *bad_then_good):
+            for args in bad_then_good[:-1] if disturb else ():
+                with pytest.raises(B.RtpError) as e:
+                    f(*args)
+                assert e.value.status == B.RTP_ERR_HIP
+            f(*bad_then_good[-1])
+
+        for i in range(2):
+            layer.ring.begin(B.RTP_PASS_FWD)
+            for t in range(n):
+                if t < n - 1:
+                    layer.ring.rotate_step(B.RTP_CW, t)
+                call(layer.lin.fwd, (t, bad_X, Y), (t, X, Y))
+            layer.ring.end()
+            layer.ring.begin(B.RTP_PASS_BWD)
+            for t in range(n):
+                if t < n - 1:
+                    layer.ring.rotate_step(B.RTP_CCW, t)
+                call(layer.lin.bwd, (t, bad_X, dY, dX), (t, X, bad_dY, dX), (t, X, dY, dX))
+            layer.ring.end()
+        layer.ring.flush()
+        layer.sync()
+        if timed:
+            B.rtp_prof_end()
+        runs.append([Y, dX, layer.home_w.clone(), layer.home_g.clone()])
+        layer.close()
+    for i, (x, y) in enumerate(zip(*runs)):
+        assert torch.equal(x, y), i
+
+
 class Seg(C.Structure):
     _fields_ = [("out", C.c_void_p), ("buf", C.c_void_p), ("src", C.c_void_p), ("bytes", C.c_size_t)]
 
