@@ -444,17 +444,17 @@ static rtp_status carry_g_turnover(rtp_ring *r, int gdst, int kprev, int kin)
     bool any = false;
     for (rtp_linear *l : r->linears) any = any || l->unsent[gdst];
     if (!any) return kin < 0 ? RTP_OK : carry_add(r, nullptr, r->d.buf_g_dev[gdst], r->home_g(kin), r->d.g_bytes);
-    size_t at = 0; // the slot in order: what lies between the layers' parts only comes in
+    size_t at = 0; // the slot in order: what lies between the layers' parts only comes in, bytes that layers share go once
     std::vector<rtp_linear *> parts(r->linears);
     std::sort(parts.begin(), parts.end(), [](const rtp_linear *a, const rtp_linear *b) { return a->d.g_offset < b->d.g_offset; });
     char *buf = (char *)r->d.buf_g_dev[gdst];
     for (rtp_linear *l : parts) {
         if (!l->unsent[gdst]) continue;
         l->unsent[gdst] = false;
-        const size_t off = l->d.g_offset;
+        const size_t off = std::max(at, l->d.g_offset), end = l->d.g_offset + l->g_shard_bytes;
         if (kin >= 0 && off > at) RTP_TRY(carry_add(r, nullptr, buf + at, r->home_g(kin) + at, off - at));
-        RTP_TRY(carry_add(r, r->home_g(kprev) + off, buf + off, kin >= 0 ? r->home_g(kin) + off : nullptr, l->g_shard_bytes));
-        at = off + l->g_shard_bytes;
+        if (end > off) RTP_TRY(carry_add(r, r->home_g(kprev) + off, buf + off, kin >= 0 ? r->home_g(kin) + off : nullptr, end - off));
+        at = std::max(at, end);
     }
     if (kin >= 0 && at < r->d.g_bytes) RTP_TRY(carry_add(r, nullptr, buf + at, r->home_g(kin) + at, r->d.g_bytes - at));
     return RTP_OK;

@@ -176,6 +176,55 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
     ring.close()
 
 
+@pytest.mark.parametrize("n,offsets", [(2, (0, 0)), (4, (0, 0)), (4, (0, 512, 0)), (3, (1536, 0, 512, 1024))])
+def test_layers_that_share_gradient_bytes(n, offsets):
+    """fp32 layers on one ring whose parts of a slot overlap (a tied weight): shared bytes are sent, and overwritten by the
+    next shard's, once.  Integers, so that every order of a sum gives the same bits."""
+    T, I, o, rank = 32, 32, 8, 1
+    part = o * I * 4                                    # bytes of a layer's part; offsets of half a part overlap
+    slot = max(offsets) + part + 256                    # a tail that no layer owns
+    draw = lambda seed, *s: torch.randint(-2, 3, s, generator=torch.Generator().manual_seed(seed)).to(DEV, torch.float32)
+    X, dY = draw(1, T, I), [draw(2 + i, T, o * n) for i in range(len(offsets))]
+    got = []
+    for streams in (False, True):
+        home_w, home_g = draw(9, n, slot // 4).view(torch.uint8), draw(10, n, slot // 4).view(torch.uint8)
+        bufs = [torch.full((slot,), 255, dtype=torch.uint8, device=DEV) for _ in range(4)]
+        cs, ss, aux = (torch.cuda.Stream() for _ in range(3))
+        ring = B.Ring(n, rank, DB, slot, slot, home_w, home_g, bufs[:2], bufs[2:], cs, ss, aux_stream=aux)
+        lins = [B.Linear(ring, T, I, o * n, B.RTP_SPLIT_OUT, B.RTP_F32, B.RTP_ACT_NONE, at, at) for at in offsets]
+        scratch = torch.zeros(2, dtype=torch.int64, device=DEV)
+        B.check(B.lib.rtp_ring_set_test_delay_compute(ring.handle, B._ptr(scratch), 1 if streams else 0), "delay")
+        Y, dX = torch.empty(T, o * n, device=DEV), [torch.empty_like(X) for _ in offsets]
+        torch.cuda.synchronize()
+        for _ in range(2):
+            ring.begin(B.RTP_PASS_FWD)
+            for t in range(n):
+                if t < n - 1:
+                    ring.rotate_step(B.RTP_CW, t)
+                for l in lins:
+                    l.fwd(t, X, Y)
+            ring.end()
+            ring.begin(B.RTP_PASS_BWD)
+            for t in range(n):
+                if t < n - 1:
+                    ring.rotate_step(B.RTP_CCW, t)
+                for l, d, dx in zip(lins, dY, dX):
+                    l.bwd(t, X, d, dx)
+            ring.end()
+        ring.flush()
+        ring.sync()
+        got.append([home_g.view(torch.float32).clone()] + [d.clone() for d in dX])
+        ring.close()
+    want = draw(10, n, slot // 4).double()
+    for at, d in zip(offsets, dY):
+        for k in range(n):
+            g = d[:, k * o:(k + 1) * o].double().T @ X.double()
+            want[k, at // 4:(at + part) // 4] += 2 * g.flatten()
+    assert torch.equal(got[0][0].double(), want)
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 def off_by_one(t):
     """The same matrix two bytes past a 16-byte boundary, where no GEMM takes an operand."""
     flat = torch.empty(t.numel() + 8, device=DEV, dtype=t.dtype)[1:1 + t.numel()]
