@@ -278,7 +278,9 @@ rtp_status rtp_ring_flush(rtp_ring *ring);
  * from zero.  Idle state only. */
 rtp_status rtp_ring_zero_grads(rtp_ring *ring);
 
-/* Joins both streams; returns RTP_ERR_HIP if anything asynchronous failed. */
+/* Joins the streams: everything asked for so far is done, a rotation whose
+ * step has no linear call yet too.  RTP_ERR_HIP if anything asynchronous
+ * failed. */
 rtp_status rtp_ring_sync(rtp_ring *ring);
 
 /* Shard currently resident (after everything enqueued so far), or -1. */

@@ -999,6 +999,7 @@ extern "C" rtp_status rtp_ring_sync(rtp_ring *r)
 {
     if (!r) return fail(RTP_ERR_INVALID, "rtp_ring_sync: null ring");
     if (r->dry) return RTP_OK;
+    RTP_TRY(carry_flush(r)); // a rotation of a riding pass that no launch has taken along yet
     HIP_TRY(hipStreamSynchronize(r->cs()));
     if (r->ss() != r->cs()) HIP_TRY(hipStreamSynchronize(r->ss()));
     if (r->as() != r->cs()) HIP_TRY(hipStreamSynchronize(r->as()));

@@ -176,6 +176,28 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
     ring.close()
 
 
+@pytest.mark.parametrize("mode", [DB, IS])
+def test_sync_covers_a_rotation_without_its_linear_call(mode):
+    """rtp_ring_sync between rtp_rotate_step and the step's linear call: the next shard is in the worker's buffer."""
+    T, I, O, n, rank = 32, 64, 96, 3, 1
+    layer = RtpLinear(normal(1, O, I), T, n, rank, mode=mode, G0=normal(2, O, I))
+    X, dY = normal(3, T, I, dtype=torch.bfloat16), normal(4, T, O, dtype=torch.bfloat16)
+    Y, dX = torch.empty_like(dY), torch.empty_like(X)
+    torch.cuda.synchronize()
+    for pass_, turn, shard in ((B.RTP_PASS_FWD, B.RTP_CW, B.rtp_fwd_shard), (B.RTP_PASS_BWD, B.RTP_CCW, B.rtp_bwd_shard)):
+        layer.ring.begin(pass_)
+        for t in range(n):
+            if t < n - 1:
+                layer.ring.rotate_step(turn, t)
+                layer.ring.sync()
+                dst = [r[4] for r in layer.ring.trace() if r[0] == "w_in"][-1]
+                assert torch.equal(layer.buf_w[dst], layer.home_w[shard(rank, t + 1, n)]), (pass_, t)
+            layer.lin.fwd(t, X, Y) if pass_ == B.RTP_PASS_FWD else layer.lin.bwd(t, X, dY, dX)
+        layer.ring.end()
+    layer.sync()
+    layer.close()
+
+
 @pytest.mark.parametrize("n,offsets", [(2, (0, 0)), (4, (0, 0)), (4, (0, 512, 0)), (3, (1536, 0, 512, 1024))])
 def test_layers_that_share_gradient_bytes(n, offsets):
     """fp32 layers on one ring whose parts of a slot overlap (a tied weight): shared bytes are sent, and overwritten by the
