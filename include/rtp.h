@@ -296,6 +296,18 @@ int rtp_ring_resident(const rtp_ring *ring);
  * weight-gradient kernels leave the shard in the buffer. */
 int rtp_ring_resident_grad(const rtp_ring *ring);
 
+/* How a ring's passes run.  A pass whose shards are narrow RIDES: everything
+ * is enqueued on the compute stream, and the transfers of a step are
+ * workgroups of its GEMM launches; the other passes use the ring's streams.
+ * rtp_pass_rides: the rule, from the sizes alone (no GPU needed): whether a
+ * pass over layers of at most T tokens rides, 1 or 0.  Blocking and
+ * RTP_FLAG_STAGE_MEMCPY rings, rings under a test delay, expert layers, units
+ * created with a schedule flag and an MLP unit's backward pass without an
+ * auxiliary stream never do.
+ * rtp_ring_rides: whether the open pass, or the last one, rides (rode). */
+int rtp_pass_rides(const rtp_ring_desc *desc, int64_t T, rtp_pass pass);
+int rtp_ring_rides(const rtp_ring *ring);
+
 /* Timing aid (the three-run measurement of how much of the staging hides
  * under compute): `rotate` = 0 skips the transfers (every step computes on the
  * shard that is resident: results are meaningless), `compute` = 0 skips the

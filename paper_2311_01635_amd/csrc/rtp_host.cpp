@@ -247,6 +247,7 @@ struct rtp_ring {
     int rotations = 0;   // rotate_step calls in the open pass
     int executed = 0;    // blocking mode: rotations already carried out
     bool may_carry = true; // (a schedule that moves the shards itself on the other streams says no before it begins)
+    bool rode = false;   // what `carry` said in the pass that is open, or was last (rtp_ring_rides)
     bool carry = false;  // the open pass runs on the compute stream alone, its transfers riding in the GEMM launches
     Riders pend;         // transfers of the rotation that has been asked for: they go out with the step's first launch
     // test aid: a bounded spin kernel ahead of every transfer on the stage stream / every GEMM on the
@@ -569,6 +570,7 @@ extern "C" rtp_status rtp_ring_destroy(rtp_ring *r)
 
 extern "C" int rtp_ring_resident(const rtp_ring *r) { return r ? r->resident : -1; }
 extern "C" int rtp_ring_resident_grad(const rtp_ring *r) { return r && r->d.g_bytes ? r->res_g : -1; }
+extern "C" int rtp_ring_rides(const rtp_ring *r) { return r && r->rode ? 1 : 0; }
 
 extern "C" int64_t rtp_ring_trace(rtp_ring *r, rtp_trace_rec *out, int64_t cap, int clear)
 {
@@ -648,16 +650,22 @@ extern "C" rtp_status rtp_ring_set_ablation(rtp_ring *r, int rotate, int compute
 constexpr size_t CARRY_FWD_BYTES = (size_t)256 << 20, CARRY_BWD_BYTES = (size_t)128 << 20;
 constexpr double CARRY_BWD_WORK = 90e9;
 
+extern "C" int rtp_pass_rides(const rtp_ring_desc *d, int64_t T, rtp_pass pass)
+{
+    if (!d || T < 0 || d->n < 2 || d->mode == RTP_INPLACE_BLOCKING || (d->flags & RTP_FLAG_STAGE_MEMCPY)) return 0;
+    if (pass == RTP_PASS_FWD) return d->w_bytes <= CARRY_FWD_BYTES;
+    if (pass != RTP_PASS_BWD) return 0;
+    return d->w_bytes + d->g_bytes <= CARRY_BWD_BYTES && (double)T * (double)d->w_bytes <= CARRY_BWD_WORK;
+}
+
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 {
-    if (r->dry || r->d.n < 2 || !r->abl_rotate || r->d.mode == RTP_INPLACE_BLOCKING) return false;
-    if (r->d.flags & RTP_FLAG_STAGE_MEMCPY) return false;
+    if (r->dry || !r->abl_rotate) return false;
     // the test delays hold the other streams back: those passes run on them
     if (r->delay_stage_ticks > 0 || r->delay_aux_ticks > 0 || r->delay_compute_ticks > 0) return false;
-    if (pass == RTP_PASS_FWD) return r->d.w_bytes <= CARRY_FWD_BYTES;
     int64_t T = 0;
     for (const rtp_linear *l : r->linears) T = std::max(T, l->d.T);
-    return r->d.w_bytes + r->d.g_bytes <= CARRY_BWD_BYTES && (double)T * (double)r->d.w_bytes <= CARRY_BWD_WORK;
+    return rtp_pass_rides(&r->d, T, pass) != 0;
 }
 
 extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
@@ -676,7 +684,7 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
     r->carry = may_carry && ring_carries(r, pass);
     r->pend.count = r->pend.sums = 0;
     RTP_TRY(begin_join(r));
-    r->joined = r->carry;
+    r->joined = r->rode = r->carry;
     r->pass = pass;
     r->rotations = 0;
     r->executed = 0;

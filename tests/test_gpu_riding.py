@@ -33,9 +33,11 @@ def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb")):
         Y, dX = torch.empty_like(dY), torch.empty_like(X)
         layer.forward(X, Y)
         out.append(Y)
+        assert B.lib.rtp_ring_rides(ring) == (not streams), "forward"
         if "b" in p:
             layer.backward(X, dY, dX)
             out.append(dX)
+            assert B.lib.rtp_ring_rides(ring) == (not streams), "backward"
     layer.sync()
     held = B.lib.rtp_ring_resident_grad(ring)
     W, G = layer.gathered()
@@ -117,7 +119,8 @@ def test_gradients_whose_sum_is_split_along_k_travel_by_copy(kind, mode):
         assert (x.double() - y.double()).norm() <= 2e-5 * y.double().norm()
 
 
-def test_two_layers_on_one_ring_and_a_bare_ring():
+@pytest.mark.parametrize("mode", [DB, IS])
+def test_two_layers_on_one_ring_and_a_bare_ring(mode):
     """Two layers share the ring's rotations: the transfers ride in the launch of the first; a ring without layers sends
     them alone."""
     T, I, O, n, rank = 64, 64, 96, 4, 2
@@ -126,7 +129,7 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
         home_w, home_g = normal(1, n, wb // 2, dtype=torch.bfloat16).view(torch.uint8), torch.zeros(n, gb, dtype=torch.uint8, device=DEV)
         bufs = [torch.full((s,), 255, dtype=torch.uint8, device=DEV) for s in (wb, wb, gb, gb)]
         cs, ss, aux = (torch.cuda.Stream() for _ in range(3))
-        ring = B.Ring(n, rank, DB, wb, gb, home_w, home_g, bufs[:2], bufs[2:], cs, ss, aux_stream=aux)
+        ring = B.Ring(n, rank, mode, wb, gb, home_w, home_g, bufs[:2], bufs[2:], cs, ss, aux_stream=aux)
         acc = [torch.empty(T, I, device=DEV) for _ in range(2)]
         lins = [B.Linear(ring, T, I, O, B.RTP_SPLIT_OUT, B.RTP_BF16, B.RTP_ACT_NONE, i * wb // 2, i * gb // 2, None, acc[i]) for i in range(2)]
         X, dY = normal(2, T, I, dtype=torch.bfloat16), normal(3, T, O, dtype=torch.bfloat16)
@@ -135,6 +138,7 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
         B.check(B.lib.rtp_ring_set_test_delay_compute(ring.handle, B._ptr(scratch), 1 if streams else 0), "delay")
         torch.cuda.synchronize()
         ring.begin(B.RTP_PASS_FWD)
+        assert ring.rides() == (not streams)
         for t in range(n):
             if t < n - 1:
                 ring.rotate_step(B.RTP_CW, t)
@@ -142,6 +146,7 @@ def test_two_layers_on_one_ring_and_a_bare_ring():
                 lins[i].fwd(t, X, Y[i])
         ring.end()
         ring.begin(B.RTP_PASS_BWD)
+        assert ring.rides() == (not streams)
         for t in range(n):
             if t < n - 1:
                 ring.rotate_step(B.RTP_CCW, t)
@@ -186,6 +191,7 @@ def test_sync_covers_a_rotation_without_its_linear_call(mode):
     torch.cuda.synchronize()
     for pass_, turn, shard in ((B.RTP_PASS_FWD, B.RTP_CW, B.rtp_fwd_shard), (B.RTP_PASS_BWD, B.RTP_CCW, B.rtp_bwd_shard)):
         layer.ring.begin(pass_)
+        assert layer.ring.rides()
         for t in range(n):
             if t < n - 1:
                 layer.ring.rotate_step(turn, t)
@@ -198,10 +204,11 @@ def test_sync_covers_a_rotation_without_its_linear_call(mode):
     layer.close()
 
 
-@pytest.mark.parametrize("n,offsets", [(2, (0, 0)), (4, (0, 0)), (4, (0, 512, 0)), (3, (1536, 0, 512, 1024))])
-def test_layers_that_share_gradient_bytes(n, offsets):
-    """fp32 layers on one ring whose parts of a slot overlap (a tied weight): shared bytes are sent, and overwritten by the
-    next shard's, once.  Integers, so that every order of a sum gives the same bits."""
+@pytest.mark.parametrize("n,offsets", [(2, (0, 0)), (4, (0, 0)), (4, (0, 512, 0)), (3, (1536, 0, 512, 1024)),
+                                       (4, (256, 1536, 2816, 4096))])   # (gaps: more segments than one launch takes)
+def test_layers_of_one_ring_and_the_gradient_bytes_between_and_under_them(n, offsets):
+    """fp32 layers on one ring whose parts of a slot overlap (a tied weight) or leave gaps: every byte is sent, and overwritten
+    by the next shard's, once.  Integers, so that every order of a sum gives the same bits."""
     T, I, o, rank = 32, 32, 8, 1
     part = o * I * 4                                    # bytes of a layer's part; offsets of half a part overlap
     slot = max(offsets) + part + 256                    # a tail that no layer owns
@@ -227,6 +234,7 @@ def test_layers_that_share_gradient_bytes(n, offsets):
                     l.fwd(t, X, Y)
             ring.end()
             ring.begin(B.RTP_PASS_BWD)
+            assert ring.rides() == (not streams)
             for t in range(n):
                 if t < n - 1:
                     ring.rotate_step(B.RTP_CCW, t)
@@ -291,6 +299,7 @@ def test_a_refused_call_can_be_made_again(split, T, n, bias, mode, timed):
                 call(layer.lin.fwd, (t, bad_X, Y), (t, X, Y))
             layer.ring.end()
             layer.ring.begin(B.RTP_PASS_BWD)
+            assert layer.ring.rides()
             for t in range(n):
                 if t < n - 1:
                     layer.ring.rotate_step(B.RTP_CCW, t)

@@ -548,3 +548,36 @@ def test_shard_layout_calls_validate_before_they_launch():
     assert st(p, 1024, 1, 4, B.RTP_SPLIT_OUT, p, 8, 8, 2, B.RTP_BF16) == B.RTP_ERR_SHAPE       # offset not a whole element
     assert B.lib.rtp_unpack_shards(p, None, 1024, 0, 4, B.RTP_SPLIT_OUT, 8, 8, 2, B.RTP_BF16, None) == B.RTP_ERR_INVALID
     assert b"rtp_unpack_shards" in B.lib.rtp_last_error()
+
+
+def test_which_passes_ride():
+    """The rule on sizes at both sides of each of its limits, and what never rides."""
+    MB = 1 << 20
+
+    def rides(pass_, T=64, n=4, mode=B.RTP_DOUBLE_BUFFER, flags=0, w=MB, g=2 * MB):
+        d = B.rtp_ring_desc(n=n, rank=0, mode=mode, flags=flags, w_bytes=w, g_bytes=g)
+        return B.lib.rtp_pass_rides(C.byref(d), T, pass_)
+
+    for mode in (B.RTP_DOUBLE_BUFFER, B.RTP_INPLACE_STAGED):
+        for T in (0, 1, 4096):
+            assert rides(B.RTP_PASS_FWD, T, mode=mode) == 1 and rides(B.RTP_PASS_BWD, T, mode=mode) == 1
+    for pass_ in (B.RTP_PASS_FWD, B.RTP_PASS_BWD):
+        assert rides(pass_, n=1) == 0 and rides(pass_, n=2) == 1
+        assert rides(pass_, mode=B.RTP_INPLACE_BLOCKING) == 0
+        assert rides(pass_, flags=B.RTP_FLAG_STAGE_MEMCPY) == 0
+        assert rides(pass_, T=-1) == 0 and B.lib.rtp_pass_rides(None, 64, pass_) == 0
+    assert rides(B.RTP_PASS_IDLE) == 0
+    assert rides(B.RTP_PASS_FWD, w=256 * MB) == 1 and rides(B.RTP_PASS_FWD, w=256 * MB + 16) == 0
+    assert rides(B.RTP_PASS_BWD, w=48 * MB, g=80 * MB) == 1 and rides(B.RTP_PASS_BWD, w=48 * MB, g=80 * MB + 16) == 0
+    w = 8 * MB
+    T = int(90e9 // w)                                   # tokens x bytes of weights a slot up to 9e10
+    assert rides(B.RTP_PASS_BWD, T, w=w) == 1 and rides(B.RTP_PASS_BWD, T + 1, w=w) == 0
+
+
+def test_a_pass_that_uses_the_streams_says_so():
+    ring = _dry_ring(3, 1, B.RTP_DOUBLE_BUFFER, w=64, g=64)
+    assert not ring.rides() and B.lib.rtp_ring_rides(None) == 0
+    ring.begin(B.RTP_PASS_FWD)
+    assert not ring.rides(), "a dry run enqueues nothing"
+    ring.abort()
+    ring.close()
