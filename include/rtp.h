@@ -237,10 +237,10 @@ rtp_status rtp_ring_seek_bwd_start(rtp_ring *ring);
  * for the previous step.  Enqueues on the stage stream: the held weights go
  * back to their home slot, the next shard's weights come into the staging
  * buffer; in a backward pass the gradient part follows each linear's dW
- * kernel (see rtp_linear_bwd).  Narrow shards: the pass runs on the compute
- * stream alone, and these transfers are workgroups of the launch that the
- * step's first linear call makes (of one of their own when the ring has no
- * linear).  Errors: RTP_ERR_STATE for a wrong direction,
+ * kernel (see rtp_linear_bwd).  A pass that rides (rtp_pass_rides) only notes
+ * them: they are enqueued with the launch that the step's first linear call
+ * makes, on the compute stream (by rtp_ring_sync, if that comes first).
+ * Errors: RTP_ERR_STATE for a wrong direction,
  * a step out of order or >= n-1, a linear lagging behind. */
 rtp_status rtp_rotate_step(rtp_ring *ring, int direction, int step);
 
@@ -303,7 +303,7 @@ int rtp_ring_resident_grad(const rtp_ring *ring);
  * pass over layers of at most T tokens rides, 1 or 0.  Blocking and
  * RTP_FLAG_STAGE_MEMCPY rings, rings under a test delay, expert layers, units
  * created with a schedule flag and an MLP unit's backward pass without an
- * auxiliary stream never do.
+ * auxiliary stream never do, nor does a ring that has no layers.
  * rtp_ring_rides: whether the open pass, or the last one, rides (rode). */
 int rtp_pass_rides(const rtp_ring_desc *desc, int64_t T, rtp_pass pass);
 int rtp_ring_rides(const rtp_ring *ring);

@@ -660,7 +660,7 @@ extern "C" int rtp_pass_rides(const rtp_ring_desc *d, int64_t T, rtp_pass pass)
 
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 {
-    if (r->dry || !r->abl_rotate) return false;
+    if (r->dry || !r->abl_rotate || r->linears.empty()) return false; // (no layers: no launch to ride in)
     // the test delays hold the other streams back: those passes run on them
     if (r->delay_stage_ticks > 0 || r->delay_aux_ticks > 0 || r->delay_compute_ticks > 0) return false;
     int64_t T = 0;
@@ -787,7 +787,7 @@ static rtp_status do_rotation(rtp_ring *r, int step)
             RTP_TRY(carry_g_turnover(r, r->g_idx(step + 1), step > 0 ? r->shard_at(step - 1) : -1, kin));
             r->rec(TR_G_IN, step, kin, r->g_idx(step + 1));
         }
-        return r->linears.empty() ? carry_flush(r) : RTP_OK; // (a bare ring has no launch to ride in)
+        return RTP_OK;
     }
     if (!r->dry && !blocking) {
         // the staging buffer was resident one step ago: wait for its readers

@@ -121,8 +121,8 @@ def test_gradients_whose_sum_is_split_along_k_travel_by_copy(kind, mode):
 
 @pytest.mark.parametrize("mode", [DB, IS])
 def test_two_layers_on_one_ring_and_a_bare_ring(mode):
-    """Two layers share the ring's rotations: the transfers ride in the launch of the first; a ring without layers sends
-    them alone."""
+    """Two layers share the ring's rotations: the transfers ride in the launch of the first; a ring without layers moves
+    them on its stage stream."""
     T, I, O, n, rank = 64, 64, 96, 4, 2
     for streams in (False, True):
         wb, gb = 2 * (O // n) * I * 2, 2 * (O // n) * I * 4
@@ -173,6 +173,7 @@ def test_two_layers_on_one_ring_and_a_bare_ring(mode):
     keep = W.clone()
     torch.cuda.synchronize()
     ring.begin(B.RTP_PASS_FWD)
+    assert not ring.rides()                      # its transfers run beside what the caller enqueues on the compute stream
     for t in range(n - 1):
         ring.rotate_step(B.RTP_CW, t)
     ring.end()
