@@ -642,20 +642,25 @@ extern "C" rtp_status rtp_ring_set_ablation(rtp_ring *r, int rotate, int compute
 // machine, and that a backward step's GEMMs follow one another where the streams run two of them at a time.
 // us a pass, streams -> riding:
 //   forward, slots of 56 MB: 512 tokens 1559 -> 1234, 4096 tokens 5252 -> 4967; of 86 MB, 512 to 8192 tokens 488 -> 416,
-//   839 -> 772, 2478 -> 2403; of 128 MB 377 -> 347; of 192 MB, 4096 tokens 3751 -> 3747; of 224 MB, 256 tokens 1069 -> 1008;
+//   839 -> 772, 2478 -> 2403; of 128 MB, 512, 4096 and 8192 tokens 824 -> 698, 2034 -> 1992, 3731 -> 3736; of 192 MB, 512 and
+//   4096 tokens 1008 -> 960, 3002 -> 2987; of 256 MB, 64, 512, 2048 and 4096 tokens 969 -> 900, 1345 -> 1312, 2393 -> 2367,
+//   4026 -> 4024.  Past 1.6e12 tokens x bytes it is 1-3 % either way and lost more often: 8192 tokens with 192 MB 5465 -> 5560
+//   (four shards), 2762 -> 2784 (two), 6385 -> 6336 (a block), with 256 MB 7356 -> 7523; 6144 with 256 MB 5990 -> 6076;
+//   below it, 8192 tokens with 144, 160 and 176 MB 4361 -> 4259, 4627 -> 4677, 5275 -> 5159.
 //   forward and backward, tokens x bytes of weights a slot, x 10^9: 69 (2048 tokens, 32 MB) 2686 -> 2631, 71 (4096 tokens,
 //   17 MB) 2765 -> 2486, 86 (8192 tokens, 10 MB) 2845 -> 2737, 104 (3072 tokens, 32 MB) 3219 -> 3330, 129 (8192 tokens, 15 MB)
 //   3909 -> 3833, 138 (8192 tokens, 16 MB) 3162 -> 3175, 139 (4096 tokens, 32 MB) 4014 -> 4341; gradients travel too: slots of
 //   32 + 64 MB, 512 tokens 1557 -> 1465; of 56 + 112 MB, 1024 tokens 6192 -> 6254 though the forward pass gains 300.
 constexpr size_t CARRY_FWD_BYTES = (size_t)256 << 20, CARRY_BWD_BYTES = (size_t)128 << 20;
-constexpr double CARRY_BWD_WORK = 90e9;
+constexpr double CARRY_FWD_WORK = 1600e9, CARRY_BWD_WORK = 90e9;
 
 extern "C" int rtp_pass_rides(const rtp_ring_desc *d, int64_t T, rtp_pass pass)
 {
     if (!d || T < 0 || d->n < 2 || d->mode == RTP_INPLACE_BLOCKING || (d->flags & RTP_FLAG_STAGE_MEMCPY)) return 0;
-    if (pass == RTP_PASS_FWD) return d->w_bytes <= CARRY_FWD_BYTES;
+    const double work = (double)T * (double)d->w_bytes;
+    if (pass == RTP_PASS_FWD) return d->w_bytes <= CARRY_FWD_BYTES && work <= CARRY_FWD_WORK;
     if (pass != RTP_PASS_BWD) return 0;
-    return d->w_bytes + d->g_bytes <= CARRY_BWD_BYTES && (double)T * (double)d->w_bytes <= CARRY_BWD_WORK;
+    return d->w_bytes + d->g_bytes <= CARRY_BWD_BYTES && work <= CARRY_BWD_WORK;
 }
 
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)

@@ -569,9 +569,9 @@ def test_which_passes_ride():
     assert rides(B.RTP_PASS_IDLE) == 0
     assert rides(B.RTP_PASS_FWD, w=256 * MB) == 1 and rides(B.RTP_PASS_FWD, w=256 * MB + 16) == 0
     assert rides(B.RTP_PASS_BWD, w=48 * MB, g=80 * MB) == 1 and rides(B.RTP_PASS_BWD, w=48 * MB, g=80 * MB + 16) == 0
-    w = 8 * MB
-    T = int(90e9 // w)                                   # tokens x bytes of weights a slot up to 9e10
-    assert rides(B.RTP_PASS_BWD, T, w=w) == 1 and rides(B.RTP_PASS_BWD, T + 1, w=w) == 0
+    for pass_, work, w in ((B.RTP_PASS_FWD, 1600e9, 192 * MB), (B.RTP_PASS_BWD, 90e9, 8 * MB)):
+        T = int(work // w)                               # tokens x bytes of weights a slot up to there
+        assert rides(pass_, T, w=w) == 1 and rides(pass_, T + 1, w=w) == 0
 
 
 def test_a_pass_that_uses_the_streams_says_so():
