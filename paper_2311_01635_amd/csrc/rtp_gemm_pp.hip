@@ -416,6 +416,20 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
     if (count == 0) return launch_riders(r, s);
     const int lay = common_layout(layouts, count);
     if (lay < 0) return hipErrorInvalidValue;
+    if (lay == LAY_NN_TN && !std::all_of(a, a + count, gemm_epilogue_vec_ok)) {
+        // one launch per layout, the transfers in the first
+        bool first = true;
+        for (int one : {LAY_NN, LAY_TN}) {
+            GemmArgs b[PP_MAX_GROUP];
+            int n = 0;
+            for (int q = 0; q < count; ++q)
+                if (layouts[q] == one) b[n++] = a[q];
+            const hipError_t e = launch_group(one, nullptr, b, n, plan_group(one, b, n, nullptr, 1), first ? &r : nullptr, s, nullptr);
+            if (e != hipSuccess) return e;
+            first = false;
+        }
+        return hipSuccess;
+    }
     return launch_group(lay, layouts, a, count, plan_group(lay, a, count, nullptr, 1), &r, s, nullptr);
 }
 

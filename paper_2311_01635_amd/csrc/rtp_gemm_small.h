@@ -35,7 +35,7 @@ constexpr int LOADS = 6; // direct loads per fetching wave and sub-tile: 2 KB of
 constexpr int EPI_BYTES = 4 * (EPI_LDS_BYTES_PER_WAVE + EPI_LAND_BYTES_PER_WAVE); // after the ring: four waves' staged epilogue
 } // namespace pps
 
-template <int LAY, typename E>
+template <int LAY, typename E, bool WIDE_ONLY>
 __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles_m, const int tiles_n, const int vec_epilogue,
                                               const int pid, const int kt_begin, const int kt_count, char *smem)
 {
@@ -213,11 +213,11 @@ __device__ __forceinline__ void pp_small_tile(const GemmArgs &p, const int tiles
     if (kt_count & 1) multiply(f0);
     asm volatile("s_barrier" ::: "memory");
 
-    if (vec_epilogue)
+    if (WIDE_ONLY || vec_epilogue)
         gemm_epilogue_staged<E, 1, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * 32, n0, wn * 32, lane,
                                                 smem + 4 * EPI_LDS_BYTES_PER_WAVE + wave * EPI_LAND_BYTES_PER_WAVE);
-    else
-        gemm_epilogue_staged_single<E, 1, FN, WN * 32>(p, acc, (float *)(smem + wave * EPI_LDS_BYTES_PER_WAVE), m0 + wm * 32, n0, wn * 32, lane);
+    else if constexpr (!WIDE_ONLY)
+        gemm_epilogue<E, 1, FN, WN * 32>(p, acc, m0 + wm * 32 + 4 * (lane >> 5), n0, wn * 32 + (lane & 31));
 }
 
 } // namespace rtp

@@ -19,8 +19,15 @@ def normal(seed, *shape, dtype=torch.float32):
     return torch.randn(*shape, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV).to(dtype)
 
 
-def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb")):
-    """Several passes in a row, so that what a pass leaves in the buffers is picked up by the next; every output of each."""
+def off_by_one(t):
+    """The same matrix two bytes past a 16-byte boundary, where no GEMM takes an operand."""
+    flat = torch.empty(t.numel() + 8, device=DEV, dtype=t.dtype)[1:1 + t.numel()]
+    return flat.copy_(t.flatten()).view(t.shape)
+
+
+def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb"), shift=False):
+    """Several passes in a row, so that what a pass leaves in the buffers is picked up by the next; every output of each.
+    shift: the outputs start two bytes past a 16-byte boundary."""
     scratch = torch.zeros(2, dtype=torch.int64, device=DEV)
     B.check(B.lib.rtp_ring_set_test_delay_compute(ring, B._ptr(scratch), 1 if streams else 0), "delay")
     out = []
@@ -30,7 +37,7 @@ def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb")):
     for p in plan:
         if "z" in p:
             layer.zero_grads()
-        Y, dX = torch.empty_like(dY), torch.empty_like(X)
+        Y, dX = (off_by_one(t) if shift else torch.empty_like(t) for t in (dY, X))
         layer.forward(X, Y)
         out.append(Y)
         assert B.lib.rtp_ring_rides(ring) == (not streams), "forward"
@@ -48,12 +55,12 @@ def passes(layer, ring, X, dY, linear, streams, plan=("fb", "fb", "f", "zfb")):
     return out, held
 
 
-def same(make, X, dY, linear):
+def same(make, X, dY, linear, shift=False):
     runs = []
     for streams in (False, True):
         layer = make()
         ring = layer.ring.handle if linear else B.lib.rtp_mlp_ring(layer.handle)
-        runs.append(passes(layer, ring, X, dY, linear, streams))
+        runs.append(passes(layer, ring, X, dY, linear, streams, shift=shift))
         layer.close()
     (a, held_a), (b, held_b) = runs
     assert held_a == held_b
@@ -94,6 +101,22 @@ def test_mlp_unit(act, bias, dtype, T, n, rank, mode):
     bs = [normal(23 + i, s[0]) for i, s in enumerate(shapes)] if bias else None
     make = lambda: RtpMlp(ws, T, n, rank, act, mode, dtype, G0=g0, biases=bs)
     same(make, X, dY, False)
+
+
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("dtype", [B.RTP_BF16, B.RTP_F16])
+@pytest.mark.parametrize("kind", ["out", "in", "mlp"])
+def test_outputs_off_a_16_byte_boundary(kind, dtype, mode):
+    """No four-wide epilogue: a backward step's two layouts are two launches, the transfers and bias sums in the first."""
+    td, T, n, rank = TD[dtype], 96, 4, 2
+    I, O = (128, 96 * n) if kind != "in" else (96 * n, 128)
+    X, W, b = normal(1, T, I, dtype=td), normal(3, O, I) * 0.1, normal(4, O)
+    if kind != "mlp":
+        make = lambda: RtpLinear(W, T, n, rank, B.RTP_SPLIT_OUT if kind == "out" else B.RTP_SPLIT_IN, mode, dtype, G0=normal(5, O, I), bias=b)
+        same(make, X, normal(2, T, O, dtype=td), True, shift=True)
+        return
+    make = lambda: RtpMlp([W, normal(6, I, O) * 0.1], T, n, rank, B.RTP_ACT_GELU_TANH, mode, dtype, biases=[b, normal(7, I)])
+    same(make, X, normal(2, T, I, dtype=td), False, shift=True)
 
 
 @pytest.mark.parametrize("mode", [DB, IS])
@@ -254,12 +277,6 @@ def test_layers_of_one_ring_and_the_gradient_bytes_between_and_under_them(n, off
     assert torch.equal(got[0][0].double(), want)
     for x, y in zip(*got):
         assert torch.equal(x, y)
-
-
-def off_by_one(t):
-    """The same matrix two bytes past a 16-byte boundary, where no GEMM takes an operand."""
-    flat = torch.empty(t.numel() + 8, device=DEV, dtype=t.dtype)[1:1 + t.numel()]
-    return flat.copy_(t.flatten()).view(t.shape)
 
 
 @pytest.mark.parametrize("timed", [False, True])
