@@ -502,12 +502,15 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s)
 // Bound: HBM (every element read once and written once).  The kernel moves units of type T: 16 bytes
 // where rows, shard width, slot and pointers are whole numbers of 16-byte units, else single elements.
 // A workgroup takes LAYOUT_PER_THREAD x 256 consecutive units of one shard, all reads of a thread in
-// flight before its first store.  That needs the workgroup whole inside the matrix: with a bounds test per
+// flight before its first store.  That needs reads without a bounds test: behind one per
 // unit the compiler kept all eight in one block of 240 registers and waited for each read before it issued the
-// next.  The workgroups at a shard's end go unit by unit.  A row block is one contiguous run of W and needs no
+// next.  Where a workgroup is not wholly inside the matrix (a shard's end, the last column block of a padded
+// partition) a unit outside is read from one that exists and dropped.  A row block is one contiguous run of W and needs no
 // row arithmetic; a column block divides by the shard width once per thread and counts from there.  Weights and
 // gradients of three [11008, 4096] matrices out and weights in, whole exchange: 958 us with an element per
 // thread, 707 with tests and divisions per unit, 396 so.
+// Single elements of column blocks go into the matrix through the caches: its rows start inside a line that the neighbouring
+// shard's workgroup fills up.  Past the caches [11008, 4096] fp32 in three shards came out in 84 us, so in 50.
 typedef __attribute__((ext_vector_type(4))) unsigned int layout_u32x4;
 constexpr int LAYOUT_PER_THREAD = 8;
 
@@ -536,6 +539,12 @@ __global__ __launch_bounds__(256) void shard_layout_kernel(char *home, size_t sl
             ++row;
         }
     };
+    auto put = [](T x, T *to) {
+        if (sizeof(T) == 16)
+            __builtin_nontemporal_store(x, to);
+        else
+            *to = x;
+    };
     const int64_t end = first + 256 * LAYOUT_PER_THREAD;
     if (COLS ? end <= per && cols_in == w : end <= rows_in * I) { // the workgroup's units all lie inside the matrix
         T v[LAYOUT_PER_THREAD];
@@ -549,26 +558,31 @@ __global__ __launch_bounds__(256) void shard_layout_kernel(char *home, size_t sl
 #pragma unroll
         for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
             if (UNPACK)
-                __builtin_nontemporal_store(v[u], at[u]);
+                put(v[u], at[u]);
             else
                 __builtin_nontemporal_store(v[u], slot + base + u * 256);
         }
         return;
     }
-#pragma unroll 1
+    T v[LAYOUT_PER_THREAD];
+    T *at[LAYOUT_PER_THREAD];
+    bool in[LAYOUT_PER_THREAD];
+#pragma unroll
     for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
         const int64_t e = base + u * 256;
-        if (e >= per) break;
-        T *at = Wk + (COLS ? row * I + col : e);
-        const bool in = COLS ? col < cols_in : e < rows_in * I;
-        if (UNPACK) {
-            if (in) __builtin_nontemporal_store(__builtin_nontemporal_load(slot + e), at);
-        } else {
-            T v = {};
-            if (in) v = __builtin_nontemporal_load(at);
-            __builtin_nontemporal_store(v, slot + e);
-        }
+        in[u] = e < per && (COLS ? col < cols_in : e < rows_in * I);
+        at[u] = in[u] ? Wk + (COLS ? row * I + col : e) : W;
         if (COLS) step();
+        v[u] = UNPACK ? __builtin_nontemporal_load(slot + min(e, per - 1)) : __builtin_nontemporal_load(at[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < LAYOUT_PER_THREAD; ++u) {
+        const int64_t e = base + u * 256;
+        if (UNPACK) {
+            if (in[u]) put(v[u], at[u]);
+        } else if (end <= per || e < per) {
+            __builtin_nontemporal_store(in[u] ? v[u] : T{}, slot + e);
+        }
     }
 }
 
