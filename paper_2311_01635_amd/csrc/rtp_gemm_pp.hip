@@ -198,7 +198,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
 // the estimate above picks.  Plans are remembered per shape.
 struct PlanKey {
     int layout, count, cu_share;
-    int dims[PP_MAX_GROUP][6]; // M, N, K, epi, forced height, may split
+    int dims[PP_MAX_GROUP][6]; // M, N, K, epi, forced height, chunks it may be split in
     bool operator<(const PlanKey &o) const { return memcmp(this, &o, sizeof *this) < 0; }
 };
 struct Plan {
@@ -212,7 +212,10 @@ static int forced_height(const GemmArgs &a, int asked)
     return built ? asked : 0;
 }
 
-static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share)
+constexpr int MAX_SPLIT = 32;
+
+// max_split (may be null): chunks of K each problem may be cut in
+static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr)
 {
     static std::map<PlanKey, Plan> cache;
     static std::mutex lock;
@@ -224,9 +227,11 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
     PlanKey key;
     memset(&key, 0, sizeof key);
     key.layout = layout; key.count = count; key.cu_share = cu_share;
+    int cap[PP_MAX_GROUP];
     for (int q = 0; q < count; ++q) {
         const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
-        const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi + (a[q].sync ? 64 : 0), forced, may_split_k(a[q]) ? 1 : 0};
+        cap[q] = !may_split_k(a[q]) ? 1 : max_split ? max_split[q] : MAX_SPLIT;
+        const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi + (a[q].sync ? 64 : 0), forced, cap[q]};
         memcpy(key.dims[q], d, sizeof d);
     }
     {
@@ -235,7 +240,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         if (it != cache.end()) return it->second;
     }
     const int heights[4] = {256, 192, 128, 64};
-    const int splits[6] = {1, 2, 4, 8, 16, 32};
+    const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
     const int cus = std::max(8, compute_units() / std::max(1, cu_share));
     const int cus_per_xcd = std::max(1, cus / 8);
     // A launch that shares the machine (cu_share > 1) seldom gets exactly its share: its partner on the other
@@ -266,11 +271,12 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         nopt[q] = 0;
         const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
-        const bool split_ok = may_split_k(a[q]) && tiles128 < cus && worth_splitting(a[q]);
+        const bool split_ok = cap[q] > 1 && tiles128 < cus && worth_splitting(a[q]);
         for (int h = 0; h < 4; ++h) {
             if (forced != 0 && forced != heights[h]) continue;
             if (heights[h] == 64 && a[q].sync) continue; // the counters are the tall tiles'
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
+                if (splits[k] > cap[q]) break;
                 if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (heights[h] == 64 ? 8 : 4)) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
@@ -394,10 +400,27 @@ static int common_layout(const int *layouts, int count)
     return lay;
 }
 
+// The plan of a riding launch, which has the machine to itself.  A sum repeats bit for bit if it is not split, and in two
+// chunks it does onto zeros; it keeps that whichever way its pass runs: where the launch of its own that the streams would
+// make (a[q].cu_share) has one chunk or two, it is cut in no more here.  Without that 8 % of shapes drawn from the layers'
+// ranges were split that are not there, and 4 % in more than two chunks.  The fp16 unit with biases (384 x 768 over 1024, two
+// chunks instead of four) 407 -> 399 us a step.
+static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count)
+{
+    int cap[PP_MAX_GROUP];
+    for (int q = 0; q < count; ++q) {
+        cap[q] = MAX_SPLIT;
+        if (!may_split_k(a[q])) continue;
+        const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share)).ks[0];
+        if (alone <= 2) cap[q] = alone;
+    }
+    return plan_group(layout, a, count, nullptr, 1, cap);
+}
+
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
-    const Plan pl = plan_group(common_layout(layouts, count), a, count, nullptr, 1);
+    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count);
     for (int q = 0; q < count; ++q) ksplit_out[q] = pl.ks[q];
 }
 
@@ -421,16 +444,16 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
         bool first = true;
         for (int one : {LAY_NN, LAY_TN}) {
             GemmArgs b[PP_MAX_GROUP];
-            int n = 0;
+            int lays[PP_MAX_GROUP], n = 0;
             for (int q = 0; q < count; ++q)
-                if (layouts[q] == one) b[n++] = a[q];
-            const hipError_t e = launch_group(one, nullptr, b, n, plan_group(one, b, n, nullptr, 1), first ? &r : nullptr, s, nullptr);
+                if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
+            const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n), first ? &r : nullptr, s, nullptr);
             if (e != hipSuccess) return e;
             first = false;
         }
         return hipSuccess;
     }
-    return launch_group(lay, layouts, a, count, plan_group(lay, a, count, nullptr, 1), &r, s, nullptr);
+    return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &r, s, nullptr);
 }
 
 hipError_t launch_gemm_bf16_pp(int layout, const GemmArgs &a, int bm_override, hipStream_t s)

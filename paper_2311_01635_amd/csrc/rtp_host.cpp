@@ -1171,7 +1171,6 @@ static rtp_status gemm_riding(rtp_linear *l, const int *layouts, GemmArgs *a, in
     bool together = !g_prof_on; // (timed launches are one GEMM each)
     for (int i = 0; i < count; ++i) {
         a[i].elem = l->d.dtype == RTP_F16 ? ELEM_F16 : ELEM_BF16;
-        a[i].cu_share = 1;
         together = together && (f32 || gemm_bf16_pp_supported(layouts[i], a[i]));
     }
     if (!together) {
@@ -1182,7 +1181,10 @@ static rtp_status gemm_riding(rtp_linear *l, const int *layouts, GemmArgs *a, in
                 return fail(RTP_ERR_HIP, "a GEMM of the step: %s", hipGetErrorString(hipErrorInvalidValue));
             }
         RTP_TRY(carry_flush(r));
-        for (int i = 0; i < count; ++i) RTP_TRY(gemm(l, layouts[i], a[i], r->cs()));
+        for (int i = 0; i < count; ++i) {
+            a[i].cu_share = 1;
+            RTP_TRY(gemm(l, layouts[i], a[i], r->cs()));
+        }
         return RTP_OK;
     }
     HIP_TRY(carry_launch(r, [&](const Riders &p) {
@@ -1455,7 +1457,7 @@ extern "C" rtp_status rtp_linear_bwd(rtp_linear *l, int step, const void *X, con
         a.ws = Gk; a.ldws = o;
     }
     a.C = a.ws; a.ldc = a.ldws;
-    a.cu_share = split ? 2 : 1;
+    a.cu_share = r->as() != r->cs() ? 2 : 1;
     // The send of the gradient part is fused into the kernel that completes it: when the shard
     // moves on after this step, the sum (arriving content + this worker's contribution) is written
     // straight to where it travels to, instead of back into the buffer and copied from there.
@@ -2245,10 +2247,12 @@ static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void
     auto first = [&](int s, GemmArgs *g) { // {dPre_s, dW2_s}
         g[0] = mlp_args_dh(m, h, r->shard_at(s), wbuf(s), dY);
         g[1] = mlp_args_dw2(m, h, r->shard_at(s), gbuf(s), dY);
+        g[0].cu_share = g[1].cu_share = 2;
     };
     auto second = [&](int s, GemmArgs *g) { // {dX_s, dW1_s}
         g[0] = mlp_args_dx(m, h, r->shard_at(s), s, wbuf(s), dX);
         g[1] = mlp_args_dw1(m, h, r->shard_at(s), gbuf(s), X);
+        g[0].cu_share = g[1].cu_share = 2;
     };
     auto whole_k = [&](const GemmArgs *g) { // a sum whose K loop is split needs the plain `+=` form: its send is a copy
         int ks[2] = {1, 1};

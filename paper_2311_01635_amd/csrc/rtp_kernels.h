@@ -104,6 +104,7 @@ struct Riders {
 // Up to PP_MAX_GROUP independent GEMMs and the transfers in one launch of the tiled kernel.  layouts[i]: all LAY_NT, or
 // LAY_NN and LAY_TN in any mix (the input and the weight gradients of a backward step).  Sums are of the GEMMs' element
 // type.  Nothing to compute: the transfers alone.  hipErrorInvalidValue as launch_gemm_bf16_pp_group, before anything is launched.
+// cu_share: what a launch of the problem's own on the streams would say (the launch here has the machine to itself).
 hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
 // the K splits that launch would use
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);

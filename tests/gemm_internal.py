@@ -20,6 +20,9 @@ class GemmArgs(C.Structure):
 _plan = getattr(B.lib, "_ZN3rtp17gemm_bf16_pp_planEiPKNS_8GemmArgsEiPKiPiS5_")
 _plan.restype = None
 _plan.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+_plan_riding = getattr(B.lib, "_ZN3rtp24gemm_bf16_pp_plan_ridingEPKiPKNS_8GemmArgsEiPi")
+_plan_riding.restype = None
+_plan_riding.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.POINTER(C.c_int)]
 _launch = getattr(B.lib, "_ZN3rtp16launch_gemm_bf16EiRKNS_8GemmArgsEiP12ihipStream_t")
 _launch.restype = C.c_int
 _launch.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.c_void_p]
@@ -35,6 +38,15 @@ def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_sha
     bm, ks = C.c_int(0), C.c_int(0)
     _plan(layout, C.byref(a), 1, C.byref(C.c_int(force)), C.byref(bm), C.byref(ks))
     return bm.value, ks.value
+
+
+def riding_split(M, N, K, dx, cu_share=2):
+    """Chunks of K of a weight gradient [M, N] over K in the launch it shares with the input gradient `dx` = (M, N, K, epi)."""
+    w = GemmArgs(M=M, N=N, K=K, epi=EPI_ACC_ADD, c_is_f32=1, cu_share=cu_share, C=0x1000, ws=0x1000, ldc=N, ldws=N, lda=M, ldb=N)
+    x = GemmArgs(M=dx[0], N=dx[1], K=dx[2], epi=dx[3], cu_share=cu_share, C=0x3000, ws=0x5000, ldc=dx[1], ldws=dx[1], lda=dx[2], ldb=dx[1])
+    ks = (C.c_int * 2)(1, 1)
+    _plan_riding((C.c_int * 2)(B.LAYOUT_NN, B.LAYOUT_TN), (GemmArgs * 2)(x, w), 2, ks)
+    return ks[1]
 
 
 def launch(layout, args, variant, stream=None):

@@ -1,4 +1,6 @@
 """Which tile, and how many chunks of K, the launcher picks for a shape (needs no GPU)."""
+import random
+
 import pytest
 
 import gemm_internal as G
@@ -53,3 +55,18 @@ def test_the_unit_tests_reach_the_small_tile():
         assert G.plan(B.LAYOUT_NT, 288, 256, 160, G.EPI_SWIGLU_FWD, 128, dtype=dtype)[0] == 64
         assert G.plan(B.LAYOUT_NN, 288, 128, 96, G.EPI_GELU_TANH_BWD, dtype=dtype)[0] == 64
         assert G.plan(B.LAYOUT_NN, 288, 128, 96, G.EPI_SWIGLU_BWD, 128, dtype=dtype)[0] == 64
+
+
+def test_a_riding_launch_does_not_split_a_sum_that_repeats_on_the_streams():
+    """One chunk stays one, two stay at most two (they repeat onto zeros), whatever the machine to itself would favour."""
+    rng = random.Random(5)
+    chunks = set()
+    shapes = [(544, 2560, 2208), (384, 768, 1024), (1792, 864, 5120), (1344, 1248, 3520), (960, 256, 1664)]
+    shapes += [(32 * rng.randint(2, 48), 64 * rng.randint(4, 64), 32 * rng.randint(1, 256)) for _ in range(150)]
+    for M, N, K in shapes:
+        alone = G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=2)[1]
+        for dx in ((K, N, M, G.EPI_ACC_ADD), (K, M, N, G.EPI_GELU_ERF_BWD)):
+            riding = G.riding_split(M, N, K, dx)
+            assert riding <= alone or alone > 2, (M, N, K, dx, alone, riding)
+            chunks.add(riding)
+    assert 1 in chunks and 2 in chunks and max(chunks) > 2
