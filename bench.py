@@ -280,15 +280,26 @@ def algorithmic_bytes_linears(w, unit):
     return total + stg
 
 
+def rings(B, unit):
+    if hasattr(unit, "layers"):
+        return [l.ring.handle for _, l, *_ in unit.layers]
+    return [B.lib.rtp_moe_ring(unit.moe.handle) if hasattr(unit, "moe") else B.lib.rtp_mlp_ring(unit.handle)]
+
+
 def grad_shard_held(B, unit):
     """Whether, after a backward pass, a gradient shard is still in the worker's buffer and not in its slot."""
-    if hasattr(unit, "layers"):
-        rings = [l.ring.handle for _, l, *_ in unit.layers]
-    elif hasattr(unit, "moe"):
-        rings = [B.lib.rtp_moe_ring(unit.moe.handle)]
-    else:
-        rings = [B.lib.rtp_mlp_ring(unit.handle)]
-    return any(B.lib.rtp_ring_resident_grad(h) >= 0 for h in rings)
+    return any(B.lib.rtp_ring_resident_grad(h) >= 0 for h in rings(B, unit))
+
+
+def passes_riding(B, unit, X, Y, dY, dX):
+    """Rings whose forward and whose backward pass ride: their transfers are workgroups of the GEMM launches, not copies
+    on the stage stream.  Makes one pass."""
+    unit.forward(X, Y)
+    fwd = sum(B.lib.rtp_ring_rides(h) for h in rings(B, unit))
+    unit.backward(X, dY, dX)
+    bwd = sum(B.lib.rtp_ring_rides(h) for h in rings(B, unit))
+    unit.sync()
+    return {"of": len(rings(B, unit)), "forward": fwd, "backward": bwd}
 
 
 def measured_traffic(workload, layout):
@@ -403,6 +414,7 @@ def main():
                 "flops_per_launch": tot_flops / launches, "traffic": measured_traffic(w.name, dom),
                 # launches on the compute and the auxiliary stream overlap, so a launch's duration includes the
                 # time it shares the compute units with another GEMM: per-launch rates understate the kernel
+                # (a riding backward step's two layouts share one launch in the timed pass; here each is timed by itself)
                 "launches_overlap": (not a.no_aux_stream),
                 "per_kernel": {k: {"launches_per_step": v[0] / a.steps, "avg_us": v[1] * 1e3 / max(v[0], 1),
                                    "tflops": v[2] / max(v[1], 1e-9) / 1e9} for k, v in prof.items()}}
@@ -429,8 +441,10 @@ def main():
         mlp.set_ablation(rotate=True, compute=True)
         timed(torch, mlp, X, Y, dY, dX, 2)
         t_b = timed(torch, mlp, X, Y, dY, dX, k) / k
+        # Three runs of one schedule: a riding pass rides in all of them, with its GEMM launches' transfers left out
+        # (compute only) or as launches of their own (staging only).
         hidden = 1.0 - max(0.0, t_b - t_c) / t_s if t_s > 0 else None
-        # what the fraction covers: the copies on the stage stream.  Per pass the weights make 2(n-1) rotations (each
+        # what the fraction covers: the copies on the stage stream, or what rides in their place.  Per pass the weights make 2(n-1) rotations (each
         # a copy out to the slot the shard travels to and a copy in from the slot it arrives in; no initial load in a
         # loop of passes: a backward pass ends on the worker's own shard); the gradient shard comes in n times by copy (n-1 rotations and the first load); the shard a pass
         # ends on is the worker's own and goes to its slot by copy only where the last kernels do not store it there.  Its other n-1 ways OUT
@@ -442,7 +456,8 @@ def main():
         # its slot by the last step's kernels or left in the buffer and copied there when the next backward pass begins
         own_by_copy = 1 if grad_shard_held(B, mlp) else 0
         overlap = {"ms_compute_only": t_c, "ms_staging_only": t_s, "ms_both": t_b, "rotation_hidden_frac": hidden,
-                   "ms_exposed": max(0.0, t_b - t_c),
+                   "ms_exposed": max(0.0, t_b - t_c), "ms_both_less_compute": t_b - t_c,
+                   "riding_rings": passes_riding(B, mlp, X, Y, dY, dX),
                    "staged_bytes": 4 * (n_ - 1) * W_ + (n_ + own_by_copy if fused else 2 * n_) * G_, "g_out_fused": fused,
                    "own_grad_shard_written_back_by_copy": bool(own_by_copy),
                    "g_out_bytes_stored_by_gemm_epilogues": (n_ - 1) * G_ if fused else 0,

@@ -312,6 +312,8 @@ int rtp_ring_rides(const rtp_ring *ring);
  * under compute): `rotate` = 0 skips the transfers (every step computes on the
  * shard that is resident: results are meaningless), `compute` = 0 skips the
  * kernels of the ring's layers (the staging traffic alone).  Idle state only.
+ * A pass that rides (rtp_pass_rides) makes the same launches without their
+ * transfers, or the transfers as launches of their own.
  * rtp_mlp_set_ablation / rtp_moe_set_ablation do the same for a unit. */
 rtp_status rtp_ring_set_ablation(rtp_ring *ring, int rotate, int compute);
 
@@ -612,7 +614,10 @@ const char *rtp_gemm_kernel_name(int layout, int variant);
  * stream it is launched on.  rtp_prof_end() waits for them and fills
  * out[layout] (0 NT, 1 NN, 2 TN) with the number of launches, the sum of
  * their durations and the sum of their flops (2 M N K each).  Process-wide,
- * not thread-safe; meant for benchmarks. */
+ * not thread-safe; meant for benchmarks.  A timed launch holds one layout and
+ * no transfers: what rides in a launch otherwise (rtp_pass_rides) goes out as a
+ * launch of its own ahead of it, and the input and the weight gradients of a
+ * riding backward step, otherwise one launch, as one each. */
 typedef struct { int64_t launches; double total_ms; double total_flops; } rtp_prof_result;
 rtp_status rtp_prof_begin(void);
 /* The same with alone != 0: the host drains the device before and after every

@@ -665,7 +665,7 @@ extern "C" int rtp_pass_rides(const rtp_ring_desc *d, int64_t T, rtp_pass pass)
 
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 {
-    if (r->dry || !r->abl_rotate || r->linears.empty()) return false; // (no layers: no launch to ride in)
+    if (r->dry || r->linears.empty()) return false; // (no layers: no launch to ride in)
     // the test delays hold the other streams back: those passes run on them
     if (r->delay_stage_ticks > 0 || r->delay_aux_ticks > 0 || r->delay_compute_ticks > 0) return false;
     int64_t T = 0;
@@ -2181,9 +2181,15 @@ static rtp_status mlp_bwd_two_stream(rtp_mlp *m, const void *X, const void *dY, 
 static rtp_status gemm_group_riding(rtp_ring *r, const int *layouts, const GemmArgs *a, int count)
 {
     if (!r->abl_compute) return carry_flush(r);
-    if (g_prof_on) { // timed launches are one GEMM each
+    if (g_prof_on) { // a timed launch is of one layout, and without the transfers
         RTP_TRY(carry_flush(r));
-        for (int i = 0; i < count; ++i) RTP_TRY(gemm_group(r, layouts[i], a + i, 1, r->cs()));
+        if (std::all_of(layouts, layouts + count, [&](int lay) { return lay == layouts[0]; }))
+            return gemm_group(r, layouts[0], a, count, r->cs());
+        for (int i = 0; i < count; ++i) {
+            GemmArgs one = a[i];
+            one.cu_share = 1;
+            RTP_TRY(gemm_group(r, layouts[i], &one, 1, r->cs()));
+        }
         return RTP_OK;
     }
     HIP_TRY(carry_launch(r, [&](const Riders &p) { return launch_gemm_bf16_pp_riding(layouts, a, count, p, r->cs()); }));
@@ -2208,18 +2214,20 @@ static rtp_status mlp_fwd_riding(rtp_mlp *m, const void *X, void *Y)
     const int n = r->d.n;
     const MlpShapes h = mlp_shapes(m);
     RTP_TRY(rtp_ring_begin(r, RTP_PASS_FWD));
+    const bool rot = r->abl_rotate;
     const size_t w1_bytes = h.w_off2, w2_bytes = r->d.w_bytes - h.w_off2;
-    auto buf = [&](int step) { return (const char *)r->d.buf_w_dev[r->w_idx(step)]; };
+    auto idx = [&](int step) { return rot ? r->w_idx(step) : r->res_idx; };
+    auto buf = [&](int step) { return (const char *)r->d.buf_w_dev[idx(step)]; };
     for (int t = 0; t <= n; ++t) {
-        if (t >= 1 && t <= n - 1)
+        if (rot && t >= 1 && t <= n - 1)
             RTP_TRY(carry_w_part(r, t - 1, r->shard_at(t - 1), r->shard_at(t), r->w_idx(t - 1), r->w_idx(t), h.w_off2, w2_bytes));
-        if (t <= n - 2)
+        if (rot && t <= n - 2)
             RTP_TRY(carry_w_part(r, t, r->shard_at(t), r->shard_at(t + 1), r->w_idx(t), r->w_idx(t + 1), 0, w1_bytes));
         static const int lay[2] = {LAY_NT, LAY_NT};
         GemmArgs g[2];
         int cnt = 0;
         if (t < n) {
-            r->rec(TR_FWD, t, r->shard_at(t), r->w_idx(t));
+            r->rec(TR_FWD, t, r->shard_at(t), idx(t));
             g[cnt++] = mlp_args_z(m, h, r->shard_at(t), X, buf(t));
         }
         if (t >= 1) g[cnt++] = mlp_args_down(m, h, r->shard_at(t - 1), t - 1, buf(t - 1), Y);
@@ -2239,11 +2247,12 @@ static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void
     const int n = r->d.n;
     const MlpShapes h = mlp_shapes(m);
     RTP_TRY(rtp_ring_begin(r, RTP_PASS_BWD));
-    const bool two_g = r->d.mode == RTP_DOUBLE_BUFFER;
+    const bool rot = r->abl_rotate, two_g = r->d.mode == RTP_DOUBLE_BUFFER;
     const size_t g1_bytes = h.g_off2, g2_bytes = r->d.g_bytes - h.g_off2;
     static const int lay[2] = {LAY_NN, LAY_TN};
-    auto wbuf = [&](int step) { return (const char *)r->d.buf_w_dev[r->w_idx(step)]; };
-    auto gbuf = [&](int step) { return (char *)r->d.buf_g_dev[r->g_idx(step)]; };
+    auto widx = [&](int step) { return rot ? r->w_idx(step) : r->res_idx; };
+    auto wbuf = [&](int step) { return (const char *)r->d.buf_w_dev[widx(step)]; };
+    auto gbuf = [&](int step) { return (char *)r->d.buf_g_dev[rot ? r->g_idx(step) : r->res_g_idx]; };
     auto first = [&](int s, GemmArgs *g) { // {dPre_s, dW2_s}
         g[0] = mlp_args_dh(m, h, r->shard_at(s), wbuf(s), dY);
         g[1] = mlp_args_dw2(m, h, r->shard_at(s), gbuf(s), dY);
@@ -2261,14 +2270,14 @@ static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void
     };
     // the last step's shard is the worker's own: both parts straight into the own slot, or neither (mlp_bwd_two_stream)
     bool own_to_slot = false;
-    if (r->abl_compute) {
+    if (rot && r->abl_compute) {
         GemmArgs g1[2], g2[2];
         first(n - 1, g1);
         second(n - 1, g2);
         own_to_slot = whole_k(g1) && whole_k(g2);
     }
     auto send = [&](int s, GemmArgs *g, size_t off) { // the sum goes straight to where the gradient part travels to
-        const bool fused = r->abl_compute && (s <= n - 2 ? whole_k(g) : own_to_slot);
+        const bool fused = rot && r->abl_compute && (s <= n - 2 ? whole_k(g) : own_to_slot);
         if (fused) {
             g[1].epi = EPI_ACC_LAST;
             g[1].C = r->home_g(r->shard_at(s)) + off;
@@ -2277,14 +2286,14 @@ static rtp_status mlp_bwd_riding(rtp_mlp *m, const void *X, const void *dY, void
     };
     bool sent1 = false, sent2 = false;
     for (int s = 0; s < n; ++s) {
-        const int k = r->shard_at(s), kin = s <= n - 2 ? r->shard_at(s + 1) : -1;
+        const int k = r->shard_at(s), kin = rot && s <= n - 2 ? r->shard_at(s + 1) : -1;
         if (kin >= 0) RTP_TRY(carry_w_part(r, s, k, kin, r->w_idx(s), r->w_idx(s + 1), 0, r->d.w_bytes));
         if (two_g) {
-            if (s > 0 || kin >= 0) RTP_TRY(carry_g_turnover(r, r->g_idx(s + 1), s > 0 ? r->shard_at(s - 1) : -1, kin));
-        } else if (s > 0) {
+            if (rot && (s > 0 || kin >= 0)) RTP_TRY(carry_g_turnover(r, r->g_idx(s + 1), s > 0 ? r->shard_at(s - 1) : -1, kin));
+        } else if (rot && s > 0) {
             RTP_TRY(carry_add(r, sent1 ? nullptr : r->home_g(r->shard_at(s - 1)), gbuf(s), r->home_g(k), g1_bytes));
         }
-        r->rec(TR_BWD, s, k, r->w_idx(s));
+        r->rec(TR_BWD, s, k, widx(s));
         GemmArgs g[2];
         first(s, g);
         sent2 = send(s, g, h.g_off2);

@@ -104,6 +104,58 @@ def test_mlp_unit(act, bias, dtype, T, n, rank, mode):
 
 
 @pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("kind", ["linear", "mlp"])
+def test_timing_aids_keep_the_schedule(kind, mode):
+    """Compute alone (no rotation) rides like the pass it stands for, moves nothing within the pass and gives what the streams
+    give without rotation; transfers alone leave the store as it is; timed forward launches are those of the pass."""
+    T, n, rank, I, O = 96, 4, 1, 128, 384
+    X, dY = normal(1, T, I, dtype=torch.bfloat16), normal(2, T, O if kind == "linear" else I, dtype=torch.bfloat16)
+    W, W2, g0, g2 = normal(3, O, I) * 0.1, normal(4, I, O) * 0.1, normal(5, O, I), normal(6, I, O)
+    runs = []
+    for streams in (False, True):
+        if kind == "linear":
+            layer = RtpLinear(W, T, n, rank, B.RTP_SPLIT_OUT, mode, G0=g0)
+            ring = layer.ring.handle
+        else:
+            layer = RtpMlp([W, W2], T, n, rank, B.RTP_ACT_GELU_ERF, mode, G0=[g0, g2])
+            ring = B.lib.rtp_mlp_ring(layer.handle)
+        scratch = torch.zeros(2, dtype=torch.int64, device=DEV)
+        B.check(B.lib.rtp_ring_set_test_delay_compute(ring, B._ptr(scratch), 1 if streams else 0), "delay")
+        count = lambda: B.lib.rtp_ring_trace(ring, None, 0, 1)
+        Y, dX = torch.empty_like(dY), torch.empty_like(X)
+        torch.cuda.synchronize()
+        B.rtp_prof_begin()
+        layer.forward(X, Y)
+        layer.sync()
+        launches = B.rtp_prof_end()["nt"][0]
+        assert launches == (n if kind == "linear" else n + 1)
+        home = layer.home_w.clone(), layer.home_g.clone()
+        layer.set_ablation(rotate=True, compute=False)
+        for _ in range(2):
+            layer.forward(X, Y)
+            assert B.lib.rtp_ring_rides(ring) == (not streams)
+            layer.backward(X, dY, dX)
+            assert B.lib.rtp_ring_rides(ring) == (not streams)
+        layer.sync()
+        assert torch.equal(home[0], layer.home_w) and torch.equal(home[1], layer.home_g)
+        layer.set_ablation(rotate=False, compute=True)
+        count()
+        layer.forward(X, Y)
+        assert B.lib.rtp_ring_rides(ring) == (not streams)
+        forward = count()
+        layer.backward(X, dY, dX)
+        assert B.lib.rtp_ring_rides(ring) == (not streams)
+        layer.sync()
+        records = forward, count()
+        held = [t.clone() for t in layer.buf_g[:1]]
+        runs.append(([Y, dX, layer.home_w.clone(), layer.home_g.clone()] + held, records))
+        layer.close()
+    assert runs[0][1] == runs[1][1] and runs[0][1][0] == n + 1, "n computes and the own shard's load"
+    for i, (x, y) in enumerate(zip(runs[0][0], runs[1][0])):
+        assert torch.equal(x, y), i
+
+
+@pytest.mark.parametrize("mode", [DB, IS])
 @pytest.mark.parametrize("dtype", [B.RTP_BF16, B.RTP_F16])
 @pytest.mark.parametrize("kind", ["out", "in", "mlp"])
 def test_outputs_off_a_16_byte_boundary(kind, dtype, mode):
