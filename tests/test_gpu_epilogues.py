@@ -134,3 +134,41 @@ def test_epilogue(variant, dtype, epi, pad):
             run()
             aux.check(acc, ROUND[dtype], what)
             c.check(ref, ROUND[dtype], what, scale=max(float(ref.abs().max()), float(acc.abs().max())))
+
+
+@pytest.mark.parametrize("pad", [8, 5])
+@pytest.mark.parametrize("epi", SUMS)
+@pytest.mark.parametrize("variant,dtype", [(1, "bf16"), (2, "bf16"), (5, "bf16"), (6, "bf16"), (7, "bf16"), (8, "bf16"), (7, "f16"), (8, "f16")])
+def test_a_piece_of_a_bias_joins_the_sum(variant, dtype, epi, pad):
+    """ldaux entries from column `half` on: inside a tile, across the edges of every tile's fragments, up to the last column
+    and past none; what lies beside the piece in the bias is never added, the other columns are those without one."""
+    td, K = TD[dtype], 200 if dtype == "bf16" else 192
+    M, N = 72, 264
+    g = torch.Generator(device=DEV).manual_seed(epi)
+    normal = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    a, b = normal(M, K).to(td), (normal(N, K) / math.sqrt(K)).to(td)
+    acc = a.double() @ b.double().T
+    args = G.GemmArgs(A=a.data_ptr(), B=b.data_ptr(), lda=K, ldb=K, M=M, N=N, K=K, epi=epi, elem=G.ELEM[dtype])
+    for half, width in ((0, 8), (16, 8), (28, 8), (60, 72), (120, 16), (128, 128), (252, 12), (0, 264)):
+        bias = torch.full((width + 8,), float("nan"), device=DEV, dtype=td)
+        bias[:width] = normal(width).to(td)
+        args.bias, args.half, args.ldaux = bias.data_ptr(), half, width
+        piece = torch.zeros(N, device=DEV, dtype=torch.float64)
+        piece[half:half + width] = bias[:width].double()
+        for out in (td, torch.float32) if epi == G.EPI_ACC_LAST else (None,):
+            what = (variant, dtype, epi, pad, half, width, out)
+            print(f"piece {what}", flush=True)
+            w0 = normal(M, N)
+            ws = Matrix(M, N, pad, torch.float32, w0)
+            args.ws, args.ldws = ws.full.data_ptr(), ws.ld
+            if out is not None:
+                c = Matrix(M, N, pad, out)
+                args.C, args.ldc, args.c_is_f32 = c.full.data_ptr(), c.ld, int(out == torch.float32)
+            assert G.launch(B.LAYOUT_NT, args, variant) == 0, what
+            torch.cuda.synchronize()
+            want = piece + acc if epi == G.EPI_ACC_FIRST else w0.double() + piece + acc
+            if out is None:
+                ws.check(want, 0.0, what)
+            else:
+                c.check(want, 0.0 if out == torch.float32 else ROUND[dtype], what)
+                assert torch.equal(ws.view, w0), what
