@@ -214,8 +214,10 @@ rtp_status rtp_ring_destroy(rtp_ring *ring);
  * n == 1 or after rtp_ring_seek_bwd_start(), any idle state; loads that shard's
  * gradient part, after writing the gradient shard an earlier backward pass
  * left in the buffer (the worker's own; see rtp_ring_resident_grad) back to
- * its slot: gradients accumulate over any number of passes.  These two gradient transfers run on
- * the stage stream; only the weight-gradient kernels wait for them.
+ * its slot: gradients accumulate over any number of passes.  These two
+ * gradient transfers run on the stage stream, and only the weight-gradient
+ * kernels wait for them; a pass that rides (rtp_pass_rides) makes them as one
+ * launch on the compute stream, ahead of everything else of the pass.
  * RTP_ERR_STATE if a pass is in progress.
  * Stream capture of a pass is not supported: the calls decide on the host,
  * when they are made, what a pass enqueues (the write-back above, for one),
@@ -425,8 +427,11 @@ rtp_status rtp_linear_fwd(rtp_linear *lin, int step, const void *X_dev, void *Y_
  *   SPLIT_IN   G_k += dY^T X[:, k*o:(k+1)*o] ;  dX[:, k*o:(k+1)*o] = dY W_k
  *              (times act'(preact) if act != NONE).
  * When this step rotates, the gradient part of this linear is handed to the
- * stage stream right after the dW kernel.  dX_dev may be NULL to skip the
- * input gradient.  Same state rules as rtp_linear_fwd, in a backward pass. */
+ * stage stream right after the dW kernel.  (Riding pass: the kernel stores its
+ * sum where the part travels to; one gradient buffer takes the next shard's part
+ * before the call returns, two with the next rotation, which also sends a sum
+ * whose kernel could not.  The two GEMMs are one launch where there is an
+ * auxiliary stream.)  dX_dev may be NULL to skip the input gradient.  Same state rules as rtp_linear_fwd, in a backward pass. */
 rtp_status rtp_linear_bwd(rtp_linear *lin, int step, const void *X_dev, const void *dY_dev, void *dX_dev);
 
 /* rtp_linear_fwd for callers that cannot allocate device memory: code under
@@ -500,19 +505,23 @@ size_t rtp_mlp_slot_g_bytes(const rtp_mlp_desc *d);
 /* An MLP block with its first GEMM output-partitioned and its second
  * input-partitioned, so that unit k is self-contained and rotates as one
  * message.  rtp_mlp_fwd runs n x (rtp_rotate_step, rtp_linear_fwd x 2);
- * rtp_mlp_bwd the mirror image.  For bf16 units in a staged mode whose shapes
- * the tiled kernel takes (all contraction lengths multiples of 32), the
- * forward pass instead issues the same GEMMs as grouped launches with the
- * second linear one step behind the first ({Z_t, down_{t-1}}), the shard
- * parts moving accordingly; so does the backward pass when no auxiliary
- * stream was given ({dX_{s-1}, dPre_s} and {dW1_s, dW2_s}).  Results, buffers
- * and bytes moved are the same; so are they for a unit with biases (the
- * pieces of the second linear's bias and the bias gradients are small kernels
- * between the launches).  RTP_FLAG_STEPWISE in `flags` keeps the
- * step-by-step sequence everywhere.  `rotate` = 0 skips the rotation calls (the
- * resident shard is used for every step: timing of compute alone, results
- * are meaningless); `compute` = 0 skips the kernels (timing of the staging
- * traffic alone). */
+ * rtp_mlp_bwd the mirror image.  A 16-bit unit in a staged mode whose shapes
+ * the tiled kernel takes makes the same GEMMs in fewer launches:
+ *   forward            {Z_t, down_{t-1}}, the second linear one step behind the
+ *                      first, the shard parts moving accordingly;
+ *   backward, riding   (rtp_pass_rides, with an auxiliary stream)
+ *                      {dPre_s, dW2_s}, {dX_s, dW1_s};
+ *   backward, else     one launch per GEMM, the weight gradients on the
+ *                      auxiliary stream; without one (or with
+ *                      RTP_FLAG_GROUPED) {dX_{s-1}, dPre_s}, {dW1_s, dW2_s}.
+ * Results, buffers and bytes moved are the same.  With biases, a piece of the
+ * second linear's bias joins the sum inside the GEMM of its step; the bias
+ * gradients are workgroups of the riding launches, and small kernels behind
+ * the weight gradients elsewhere.  RTP_FLAG_STEPWISE in `flags` keeps the
+ * step-by-step sequence everywhere.  Ablation: `rotate` = 0 skips the rotation
+ * calls (the resident shard is used for every step: timing of compute alone,
+ * results are meaningless); `compute` = 0 skips the kernels (timing of the
+ * staging traffic alone). */
 rtp_status rtp_mlp_create(rtp_mlp **out, const rtp_mlp_desc *desc);
 rtp_status rtp_mlp_destroy(rtp_mlp *mlp);
 rtp_status rtp_mlp_fwd(rtp_mlp *mlp, const void *X_dev, void *Y_dev);

@@ -352,9 +352,9 @@ static rtp_status copy_batch_flush(rtp_ring *r, CopyBatch &b, hipStream_t s, hip
     const int n = b.n;
     b.n = 0;
     // Large transfers go out one by one, in the order they were added (callers add the transfer a kernel waits for
-    // first): beside a GEMM that fills the machine, copies that follow one another disturb it less than the same
-    // bytes all at once (Llama-shaped unit: 4.31 against 4.39 ms per pass, expert unit 16.9 against 17.2; the
-    // large unit with its few tokens per shard is the exception, 9.1 against 8.9), and a launch is nothing beside them.
+    // first): beside GEMMs that fill the machine, copies that follow one another disturb them less than the same bytes
+    // all at once, and a launch is nothing beside them.  us a training step, in one launch -> one by one: expert unit
+    // 17459 -> 17076, Llama-shaped unit 4133 -> 4126, large unit 8543 -> 8553.
     size_t total = 0;
     for (int i = 0; i < n; ++i) total += b.bytes[i];
     if (n == 1 || (r->d.flags & RTP_FLAG_STAGE_MEMCPY) || total >= COPY_BATCH_MAX_BYTES) {
@@ -697,10 +697,10 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
         l->next_step = 0;
         l->unsent[0] = l->unsent[1] = false;
     }
-    // The forward pass of a ring whose linears are all output-partitioned enqueues nothing on the auxiliary stream, so
-    // its rotations and its end need not be ordered after that stream (a record and a wait each; such a pass is bound
-    // by how fast the host enqueues: 200 tokens, 2048 -> 6144 over 8 workers, 290-369 us with them and 238-271 without,
-    // six runs of each; 64 tokens, 512 -> 1024 over 16, 530-691 and 440-470).  An input-partitioned
+    // On the streams, the forward pass of a ring whose linears are all output-partitioned enqueues nothing on the auxiliary
+    // one, so its rotations and its end need not be ordered after it (a record and a wait each; 200 tokens, 2048 -> 6144
+    // over 8 workers, which rides otherwise, 290-369 us with them and 238-271 without, six runs of each; 64 tokens,
+    // 512 -> 1024 over 16, 530-691 and 440-470).  An input-partitioned
     // linear created while the pass is open says so when it uses the stream; the caller of a bare ring, a unit and a
     // backward pass may use it at any time.
     if (pass == RTP_PASS_FWD && !r->linears.empty() &&

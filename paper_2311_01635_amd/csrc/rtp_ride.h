@@ -113,7 +113,8 @@ __device__ __forceinline__ void ride_sum(const RideList &g, const unsigned block
 // the list of a launch that has about `idle` compute units to spare for it
 hipError_t ride_list(const Riders &r, int idle, RideList *out);
 
-// Bound: memory latency (a few megabytes a launch), hence eight 16-byte reads in flight per thread and direction.
+// Bound: memory latency (a few megabytes a launch), hence all of a thread's 16-byte reads in flight, up to eight a
+// direction: eight in a workgroup of 512 threads with a piece of 64 KB, two with the smallest of 16 KB.
 // The units go in runs of 8, 4 and 2 a thread without a bounds test: behind a test per unit the compiler waited for each
 // read before it issued the next (512-token pass of the Llama-shaped unit 450 -> 437).
 // A thread reads its units of `buf` and `in` before it writes them, so a segment may send what `buf` holds and
