@@ -8,10 +8,10 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librtp.so")
 # (the files that take longest to compile first)
-SOURCES = ["rtp_gemm_pp_nn_tn.hip", "rtp_gemm_pp_nn_tn_f16.hip",
-           "rtp_gemm_pp_nt.hip", "rtp_gemm_pp_nn.hip", "rtp_gemm_pp_tn.hip",
+SOURCES = ["rtp_gemm_pp_nt.hip", "rtp_gemm_pp_nn.hip", "rtp_gemm_pp_tn.hip",
            "rtp_gemm_pp_nt_f16.hip", "rtp_gemm_pp_nn_f16.hip", "rtp_gemm_pp_tn_f16.hip",
-           "rtp_gemm_bf16.hip", "rtp_gemm_pp.hip", "rtp_misc_kernels.hip", "rtp_host.cpp"]
+           "rtp_gemm_bf16.hip", "rtp_gemm_pp_nn_tn.hip", "rtp_gemm_pp_nn_tn_f16.hip",
+           "rtp_gemm_pp.hip", "rtp_misc_kernels.hip", "rtp_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops off: the compiler must not form packed fp32 arithmetic from scalar code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

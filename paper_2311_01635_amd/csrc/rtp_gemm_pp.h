@@ -97,9 +97,9 @@ struct PpGroup {
     PpProblem p[PP_MAX_GROUP];
     RideList ride;
 };
-// The kernel of a backward step: LAY_NN and LAY_TN problems in one launch.  Its results are written four-wide: with the
-// element-wise epilogue too, on two layouts and four heights, the library took 7:20 to build instead of 2:10, for callers
-// whose tensors start off a 16-byte boundary; those get one launch per layout.
+// The kernel of a backward step: LAY_NN and LAY_TN problems in one launch.  Four-wide results only: with an element-wise
+// form of it too, on two layouts and four heights, the library took 7:20 to build instead of 3:20, for callers whose tensors
+// start off a 16-byte boundary; those get one launch per layout.
 constexpr int LAY_NN_TN = 3;
 
 // The transposing fragment read, issued as an instruction of our own.  Through the builtin the compiler puts a
@@ -479,10 +479,9 @@ __device__ __forceinline__ void pp_any_tile(const PpProblem &P, const int pid, c
 // Workgroup ids are dealt round-robin to the 8 XCDs.  XCD x works through its own list: its
 // contiguous eighth of problem 0's tiles, then of problem 1's, ...; workgroup 8 l + x takes entry l
 // of that list (the host sizes the grid for the longest list; surplus workgroups leave at once).
-template <int LAY, typename E>
-__global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
+template <int LAY, typename E, bool WIDE_ONLY>
+__device__ __forceinline__ void pp_workgroup(const PpGroup &g, char *smem)
 {
-    __shared__ __attribute__((aligned(1024))) char smem[pp::SMEM_BYTES];
     if (blockIdx.x < g.sum_blocks) {
         if (blockIdx.x < g.ride.sum_blocks) ride_sum<E, pp::NTHR>(g.ride, blockIdx.x, (float *)smem);
         return;
@@ -518,11 +517,27 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
     const int kt_count = min(kt_each, kt_total - kt_begin);
     if (kt_count <= 0) return;
     if constexpr (LAY != LAY_NN_TN)
-        pp_any_tile<LAY, E, false>(P, pid, kt_begin, kt_count, smem);
+        pp_any_tile<LAY, E, WIDE_ONLY>(P, pid, kt_begin, kt_count, smem);
     else if (P.lay == LAY_NN)
-        pp_any_tile<LAY_NN, E, true>(P, pid, kt_begin, kt_count, smem);
+        pp_any_tile<LAY_NN, E, WIDE_ONLY>(P, pid, kt_begin, kt_count, smem);
     else
-        pp_any_tile<LAY_TN, E, true>(P, pid, kt_begin, kt_count, smem);
+        pp_any_tile<LAY_TN, E, WIDE_ONLY>(P, pid, kt_begin, kt_count, smem);
+}
+
+// A launch whose results all take four-wide accesses, and any launch.  The element-wise epilogue has kernels of its own: beside
+// the four-wide one it cost the others 0.4-0.6 % (512-token pass of the Llama-shaped unit 412 -> 414.6 us, its training
+// step 4010 -> 4027).
+template <int LAY, typename E>
+__global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[pp::SMEM_BYTES];
+    pp_workgroup<LAY, E, true>(g, smem);
+}
+template <int LAY, typename E>
+__global__ __launch_bounds__(pp::NTHR) void gemm_pp_element_kernel(const PpGroup g)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[pp::SMEM_BYTES];
+    pp_workgroup<LAY, E, false>(g, smem);
 }
 
 // done: an event that completes with the kernel (its completion signal is the event's: no packet of its own in
@@ -530,11 +545,19 @@ __global__ __launch_bounds__(pp::NTHR) void gemm_pp_kernel(const PpGroup g)
 template <int LAY, typename E>
 static hipError_t launch_gemm_pp_layout(const PpGroup &g, hipStream_t s, hipEvent_t done)
 {
+    void (*kernel)(PpGroup) = gemm_pp_kernel<LAY, E>;
+    for (int q = 0; q < g.count; ++q)
+        if (!g.p[q].vec_epilogue) {
+            if constexpr (LAY == LAY_NN_TN)
+                return hipErrorInvalidValue; // (such a pair goes out as one launch per layout)
+            else
+                kernel = gemm_pp_element_kernel<LAY, E>;
+        }
     const unsigned blocks = g.sum_blocks + g.tile_blocks + g.ride.blocks;
     if (done)
-        hipExtLaunchKernelGGL((gemm_pp_kernel<LAY, E>), dim3(blocks), dim3(pp::NTHR), 0, s, nullptr, done, 0, g);
+        hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(pp::NTHR), 0, s, nullptr, done, 0, g);
     else
-        hipLaunchKernelGGL((gemm_pp_kernel<LAY, E>), dim3(blocks), dim3(pp::NTHR), 0, s, g);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(pp::NTHR), 0, s, g);
     return hipGetLastError();
 }
 
