@@ -194,33 +194,32 @@ __device__ __forceinline__ void gemm_f32_small_tile(const GemmArgs &p, const int
         }
 }
 
-template <bool SMALL>
-__global__ __launch_bounds__(SMALL ? STHR : 256) void gemm_f32_kernel(const F32Group g)
+__global__ __launch_bounds__(STHR) void gemm_f32_kernel(const F32Group g)
 {
     __shared__ __attribute__((aligned(16))) float lds[(SM + SN) * SPITCH];
-    static_assert(2 * FK * (FT + 4) <= (SM + SN) * SPITCH, "both tiles' LDS");
     if (blockIdx.x >= g.tile_blocks) {
-        ride<SMALL ? STHR : 256>(g.ride, blockIdx.x - g.tile_blocks);
+        ride<STHR>(g.ride, blockIdx.x - g.tile_blocks);
         return;
     }
     const int q = g.count > 1 && blockIdx.x >= g.p[1].first ? 1 : 0;
     const unsigned b = blockIdx.x - g.p[q].first;
     const int m = (int)(b / g.p[q].tiles_n), n = (int)(b % g.p[q].tiles_n);
-    if constexpr (SMALL) {
-        float(*sA)[SPITCH] = (float(*)[SPITCH])lds, (*sB)[SPITCH] = sA + SM;
-        switch (g.p[q].lay) {
-        case LAY_NT: gemm_f32_small_tile<LAY_NT>(g.p[q].a, m * SM, n * SN, sA, sB); break;
-        case LAY_NN: gemm_f32_small_tile<LAY_NN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
-        default: gemm_f32_small_tile<LAY_TN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
-        }
-    } else {
-        float(*sA)[FT + 4] = (float(*)[FT + 4])lds, (*sB)[FT + 4] = sA + FK;
-        switch (g.p[q].lay) {
-        case LAY_NT: gemm_f32_tile<LAY_NT>(g.p[q].a, m * FT, n * FT, sA, sB); break;
-        case LAY_NN: gemm_f32_tile<LAY_NN>(g.p[q].a, m * FT, n * FT, sA, sB); break;
-        default: gemm_f32_tile<LAY_TN>(g.p[q].a, m * FT, n * FT, sA, sB); break;
-        }
+    float(*sA)[SPITCH] = (float(*)[SPITCH])lds, (*sB)[SPITCH] = sA + SM;
+    switch (g.p[q].lay) {
+    case LAY_NT: gemm_f32_small_tile<LAY_NT>(g.p[q].a, m * SM, n * SN, sA, sB); break;
+    case LAY_NN: gemm_f32_small_tile<LAY_NN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
+    default: gemm_f32_small_tile<LAY_TN>(g.p[q].a, m * SM, n * SN, sA, sB); break;
     }
+}
+
+// 64x64 tiles, one layout and no transfers a kernel: in one with them and all three layouts, whose registers the greediest
+// sets, 4096 x 4096 over K = 512 took 289 / 288 / 321 us (NT / NN / TN) instead of 245 / 257 / 252.
+template <int LAY>
+__global__ __launch_bounds__(256) void gemm_f32_large_kernel(const GemmArgs p, const unsigned tiles_n)
+{
+    __shared__ float sA[FK][FT + 4];
+    __shared__ float sB[FK][FT + 4];
+    gemm_f32_tile<LAY>(p, (int)(blockIdx.x / tiles_n) * FT, (int)(blockIdx.x % tiles_n) * FT, sA, sB);
 }
 
 // Up to this many small tiles the small tile is the faster one.  us, K = 1024, 64x64 -> 16x32: 256 tiles (512 x 256) 93.9 -> 24.2,
@@ -251,14 +250,24 @@ hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int cou
     }
     if (g.count == 0) return launch_riders(r, s);
     if (blocks >= (int64_t)1 << 30) return hipErrorInvalidValue;
+    if (!small) { // the transfers are nothing beside such a product
+        const hipError_t e = launch_riders(r, s);
+        if (e != hipSuccess) return e;
+        for (int i = 0; i < g.count; ++i) {
+            const auto &p = g.p[i];
+            const dim3 grid((unsigned)((i + 1 < g.count ? g.p[i + 1].first : blocks) - p.first)), block(256);
+            switch (p.lay) {
+            case LAY_NT: hipLaunchKernelGGL(gemm_f32_large_kernel<LAY_NT>, grid, block, 0, s, p.a, p.tiles_n); break;
+            case LAY_NN: hipLaunchKernelGGL(gemm_f32_large_kernel<LAY_NN>, grid, block, 0, s, p.a, p.tiles_n); break;
+            default: hipLaunchKernelGGL(gemm_f32_large_kernel<LAY_TN>, grid, block, 0, s, p.a, p.tiles_n); break;
+            }
+        }
+        return hipGetLastError();
+    }
     g.tile_blocks = (unsigned)blocks;
     const hipError_t e = ride_list(r, 256, &g.ride);
     if (e != hipSuccess) return e;
-    const dim3 grid(g.tile_blocks + g.ride.blocks);
-    if (small)
-        hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(STHR), 0, s, g);
-    else
-        hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3(g.tile_blocks + g.ride.blocks), dim3(STHR), 0, s, g);
     return hipGetLastError();
 }
 

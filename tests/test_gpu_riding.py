@@ -104,6 +104,14 @@ def test_mlp_unit(act, bias, dtype, T, n, rank, mode):
 
 
 @pytest.mark.parametrize("mode", [DB, IS])
+def test_fp32_layer_on_the_large_tile(mode):
+    """Past 4096 small tiles an fp32 step's GEMMs are launches of their own, behind the transfers'."""
+    T, I, O, n = 2100, 256, 2100, 2
+    make = lambda: RtpLinear(normal(1, O, I) * 0.1, T, n, 1, B.RTP_SPLIT_OUT, mode, B.RTP_F32, G0=normal(2, O, I))
+    same(make, normal(3, T, I), normal(4, T, O), True)
+
+
+@pytest.mark.parametrize("mode", [DB, IS])
 @pytest.mark.parametrize("kind", ["linear", "mlp"])
 def test_timing_aids_keep_the_schedule(kind, mode):
     """Compute alone (no rotation) rides like the pass it stands for, moves nothing within the pass and gives what the streams
