@@ -98,9 +98,11 @@ struct PpGroup {
     RideList ride;
 };
 // The kernel of a backward step: LAY_NN and LAY_TN problems in one launch.  Four-wide results only: with an element-wise
-// form of it too, on two layouts and four heights, the library took 7:20 to build instead of 3:20, for callers whose tensors
+// form of it too, on two layouts and four heights, the library took 7:20 to build instead of 3:40, for callers whose tensors
 // start off a 16-byte boundary; those get one launch per layout.
 constexpr int LAY_NN_TN = 3;
+// whose launches carry bias gradients: those that hold weight gradients (the others' kernels are built without)
+constexpr bool takes_sums(int lay) { return lay == LAY_TN || lay == LAY_NN_TN; }
 
 // The transposing fragment read, issued as an instruction of our own.  Through the builtin the compiler puts a
 // wait for ALL outstanding direct loads in front of these reads (it cannot tell that the LDS stage being read is
@@ -482,11 +484,14 @@ __device__ __forceinline__ void pp_any_tile(const PpProblem &P, const int pid, c
 template <int LAY, typename E, bool WIDE_ONLY>
 __device__ __forceinline__ void pp_workgroup(const PpGroup &g, char *smem)
 {
-    if (blockIdx.x < g.sum_blocks) {
-        if (blockIdx.x < g.ride.sum_blocks) ride_sum<E, pp::NTHR>(g.ride, blockIdx.x, (float *)smem);
-        return;
+    unsigned tile_block = blockIdx.x;
+    if constexpr (takes_sums(LAY)) {
+        if (tile_block < g.sum_blocks) {
+            if (tile_block < g.ride.sum_blocks) ride_sum<E, pp::NTHR>(g.ride, tile_block, (float *)smem);
+            return;
+        }
+        tile_block -= g.sum_blocks;
     }
-    const unsigned tile_block = blockIdx.x - g.sum_blocks;
     if (tile_block >= g.tile_blocks) {
         ride<pp::NTHR>(g.ride, tile_block - g.tile_blocks);
         return;

@@ -356,6 +356,7 @@ static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a
     }
     g.tile_blocks = per_xcd * 8;
     if (riders) {
+        if (riders->sums > 0 && !takes_sums(layout)) return hipErrorInvalidValue;
         const hipError_t e = ride_list(*riders, std::max(64, compute_units() - (int)std::min<long>(tiles, 1 << 20)), &g.ride);
         if (e != hipSuccess) return e;
         g.sum_blocks = (g.ride.sum_blocks + 7) / 8 * 8;
@@ -439,21 +440,28 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
     if (count == 0) return launch_riders(r, s);
     const int lay = common_layout(layouts, count);
     if (lay < 0) return hipErrorInvalidValue;
-    if (lay == LAY_NN_TN && !std::all_of(a, a + count, gemm_epilogue_vec_ok)) {
-        // one launch per layout, the transfers in the first
-        bool first = true;
-        for (int one : {LAY_NN, LAY_TN}) {
-            GemmArgs b[PP_MAX_GROUP];
-            int lays[PP_MAX_GROUP], n = 0;
-            for (int q = 0; q < count; ++q)
-                if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
-            const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n), first ? &r : nullptr, s, nullptr);
-            if (e != hipSuccess) return e;
-            first = false;
-        }
-        return hipSuccess;
+    const bool wide = std::all_of(r.sum, r.sum + r.sums, [](const RideSum &q) { return colsum_wide(q.Y, q.ld, q.cols); });
+    const bool one_each = lay == LAY_NN_TN && !std::all_of(a, a + count, gemm_epilogue_vec_ok);
+    if (!one_each && (r.sums == 0 || (wide && takes_sums(lay))))
+        return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &r, s, nullptr);
+    Riders moves = r, sums = r;
+    moves.sums = sums.count = 0;
+    if (!wide || !takes_sums(lay)) {
+        const hipError_t e = launch_riders(sums, s);
+        if (e != hipSuccess) return e;
+        sums.sums = 0;
     }
-    return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &r, s, nullptr);
+    if (!one_each) return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &moves, s, nullptr);
+    // one launch per layout, the transfers in the first and the sums in the second
+    for (int one : {LAY_NN, LAY_TN}) {
+        GemmArgs b[PP_MAX_GROUP];
+        int lays[PP_MAX_GROUP], n = 0;
+        for (int q = 0; q < count; ++q)
+            if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
+        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n), one == LAY_NN ? &moves : &sums, s, nullptr);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_gemm_bf16_pp(int layout, const GemmArgs &a, int bm_override, hipStream_t s)

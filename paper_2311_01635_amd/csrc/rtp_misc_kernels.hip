@@ -461,9 +461,9 @@ hipError_t ride_list(const Riders &r, int idle, RideList *out)
         const RideSum &q = r.sum[i];
         if (q.rows < 0 || !q.in || !q.out || (q.rows > 0 && !q.Y)) return hipErrorInvalidValue;
         if (q.cols <= 0) continue;
+        if (!colsum_wide(q.Y, q.ld, q.cols)) return hipErrorInvalidValue;
         auto &d = out->sum[out->sums++];
         d.Y = q.Y; d.ld = q.ld; d.rows = q.rows; d.cols = q.cols; d.in = q.in; d.out = q.out;
-        d.wide = colsum_wide(q.Y, q.ld, q.cols);
         d.first = out->sum_blocks;
         out->sum_blocks += (unsigned)((q.cols + COLSUM_COLS - 1) / COLSUM_COLS);
     }
@@ -479,8 +479,10 @@ hipError_t launch_riders(const Riders &r, hipStream_t s)
         const hipError_t e = launch_colsum(q.elem, q.Y, q.ld, q.rows, q.cols, q.in, q.out, s);
         if (e != hipSuccess) return e;
     }
+    Riders moves = r;
+    moves.sums = 0;
     RideList g;
-    const hipError_t e = ride_list(r, 512, &g);
+    const hipError_t e = ride_list(moves, 512, &g);
     if (e != hipSuccess || g.blocks == 0) return e;
     hipLaunchKernelGGL(ride_kernel, dim3(g.blocks), dim3(COPY_THREADS), 0, s, g);
     return hipGetLastError();

@@ -167,7 +167,8 @@ def test_timing_aids_keep_the_schedule(kind, mode):
 @pytest.mark.parametrize("dtype", [B.RTP_BF16, B.RTP_F16])
 @pytest.mark.parametrize("kind", ["out", "in", "mlp"])
 def test_outputs_off_a_16_byte_boundary(kind, dtype, mode):
-    """No four-wide epilogue: a backward step's two layouts are two launches, the transfers and bias sums in the first."""
+    """No four-wide epilogue: a backward step's two layouts are two launches, the transfers in the first, the bias sums in the
+    second."""
     td, T, n, rank = TD[dtype], 96, 4, 2
     I, O = (128, 96 * n) if kind != "in" else (96 * n, 128)
     X, W, b = normal(1, T, I, dtype=td), normal(3, O, I) * 0.1, normal(4, O)
