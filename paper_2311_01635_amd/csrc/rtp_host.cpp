@@ -321,7 +321,8 @@ static rtp_status copy_async(rtp_ring *r, void *dst, const void *src, size_t byt
         HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
         if (done) HIP_TRY(hipEventRecord(done, s));
     } else {
-        HIP_TRY(launch_copy(dst, src, bytes, s, done));
+        // (on the compute stream a copy runs between the kernels, on the stage stream beside them)
+        HIP_TRY((s == r->cs() ? launch_copy_alone : launch_copy)(dst, src, bytes, s, done));
     }
     return RTP_OK;
 }

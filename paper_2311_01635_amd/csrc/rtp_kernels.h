@@ -124,6 +124,8 @@ hipError_t launch_act_f32(int kind, const float *pre, int64_t ldpre, const float
 
 // device-to-device staging copy with a bounded number of workgroups
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr);
+// the same where nothing else runs beside the copy
+hipError_t launch_copy_alone(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr);
 // up to COPY_MAX_SEGS copies that do not overlap one another, as one launch (no order among them)
 constexpr int COPY_MAX_SEGS = 4;
 hipError_t launch_copy_multi(void *const *dst, const void *const *src, const size_t *bytes, int count, hipStream_t s,

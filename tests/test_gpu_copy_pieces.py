@@ -11,20 +11,23 @@ DEV = "cuda:0"
 PIECE = 4096                                     # 16-byte units
 
 
-@pytest.mark.parametrize("units", [1, 255, PIECE - 1, PIECE, PIECE + 1, 3 * PIECE, 3 * PIECE + 257])
+@pytest.mark.parametrize("units", [1, 255, PIECE // 4 - 1, PIECE // 4, PIECE // 4 + 1, PIECE - 1, PIECE, PIECE + 1, 3 * PIECE, 3 * PIECE + 257])
 def test_copy(units):
     one = getattr(B.lib, "_ZN3rtp11launch_copyEPvPKvmP12ihipStream_tP11ihipEvent_t")
     one.restype, one.argtypes = C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
+    alone = getattr(B.lib, "_ZN3rtp17launch_copy_aloneEPvPKvmP12ihipStream_tP11ihipEvent_t")   # (pieces of a quarter)
+    alone.restype, alone.argtypes = one.restype, one.argtypes
     many = getattr(B.lib, "_ZN3rtp17launch_copy_multiEPKPvPKPKvPKmiP12ihipStream_tP11ihipEvent_t")
     many.restype = C.c_int
     many.argtypes = [C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.POINTER(C.c_size_t), C.c_int, C.c_void_p, C.c_void_p]
     stream = torch.cuda.current_stream().cuda_stream
-    for count in (1, 3):
+    for count in (1, 3, "alone"):
+        call, count = (alone, 1) if count == "alone" else (one, count)
         src = [torch.randint(0, 2 ** 31, (units * 4 + 8,), dtype=torch.int32, device=DEV) for _ in range(count)]
         dst = [torch.full_like(s, 7) for s in src]
         print(f"copy of {units} units, {count} segments", flush=True)
         if count == 1:
-            assert one(dst[0].data_ptr() + 16, src[0].data_ptr() + 16, units * 16, stream, None) == 0
+            assert call(dst[0].data_ptr() + 16, src[0].data_ptr() + 16, units * 16, stream, None) == 0
         else:
             at = lambda ts: (C.c_void_p * count)(*[t.data_ptr() + 16 for t in ts])
             assert many(at(dst), at(src), (C.c_size_t * count)(*[units * 16] * count), count, stream, None) == 0
