@@ -512,20 +512,25 @@ hipError_t launch_riders(const Riders &r, hipStream_t s)
     return hipGetLastError();
 }
 
-__global__ void fill_zero_kernel(u32x4 *dst, int64_t n16)
+// Bound: HBM writes.  A thread stores one unit, past the caches, and its workgroup of 4 KB is done: the many short workgroups
+// keep the stores of a slot's pages together.  us, 4096 workgroups that walk the buffer -> so: 16 MB 5.3 -> 4.5, 90 MB 15.1 ->
+// 14.5, 541 MB 122 -> 86, 1.9 GB 488 -> 296, 5.6 GB 1331 -> 879 (6.7 TB/s); 16 KB a workgroup 984, 64 KB 1040.
+__global__ __launch_bounds__(256) void fill_zero_kernel(u32x4 *dst, int64_t n16)
 {
     const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n16; e += (int64_t)gridDim.x * blockDim.x)
-        dst[e] = z;
+    const int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (e < n16) __builtin_nontemporal_store(z, dst + e);
 }
 
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s)
 {
     if (bytes == 0) return hipSuccess;
     if ((bytes & 15) || ((uintptr_t)dst & 15)) return hipErrorInvalidValue;
-    const int64_t n16 = (int64_t)(bytes >> 4);
-    const int blocks = (int)((n16 + 255) / 256 > 4096 ? 4096 : (n16 + 255) / 256);
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, s, (u32x4 *)dst, n16);
+    constexpr int64_t MOST = (int64_t)1 << 30; // units a launch (a grid holds 2^32 threads)
+    for (int64_t at = 0, n16 = (int64_t)(bytes >> 4); at < n16; at += MOST) {
+        const int64_t n = std::min(MOST, n16 - at);
+        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (u32x4 *)dst + at, n);
+    }
     return hipGetLastError();
 }
 
