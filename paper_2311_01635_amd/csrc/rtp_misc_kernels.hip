@@ -330,14 +330,16 @@ hipError_t launch_act_f32(int kind, const float *pre, int64_t ldpre, const float
 }
 
 // ---- staging copy ---------------------------------------------------------------------
-// Each workgroup moves one 64 KB piece with 16-byte accesses and exits, so the
+// Each workgroup moves one 32 KB piece with 16-byte accesses and exits, so the
 // copy slips into whatever wave slots the GEMM running beside it leaves free
 // instead of holding compute units for the whole transfer.  A whole piece is moved without a bounds test per unit:
 // behind one, the compiler waits ahead of every store for all stores before it (Llama-shaped unit's training step
-// against one reference on one box: 1.004 -> 1.027 x as fast).
+// against one reference on one box: 1.004 -> 1.027 x as fast).  Pieces of 64 KB -> 32 KB -> 16 KB beside the GEMMs, us a
+// training step: large unit 8122 -> 7953 -> 8032, expert unit 15973 -> 15792 -> 15709, Llama-shaped 3999 -> 3993 -> 3999;
+// alone, 541 MB 225 -> 183 -> 189.
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 constexpr int COPY_THREADS = 256;
-constexpr int COPY_PER_THREAD = 16; // x 16 bytes
+constexpr int COPY_PER_THREAD = 8; // x 16 bytes
 
 // the units of a thread from `base` on
 template <int PER>
@@ -406,7 +408,7 @@ hipError_t launch_copy_alone(void *dst, const void *src, size_t bytes, hipStream
     return launch_copy_pieces(copy_alone_kernel, COPY_ALONE_PER_THREAD, dst, src, bytes, s, done);
 }
 
-// Up to COPY_MAX_SEGS independent copies as one launch: workgroups [first[i], first[i + 1]) move segment i, 64 KB
+// Up to COPY_MAX_SEGS independent copies as one launch: workgroups [first[i], first[i + 1]) move segment i, 32 KB
 // each as above, so the segments go through the machine one after the other as separate launches would, for one
 // launch's worth of host time.  The segments must not overlap one another (no order among them).
 struct CopySegs {
@@ -512,8 +514,7 @@ hipError_t launch_riders(const Riders &r, hipStream_t s)
     return hipGetLastError();
 }
 
-// Bound: HBM writes.  A thread stores one unit, past the caches, and its workgroup of 4 KB is done: the many short workgroups
-// keep the stores of a slot's pages together.  us, 4096 workgroups that walk the buffer -> so: 16 MB 5.3 -> 4.5, 90 MB 15.1 ->
+// Bound: HBM writes.  A thread stores one unit, past the caches, and its workgroup of 4 KB is done.  us, 4096 workgroups that walk the buffer -> so: 16 MB 5.3 -> 4.5, 90 MB 15.1 ->
 // 14.5, 541 MB 122 -> 86, 1.9 GB 488 -> 296, 5.6 GB 1331 -> 879 (6.7 TB/s); 16 KB a workgroup 984, 64 KB 1040.
 __global__ __launch_bounds__(256) void fill_zero_kernel(u32x4 *dst, int64_t n16)
 {
