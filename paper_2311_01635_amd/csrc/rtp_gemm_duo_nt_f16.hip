@@ -1,0 +1,6 @@
+// Instantiation of the GEMM of two workgroups a compute unit for fp16 inputs, NT operand layout (see rtp_gemm_duo.h).
+#include "rtp_gemm_duo.h"
+
+namespace rtp {
+hipError_t launch_gemm_duo_nt_f16(const PpGroup &g, hipStream_t s) { return launch_gemm_duo_layout<LAY_NT, _Float16>(g, s); }
+} // namespace rtp

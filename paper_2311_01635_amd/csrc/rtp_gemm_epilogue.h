@@ -69,14 +69,14 @@ template <typename E, int FN, int NSTRIDE>
 __device__ __forceinline__ void gemm_epilogue_bias(const GemmArgs &p, int col0, float (&bj)[FN])
 {
     const E *bias = (const E *)p.bias;
-    const bool gated = p.epi == EPI_SWIGLU_FWD;
+    const bool gated = FN > 1 && p.epi == EPI_SWIGLU_FWD;
     const bool on = bias && (gated || p.epi == EPI_STORE || p.epi == EPI_GELU_ERF_FWD || p.epi == EPI_GELU_TANH_FWD);
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
         int idx;
         bool lim;
         if (gated) {
-            const int col = col0 + (j % (FN / 2)) * NSTRIDE;
+            const int col = col0 + (j % (FN > 1 ? FN / 2 : 1)) * NSTRIDE;
             lim = col < p.half;
             idx = col + (j >= FN / 2 ? p.half : 0);
         } else {
@@ -268,7 +268,10 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
                                                      int rbase_wave, int n0, int wn32, int lane, char *land = nullptr)
 {
     typedef typename ElemVec<E>::v4 out4; // four consecutive elements of the 16-bit output type
-    static_assert(FN == 2, "staging layout is written for two 32-column fragments per wave");
+    static_assert(FN == 2 || FN == 1, "staging layout is written for one or two 32-column fragments per wave");
+    // a parked fragment row is read back four columns per lane: LPR lanes to a row, ROWS rows at a time
+    constexpr int LPR = 8 * FN, ROWS = 64 / LPR, ROUNDS = 32 / ROWS;
+    const int lrow = lane / LPR, c4 = lane % LPR;
     const int M = p.M, N = p.N;
     const int64_t ldc = p.ldc, ldws = p.ldws, ldaux = p.ldaux;
     const int half = p.half;
@@ -284,7 +287,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
     f32x4 pv = {0.0f, 0.0f, 0.0f, 0.0f};
     const bool pieced = p.bias && p.epi >= EPI_ACC_FIRST && p.epi <= EPI_ACC_LAST;
     if (pieced) {
-        const int c4 = lane & 15, at = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4 - half;
+        const int at = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4 - half;
         if (at >= 0 && at < (int)ldaux) pv = from_elem4<E>(*(const out4 *)((const E *)p.bias + at));
     }
     auto piece = [&](f32x4 old) { return pieced ? old + pv : old; };
@@ -301,7 +304,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
         __builtin_amdgcn_wave_barrier();
     };
 
-    if (p.epi == EPI_SWIGLU_FWD) {
+    if (FN == 2 && p.epi == EPI_SWIGLU_FWD) { // (a wave of one fragment column is not asked for pairs)
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             park(i);
@@ -331,8 +334,8 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
         for (int i = 0; i < FM; ++i) {
             park(i);
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int row = 4 * r + (lane >> 4), c4 = lane & 15;
+            for (int r = 0; r < ROUNDS; ++r) {
+                const int row = ROWS * r + lrow;
                 const f32x4 x = *(const f32x4 *)(wlds + row * EPI_LDS_PITCH + c4 * 4);
                 const int grow = rbase_wave + i * 32 + row;
                 const int col = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4;
@@ -354,18 +357,17 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
         for (int i = 0; i < FM; ++i) {
             park(i);
 #pragma unroll
-            for (int r0 = 0; r0 < 8; r0 += DEPTH) {
+            for (int r0 = 0; r0 < ROUNDS; r0 += DEPTH) {
                 decltype(load(0, 0)) in[DEPTH];
 #pragma unroll
                 for (int r = r0; r < r0 + DEPTH; ++r) {
-                    const int c4 = lane & 15;
-                    const int grow = rbase_wave + i * 32 + 4 * r + (lane >> 4);
+                    const int grow = rbase_wave + i * 32 + ROWS * r + lrow;
                     const int col = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4;
                     in[r - r0] = load(min(grow, M - 1), min(col, N - 4));
                 }
 #pragma unroll
                 for (int r = r0; r < r0 + DEPTH; ++r) {
-                    const int row = 4 * r + (lane >> 4), c4 = lane & 15;
+                    const int row = ROWS * r + lrow;
                     const f32x4 x = *(const f32x4 *)(wlds + row * EPI_LDS_PITCH + c4 * 4);
                     const int grow = rbase_wave + i * 32 + row;
                     const int col = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4;
@@ -385,9 +387,8 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
         const __amdgpu_buffer_rsrc_t rws = __builtin_amdgcn_make_buffer_rsrc((void *)ws, 0, ws_bytes, 0x00020000);
         auto fetch = [&](int i) {
 #pragma unroll
-            for (int r = 0; r < EPI_LAND_ROUNDS; ++r) {
-                const int c4 = lane & 15;
-                const int grow = rbase_wave + i * 32 + 4 * r + (lane >> 4);
+            for (int r = 0; r < ROUNDS; ++r) {
+                const int grow = rbase_wave + i * 32 + ROWS * r + lrow;
                 const int col = n0 + (c4 >> 3) * NSTRIDE + wn32 + (c4 & 7) * 4;
                 const unsigned off = ((unsigned)min(grow, M - 1) * (unsigned)ldws + (unsigned)min(col, N - 4)) * 4u;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rws, (lds_vp)(land + r * 1024), 16, off, 0, 0, 0);
@@ -399,8 +400,8 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
             park(i);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this fragment row's reads have landed
 #pragma unroll
-            for (int r = 0; r < EPI_LAND_ROUNDS; ++r) {
-                const int row = 4 * r + (lane >> 4), c4 = lane & 15;
+            for (int r = 0; r < ROUNDS; ++r) {
+                const int row = ROWS * r + lrow;
                 const f32x4 x = *(const f32x4 *)(wlds + row * EPI_LDS_PITCH + c4 * 4);
                 const f32x4 old = *(const f32x4 *)(land + r * 1024 + lane * 16);
                 const int grow = rbase_wave + i * 32 + row;
@@ -441,10 +442,11 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs &p, f32x16 (
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             park(i);
-            const int j = lane >> 5, c = lane & 31;
+            const int j = FN == 2 ? lane >> 5 : 0, c = lane & 31;
             const int col = n0 + j * NSTRIDE + wn32 + c;
 #pragma unroll 8
-            for (int row = 0; row < 32; ++row) {
+            for (int at = 0; at < 32; at += 2 / FN) {
+                const int row = FN == 2 ? at : at + (lane >> 5);
                 const float x = wlds[row * EPI_LDS_PITCH + j * 32 + c];
                 const int grow = rbase_wave + i * 32 + row;
                 if (grow < M && col < N) unsafeAtomicAdd(ws + (int64_t)grow * ldws + col, x);

@@ -82,7 +82,7 @@ constexpr int BUFFER_RSRC_FLAGS = 0x00020000;
 // One GEMM of a group launch and the whole group (a kernel argument, passed by value).
 struct PpProblem {
     GemmArgs a;
-    int bm;               // tile height: 256, 192 or 128 (tiles 256 wide), or 64 (128 wide, rtp_gemm_small.h)
+    int bm, bn;           // tile: 256, 192 or 128 x 256, or 64 x 128 (rtp_gemm_small.h); 128 or 64 x 128, or 64 x 64 (rtp_gemm_duo.h)
     int tiles_m, tiles_n;
     int vec_epilogue;
     int ksplit;           // > 1: the K loop is cut into this many chunks, one workgroup each, whose partial
@@ -481,6 +481,37 @@ __device__ __forceinline__ void pp_any_tile(const PpProblem &P, const int pid, c
 // Workgroup ids are dealt round-robin to the 8 XCDs.  XCD x works through its own list: its
 // contiguous eighth of problem 0's tiles, then of problem 1's, ...; workgroup 8 l + x takes entry l
 // of that list (the host sizes the grid for the longest list; surplus workgroups leave at once).
+// bk: sub-tile depth of problem P
+template <typename BkOf>
+__device__ __forceinline__ bool pp_find_tile(const PpGroup &g, const unsigned tile_block, BkOf bk_of, int &q, int &pid, int &kt_begin, int &kt_count)
+{
+    const int xcd = tile_block & 7;
+    int l = tile_block >> 3;
+    pid = -1;
+    for (q = 0; q < g.count; ++q) {
+        const int tiles = g.p[q].tiles_m * g.p[q].tiles_n * g.p[q].ksplit;
+        const int base = tiles >> 3, rem = tiles & 7;
+        const int mine = base + (xcd < rem ? 1 : 0);
+        if (l < mine) {
+            pid = xcd * base + min(xcd, rem) + l;
+            break;
+        }
+        l -= mine;
+    }
+    if (pid < 0) return false;
+    const PpProblem &P = g.p[q];
+    // K chunk of this workgroup: consecutive ids are different tiles of the same chunk, so they share panels
+    const int per_chunk = P.tiles_m * P.tiles_n;
+    const int chunk = pid / per_chunk;
+    pid -= chunk * per_chunk;
+    const int bk = bk_of(P);
+    const int kt_total = (P.a.K + bk - 1) / bk;
+    const int kt_each = (kt_total + P.ksplit - 1) / P.ksplit;
+    kt_begin = chunk * kt_each;
+    kt_count = min(kt_each, kt_total - kt_begin);
+    return kt_count > 0;
+}
+
 template <int LAY, typename E, bool WIDE_ONLY>
 __device__ __forceinline__ void pp_workgroup(const PpGroup &g, char *smem)
 {
@@ -496,31 +527,9 @@ __device__ __forceinline__ void pp_workgroup(const PpGroup &g, char *smem)
         ride<pp::NTHR>(g.ride, tile_block - g.tile_blocks);
         return;
     }
-    const int xcd = tile_block & 7;
-    int l = tile_block >> 3;
-    int q = 0, pid = -1;
-    for (; q < g.count; ++q) {
-        const int tiles = g.p[q].tiles_m * g.p[q].tiles_n * g.p[q].ksplit;
-        const int base = tiles >> 3, rem = tiles & 7;
-        const int mine = base + (xcd < rem ? 1 : 0);
-        if (l < mine) {
-            pid = xcd * base + min(xcd, rem) + l;
-            break;
-        }
-        l -= mine;
-    }
-    if (pid < 0) return;
+    int q, pid, kt_begin, kt_count;
+    if (!pp_find_tile(g, tile_block, [](const PpProblem &P) { return P.bm == 64 ? pps::BK : pp::BK; }, q, pid, kt_begin, kt_count)) return;
     const PpProblem &P = g.p[q];
-    // K chunk of this workgroup: consecutive ids are different tiles of the same chunk, so they share panels
-    const int per_chunk = P.tiles_m * P.tiles_n;
-    const int chunk = pid / per_chunk;
-    pid -= chunk * per_chunk;
-    const int bk = P.bm == 64 ? pps::BK : pp::BK;
-    const int kt_total = (P.a.K + bk - 1) / bk;
-    const int kt_each = (kt_total + P.ksplit - 1) / P.ksplit;
-    const int kt_begin = chunk * kt_each;
-    const int kt_count = min(kt_each, kt_total - kt_begin);
-    if (kt_count <= 0) return;
     if constexpr (LAY != LAY_NN_TN)
         pp_any_tile<LAY, E, WIDE_ONLY>(P, pid, kt_begin, kt_count, smem);
     else if (P.lay == LAY_NN)

@@ -1,6 +1,6 @@
-// Launcher of the ping-pong bf16 GEMM: shape rules, the choice of tile heights for a
+// Launcher of the tiled 16-bit GEMMs (rtp_gemm_pp.h, rtp_gemm_duo.h): shape rules, the choice of tiles for a
 // launch (one GEMM or a group of independent ones) and the order of the group's problems.
-#include "rtp_gemm_pp.h"
+#include "rtp_gemm_duo.h"
 
 #include <string.h>
 
@@ -21,6 +21,10 @@ hipError_t launch_gemm_pp_nn_f16(const PpGroup &g, hipStream_t s, hipEvent_t don
 hipError_t launch_gemm_pp_tn_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
 hipError_t launch_gemm_pp_nn_tn_bf16(const PpGroup &g, hipStream_t s, hipEvent_t done);
 hipError_t launch_gemm_pp_nn_tn_f16(const PpGroup &g, hipStream_t s, hipEvent_t done);
+hipError_t launch_gemm_duo_nt_bf16(const PpGroup &g, hipStream_t s);
+hipError_t launch_gemm_duo_nn_tn_bf16(const PpGroup &g, hipStream_t s);
+hipError_t launch_gemm_duo_nt_f16(const PpGroup &g, hipStream_t s);
+hipError_t launch_gemm_duo_nn_tn_f16(const PpGroup &g, hipStream_t s);
 
 bool gemm_bf16_pp_supported(int layout, const GemmArgs &a)
 {
@@ -50,21 +54,24 @@ static int compute_units()
     return cus;
 }
 
-// output columns of a tile of height bm (of each half for the paired epilogue)
-static int tile_width(const GemmArgs &a, int bm)
-{
-    const int bn = bm == 64 ? pps::BN : pp::BN;
-    return a.epi == EPI_SWIGLU_FWD ? bn / 2 : bn;
-}
+// A tile is named by its height in gemm_pp_kernel (256, 192, 128: 256 wide; 64: 128 wide), by one of the codes DUO_* in
+// gemm_duo_kernel.
+static bool is_duo(int tile) { return tile >= DUO_128X128; }
+static int tile_rows(int tile) { return !is_duo(tile) ? tile : tile == DUO_128X128 ? 128 : 64; }
+// output columns of a tile, and of each half for the paired epilogue
+static int tile_cols(int tile) { return is_duo(tile) ? (tile == DUO_64X64 ? 64 : 128) : tile == 64 ? pps::BN : pp::BN; }
+static int tile_width(const GemmArgs &a, int tile) { return a.epi == EPI_SWIGLU_FWD ? tile_cols(tile) / 2 : tile_cols(tile); }
+static int tile_bk(int tile, int lay) { return is_duo(tile) ? ppd::sub_tile(lay, tile_rows(tile)) : tile == 64 ? pps::BK : pp::BK; }
 static int tiles_n_of(const GemmArgs &a, int bm)
 {
     const int ncols = a.epi == EPI_SWIGLU_FWD ? a.half : a.N, bn = tile_width(a, bm);
     return (ncols + bn - 1) / bn;
 }
+static int tiles_m_of(const GemmArgs &a, int bm) { return (a.M + tile_rows(bm) - 1) / tile_rows(bm); }
 // K chunks that are not empty when the K loop of a tile of height bm is cut in `ksplit`; *each: sub-tiles of a chunk
-static int k_chunks(const GemmArgs &a, int bm, int ksplit, int *each)
+static int k_chunks(const GemmArgs &a, int bm, int ksplit, int *each, int lay = LAY_NT)
 {
-    const int bk = bm == 64 ? pps::BK : pp::BK;
+    const int bk = tile_bk(bm, lay);
     const int kt = (a.K + bk - 1) / bk;
     *each = (kt + ksplit - 1) / ksplit;
     return (kt + *each - 1) / *each;
@@ -158,7 +165,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
         const int q = order[i];
         int each;
         const int chunks = k_chunks(a[q], bm[q], ks[q], &each);
-        const long tm = (a[q].M + bm[q] - 1) / bm[q], tn = tiles_n_of(a[q], bm[q]);
+        const long tm = tiles_m_of(a[q], bm[q]), tn = tiles_n_of(a[q], bm[q]);
         const long tiles = tm * tn * chunks;
         const long mine = (tiles + 7) / 8;
         // interior tiles, then the last tile column, the last tile row and the corner, each with its own cost
@@ -204,6 +211,13 @@ struct PlanKey {
 struct Plan {
     int bm[PP_MAX_GROUP], ks[PP_MAX_GROUP], order[PP_MAX_GROUP];
 };
+
+// whether a tile of gemm_duo_kernel takes the problem
+static bool duo_takes(const GemmArgs &a, int tile)
+{
+    if (tile < DUO_128X128 || tile > DUO_64X64 || a.sync || !gemm_epilogue_vec_ok(a)) return false;
+    return tile != DUO_64X64 || a.epi != EPI_SWIGLU_FWD; // (a wave of it holds one fragment column: no pairs)
+}
 
 // the height a caller asks for; 0 (pick) also for one that is not built, or that the problem's counters cannot take
 static int forced_height(const GemmArgs &a, int asked)
@@ -318,6 +332,132 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
     return best_plan;
 }
 
+// ---- the kernel of a riding launch -------------------------------------------------------
+// A launch that rides has the machine to itself and is priced in us for both kernels.  `once` a launch, and for each tile
+// a compute unit works through `fixed` and `step` a sub-tile (of 32 K in tall tiles, else 64; `step_full` more where the
+// machine is full of accumulators and its clock drops).  Fitted to the kernel times of 70 shapes drawn from the layers' ranges
+// (16 to 8192 tokens, shards of 64 to 1536) and of 4096^3 products: within 7 (64 x 64) to 15 % (192 x 256).  A compute unit with
+// one workgroup of the duo kernel waits for its operands between the sub-tiles of the two wider tiles (`one_each`).
+// Passes of 75 units and layers of all sizes, the tall tiles everywhere -> the cheaper of the two by this estimate: 0.92 to
+// 1.39 times as fast, geometric mean 1.097 (the duo kernel everywhere 1.075, the better one known beforehand 1.11).
+struct TileTime {
+    double once, fixed, step, step_full;
+};
+static TileTime tile_time(int tile, int epi, bool one_each)
+{
+    const double pairs = epi == EPI_SWIGLU_FWD ? 1.08 : 1.0; // (such launches came out that much later than their estimate)
+    switch (tile) {
+    case 256: return {0.0, 9.1, 0.406, 0.27};
+    case 192: return {0.0, 7.8, 0.380, 0.16};
+    case 128: return {0.0, 6.7, 0.316, 0.14};
+    case 64: return {1.4, 4.3, 0.208, 0.05};
+    case DUO_128X128: return {3.8, 1.9, pairs * (one_each ? 0.70 : 0.44), 0.0};
+    case DUO_64X128: return {3.9, 1.7, pairs * (one_each ? 0.40 : 0.285), 0.0};
+    default: return {3.4, 1.25, one_each ? 0.21 : 0.178, 0.0};
+    }
+}
+// bytes the epilogue moves per element of the product
+static double epilogue_bytes(int epi, int c_is_f32)
+{
+    switch (epi) {
+    case EPI_ACC_ADD: return 8.0;
+    case EPI_ACC_ATOMIC: return 16.0;
+    case EPI_ACC_FIRST: return 4.0;
+    case EPI_ACC_LAST: return c_is_f32 ? 8.0 : 6.0;
+    case EPI_SWIGLU_FWD: return 3.0;
+    case EPI_SWIGLU_BWD: return 8.0;
+    case EPI_STORE: return c_is_f32 ? 4.0 : 2.0;
+    default: return 4.0;
+    }
+}
+// Greedy list schedule of one XCD's share over its compute units (the two workgroups a unit may hold of the duo kernel share
+// its load path, so they count as one after the other).  ride_bytes: what the transfers read and write.
+static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const int *order, int count, double ride_bytes)
+{
+    const int cus = compute_units(), servers = std::max(1, cus / 8);
+    double area = 0.0, once = 0.0;
+    long tiles = 0;
+    for (int q = 0; q < count; ++q) {
+        int each;
+        const long n = (long)tiles_m_of(a[q], tile[q]) * tiles_n_of(a[q], tile[q]) * k_chunks(a[q], tile[q], ks[q], &each);
+        tiles += n;
+        area += (double)n * tile_rows(tile[q]) * tile_cols(tile[q]);
+    }
+    const double full = std::min(1.0, area / (cus * 65536.0));
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    for (int i = 0; i < servers; ++i) free_at.push(0.0);
+    double end = 0.0, busy[PP_MAX_GROUP], loop[PP_MAX_GROUP], whole[PP_MAX_GROUP];
+    long count_of[PP_MAX_GROUP];
+    for (int i = 0; i < count; ++i) {
+        const int q = order[i];
+        int each;
+        const int chunks = k_chunks(a[q], tile[q], ks[q], &each);
+        const long n = ((long)tiles_m_of(a[q], tile[q]) * tiles_n_of(a[q], tile[q]) * chunks + 7) / 8;
+        const TileTime t = tile_time(tile[q], a[q].epi, tiles <= cus);
+        once = std::max(once, t.once);
+        const double cost = t.fixed + each * (t.step + full * t.step_full) +
+                            full * tile_rows(tile[q]) * tile_cols(tile[q]) * epilogue_bytes(chunks > 1 ? EPI_ACC_ATOMIC : a[q].epi, a[q].c_is_f32) * cus / 10e6;
+        busy[q] = each * t.step / cost;
+        loop[q] = each * t.step;
+        whole[q] = cost;
+        count_of[q] = n;
+        for (long k = 0; k < n; ++k) {
+            const double done = free_at.top() + cost;
+            free_at.pop();
+            free_at.push(done);
+            end = std::max(end, done);
+        }
+    }
+    if (is_duo(tile[0]) && tiles > cus) { // a tile beside another all along: the slower, the longer that one multiplies
+        double share = 0.0, sum = 0.0;
+        for (int q = 0; q < count; ++q) share += busy[q] * whole[q] * count_of[q], sum += whole[q] * count_of[q];
+        for (int q = 0; q < count; ++q) end = std::max(end, whole[q] + 1.2 * loop[q] * share / sum);
+    }
+    end += once;
+    // half of the shorter of the two, tiles or transfers, is hidden by the other where no compute unit is idle
+    const double ride = ride_bytes > 0.0 ? 2.0 + ride_bytes / 4.6e6 : 0.0;
+    const double idle = std::max(0.0, 1.0 - (double)tiles / (is_duo(tile[0]) ? 1.5 * cus : cus));
+    return std::max(end, ride) + 0.5 * (1.0 - idle) * std::min(end, ride);
+}
+
+// The best plan of gemm_duo_kernel for the group; cap: chunks of K each problem may be cut in.  False if it does not take it.
+static bool plan_duo(const GemmArgs *a, int count, const int *cap, Plan *best_plan, double ride_bytes, double *best)
+{
+    const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
+    int nopt[PP_MAX_GROUP], otile[PP_MAX_GROUP][18], oks[PP_MAX_GROUP][18];
+    for (int q = 0; q < count; ++q) {
+        nopt[q] = 0;
+        for (int tile = DUO_128X128; tile <= DUO_64X64; ++tile)
+            for (int k : splits) {
+                if (!duo_takes(a[q], tile) || k > cap[q] || (k > 1 && a[q].K / 32 / k < 8)) break;
+                otile[q][nopt[q]] = tile;
+                oks[q][nopt[q]++] = k;
+            }
+        if (nopt[q] == 0) return false;
+    }
+    *best = 1e300;
+    int idx[PP_MAX_GROUP] = {0, 0, 0, 0};
+    for (;;) {
+        Plan p;
+        memset(&p, 0, sizeof p);
+        double cost[PP_MAX_GROUP];
+        for (int q = 0; q < count; ++q) {
+            p.bm[q] = otile[q][idx[q]];
+            p.ks[q] = oks[q][idx[q]];
+            p.order[q] = q;
+            int each;
+            (void)k_chunks(a[q], p.bm[q], p.ks[q], &each);
+            cost[q] = each * tile_time(p.bm[q], a[q].epi, false).step;
+        }
+        std::stable_sort(p.order, p.order + count, [&](int i, int j) { return cost[i] > cost[j]; });
+        const double t = launch_us(a, p.bm, p.ks, p.order, count, ride_bytes);
+        if (t < *best - 1e-9) *best = t, *best_plan = p;
+        int q = 0;
+        while (q < count && ++idx[q] == nopt[q]) idx[q++] = 0;
+        if (q == count) return true;
+    }
+}
+
 void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_override, int *bm_out, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
@@ -333,6 +473,7 @@ static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a
                                hipStream_t s, hipEvent_t done)
 {
     const int *bm = pl.bm, *order = pl.order;
+    const bool duo = is_duo(bm[0]); // (a plan's tiles are of one kernel)
     PpGroup g;
     memset(&g, 0, sizeof g);
     g.count = count;
@@ -343,13 +484,14 @@ static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a
         PpProblem &p = g.p[i];
         p.a = a[q];
         p.lay = layouts ? layouts[q] : layout;
-        p.bm = bm[q];
-        p.tiles_m = (a[q].M + bm[q] - 1) / bm[q];
+        p.bm = tile_rows(bm[q]);
+        p.bn = tile_cols(bm[q]);
+        p.tiles_m = tiles_m_of(a[q], bm[q]);
         p.tiles_n = tiles_n_of(a[q], bm[q]);
         p.vec_epilogue = gemm_epilogue_vec_ok(a[q]) ? 1 : 0;
         // as many chunks as are not empty
         int each;
-        p.ksplit = k_chunks(a[q], bm[q], pl.ks[q], &each);
+        p.ksplit = k_chunks(a[q], bm[q], pl.ks[q], &each, p.lay);
         if (p.ksplit > 1) p.a.epi = EPI_ACC_ATOMIC;
         per_xcd += (unsigned)(((long)p.tiles_m * p.tiles_n * p.ksplit + 7) / 8);
         tiles += (long)p.tiles_m * p.tiles_n * p.ksplit;
@@ -357,13 +499,19 @@ static hipError_t launch_group(int layout, const int *layouts, const GemmArgs *a
     g.tile_blocks = per_xcd * 8;
     if (riders) {
         if (riders->sums > 0 && !takes_sums(layout)) return hipErrorInvalidValue;
-        const hipError_t e = ride_list(*riders, std::max(64, compute_units() - (int)std::min<long>(tiles, 1 << 20)), &g.ride);
+        const int slots = compute_units() * (duo ? 2 : 1);
+        const hipError_t e = ride_list(*riders, std::max(64, slots - (int)std::min<long>(tiles, 1 << 20)), &g.ride);
         if (e != hipSuccess) return e;
         g.sum_blocks = (g.ride.sum_blocks + 7) / 8 * 8;
         for (int i = 0; i < riders->sums; ++i)
             if (riders->sum[i].elem != a[0].elem) return hipErrorInvalidValue;
     }
     const bool f16 = a[0].elem == ELEM_F16;
+    if (duo) {
+        if (done) return hipErrorInvalidValue;
+        if (layout == LAY_NT) return f16 ? launch_gemm_duo_nt_f16(g, s) : launch_gemm_duo_nt_bf16(g, s);
+        return f16 ? launch_gemm_duo_nn_tn_f16(g, s) : launch_gemm_duo_nn_tn_bf16(g, s);
+    }
     switch (layout) {
     case LAY_NT: return f16 ? launch_gemm_pp_nt_f16(g, s, done) : launch_gemm_pp_nt_bf16(g, s, done);
     case LAY_NN: return f16 ? launch_gemm_pp_nn_f16(g, s, done) : launch_gemm_pp_nn_bf16(g, s, done);
@@ -388,6 +536,13 @@ hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a_in, int count
         a[count++] = a_in[q];
     }
     if (count == 0) return done ? hipEventRecord(done, s) : hipSuccess; // nothing to launch: the event still marks this point
+    if (count == 1 && is_duo(forced[0])) {
+        if (!duo_takes(a[0], forced[0])) return hipErrorInvalidValue;
+        Plan pl;
+        memset(&pl, 0, sizeof pl);
+        pl.bm[0] = forced[0], pl.ks[0] = 1;
+        return launch_group(layout, nullptr, a, 1, pl, nullptr, s, done);
+    }
     const Plan pl = plan_group(layout, a, count, forced, count == 1 ? a[0].cu_share : 1);
     return launch_group(layout, nullptr, a, count, pl, nullptr, s, done);
 }
@@ -406,22 +561,63 @@ static int common_layout(const int *layouts, int count)
 // make (a[q].cu_share) has one chunk or two, it is cut in no more here.  Without that 8 % of shapes drawn from the layers'
 // ranges were split that are not there, and 4 % in more than two chunks.  The fp16 unit with biases (384 x 768 over 1024, two
 // chunks instead of four) 407 -> 399 us a step.
-static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count)
+static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count, double ride_bytes)
 {
-    int cap[PP_MAX_GROUP];
+    struct Key {
+        int layout, count, takes, ride;
+        int dims[PP_MAX_GROUP][6];
+        bool operator<(const Key &o) const { return memcmp(this, &o, sizeof *this) < 0; }
+    } key;
+    static std::map<Key, Plan> cache;
+    static std::mutex lock;
+    memset(&key, 0, sizeof key);
+    key.layout = layout; key.count = count; key.ride = (int)(ride_bytes / (1 << 16)); key.takes = 1;
+    for (int q = 0; q < count; ++q) {
+        const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi, a[q].c_is_f32 + 2 * may_split_k(a[q]), a[q].cu_share};
+        memcpy(key.dims[q], d, sizeof d);
+        key.takes = key.takes && duo_takes(a[q], DUO_128X128);
+    }
+    {
+        std::lock_guard<std::mutex> g(lock);
+        const auto it = cache.find(key);
+        if (it != cache.end()) return it->second;
+    }
+    int cap[PP_MAX_GROUP], split_duo[PP_MAX_GROUP];
     for (int q = 0; q < count; ++q) {
         cap[q] = MAX_SPLIT;
         if (!may_split_k(a[q])) continue;
         const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share)).ks[0];
         if (alone <= 2) cap[q] = alone;
     }
-    return plan_group(layout, a, count, nullptr, 1, cap);
+    Plan best = plan_group(layout, a, count, nullptr, 1, cap), duo;
+    double us = 0.0;
+    for (int q = 0; q < count; ++q) split_duo[q] = best.ks[q] > 1 ? cap[q] : 1; // split only where the other kernel would
+    const double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes);
+    // (the estimate flatters 128 x 128 tiles in launches that fill the machine several times over)
+    if (key.takes && plan_duo(a, count, split_duo, &duo, ride_bytes, &us) && us < tall * (tall < 40.0 ? 1.05 : 0.90)) best = duo;
+    std::lock_guard<std::mutex> g(lock);
+    cache[key] = best;
+    return best;
+}
+
+static double ride_traffic(const Riders &r)
+{
+    double bytes = 0.0;
+    for (int i = 0; i < r.count; ++i) bytes += 2.0 * (double)r.seg[i].bytes * ((r.seg[i].out ? 1 : 0) + (r.seg[i].in ? 1 : 0));
+    return bytes;
+}
+
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out)
+{
+    if (count < 1 || count > PP_MAX_GROUP) return;
+    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count, ride_bytes);
+    for (int q = 0; q < count; ++q) tiles_out[q] = pl.bm[q];
 }
 
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
-    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count);
+    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count, 0.0);
     for (int q = 0; q < count; ++q) ksplit_out[q] = pl.ks[q];
 }
 
@@ -443,7 +639,7 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
     const bool wide = std::all_of(r.sum, r.sum + r.sums, [](const RideSum &q) { return colsum_wide(q.Y, q.ld, q.cols); });
     const bool one_each = lay == LAY_NN_TN && !std::all_of(a, a + count, gemm_epilogue_vec_ok);
     if (!one_each && (r.sums == 0 || (wide && takes_sums(lay))))
-        return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &r, s, nullptr);
+        return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count, ride_traffic(r)), &r, s, nullptr);
     Riders moves = r, sums = r;
     moves.sums = sums.count = 0;
     if (!wide || !takes_sums(lay)) {
@@ -451,14 +647,14 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
         if (e != hipSuccess) return e;
         sums.sums = 0;
     }
-    if (!one_each) return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &moves, s, nullptr);
+    if (!one_each) return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count, ride_traffic(moves)), &moves, s, nullptr);
     // one launch per layout, the transfers in the first and the sums in the second
     for (int one : {LAY_NN, LAY_TN}) {
         GemmArgs b[PP_MAX_GROUP];
         int lays[PP_MAX_GROUP], n = 0;
         for (int q = 0; q < count; ++q)
             if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
-        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n), one == LAY_NN ? &moves : &sums, s, nullptr);
+        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n, 0.0), one == LAY_NN ? &moves : &sums, s, nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -3056,7 +3056,7 @@ extern "C" rtp_status rtp_gemm(int layout, rtp_dtype in_dtype, rtp_dtype out_dty
         if (out_dtype != RTP_F32 && out_dtype != in_dtype) return fail(RTP_ERR_UNSUPPORTED, "rtp_gemm: bad output type");
         a.elem = in_dtype == RTP_F16 ? ELEM_F16 : ELEM_BF16;
         hipError_t e = timed_launch(layout, 2.0 * a.M * a.N * a.K, (hipStream_t)stream,
-                                    [&] { return launch_gemm_bf16(layout, a, variant, (hipStream_t)stream); });
+                                    [&] { return variant > 8 && M > 0 && N > 0 ? hipErrorInvalidValue : launch_gemm_bf16(layout, a, variant, (hipStream_t)stream); });
         if (e == hipErrorInvalidValue) return fail(RTP_ERR_SHAPE, "rtp_gemm: sizes/alignment the bf16 kernels need are not met");
         HIP_TRY(e);
     } else if (in_dtype == RTP_F32) {

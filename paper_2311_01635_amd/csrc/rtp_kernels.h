@@ -57,7 +57,9 @@ constexpr int SYNC_ROWS = 64;
 
 // bf16 inputs, fp32 MFMA accumulation.  variant: 0 = pick by shape; 1, 2, 3 = register-staged
 // tiles (256x256/8 waves, 128x128/4 waves, 256x256/4 waves); 4 = the ping-pong kernel with the
-// tile height picked by shape; 5, 6, 7, 8 = the ping-pong kernel with tile height 256, 192, 128 (256 wide), 64 (128 wide).
+// tile height picked by shape; 5, 6, 7, 8 = the ping-pong kernel with tile height 256, 192, 128 (256 wide), 64 (128 wide);
+// 9, 10, 11 = the kernel of two workgroups a compute unit, DUO_128X128, DUO_64X128, DUO_64X64.
+enum : int { DUO_128X128 = 1024, DUO_64X128, DUO_64X64 };
 hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStream_t s);
 // alignment and minimum sizes every bf16 kernel needs (M, N > 0 assumed)
 bool gemm_bf16_args_ok(int layout, const GemmArgs &a);
@@ -108,6 +110,8 @@ struct Riders {
 hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
 // the K splits that launch would use
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);
+// the tiles it would use: heights of gemm_pp_kernel or codes DUO_* (ride_bytes: what its transfers read and write)
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out);
 // the transfers as a launch of their own
 hipError_t launch_riders(const Riders &r, hipStream_t s);
 

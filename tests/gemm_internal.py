@@ -49,6 +49,23 @@ def riding_split(M, N, K, dx, cu_share=2):
     return ks[1]
 
 
+_riding_tiles = getattr(B.lib, "_ZN3rtp25gemm_bf16_pp_riding_tilesEPKiPKNS_8GemmArgsEidPi")
+_riding_tiles.restype = None
+_riding_tiles.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.c_double, C.POINTER(C.c_int)]
+
+
+def riding_tiles(group, ride_bytes=0.0, ldc_pad=0):
+    """Tiles of a riding launch of (layout, M, N, K, epi) problems whose transfers read and write `ride_bytes`."""
+    args = (GemmArgs * len(group))()
+    for a, (_, M, N, K, epi) in zip(args, group):
+        a.M, a.N, a.K, a.epi, a.half, a.C, a.ws, a.aux = M, N, K, epi, N // 2 if epi == EPI_SWIGLU_FWD else N, 0x1000, 0x1000, 0x2000
+        a.ldc = a.ldws = (a.half if epi == EPI_SWIGLU_FWD else N) + ldc_pad
+        a.ldaux, a.cu_share, a.c_is_f32 = 2 * N, 2, int(epi == EPI_ACC_ADD)
+    out = (C.c_int * len(group))()
+    _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), ride_bytes, out)
+    return list(out)
+
+
 def launch(layout, args, variant, stream=None):
     """launch_gemm_bf16 with the given arguments on kernel `variant`; the HIP status."""
     return _launch(layout, C.byref(args), variant, stream)

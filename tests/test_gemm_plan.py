@@ -70,3 +70,33 @@ def test_a_riding_launch_does_not_split_a_sum_that_repeats_on_the_streams():
             assert riding <= alone or alone > 2, (M, N, K, dx, alone, riding)
             chunks.add(riding)
     assert 1 in chunks and 2 in chunks and max(chunks) > 2
+
+
+DUO_128X128, DUO_64X128, DUO_64X64 = 1024, 1025, 1026
+
+
+def test_which_kernel_a_riding_launch_runs_on():
+    """Few or short tiles: two workgroups a compute unit; a machine full of long ones: the tall tiles."""
+    duo, tall = (DUO_128X128, DUO_64X128, DUO_64X64), (256, 192, 128, 64)
+    for M, N, K in ((200, 768, 2048), (32, 768, 2048), (512, 2048, 1024), (1024, 384, 768)):
+        assert G.riding_tiles([(B.LAYOUT_NT, M, N, K, G.EPI_STORE)])[0] in duo, (M, N, K)
+    for M, N, K in ((4096, 4096, 4096), (8192, 2048, 2048)):
+        assert G.riding_tiles([(B.LAYOUT_NT, M, N, K, G.EPI_STORE)])[0] in tall, (M, N, K)
+    for last in (G.EPI_GELU_TANH_BWD, G.EPI_ACC_LAST):
+        assert all(t in duo for t in G.riding_tiles([(B.LAYOUT_NN, 1024, 384, 768, last), (B.LAYOUT_TN, 768, 384, 1024, G.EPI_ACC_LAST)]))
+
+
+def test_a_riding_launch_is_of_one_kernel_and_of_tiles_that_take_the_problem():
+    rng = random.Random(11)
+    seen = set()
+    for _ in range(300):
+        T, w, I = 8 * rng.randint(1, 1024), 8 * rng.randint(1, 200), 8 * rng.randint(16, 1000)
+        epi = rng.choice([G.EPI_STORE, G.EPI_ACC_ADD, G.EPI_SWIGLU_FWD, G.EPI_GELU_ERF_FWD])
+        group = [(B.LAYOUT_NT, T, 2 * w if epi == G.EPI_SWIGLU_FWD else w, I, epi), (B.LAYOUT_NT, T, I, w, G.EPI_ACC_ADD)]
+        tiles = G.riding_tiles(group, ride_bytes=4.0 * w * I)
+        seen.update(tiles)
+        assert len({t >= DUO_128X128 for t in tiles}) == 1, (group, tiles)
+        assert epi != G.EPI_SWIGLU_FWD or tiles[0] != DUO_64X64, (group, tiles)
+        # an odd leading dimension takes the element-wise epilogue, which the tall tiles have
+        assert all(t < DUO_128X128 for t in G.riding_tiles(group, ldc_pad=1)), group
+    assert seen >= {DUO_128X128, DUO_64X128, DUO_64X64, 256}
