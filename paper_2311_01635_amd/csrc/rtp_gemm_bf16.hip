@@ -366,10 +366,10 @@ hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStrea
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_bf16_args_ok(layout, a)) return hipErrorInvalidValue;
     if (variant == 0) variant = pick_variant(layout, a);
-    if (a.elem != ELEM_BF16 && (variant < 4 || variant > 11)) return hipErrorInvalidValue; // fp16: tiled kernel only
-    if (variant >= 4 && variant <= 11) {
+    if (a.elem != ELEM_BF16 && (variant < 4 || variant > 12)) return hipErrorInvalidValue; // fp16: tiled kernel only
+    if (variant >= 4 && variant <= 12) {
         if (!gemm_bf16_pp_supported(layout, a)) return hipErrorInvalidValue;
-        const int bm[8] = {0, 256, 192, 128, 64, DUO_128X128, DUO_64X128, DUO_64X64};
+        const int bm[9] = {0, 256, 192, 128, 64, DUO_128X128, DUO_64X128, DUO_64X64, SMALL_128X128};
         return launch_gemm_bf16_pp(layout, a, bm[variant - 4], s);
     }
     switch (variant) {

@@ -82,7 +82,7 @@ constexpr int BUFFER_RSRC_FLAGS = 0x00020000;
 // One GEMM of a group launch and the whole group (a kernel argument, passed by value).
 struct PpProblem {
     GemmArgs a;
-    int bm, bn;           // tile: 256, 192 or 128 x 256, or 64 x 128 (rtp_gemm_small.h); 128 or 64 x 128, or 64 x 64 (rtp_gemm_duo.h)
+    int bm, bn;           // tile: 256, 192 or 128 x 256, or 128 or 64 x 128 (rtp_gemm_small.h); 128 or 64 x 128, or 64 x 64 (rtp_gemm_duo.h)
     int tiles_m, tiles_n;
     int vec_epilogue;
     int ksplit;           // > 1: the K loop is cut into this many chunks, one workgroup each, whose partial
@@ -473,8 +473,13 @@ __device__ __forceinline__ void pp_any_tile(const PpProblem &P, const int pid, c
     switch (P.bm) {
     case 256: pp_tile<LAY, 256, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
     case 192: pp_tile<LAY, 192, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    case 64: pp_small_tile<LAY, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
-    default: pp_tile<LAY, 128, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    case 64: pp_small_tile<LAY, 1, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem); break;
+    default:
+        if (P.bn == 128)
+            pp_small_tile<LAY, 2, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem);
+        else
+            pp_tile<LAY, 128, E, WIDE_ONLY>(P.a, P.tiles_m, P.tiles_n, P.vec_epilogue, pid, kt_begin, kt_count, smem);
+        break;
     }
 }
 
@@ -528,7 +533,7 @@ __device__ __forceinline__ void pp_workgroup(const PpGroup &g, char *smem)
         return;
     }
     int q, pid, kt_begin, kt_count;
-    if (!pp_find_tile(g, tile_block, [](const PpProblem &P) { return P.bm == 64 ? pps::BK : pp::BK; }, q, pid, kt_begin, kt_count)) return;
+    if (!pp_find_tile(g, tile_block, [](const PpProblem &P) { return P.bn == pps::BN ? pps::BK : pp::BK; }, q, pid, kt_begin, kt_count)) return;
     const PpProblem &P = g.p[q];
     if constexpr (LAY != LAY_NN_TN)
         pp_any_tile<LAY, E, WIDE_ONLY>(P, pid, kt_begin, kt_count, smem);

@@ -54,14 +54,15 @@ static int compute_units()
     return cus;
 }
 
-// A tile is named by its height in gemm_pp_kernel (256, 192, 128: 256 wide; 64: 128 wide), by one of the codes DUO_* in
-// gemm_duo_kernel.
+// A tile is named by its height in gemm_pp_kernel (256, 192, 128: 256 wide; 64: 128 wide) or the code SMALL_128X128, by one of
+// the codes DUO_* in gemm_duo_kernel.
 static bool is_duo(int tile) { return tile >= DUO_128X128; }
-static int tile_rows(int tile) { return !is_duo(tile) ? tile : tile == DUO_128X128 ? 128 : 64; }
+static bool is_small(int tile) { return tile == 64 || tile == SMALL_128X128; } // rtp_gemm_small.h
+static int tile_rows(int tile) { return tile == DUO_128X128 || tile == SMALL_128X128 ? 128 : is_duo(tile) ? 64 : tile; }
 // output columns of a tile, and of each half for the paired epilogue
-static int tile_cols(int tile) { return is_duo(tile) ? (tile == DUO_64X64 ? 64 : 128) : tile == 64 ? pps::BN : pp::BN; }
+static int tile_cols(int tile) { return is_duo(tile) ? (tile == DUO_64X64 ? 64 : 128) : is_small(tile) ? pps::BN : pp::BN; }
 static int tile_width(const GemmArgs &a, int tile) { return a.epi == EPI_SWIGLU_FWD ? tile_cols(tile) / 2 : tile_cols(tile); }
-static int tile_bk(int tile, int lay) { return is_duo(tile) ? ppd::sub_tile(lay, tile_rows(tile)) : tile == 64 ? pps::BK : pp::BK; }
+static int tile_bk(int tile, int lay) { return is_duo(tile) ? ppd::sub_tile(lay, tile_rows(tile)) : is_small(tile) ? pps::BK : pp::BK; }
 static int tiles_n_of(const GemmArgs &a, int bm)
 {
     const int ncols = a.epi == EPI_SWIGLU_FWD ? a.half : a.N, bn = tile_width(a, bm);
@@ -101,7 +102,8 @@ static double epilogue_steps(int epi, int c_is_f32)
     }
 }
 
-// The small tile: a fixed part and a part per 64 K.  Launches alone (us, launch included): one round 512 x 2752 x 4096
+// The 64 x 128 tile: a fixed part and a part per 64 K (the 128 x 128 one half a unit more and 1.45 times; beside another GEMM 1.6
+// times, with 1.45 a step of three 4864-wide shards on the streams took 2 % longer).  Launches alone (us, launch included): one round 512 x 2752 x 4096
 // 21.0, two rounds 2048 x 1792 x 8192 75 and 992 x 4096 x 14336 139, three rounds 8192 x 768 x 2048 37.3 and
 // 8192 x 768 x 384 16.6 (the 128-high tile: 50.4, 91, 168, 31.6, 11.6) give 1.5 and 0.44.  Beside another GEMM both are
 // larger, as it fetches twice the bytes per flop: with 1.5 and 0.44 there too the ragged Llama-shaped step took 3.80 ms
@@ -118,6 +120,8 @@ static double tile_cost(const GemmArgs &a, int bm, int ksplit, double frac = 1.0
     int each;
     (void)k_chunks(a, bm, ksplit, &each);
     const SmallCost small = a.cu_share > 1 ? SMALL_SHARED : SMALL_ALONE;
+    if (bm == SMALL_128X128)
+        return small.fixed + 0.5 + (a.cu_share > 1 ? 1.6 : 1.45) * small.step * each + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32) / 4.0;
     if (bm == 64) // 64 x 128, sub-tiles of 64
         return small.fixed + small.step * each + area * epilogue_steps(ksplit > 1 ? EPI_ACC_ATOMIC : a.epi, a.c_is_f32) / 8.0;
     const double handicap = bm == 256 ? 1.0 : bm == 192 ? 1.04 : 1.12;
@@ -131,14 +135,14 @@ static double tile_cost(const GemmArgs &a, int bm, int ksplit, double frac = 1.0
 // fragment columns 128 apart (gate / up halves of the paired epilogue: always both or none).
 static void edge_shares(const GemmArgs &a, int bm, double *frac_m, double *area_m, double *frac_n, double *area_n)
 {
-    const int tm = (a.M + bm - 1) / bm, vr = a.M - (tm - 1) * bm; // valid rows of the last tile row
-    const int fm = bm / 64;
-    *frac_m = vr >= bm / 2 || bm == 64 ? 1.0 : (double)((vr + 31) / 32) / fm; // (the small tile skips nothing)
-    *area_m = (double)vr / bm;
+    const int rows = tile_rows(bm), tm = (a.M + rows - 1) / rows, vr = a.M - (tm - 1) * rows; // valid rows of the last tile row
+    const int fm = rows / 64;
+    *frac_m = vr >= rows / 2 || is_small(bm) ? 1.0 : (double)((vr + 31) / 32) / fm; // (the small tile skips nothing)
+    *area_m = (double)vr / rows;
     const bool paired = a.epi == EPI_SWIGLU_FWD;
     const int ncols = paired ? a.half : a.N, bn = tile_width(a, bm);
     const int tn = (ncols + bn - 1) / bn, vc = ncols - (tn - 1) * bn;
-    *frac_n = paired || vc > 128 || bm == 64 ? 1.0 : 0.5;
+    *frac_n = paired || vc > 128 || is_small(bm) ? 1.0 : 0.5;
     *area_n = (double)vc / bn;
 }
 
@@ -204,7 +208,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
 // (4 tiles, and up to 6 split factors for a problem that may be split and is short of tiles);
 // the estimate above picks.  Plans are remembered per shape.
 struct PlanKey {
-    int layout, count, cu_share;
+    int layout, count, cu_share, square;
     int dims[PP_MAX_GROUP][6]; // M, N, K, epi, forced height, chunks it may be split in
     bool operator<(const PlanKey &o) const { return memcmp(this, &o, sizeof *this) < 0; }
 };
@@ -222,14 +226,15 @@ static bool duo_takes(const GemmArgs &a, int tile)
 // the height a caller asks for; 0 (pick) also for one that is not built, or that the problem's counters cannot take
 static int forced_height(const GemmArgs &a, int asked)
 {
-    const bool built = asked == 256 || asked == 192 || asked == 128 || (asked == 64 && !a.sync);
+    const bool built = asked == 256 || asked == 192 || asked == 128 || (is_small(asked) && !a.sync);
     return built ? asked : 0;
 }
 
 constexpr int MAX_SPLIT = 32;
 
-// max_split (may be null): chunks of K each problem may be cut in
-static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr)
+// max_split (may be null): chunks of K each problem may be cut in; square: whether 128 x 128 tiles are considered
+static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr,
+                       bool square = true)
 {
     static std::map<PlanKey, Plan> cache;
     static std::mutex lock;
@@ -240,7 +245,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
     }
     PlanKey key;
     memset(&key, 0, sizeof key);
-    key.layout = layout; key.count = count; key.cu_share = cu_share;
+    key.layout = layout; key.count = count; key.cu_share = cu_share; key.square = square;
     int cap[PP_MAX_GROUP];
     for (int q = 0; q < count; ++q) {
         const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
@@ -253,7 +258,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
-    const int heights[4] = {256, 192, 128, 64};
+    const int heights[5] = {256, 192, 128, 64, SMALL_128X128};
     const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
     const int cus = std::max(8, compute_units() / std::max(1, cu_share));
     const int cus_per_xcd = std::max(1, cus / 8);
@@ -280,18 +285,19 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         return split;
     };
     // options per problem
-    int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][24], oks[PP_MAX_GROUP][24];
+    int nopt[PP_MAX_GROUP], obm[PP_MAX_GROUP][30], oks[PP_MAX_GROUP][30];
     for (int q = 0; q < count; ++q) {
         nopt[q] = 0;
         const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
         const bool split_ok = cap[q] > 1 && tiles128 < cus && worth_splitting(a[q]);
-        for (int h = 0; h < 4; ++h) {
+        for (int h = 0; h < 5; ++h) {
+            if (!square && forced == 0 && heights[h] == SMALL_128X128) continue;
             if (forced != 0 && forced != heights[h]) continue;
-            if (heights[h] == 64 && a[q].sync) continue; // the counters are the tall tiles'
+            if (is_small(heights[h]) && a[q].sync) continue; // the counters are the tall tiles'
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
                 if (splits[k] > cap[q]) break;
-                if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (heights[h] == 64 ? 8 : 4)) break; // keep at least four sub-tiles per chunk
+                if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (is_small(heights[h]) ? 8 : 4)) break; // keep at least four sub-tiles per chunk
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
@@ -337,13 +343,15 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
 // a compute unit works through `fixed` and `step` a sub-tile (of 32 K in tall tiles, else 64; `step_full` more where the
 // machine is full of accumulators and its clock drops).  Fitted to the kernel times of 70 shapes drawn from the layers' ranges
 // (16 to 8192 tokens, shards of 64 to 1536) and of 4096^3 products: within 7 (64 x 64) to 15 % (192 x 256).  A compute unit with
-// one workgroup of the duo kernel waits for its operands between the sub-tiles of the two wider tiles (`one_each`).
-// Passes of 75 units and layers of all sizes, the tall tiles everywhere -> the cheaper of the two by this estimate: 0.92 to
-// 1.39 times as fast, geometric mean 1.097 (the duo kernel everywhere 1.075, the better one known beforehand 1.11).
+// one workgroup of the duo kernel waits for its operands between the sub-tiles of the two wider tiles (per_unit: tiles a
+// unit).
+// Passes of 75 units and layers of all sizes, the tall and the 64 x 128 tile everywhere -> the duo kernel where this estimate
+// prefers it: 0.92 to 1.39 times as fast, geometric mean 1.097 (the duo kernel everywhere 1.075, the better one known
+// beforehand 1.11).  47 more, the 128 x 128 tile of gemm_pp_kernel beside those: 1.019, units of 1000 to 5000 tokens 1.03 to 1.17.
 struct TileTime {
     double once, fixed, step, step_full;
 };
-static TileTime tile_time(int tile, int epi, bool one_each)
+static TileTime tile_time(int tile, int epi, int per_unit)
 {
     const double pairs = epi == EPI_SWIGLU_FWD ? 1.08 : 1.0; // (such launches came out that much later than their estimate)
     switch (tile) {
@@ -351,9 +359,10 @@ static TileTime tile_time(int tile, int epi, bool one_each)
     case 192: return {0.0, 7.8, 0.380, 0.16};
     case 128: return {0.0, 6.7, 0.316, 0.14};
     case 64: return {1.4, 4.3, 0.208, 0.05};
-    case DUO_128X128: return {3.8, 1.9, pairs * (one_each ? 0.70 : 0.44), 0.0};
-    case DUO_64X128: return {3.9, 1.7, pairs * (one_each ? 0.40 : 0.285), 0.0};
-    default: return {3.4, 1.25, one_each ? 0.21 : 0.178, 0.0};
+    case SMALL_128X128: return {1.4, 5.5, 0.35, 0.11};
+    case DUO_128X128: return {3.8, 1.9, pairs * (per_unit <= 1 ? 0.70 : per_unit == 2 ? 0.42 : 0.44), 0.0};
+    case DUO_64X128: return {3.9, 1.7, pairs * (per_unit <= 1 ? 0.40 : per_unit == 2 ? 0.30 : 0.285), 0.0};
+    default: return {3.4, 1.25, per_unit <= 1 ? 0.21 : 0.178, 0.0};
     }
 }
 // bytes the epilogue moves per element of the product
@@ -393,7 +402,7 @@ static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const
         int each;
         const int chunks = k_chunks(a[q], tile[q], ks[q], &each);
         const long n = ((long)tiles_m_of(a[q], tile[q]) * tiles_n_of(a[q], tile[q]) * chunks + 7) / 8;
-        const TileTime t = tile_time(tile[q], a[q].epi, tiles <= cus);
+        const TileTime t = tile_time(tile[q], a[q].epi, (int)std::min<long>(3, (tiles + cus - 1) / cus));
         once = std::max(once, t.once);
         const double cost = t.fixed + each * (t.step + full * t.step_full) +
                             full * tile_rows(tile[q]) * tile_cols(tile[q]) * epilogue_bytes(chunks > 1 ? EPI_ACC_ATOMIC : a[q].epi, a[q].c_is_f32) * cus / 10e6;
@@ -447,7 +456,7 @@ static bool plan_duo(const GemmArgs *a, int count, const int *cap, Plan *best_pl
             p.order[q] = q;
             int each;
             (void)k_chunks(a[q], p.bm[q], p.ks[q], &each);
-            cost[q] = each * tile_time(p.bm[q], a[q].epi, false).step;
+            cost[q] = each * tile_time(p.bm[q], a[q].epi, 3).step;
         }
         std::stable_sort(p.order, p.order + count, [&](int i, int j) { return cost[i] > cost[j]; });
         const double t = launch_us(a, p.bm, p.ks, p.order, count, ride_bytes);
@@ -463,7 +472,7 @@ void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_o
     if (count < 1 || count > PP_MAX_GROUP) return;
     const Plan pl = plan_group(layout, a, count, bm_override, count == 1 ? a[0].cu_share : 1);
     for (int q = 0; q < count; ++q) {
-        if (bm_out) bm_out[q] = pl.bm[q];
+        if (bm_out) bm_out[q] = tile_rows(pl.bm[q]);
         if (ksplit_out) ksplit_out[q] = pl.ks[q];
     }
 }
@@ -589,12 +598,21 @@ static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int c
         const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share)).ks[0];
         if (alone <= 2) cap[q] = alone;
     }
-    Plan best = plan_group(layout, a, count, nullptr, 1, cap), duo;
-    double us = 0.0;
+    Plan best = plan_group(layout, a, count, nullptr, 1, cap, false), duo;
+    double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes), us = 0.0;
+    const Plan square = plan_group(layout, a, count, nullptr, 1, cap);
+    const double square_us = launch_us(a, square.bm, square.ks, square.order, count, ride_bytes);
+    const bool with_square = square_us < 0.95 * tall; // (a tie by the estimate came out 1-2 % slower)
+    if (with_square) best = square, tall = square_us;
     for (int q = 0; q < count; ++q) split_duo[q] = best.ks[q] > 1 ? cap[q] : 1; // split only where the other kernel would
-    const double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes);
-    // (the estimate flatters 128 x 128 tiles in launches that fill the machine several times over)
-    if (key.takes && plan_duo(a, count, split_duo, &duo, ride_bytes, &us) && us < tall * (tall < 40.0 ? 1.05 : 0.90)) best = duo;
+    if (key.takes && plan_duo(a, count, split_duo, &duo, ride_bytes, &us)) {
+        long tiles = 0;
+        for (int q = 0; q < count; ++q) tiles += (long)tiles_m_of(a[q], duo.bm[q]) * tiles_n_of(a[q], duo.bm[q]) * duo.ks[q];
+        // (short launches come out better than their estimate, 128 x 128 tiles one to a unit in them do not; long ones come out
+        // later, but those of one to two tiles a unit)
+        const bool pairs = tiles > compute_units() && tiles <= 2 * compute_units();
+        if (us < tall * (tall < 40.0 ? (with_square ? 1.15 : 1.05) : pairs ? 1.05 : 0.90)) best = duo;
+    }
     std::lock_guard<std::mutex> g(lock);
     cache[key] = best;
     return best;

@@ -59,7 +59,8 @@ constexpr int SYNC_ROWS = 64;
 // tiles (256x256/8 waves, 128x128/4 waves, 256x256/4 waves); 4 = the ping-pong kernel with the
 // tile height picked by shape; 5, 6, 7, 8 = the ping-pong kernel with tile height 256, 192, 128 (256 wide), 64 (128 wide);
 // 9, 10, 11 = the kernel of two workgroups a compute unit, DUO_128X128, DUO_64X128, DUO_64X64.
-enum : int { DUO_128X128 = 1024, DUO_64X128, DUO_64X64 };
+// 12 = the ping-pong kernel with tile SMALL_128X128.
+enum : int { SMALL_128X128 = 1000, DUO_128X128 = 1024, DUO_64X128, DUO_64X64 };
 hipError_t launch_gemm_bf16(int layout, const GemmArgs &a, int variant, hipStream_t s);
 // alignment and minimum sizes every bf16 kernel needs (M, N > 0 assumed)
 bool gemm_bf16_args_ok(int layout, const GemmArgs &a);

@@ -72,7 +72,7 @@ def test_a_riding_launch_does_not_split_a_sum_that_repeats_on_the_streams():
     assert 1 in chunks and 2 in chunks and max(chunks) > 2
 
 
-DUO_128X128, DUO_64X128, DUO_64X64 = 1024, 1025, 1026
+SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = 1000, 1024, 1025, 1026
 
 
 def test_which_kernel_a_riding_launch_runs_on():
@@ -82,6 +82,8 @@ def test_which_kernel_a_riding_launch_runs_on():
         assert G.riding_tiles([(B.LAYOUT_NT, M, N, K, G.EPI_STORE)])[0] in duo, (M, N, K)
     for M, N, K in ((4096, 4096, 4096), (8192, 2048, 2048)):
         assert G.riding_tiles([(B.LAYOUT_NT, M, N, K, G.EPI_STORE)])[0] in tall, (M, N, K)
+    # a machine that 128 x 128 tiles fill about once, and taller ones do not
+    assert G.riding_tiles([(B.LAYOUT_NT, 1990, 1376, 4096, G.EPI_SWIGLU_FWD), (B.LAYOUT_NT, 1990, 4096, 688, G.EPI_ACC_ADD)])[0] == SMALL_128X128
     for last in (G.EPI_GELU_TANH_BWD, G.EPI_ACC_LAST):
         assert all(t in duo for t in G.riding_tiles([(B.LAYOUT_NN, 1024, 384, 768, last), (B.LAYOUT_TN, 768, 384, 1024, G.EPI_ACC_LAST)]))
 

@@ -1,5 +1,6 @@
-"""The tiles of two workgroups a compute unit (9, 10, 11: 128 x 128, 64 x 128, 64 x 64) against the tall tiles, bit for bit:
-every tile adds up an element's products in the order of K and shares the epilogues."""
+"""The tiles of two workgroups a compute unit (9, 10, 11: 128 x 128, 64 x 128, 64 x 64) and the 128 x 128 one that has a unit
+to itself (12) against the tall tiles, bit for bit: every tile adds up an element's products in the order of K and shares
+the epilogues."""
 import pytest
 import torch
 
@@ -9,7 +10,7 @@ from paper_2311_01635_amd import binding as B
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 TD = {"bf16": torch.bfloat16, "f16": torch.float16}
-TILES = [9, 10, 11]
+TILES = [9, 10, 11, 12]
 # one fragment of one tile; a tile and its neighbours by one unit; K of one sub-tile of 64, of none whole, of an odd and
 # an even number of them, of more than the LDS ring holds; an edge in both directions
 SHAPES = [(8, 8, 8), (64, 64, 64), (72, 136, 72), (136, 264, 128), (120, 56, 200), (200, 328, 448), (264, 136, 1000)]
@@ -51,10 +52,10 @@ def test_the_bits_are_the_tall_tiles(layout, tile, dtype):
                 assert torch.equal(out[0], out[1]), (M, N, K, accumulate)
 
 
-@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("tile,pad", [(9, 8), (10, 8), (11, 8), (12, 8), (12, 5)])  # 16-byte accesses; the element-wise form
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("epi", range(10))
-def test_every_epilogue(epi, dtype, tile):
+def test_every_epilogue(epi, dtype, tile, pad):
     if tile == 11 and epi == G.EPI_SWIGLU_FWD:
         pytest.skip("a wave of the 64 x 64 tile holds one fragment column: no gate / up pairs")
     td = TD[dtype]
@@ -72,10 +73,10 @@ def test_every_epilogue(epi, dtype, tile):
             for variant in (7, tile):
                 print(f"epilogue {epi} {dtype} variant={variant} M={M} N={N} f32={f32}", flush=True)
                 width = 2 * N if epi == G.EPI_SWIGLU_BWD else N
-                c = torch.full((M + 1, width + 8), 3.0, device=DEV, dtype=torch.float32 if f32 else td)
+                c = torch.full((M + 1, width + pad), 3.0, device=DEV, dtype=torch.float32 if f32 else td)
                 ws, aux = old.clone(), aux0.clone()
                 args = G.GemmArgs(A=a.data_ptr(), B=b.data_ptr(), lda=lda, ldb=ldb, M=M, N=cols, K=192, epi=epi, C=c.data_ptr(),
-                                  ldc=width + 8, ws=ws.data_ptr(), ldws=N, aux=aux.data_ptr(), ldaux=2 * N, half=N if paired else 0,
+                                  ldc=width + pad, ws=ws.data_ptr(), ldws=N, aux=aux.data_ptr(), ldaux=2 * N, half=N if paired else 0,
                                   c_is_f32=f32, elem=G.ELEM[dtype])
                 if epi == G.EPI_STORE or (not backward and not 1 <= epi <= 3):
                     args.bias = bias.data_ptr()
