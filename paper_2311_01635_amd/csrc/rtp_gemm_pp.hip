@@ -232,6 +232,19 @@ static int forced_height(const GemmArgs &a, int asked)
 
 constexpr int MAX_SPLIT = 32;
 
+// Where a sum's K loop is cut is part of its result: it decides the order of the additions, and whether they have one (one
+// chunk repeats bit for bit, two do onto zeros).  The plan of the tall and the 64 x 128 tiles decides that; whatever tile then
+// runs the problem cuts a sum of one chunk or two where that plan does, and one of more, which does not repeat, in two or
+// more but not in more than that.  (Free to cut them anew, the other tiles took 1.5 % off the GPT-2-shaped step, 817 -> 804 us,
+with four chunks of a 384 x 768 sum over 8192 instead of two.)
+static bool keeps_cuts(const GemmArgs &a, int ref_tile, int ref_ks, int tile, int ks, int lay)
+{
+    int ref_each, each;
+    const int ref = k_chunks(a, ref_tile, ref_ks, &ref_each, lay), chunks = k_chunks(a, tile, ks, &each, lay);
+    if (ref > 2) return chunks >= 2 && chunks <= ref;
+    return chunks == ref && (chunks == 1 || each * tile_bk(tile, lay) == ref_each * tile_bk(ref_tile, lay));
+}
+
 // max_split (may be null): chunks of K each problem may be cut in; square: whether 128 x 128 tiles are considered
 static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr,
                        bool square = true)
@@ -258,6 +271,8 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
+    Plan ref; // the plan without 128 x 128 tiles
+    if (square) ref = plan_group(layout, given, count, bm_override, cu_share, max_split, false);
     const int heights[5] = {256, 192, 128, 64, SMALL_128X128};
     const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
     const int cus = std::max(8, compute_units() / std::max(1, cu_share));
@@ -290,7 +305,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         nopt[q] = 0;
         const int forced = bm_override ? forced_height(a[q], bm_override[q]) : 0;
         const long tiles128 = (long)((a[q].M + 127) / 128) * tiles_n_of(a[q], 128);
-        const bool split_ok = cap[q] > 1 && tiles128 < cus && worth_splitting(a[q]);
+        const bool split_ok = cap[q] > 1 && (square ? ref.ks[q] > 1 : tiles128 < cus && worth_splitting(a[q]));
         for (int h = 0; h < 5; ++h) {
             if (!square && forced == 0 && heights[h] == SMALL_128X128) continue;
             if (forced != 0 && forced != heights[h]) continue;
@@ -298,6 +313,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
                 if (splits[k] > cap[q]) break;
                 if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (is_small(heights[h]) ? 8 : 4)) break; // keep at least four sub-tiles per chunk
+                if (square && !keeps_cuts(a[q], ref.bm[q], ref.ks[q], heights[h], splits[k], layout)) continue;
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];
                 ++nopt[q];
@@ -307,6 +323,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
     Plan best_plan;
     memset(&best_plan, 0, sizeof best_plan);
     double best = 1e300;
+    if (square) best_plan = ref, best = estimate(a, ref.bm, ref.ks, ref.order, count);
     int idx[PP_MAX_GROUP] = {0, 0, 0, 0};
     for (;;) {
         int bm[PP_MAX_GROUP], ks[PP_MAX_GROUP], order[PP_MAX_GROUP];
@@ -429,8 +446,8 @@ static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const
     return std::max(end, ride) + 0.5 * (1.0 - idle) * std::min(end, ride);
 }
 
-// The best plan of gemm_duo_kernel for the group; cap: chunks of K each problem may be cut in.  False if it does not take it.
-static bool plan_duo(const GemmArgs *a, int count, const int *cap, Plan *best_plan, double ride_bytes, double *best)
+// The best plan of gemm_duo_kernel for the group that keeps the cuts of `ref`.  False if there is none.
+static bool plan_duo(const int *layouts, const GemmArgs *a, int count, const Plan &ref, Plan *best_plan, double ride_bytes, double *best)
 {
     const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
     int nopt[PP_MAX_GROUP], otile[PP_MAX_GROUP][18], oks[PP_MAX_GROUP][18];
@@ -438,7 +455,8 @@ static bool plan_duo(const GemmArgs *a, int count, const int *cap, Plan *best_pl
         nopt[q] = 0;
         for (int tile = DUO_128X128; tile <= DUO_64X64; ++tile)
             for (int k : splits) {
-                if (!duo_takes(a[q], tile) || k > cap[q] || (k > 1 && a[q].K / 32 / k < 8)) break;
+                if (!duo_takes(a[q], tile) || (k > 1 && (ref.ks[q] == 1 || a[q].K / 32 / k < 8))) break;
+                if (!keeps_cuts(a[q], ref.bm[q], ref.ks[q], tile, k, layouts[q])) continue;
                 otile[q][nopt[q]] = tile;
                 oks[q][nopt[q]++] = k;
             }
@@ -472,7 +490,7 @@ void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_o
     if (count < 1 || count > PP_MAX_GROUP) return;
     const Plan pl = plan_group(layout, a, count, bm_override, count == 1 ? a[0].cu_share : 1);
     for (int q = 0; q < count; ++q) {
-        if (bm_out) bm_out[q] = tile_rows(pl.bm[q]);
+        if (bm_out) bm_out[q] = pl.bm[q];
         if (ksplit_out) ksplit_out[q] = pl.ks[q];
     }
 }
@@ -591,21 +609,21 @@ static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int c
         const auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
-    int cap[PP_MAX_GROUP], split_duo[PP_MAX_GROUP];
+    int cap[PP_MAX_GROUP];
     for (int q = 0; q < count; ++q) {
         cap[q] = MAX_SPLIT;
         if (!may_split_k(a[q])) continue;
-        const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share)).ks[0];
+        const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share), nullptr, false).ks[0];
         if (alone <= 2) cap[q] = alone;
     }
-    Plan best = plan_group(layout, a, count, nullptr, 1, cap, false), duo;
+    const Plan ref = plan_group(layout, a, count, nullptr, 1, cap, false);
+    Plan best = ref, duo;
     double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes), us = 0.0;
     const Plan square = plan_group(layout, a, count, nullptr, 1, cap);
     const double square_us = launch_us(a, square.bm, square.ks, square.order, count, ride_bytes);
     const bool with_square = square_us < 0.95 * tall; // (a tie by the estimate came out 1-2 % slower)
     if (with_square) best = square, tall = square_us;
-    for (int q = 0; q < count; ++q) split_duo[q] = best.ks[q] > 1 ? cap[q] : 1; // split only where the other kernel would
-    if (key.takes && plan_duo(a, count, split_duo, &duo, ride_bytes, &us)) {
+    if (key.takes && plan_duo(layouts, a, count, ref, &duo, ride_bytes, &us)) {
         long tiles = 0;
         for (int q = 0; q < count; ++q) tiles += (long)tiles_m_of(a[q], duo.bm[q]) * tiles_n_of(a[q], duo.bm[q]) * duo.ks[q];
         // (short launches come out better than their estimate, 128 x 128 tiles one to a unit in them do not; long ones come out
@@ -625,11 +643,14 @@ static double ride_traffic(const Riders &r)
     return bytes;
 }
 
-void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out)
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
     const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count, ride_bytes);
-    for (int q = 0; q < count; ++q) tiles_out[q] = pl.bm[q];
+    for (int q = 0; q < count; ++q) {
+        tiles_out[q] = pl.bm[q];
+        if (ksplit_out) ksplit_out[q] = pl.ks[q];
+    }
 }
 
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out)

@@ -75,7 +75,7 @@ constexpr int PP_MAX_GROUP = 4;
 // done (may be null): an event that completes when the launch does, as if recorded right after it
 hipError_t launch_gemm_bf16_pp_group(int layout, const GemmArgs *a, int count, const int *bm_override, hipStream_t s,
                                      hipEvent_t done = nullptr);
-// the tile heights and K splits that launch would use (either output may be null)
+// the tiles (heights or SMALL_128X128) and K splits that launch would use (either output may be null)
 void gemm_bf16_pp_plan(int layout, const GemmArgs *a, int count, const int *bm_override, int *bm_out, int *ksplit_out);
 // column tiles the tiled kernel cuts a problem into (what a producer problem adds to each row block's counter)
 int gemm_bf16_pp_tiles_n(const GemmArgs &a);
@@ -111,8 +111,9 @@ struct Riders {
 hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
 // the K splits that launch would use
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);
-// the tiles it would use: heights of gemm_pp_kernel or codes DUO_* (ride_bytes: what its transfers read and write)
-void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out);
+// the tiles it would use, heights of gemm_pp_kernel or the codes above, and its K splits (may be null); ride_bytes: what its
+// transfers read and write
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out, int *ksplit_out);
 // the transfers as a launch of their own
 hipError_t launch_riders(const Riders &r, hipStream_t s);
 

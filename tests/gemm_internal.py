@@ -29,7 +29,7 @@ _launch.argtypes = [C.c_int, C.POINTER(GemmArgs), C.c_int, C.c_void_p]
 
 
 def plan(layout, M, N, K, epi=EPI_STORE, half=0, f32=False, dtype="bf16", cu_share=1, force=0, sync=False):
-    """(tile height, K split) the launcher picks for one GEMM.  Needs no GPU: an fp32 sum lives at a made-up address."""
+    """(tile, K split) the launcher picks for one GEMM.  Needs no GPU: an fp32 sum lives at a made-up address."""
     a = GemmArgs(M=M, N=N, K=K, epi=epi, half=half, c_is_f32=int(f32), elem=ELEM[dtype], cu_share=cu_share, C=0x1000, ldc=N)
     if epi in (EPI_ACC_FIRST, EPI_ACC_ADD):
         a.ws, a.ldws, a.c_is_f32 = 0x1000, N, 1
@@ -49,21 +49,38 @@ def riding_split(M, N, K, dx, cu_share=2):
     return ks[1]
 
 
-_riding_tiles = getattr(B.lib, "_ZN3rtp25gemm_bf16_pp_riding_tilesEPKiPKNS_8GemmArgsEidPi")
+_riding_tiles = getattr(B.lib, "_ZN3rtp25gemm_bf16_pp_riding_tilesEPKiPKNS_8GemmArgsEidPiS5_")
 _riding_tiles.restype = None
-_riding_tiles.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.c_double, C.POINTER(C.c_int)]
+_riding_tiles.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.c_double, C.POINTER(C.c_int), C.POINTER(C.c_int)]
 
 
-def riding_tiles(group, ride_bytes=0.0, ldc_pad=0):
-    """Tiles of a riding launch of (layout, M, N, K, epi) problems whose transfers read and write `ride_bytes`."""
+def riding_plan(group, ride_bytes=0.0, ldc_pad=0):
+    """(tile, K split) of each problem of a riding launch of (layout, M, N, K, epi) problems whose transfers read and write
+    `ride_bytes`."""
     args = (GemmArgs * len(group))()
     for a, (_, M, N, K, epi) in zip(args, group):
         a.M, a.N, a.K, a.epi, a.half, a.C, a.ws, a.aux = M, N, K, epi, N // 2 if epi == EPI_SWIGLU_FWD else N, 0x1000, 0x1000, 0x2000
         a.ldc = a.ldws = (a.half if epi == EPI_SWIGLU_FWD else N) + ldc_pad
         a.ldaux, a.cu_share, a.c_is_f32 = 2 * N, 2, int(epi == EPI_ACC_ADD)
-    out = (C.c_int * len(group))()
-    _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), ride_bytes, out)
-    return list(out)
+    tiles, ks = (C.c_int * len(group))(), (C.c_int * len(group))()
+    _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), ride_bytes, tiles, ks)
+    return list(zip(tiles, ks))
+
+
+def riding_tiles(group, ride_bytes=0.0, ldc_pad=0):
+    """Its tiles alone."""
+    return [tile for tile, _ in riding_plan(group, ride_bytes, ldc_pad)]
+
+
+SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = 1000, 1024, 1025, 1026
+
+
+def chunks(K, tile, ks, layout):
+    """(chunks, K of each but the last) of a contraction over K that `tile` cuts in `ks`."""
+    bk = 32 if tile in (256, 192, 128) or (tile == DUO_128X128 and layout == B.LAYOUT_TN) else 64
+    subs = -(-K // bk)
+    each = -(-subs // ks)
+    return -(-subs // each), each * bk if ks > 1 else 0
 
 
 def launch(layout, args, variant, stream=None):

@@ -72,7 +72,65 @@ def test_a_riding_launch_does_not_split_a_sum_that_repeats_on_the_streams():
     assert 1 in chunks and 2 in chunks and max(chunks) > 2
 
 
-SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = 1000, 1024, 1025, 1026
+# Weight gradients [M, N] over K and the input gradient of their launch (columns, K, epilogue) -> how many chunks the sum is
+# cut in and the K of each but the last, 0 for one: in a riding launch, in a launch of its own, beside another GEMM.
+CUTS = [
+    (384, 768, 8192, 768, 384, 2, 2, 4096, 4, 2048, 4, 2048),
+    (768, 384, 8192, 384, 768, 7, 8, 1024, 4, 2048, 4, 2048),
+    (576, 832, 5056, 832, 576, 2, 2, 2560, 4, 1280, 4, 1280),
+    (1344, 576, 7904, 576, 1344, 7, 1, 0, 2, 3968, 2, 3968),
+    (576, 1344, 7904, 1344, 576, 2, 1, 0, 2, 3968, 4, 1984),
+    (832, 1120, 7904, 1120, 832, 2, 1, 0, 2, 3968, 2, 3968),
+    (704, 2688, 5216, 2688, 704, 2, 1, 0, 1, 0, 1, 0),
+    (2688, 352, 5216, 704, 2688, 9, 1, 0, 2, 2624, 2, 2624),
+    (896, 1152, 7968, 1152, 896, 2, 2, 4032, 2, 4032, 2, 4032),
+    (1152, 896, 7968, 896, 1152, 7, 1, 0, 2, 4032, 2, 4032),
+    (1248, 2432, 2560, 2432, 1248, 2, 1, 0, 2, 1280, 1, 0),
+    (2432, 1248, 2560, 1248, 2432, 7, 1, 0, 2, 1280, 1, 0),
+    (1280, 2176, 3648, 2176, 1280, 2, 2, 1824, 4, 928, 2, 1824),
+    (1024, 2432, 6496, 2432, 1024, 2, 2, 3264, 4, 1632, 4, 1632),
+    (3200, 1280, 4512, 1280, 3200, 9, 1, 0, 2, 2272, 2, 2272),
+    (928, 1856, 6464, 1856, 928, 2, 4, 1632, 1, 0, 4, 1632),
+    (1856, 928, 6464, 928, 1856, 9, 2, 3232, 1, 0, 4, 1632),
+    (928, 3392, 6144, 3392, 928, 2, 2, 3072, 2, 3072, 2, 3072),
+    (3392, 928, 6144, 928, 3392, 9, 1, 0, 2, 3072, 2, 3072),
+    (768, 2432, 5312, 2432, 768, 2, 1, 0, 1, 0, 2, 2656),
+    (2432, 768, 5312, 768, 2432, 9, 2, 2656, 1, 0, 2, 2656),
+    (512, 3904, 5408, 3904, 512, 2, 2, 2720, 1, 0, 4, 1376),
+    (3904, 512, 5408, 512, 3904, 9, 4, 1376, 1, 0, 4, 1376),
+    (704, 2432, 6336, 2432, 704, 2, 1, 0, 1, 0, 4, 1600),
+    (2176, 1280, 3648, 1280, 2176, 7, 2, 1824, 4, 928, 2, 1824),
+    (2432, 1024, 6496, 1024, 2432, 9, 2, 3264, 4, 1632, 4, 1632),
+    (1344, 3776, 3872, 3776, 1344, 2, 1, 0, 2, 1952, 1, 0),
+    (3776, 1344, 3872, 1344, 3776, 7, 1, 0, 2, 1952, 1, 0),
+    (2944, 64, 6688, 64, 2944, 7, 2, 3392, 4, 1728, 4, 1728),
+    (1248, 384, 1920, 384, 1248, 2, 2, 960, 4, 512, 2, 960),
+    (384, 1248, 1920, 1248, 384, 9, 2, 960, 4, 512, 2, 960),
+    (3584, 96, 7008, 96, 3584, 9, 2, 3520, 4, 1792, 4, 1792),
+    (640, 800, 1728, 800, 640, 7, 1, 0, 2, 896, 1, 0),
+    (3648, 1088, 4064, 1088, 3648, 9, 1, 0, 2, 2048, 1, 0),
+    (3712, 96, 6208, 96, 3712, 9, 2, 3136, 4, 1600, 4, 1600),
+    (1408, 3072, 5600, 3072, 1408, 2, 1, 0, 2, 2816, 1, 0),
+    (3072, 1408, 5600, 1408, 3072, 7, 1, 0, 2, 2816, 1, 0),
+    (192, 1920, 3456, 1920, 192, 2, 2, 1728, 4, 896, 2, 1728),
+]
+
+
+def test_which_sums_repeat_does_not_depend_on_the_tile():
+    """Where a sum is cut decides its bits, and whether they repeat (one chunk always, two onto zeros).  The tall and the
+    64 x 128 tiles' plans decide it: every tile cuts such a sum there.  More chunks do not repeat, and do not become more."""
+    def same(want, got, what):
+        assert got == want if want[0] <= 2 else 2 <= got[0] <= want[0], (what, want, got)
+
+    for M, N, K, cols, depth, epi, rc, rk, ac, ak, sc, sk in CUTS:
+        pair = [(B.LAYOUT_NN, K, cols, depth, epi), (B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD)]
+        for ride in (0.0, 4.0 * M * N, 16.0 * M * N, 64.0 * M * N):
+            same((rc, rk), G.chunks(K, *G.riding_plan(pair, ride)[1], B.LAYOUT_TN), ("riding", M, N, K, ride))
+        for share, want in ((1, (ac, ak)), (2, (sc, sk))):
+            same(want, G.chunks(K, *G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=share), B.LAYOUT_TN), (share, M, N, K))
+
+
+SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = G.SMALL_128X128, G.DUO_128X128, G.DUO_64X128, G.DUO_64X64
 
 
 def test_which_kernel_a_riding_launch_runs_on():
