@@ -236,7 +236,7 @@ constexpr int MAX_SPLIT = 32;
 // chunk repeats bit for bit, two do onto zeros).  The plan of the tall and the 64 x 128 tiles decides that; whatever tile then
 // runs the problem cuts a sum of one chunk or two where that plan does, and one of more, which does not repeat, in two or
 // more but not in more than that.  (Free to cut them anew, the other tiles took 1.5 % off the GPT-2-shaped step, 817 -> 804 us,
-with four chunks of a 384 x 768 sum over 8192 instead of two.)
+// with four chunks of a 384 x 768 sum over 8192 instead of two.)
 static bool keeps_cuts(const GemmArgs &a, int ref_tile, int ref_ks, int tile, int ks, int lay)
 {
     int ref_each, each;
