@@ -583,22 +583,20 @@ static int common_layout(const int *layouts, int count)
     return lay;
 }
 
-// The plan of a riding launch, which has the machine to itself.  A sum repeats bit for bit if it is not split, and in two
-// chunks it does onto zeros; it keeps that whichever way its pass runs: where the launch of its own that the streams would
-// make (a[q].cu_share) has one chunk or two, it is cut in no more here.  Without that 8 % of shapes drawn from the layers'
-// ranges were split that are not there, and 4 % in more than two chunks.  The fp16 unit with biases (384 x 768 over 1024, two
-// chunks instead of four) 407 -> 399 us a step.
-static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count, double ride_bytes)
+// What a riding launch is planned from; ride: 64 KB of transfers, -1 for the plan that decides the cuts
+struct RidingKey {
+    int layout, count, takes, ride;
+    int dims[PP_MAX_GROUP][6];
+    bool operator<(const RidingKey &o) const { return memcmp(this, &o, sizeof *this) < 0; }
+};
+template <typename Make>
+static Plan riding_plan(int layout, const GemmArgs *a, int count, int ride, Make make)
 {
-    struct Key {
-        int layout, count, takes, ride;
-        int dims[PP_MAX_GROUP][6];
-        bool operator<(const Key &o) const { return memcmp(this, &o, sizeof *this) < 0; }
-    } key;
-    static std::map<Key, Plan> cache;
+    static std::map<RidingKey, Plan> cache;
     static std::mutex lock;
+    RidingKey key;
     memset(&key, 0, sizeof key);
-    key.layout = layout; key.count = count; key.ride = (int)(ride_bytes / (1 << 16)); key.takes = 1;
+    key.layout = layout; key.count = count; key.ride = ride; key.takes = 1;
     for (int q = 0; q < count; ++q) {
         const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi, a[q].c_is_f32 + 2 * may_split_k(a[q]), a[q].cu_share};
         memcpy(key.dims[q], d, sizeof d);
@@ -609,31 +607,59 @@ static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int c
         const auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
-    int cap[PP_MAX_GROUP];
+    const Plan made = make(key);
+    std::lock_guard<std::mutex> g(lock);
+    cache[key] = made;
+    return made;
+}
+
+// Chunks of K each problem of a riding launch, which has the machine to itself, may be cut in.  A sum repeats bit for bit if
+// it is not split, and in two chunks it does onto zeros; it keeps that whichever way its pass runs: where the launch of its
+// own that the streams would make (a[q].cu_share) has one chunk or two, it is cut in no more here.  Without that 8 % of
+// shapes drawn from the layers' ranges were split that are not there, and 4 % in more than two chunks.  The fp16 unit with
+// biases (384 x 768 over 1024, two chunks instead of four) 407 -> 399 us a step.
+static void riding_caps(const int *layouts, const GemmArgs *a, int count, int *cap)
+{
     for (int q = 0; q < count; ++q) {
         cap[q] = MAX_SPLIT;
         if (!may_split_k(a[q])) continue;
         const int alone = plan_group(layouts[q], &a[q], 1, nullptr, std::max(1, a[q].cu_share), nullptr, false).ks[0];
         if (alone <= 2) cap[q] = alone;
     }
-    const Plan ref = plan_group(layout, a, count, nullptr, 1, cap, false);
-    Plan best = ref, duo;
-    double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes), us = 0.0;
-    const Plan square = plan_group(layout, a, count, nullptr, 1, cap);
-    const double square_us = launch_us(a, square.bm, square.ks, square.order, count, ride_bytes);
-    const bool with_square = square_us < 0.95 * tall; // (a tie by the estimate came out 1-2 % slower)
-    if (with_square) best = square, tall = square_us;
-    if (key.takes && plan_duo(layouts, a, count, ref, &duo, ride_bytes, &us)) {
-        long tiles = 0;
-        for (int q = 0; q < count; ++q) tiles += (long)tiles_m_of(a[q], duo.bm[q]) * tiles_n_of(a[q], duo.bm[q]) * duo.ks[q];
-        // (short launches come out better than their estimate, 128 x 128 tiles one to a unit in them do not; long ones come out
-        // later, but those of one to two tiles a unit)
-        const bool pairs = tiles > compute_units() && tiles <= 2 * compute_units();
-        if (us < tall * (tall < 40.0 ? (with_square ? 1.15 : 1.05) : pairs ? 1.05 : 0.90)) best = duo;
-    }
-    std::lock_guard<std::mutex> g(lock);
-    cache[key] = best;
-    return best;
+}
+
+// The plan of the tall and the 64 x 128 tiles, which decides where the launch cuts its sums (keeps_cuts), whatever rides in it
+static Plan riding_cuts(int layout, const int *layouts, const GemmArgs *a, int count)
+{
+    return riding_plan(layout, a, count, -1, [&](const RidingKey &) {
+        int cap[PP_MAX_GROUP];
+        riding_caps(layouts, a, count, cap);
+        return plan_group(layout, a, count, nullptr, 1, cap, false);
+    });
+}
+
+static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count, double ride_bytes)
+{
+    return riding_plan(layout, a, count, (int)(ride_bytes / (1 << 16)), [&](const RidingKey &key) {
+        const Plan ref = riding_cuts(layout, layouts, a, count);
+        Plan best = ref, duo;
+        double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes), us = 0.0;
+        int cap[PP_MAX_GROUP];
+        riding_caps(layouts, a, count, cap);
+        const Plan square = plan_group(layout, a, count, nullptr, 1, cap);
+        const double square_us = launch_us(a, square.bm, square.ks, square.order, count, ride_bytes);
+        const bool with_square = square_us < 0.95 * tall; // (a tie by the estimate came out 1-2 % slower)
+        if (with_square) best = square, tall = square_us;
+        if (key.takes && plan_duo(layouts, a, count, ref, &duo, ride_bytes, &us)) {
+            long tiles = 0;
+            for (int q = 0; q < count; ++q) tiles += (long)tiles_m_of(a[q], duo.bm[q]) * tiles_n_of(a[q], duo.bm[q]) * duo.ks[q];
+            // (short launches come out better than their estimate, 128 x 128 tiles one to a unit in them do not; long ones come out
+            // later, but those of one to two tiles a unit)
+            const bool pairs = tiles > compute_units() && tiles <= 2 * compute_units();
+            if (us < tall * (tall < 40.0 ? (with_square ? 1.15 : 1.05) : pairs ? 1.05 : 0.90)) best = duo;
+        }
+        return best;
+    });
 }
 
 static double ride_traffic(const Riders &r)
@@ -656,7 +682,7 @@ void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count,
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
-    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count, 0.0);
+    const Plan pl = riding_cuts(common_layout(layouts, count), layouts, a, count);
     for (int q = 0; q < count; ++q) ksplit_out[q] = pl.ks[q];
 }
 
@@ -693,7 +719,8 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
         int lays[PP_MAX_GROUP], n = 0;
         for (int q = 0; q < count; ++q)
             if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
-        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n, 0.0), one == LAY_NN ? &moves : &sums, s, nullptr);
+        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n, one == LAY_NN ? ride_traffic(moves) : 0.0),
+                                          one == LAY_NN ? &moves : &sums, s, nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

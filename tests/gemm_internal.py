@@ -58,10 +58,11 @@ def riding_plan(group, ride_bytes=0.0, ldc_pad=0):
     """(tile, K split) of each problem of a riding launch of (layout, M, N, K, epi) problems whose transfers read and write
     `ride_bytes`."""
     args = (GemmArgs * len(group))()
-    for a, (_, M, N, K, epi) in zip(args, group):
-        a.M, a.N, a.K, a.epi, a.half, a.C, a.ws, a.aux = M, N, K, epi, N // 2 if epi == EPI_SWIGLU_FWD else N, 0x1000, 0x1000, 0x2000
+    for a, (layout, M, N, K, epi) in zip(args, group):
+        sum_ = layout == B.LAYOUT_TN and epi == EPI_ACC_ADD  # a weight gradient: fp32, in place
+        a.M, a.N, a.K, a.epi, a.half, a.C, a.ws, a.aux = M, N, K, epi, N // 2 if epi == EPI_SWIGLU_FWD else N, 0x1000 if sum_ else 0x3000, 0x1000, 0x2000
         a.ldc = a.ldws = (a.half if epi == EPI_SWIGLU_FWD else N) + ldc_pad
-        a.ldaux, a.cu_share, a.c_is_f32 = 2 * N, 2, int(epi == EPI_ACC_ADD)
+        a.ldaux, a.cu_share, a.c_is_f32 = 2 * N, 2, int(sum_)
     tiles, ks = (C.c_int * len(group))(), (C.c_int * len(group))()
     _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), ride_bytes, tiles, ks)
     return list(zip(tiles, ks))

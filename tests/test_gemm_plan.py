@@ -130,6 +130,24 @@ def test_which_sums_repeat_does_not_depend_on_the_tile():
             same(want, G.chunks(K, *G.plan(B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD, cu_share=share), B.LAYOUT_TN), (share, M, N, K))
 
 
+def test_the_splits_asked_about_are_the_launchs():
+    """A gradient's send is fused into the launch that completes it only where that launch does not split its sum, which is
+    asked before anyone knows what rides in it."""
+    rng = random.Random(17)
+    shapes = [(384, 864, 2016, (2016, 864, 384, G.EPI_GELU_ERF_BWD)), (1472, 1728, 3008, (3008, 1728, 1472, G.EPI_ACC_ADD))]
+    for _ in range(150):
+        M, N, K = 32 * rng.randint(2, 48), 64 * rng.randint(4, 64), 32 * rng.randint(8, 256)
+        shapes += [(M, N, K, (K, N, M, G.EPI_ACC_ADD)), (N, M, K, (K, M, N, G.EPI_GELU_ERF_BWD))]
+    split = 0
+    for M, N, K, dx in shapes:
+        asked = G.riding_split(M, N, K, dx)
+        for ride in (0.0, 2.0 * M * N, 8.0 * M * N, 16.0 * M * N, 48.0 * M * N):
+            launched = G.riding_plan([(B.LAYOUT_NN,) + dx, (B.LAYOUT_TN, M, N, K, G.EPI_ACC_ADD)], ride)[1][1]
+            assert launched == asked if asked <= 2 else 2 <= launched <= asked, (M, N, K, dx, ride, asked, launched)
+        split += asked > 2
+    assert 5 < split < 100
+
+
 SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = G.SMALL_128X128, G.DUO_128X128, G.DUO_64X128, G.DUO_64X64
 
 
