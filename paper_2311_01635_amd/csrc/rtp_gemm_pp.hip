@@ -254,6 +254,29 @@ struct PlanKey {
 struct Plan {
     int bm[PP_MAX_GROUP], ks[PP_MAX_GROUP], order[PP_MAX_GROUP];
 };
+// Plans by what they were made from.  An expert layer plans for each number of tokens that it meets: once full the store
+// starts anew (a plan takes some ten us).
+template <typename Key>
+class PlanStore {
+    static constexpr size_t MOST = 8192;
+    std::map<Key, Plan> plans;
+    std::mutex lock;
+public:
+    bool find(const Key &key, Plan *plan)
+    {
+        std::lock_guard<std::mutex> g(lock);
+        const auto it = plans.find(key);
+        if (it == plans.end()) return false;
+        *plan = it->second;
+        return true;
+    }
+    void keep(const Key &key, const Plan &plan)
+    {
+        std::lock_guard<std::mutex> g(lock);
+        if (plans.size() >= MOST) plans.clear();
+        plans[key] = plan;
+    }
+};
 
 // whether a tile of gemm_duo_kernel takes the problem
 static bool duo_takes(const GemmArgs &a, int tile)
@@ -288,8 +311,7 @@ static bool keeps_cuts(const GemmArgs &a, int ref_tile, int ref_ks, int tile, in
 static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr,
                        bool square = true)
 {
-    static std::map<PlanKey, Plan> cache;
-    static std::mutex lock;
+    static PlanStore<PlanKey> plans;
     GemmArgs a[PP_MAX_GROUP]; // priced for the share the plan is remembered under, not for what each problem says
     for (int q = 0; q < count; ++q) {
         a[q] = given[q];
@@ -305,11 +327,8 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi + (a[q].sync ? 64 : 0), forced, cap[q]};
         memcpy(key.dims[q], d, sizeof d);
     }
-    {
-        std::lock_guard<std::mutex> g(lock);
-        auto it = cache.find(key);
-        if (it != cache.end()) return it->second;
-    }
+    Plan best_plan;
+    if (plans.find(key, &best_plan)) return best_plan;
     Plan ref; // the plan without 128 x 128 tiles
     if (square) ref = plan_group(layout, given, count, bm_override, cu_share, max_split, false);
     const int heights[5] = {256, 192, 128, 64, SMALL_128X128};
@@ -359,7 +378,6 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
             }
         }
     }
-    Plan best_plan;
     memset(&best_plan, 0, sizeof best_plan);
     double best = 1e300;
     if (square) best_plan = ref, best = estimate(a, ref.bm, ref.ks, ref.order, count);
@@ -391,8 +409,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
         while (q < count && ++idx[q] == nopt[q]) idx[q++] = 0;
         if (q == count) break;
     }
-    std::lock_guard<std::mutex> g(lock);
-    cache[key] = best_plan;
+    plans.keep(key, best_plan);
     return best_plan;
 }
 
@@ -627,8 +644,7 @@ struct RidingKey {
 template <typename Make>
 static Plan riding_plan(int layout, const GemmArgs *a, int count, int ride, Make make)
 {
-    static std::map<RidingKey, Plan> cache;
-    static std::mutex lock;
+    static PlanStore<RidingKey> plans;
     RidingKey key;
     memset(&key, 0, sizeof key);
     key.layout = layout; key.count = count; key.ride = ride; key.takes = 1;
@@ -637,15 +653,11 @@ static Plan riding_plan(int layout, const GemmArgs *a, int count, int ride, Make
         memcpy(key.dims[q], d, sizeof d);
         key.takes = key.takes && duo_takes(a[q], DUO_128X128);
     }
-    {
-        std::lock_guard<std::mutex> g(lock);
-        const auto it = cache.find(key);
-        if (it != cache.end()) return it->second;
-    }
-    const Plan made = make(key);
-    std::lock_guard<std::mutex> g(lock);
-    cache[key] = made;
-    return made;
+    Plan plan;
+    if (plans.find(key, &plan)) return plan;
+    plan = make(key);
+    plans.keep(key, plan);
+    return plan;
 }
 
 // Chunks of K each problem of a riding launch, which has the machine to itself, may be cut in.  A sum repeats bit for bit if

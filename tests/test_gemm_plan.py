@@ -148,6 +148,17 @@ def test_the_splits_asked_about_are_the_launchs():
     assert 5 < split < 100
 
 
+def test_plans_are_not_kept_without_end():
+    """An expert layer meets another number of tokens every step: 150 000 plans of 200 bytes and more would be 30 MB."""
+    grown = []
+    for at in range(4):
+        for T in range(25000):
+            G.plan(B.LAYOUT_NT, 8 + T, 64 + 8 * at, 64)
+        with open("/proc/self/statm") as f:
+            grown.append(int(f.read().split()[1]) * 4096)
+    assert grown[3] - grown[0] < 8 << 20, grown
+
+
 SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = G.SMALL_128X128, G.DUO_128X128, G.DUO_64X128, G.DUO_64X64
 
 
