@@ -89,6 +89,28 @@ def launch(layout, args, variant, stream=None):
     return _launch(layout, C.byref(args), variant, stream)
 
 
+class RideSeg(C.Structure):
+    _fields_ = [("out", C.c_void_p), ("buf", C.c_void_p), ("in_", C.c_void_p), ("bytes", C.c_size_t)]
+
+
+class RideSum(C.Structure):
+    _fields_ = [("elem", C.c_int), ("Y", C.c_void_p), ("ld", C.c_int64), ("rows", C.c_int), ("cols", C.c_int), ("in_", C.c_void_p), ("out", C.c_void_p)]
+
+
+class Riders(C.Structure):
+    _fields_ = [("count", C.c_int), ("sums", C.c_int), ("seg", RideSeg * 8), ("sum", RideSum * 2)]
+
+
+_launch_riding = getattr(B.lib, "_ZN3rtp26launch_gemm_bf16_pp_ridingEPKiPKNS_8GemmArgsEiRKNS_6RidersEP12ihipStream_t")
+_launch_riding.restype = C.c_int
+_launch_riding.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.POINTER(Riders), C.c_void_p]
+
+
+def launch_riding(layouts, args, riders, stream=None):
+    """One riding launch; the HIP status."""
+    return _launch_riding((C.c_int * len(layouts))(*layouts), (GemmArgs * len(args))(*args), len(args), C.byref(riders), stream)
+
+
 _colsum = getattr(B.lib, "_ZN3rtp13launch_colsumEiPKvliiPKfPfP12ihipStream_t")
 _colsum.restype = C.c_int
 _colsum.argtypes = [C.c_int, C.c_void_p, C.c_int64, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]

@@ -6,6 +6,7 @@ import ctypes as C
 import pytest
 import torch
 
+import gemm_internal as G
 from paper_2311_01635_amd import binding as B
 from paper_2311_01635_amd.layers import RtpLinear, RtpMlp
 
@@ -101,6 +102,35 @@ def test_mlp_unit(act, bias, dtype, T, n, rank, mode):
     bs = [normal(23 + i, s[0]) for i, s in enumerate(shapes)] if bias else None
     make = lambda: RtpMlp(ws, T, n, rank, act, mode, dtype, G0=g0, biases=bs)
     same(make, X, dY, False)
+
+
+BACKWARD = {B.RTP_ACT_GELU_ERF: G.EPI_GELU_ERF_BWD, B.RTP_ACT_SWIGLU: G.EPI_SWIGLU_BWD}
+SQUARE, D128, D64, D64S = G.SMALL_128X128, G.DUO_128X128, G.DUO_64X128, G.DUO_64X64
+
+
+# The kernel with a compute unit to itself, and the wider tiles of the one that shares it, in the launches that hold both
+# layouts and have bias sums in front of their tiles: tiles of {dPre, dW2} and of {dX, dW1}
+@pytest.mark.parametrize("mode", [DB, IS])
+@pytest.mark.parametrize("act,dtype,T,I,o,first,second", [(B.RTP_ACT_SWIGLU, B.RTP_F16, 416, 960, 320, (D64S, D64S), (64, 64)),
+                                                          (B.RTP_ACT_SWIGLU, B.RTP_BF16, 500, 1024, 272, (D64S, D64S), (64, 64)),
+                                                          (B.RTP_ACT_SWIGLU, B.RTP_BF16, 1300, 960, 392, (64, 64), (SQUARE, 64)),
+                                                          (B.RTP_ACT_GELU_ERF, B.RTP_BF16, 1990, 448, 432, (D128, D64S), (D128, D64S)),
+                                                          (B.RTP_ACT_GELU_ERF, B.RTP_BF16, 1300, 768, 456, (D64, D64S), (D64, D64S)),
+                                                          (B.RTP_ACT_SWIGLU, B.RTP_F16, 832, 1024, 224, (D64S, D64S), (D64, D64S))])
+def test_biased_units_on_every_kernel(act, dtype, T, I, o, first, second, mode):
+    g = 2 * o if act == B.RTP_ACT_SWIGLU else o
+    w, g1, g2 = 2 * I * (g + o), 4 * I * g, 4 * I * o
+    rides = ((4 * w + 2 * (g1 + g2), 0), (0,)) if mode == DB else ((4 * w + 2 * g1, 4 * w, 2 * g1, 0), (2 * g2, 0))
+    for ride in rides[0]:
+        assert tuple(G.riding_tiles([(B.LAYOUT_NN, T, o, I, BACKWARD[act]), (B.LAYOUT_TN, I, o, T, G.EPI_ACC_LAST)], ride)) == first
+    for ride in rides[1]:
+        assert tuple(G.riding_tiles([(B.LAYOUT_NN, T, I, g, G.EPI_ACC_LAST), (B.LAYOUT_TN, g, I, T, G.EPI_ACC_LAST)], ride)) == second
+    td, n = TD[dtype], 2
+    shapes = [(n * o, I)] * (g // o) + [(I, n * o)]
+    ws, g0 = [normal(3 + i, *s) * 0.1 for i, s in enumerate(shapes)], [normal(13 + i, *s) for i, s in enumerate(shapes)]
+    bs = [normal(23 + i, s[0]) for i, s in enumerate(shapes)]
+    make = lambda: RtpMlp(ws, T, n, 1, act, mode, dtype, G0=g0, biases=bs)
+    same(make, normal(1, T, I, dtype=td), normal(2, T, I, dtype=td), False)
 
 
 @pytest.mark.parametrize("mode", [DB, IS])
