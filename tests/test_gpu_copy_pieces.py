@@ -1,4 +1,4 @@
-"""The staging copy at the edges of its 64 KB pieces: every unit arrives, nothing beyond them is touched."""
+"""The staging copy at the edges of its 32 KB pieces (16 KB where nothing runs beside it): every unit arrives, nothing beyond them is touched."""
 import ctypes as C
 
 import pytest
@@ -8,14 +8,14 @@ from paper_2311_01635_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-PIECE = 4096                                     # 16-byte units
+PIECE = 2048                                     # 16-byte units
 
 
-@pytest.mark.parametrize("units", [1, 255, PIECE // 4 - 1, PIECE // 4, PIECE // 4 + 1, PIECE - 1, PIECE, PIECE + 1, 3 * PIECE, 3 * PIECE + 257])
+@pytest.mark.parametrize("units", [1, 255, PIECE // 2 - 1, PIECE // 2, PIECE // 2 + 1, PIECE - 1, PIECE, PIECE + 1, 3 * PIECE, 3 * PIECE + 257])
 def test_copy(units):
     one = getattr(B.lib, "_ZN3rtp11launch_copyEPvPKvmP12ihipStream_tP11ihipEvent_t")
     one.restype, one.argtypes = C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
-    alone = getattr(B.lib, "_ZN3rtp17launch_copy_aloneEPvPKvmP12ihipStream_tP11ihipEvent_t")   # (pieces of a quarter)
+    alone = getattr(B.lib, "_ZN3rtp17launch_copy_aloneEPvPKvmP12ihipStream_tP11ihipEvent_t")   # (pieces of half)
     alone.restype, alone.argtypes = one.restype, one.argtypes
     many = getattr(B.lib, "_ZN3rtp17launch_copy_multiEPKPvPKPKvPKmiP12ihipStream_tP11ihipEvent_t")
     many.restype = C.c_int
