@@ -158,7 +158,7 @@ static bool may_split_k(const GemmArgs &a)
 
 // Greedy list schedule: each job goes to the server that is free first.  Servers free at one time are kept as one entry, so a
 // run of equal jobs costs an entry a round, not a heap operation a job; the times are those of one job at a time.  (First
-// plans on the host, mean of 1000 backward pairs with two sizes of transfers: 165 -> 48 us; forward 89 -> 35.)
+// plans on the host, mean of 1000 backward pairs: 165 -> 48 us; forward 89 -> 35.)
 class Servers {
     static constexpr int MOST = 128;
     struct {
@@ -455,8 +455,13 @@ static double epilogue_bytes(int epi, int c_is_f32)
     }
 }
 // Schedule of one XCD's share over its compute units (the two workgroups a unit may hold of the duo kernel share
-// its load path, so they count as one after the other).  ride_bytes: what the transfers read and write.
-static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const int *order, int count, double ride_bytes)
+// its load path, so they count as one after the other).  The transfers have no part in it: priced beside the tiles, those of a
+// prompt hid what the tiles cost, and gated units of 16 to 768 tokens went to the duo kernel, whose tiles for them take half
+// as long again (us a forward pass, 320 tokens 3456 -> 13120 over 8: 349 on the tall tiles, 411, now 353; 160 tokens 2688 ->
+// 8928 over 6: 218, 258, 215; without gates 200 tokens 4928 -> 18144 over 12: 536, 566, 497.  240 units and layers, against
+// the transfers priced: 0.94 to 1.2 times as fast, the slower ones where the estimate had been off both ways, 536 -> 571 for 256
+// tokens 5696 -> 15536 gated over 2).
+static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const int *order, int count)
 {
     const int cus = compute_units(), servers = std::max(1, cus / 8);
     double area = 0.0, once = 0.0;
@@ -491,15 +496,11 @@ static double launch_us(const GemmArgs *a, const int *tile, const int *ks, const
         for (int q = 0; q < count; ++q) share += busy[q] * whole[q] * count_of[q], sum += whole[q] * count_of[q];
         for (int q = 0; q < count; ++q) end = std::max(end, whole[q] + 1.2 * loop[q] * share / sum);
     }
-    end += once;
-    // half of the shorter of the two, tiles or transfers, is hidden by the other where no compute unit is idle
-    const double ride = ride_bytes > 0.0 ? 2.0 + ride_bytes / 4.6e6 : 0.0;
-    const double idle = std::max(0.0, 1.0 - (double)tiles / (is_duo(tile[0]) ? 1.5 * cus : cus));
-    return std::max(end, ride) + 0.5 * (1.0 - idle) * std::min(end, ride);
+    return end + once;
 }
 
 // The best plan of gemm_duo_kernel for the group that keeps the cuts of `ref`.  False if there is none.
-static bool plan_duo(const int *layouts, const GemmArgs *a, int count, const Plan &ref, Plan *best_plan, double ride_bytes, double *best)
+static bool plan_duo(const int *layouts, const GemmArgs *a, int count, const Plan &ref, Plan *best_plan, double *best)
 {
     const int splits[6] = {1, 2, 4, 8, 16, MAX_SPLIT};
     int nopt[PP_MAX_GROUP], otile[PP_MAX_GROUP][18], oks[PP_MAX_GROUP][18];
@@ -529,7 +530,7 @@ static bool plan_duo(const int *layouts, const GemmArgs *a, int count, const Pla
             cost[q] = each * tile_time(p.bm[q], a[q].epi, 3).step;
         }
         longest_first(p.order, cost, count);
-        const double t = launch_us(a, p.bm, p.ks, p.order, count, ride_bytes);
+        const double t = launch_us(a, p.bm, p.ks, p.order, count);
         if (t < *best - 1e-9) *best = t, *best_plan = p;
         int q = 0;
         while (q < count && ++idx[q] == nopt[q]) idx[q++] = 0;
@@ -635,19 +636,19 @@ static int common_layout(const int *layouts, int count)
     return lay;
 }
 
-// What a riding launch is planned from; ride: 64 KB of transfers, -1 for the plan that decides the cuts
+// What a riding launch is planned from; cuts: the plan that decides the cuts, not the one that is launched
 struct RidingKey {
-    int layout, count, takes, ride;
+    int layout, count, takes, cuts;
     int dims[PP_MAX_GROUP][6];
     bool operator<(const RidingKey &o) const { return memcmp(this, &o, sizeof *this) < 0; }
 };
 template <typename Make>
-static Plan riding_plan(int layout, const GemmArgs *a, int count, int ride, Make make)
+static Plan riding_plan(int layout, const GemmArgs *a, int count, bool cuts, Make make)
 {
     static PlanStore<RidingKey> plans;
     RidingKey key;
     memset(&key, 0, sizeof key);
-    key.layout = layout; key.count = count; key.ride = ride; key.takes = 1;
+    key.layout = layout; key.count = count; key.cuts = cuts; key.takes = 1;
     for (int q = 0; q < count; ++q) {
         const int d[6] = {a[q].M, a[q].N, a[q].K, a[q].epi, a[q].c_is_f32 + 2 * may_split_k(a[q]), a[q].cu_share};
         memcpy(key.dims[q], d, sizeof d);
@@ -675,29 +676,29 @@ static void riding_caps(const int *layouts, const GemmArgs *a, int count, int *c
     }
 }
 
-// The plan of the tall and the 64 x 128 tiles, which decides where the launch cuts its sums (keeps_cuts), whatever rides in it
+// The plan of the tall and the 64 x 128 tiles, which decides where the launch cuts its sums (keeps_cuts)
 static Plan riding_cuts(int layout, const int *layouts, const GemmArgs *a, int count)
 {
-    return riding_plan(layout, a, count, -1, [&](const RidingKey &) {
+    return riding_plan(layout, a, count, true, [&](const RidingKey &) {
         int cap[PP_MAX_GROUP];
         riding_caps(layouts, a, count, cap);
         return plan_group(layout, a, count, nullptr, 1, cap, false);
     });
 }
 
-static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count, double ride_bytes)
+static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int count)
 {
-    return riding_plan(layout, a, count, (int)(ride_bytes / (1 << 16)), [&](const RidingKey &key) {
+    return riding_plan(layout, a, count, false, [&](const RidingKey &key) {
         const Plan ref = riding_cuts(layout, layouts, a, count);
         Plan best = ref, duo;
-        double tall = launch_us(a, best.bm, best.ks, best.order, count, ride_bytes), us = 0.0;
+        double tall = launch_us(a, best.bm, best.ks, best.order, count), us = 0.0;
         int cap[PP_MAX_GROUP];
         riding_caps(layouts, a, count, cap);
         const Plan square = plan_group(layout, a, count, nullptr, 1, cap);
-        const double square_us = launch_us(a, square.bm, square.ks, square.order, count, ride_bytes);
+        const double square_us = launch_us(a, square.bm, square.ks, square.order, count);
         const bool with_square = square_us < 0.95 * tall; // (a tie by the estimate came out 1-2 % slower)
         if (with_square) best = square, tall = square_us;
-        if (key.takes && plan_duo(layouts, a, count, ref, &duo, ride_bytes, &us)) {
+        if (key.takes && plan_duo(layouts, a, count, ref, &duo, &us)) {
             long tiles = 0;
             for (int q = 0; q < count; ++q) tiles += (long)tiles_m_of(a[q], duo.bm[q]) * tiles_n_of(a[q], duo.bm[q]) * duo.ks[q];
             // (short launches come out better than their estimate, 128 x 128 tiles one to a unit in them do not; long ones come out
@@ -709,17 +710,10 @@ static Plan plan_riding(int layout, const int *layouts, const GemmArgs *a, int c
     });
 }
 
-static double ride_traffic(const Riders &r)
-{
-    double bytes = 0.0;
-    for (int i = 0; i < r.count; ++i) bytes += 2.0 * (double)r.seg[i].bytes * ((r.seg[i].out ? 1 : 0) + (r.seg[i].in ? 1 : 0));
-    return bytes;
-}
-
-void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out, int *ksplit_out)
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, int *tiles_out, int *ksplit_out)
 {
     if (count < 1 || count > PP_MAX_GROUP) return;
-    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count, ride_bytes);
+    const Plan pl = plan_riding(common_layout(layouts, count), layouts, a, count);
     for (int q = 0; q < count; ++q) {
         tiles_out[q] = pl.bm[q];
         if (ksplit_out) ksplit_out[q] = pl.ks[q];
@@ -751,7 +745,7 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
     const bool wide = std::all_of(r.sum, r.sum + r.sums, [](const RideSum &q) { return colsum_wide(q.Y, q.ld, q.cols); });
     const bool one_each = lay == LAY_NN_TN && !std::all_of(a, a + count, gemm_epilogue_vec_ok);
     if (!one_each && (r.sums == 0 || (wide && takes_sums(lay))))
-        return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count, ride_traffic(r)), &r, s, nullptr);
+        return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &r, s, nullptr);
     Riders moves = r, sums = r;
     moves.sums = sums.count = 0;
     if (!wide || !takes_sums(lay)) {
@@ -759,15 +753,14 @@ hipError_t launch_gemm_bf16_pp_riding(const int *layouts_in, const GemmArgs *a_i
         if (e != hipSuccess) return e;
         sums.sums = 0;
     }
-    if (!one_each) return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count, ride_traffic(moves)), &moves, s, nullptr);
+    if (!one_each) return launch_group(lay, layouts, a, count, plan_riding(lay, layouts, a, count), &moves, s, nullptr);
     // one launch per layout, the transfers in the first and the sums in the second
     for (int one : {LAY_NN, LAY_TN}) {
         GemmArgs b[PP_MAX_GROUP];
         int lays[PP_MAX_GROUP], n = 0;
         for (int q = 0; q < count; ++q)
             if (layouts[q] == one) lays[n] = one, b[n++] = a[q];
-        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n, one == LAY_NN ? ride_traffic(moves) : 0.0),
-                                          one == LAY_NN ? &moves : &sums, s, nullptr);
+        const hipError_t e = launch_group(one, nullptr, b, n, plan_riding(one, lays, b, n), one == LAY_NN ? &moves : &sums, s, nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

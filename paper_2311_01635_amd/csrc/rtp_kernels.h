@@ -109,12 +109,11 @@ struct Riders {
 // type.  Nothing to compute: the transfers alone.  hipErrorInvalidValue as launch_gemm_bf16_pp_group, before anything is launched.
 // cu_share: what a launch of the problem's own on the streams would say (the launch here has the machine to itself).
 hipError_t launch_gemm_bf16_pp_riding(const int *layouts, const GemmArgs *a, int count, const Riders &r, hipStream_t s);
-// Whether that launch cuts a problem's K loop, whatever rides in it: 1 no, 2 in two chunks, more: in two to as many, as the
-// tiles have it that the transfers make it take.  (A launch that goes out layout by layout is planned layout by layout.)
+// Whether that launch cuts a problem's K loop: 1 no, 2 in two chunks, more: in two to as many.  (A launch that goes out layout by
+// layout is planned layout by layout.)
 void gemm_bf16_pp_plan_riding(const int *layouts, const GemmArgs *a, int count, int *ksplit_out);
-// the tiles it would use, heights of gemm_pp_kernel or the codes above, and its K splits (may be null); ride_bytes: what its
-// transfers read and write
-void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, double ride_bytes, int *tiles_out, int *ksplit_out);
+// the tiles it would use, heights of gemm_pp_kernel or the codes above, and its K splits (may be null)
+void gemm_bf16_pp_riding_tiles(const int *layouts, const GemmArgs *a, int count, int *tiles_out, int *ksplit_out);
 // the transfers as a launch of their own
 hipError_t launch_riders(const Riders &r, hipStream_t s);
 

@@ -49,14 +49,13 @@ def riding_split(M, N, K, dx, cu_share=2):
     return ks[1]
 
 
-_riding_tiles = getattr(B.lib, "_ZN3rtp25gemm_bf16_pp_riding_tilesEPKiPKNS_8GemmArgsEidPiS5_")
+_riding_tiles = getattr(B.lib, "_ZN3rtp25gemm_bf16_pp_riding_tilesEPKiPKNS_8GemmArgsEiPiS5_")
 _riding_tiles.restype = None
-_riding_tiles.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.c_double, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+_riding_tiles.argtypes = [C.POINTER(C.c_int), C.POINTER(GemmArgs), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
 
 
-def riding_plan(group, ride_bytes=0.0, ldc_pad=0):
-    """(tile, K split) of each problem of a riding launch of (layout, M, N, K, epi) problems whose transfers read and write
-    `ride_bytes`."""
+def riding_plan(group, ldc_pad=0):
+    """(tile, K split) of each problem of a riding launch of (layout, M, N, K, epi) problems."""
     args = (GemmArgs * len(group))()
     for a, (layout, M, N, K, epi) in zip(args, group):
         sum_ = layout == B.LAYOUT_TN and epi == EPI_ACC_ADD  # a weight gradient: fp32, in place
@@ -64,13 +63,13 @@ def riding_plan(group, ride_bytes=0.0, ldc_pad=0):
         a.ldc = a.ldws = (a.half if epi == EPI_SWIGLU_FWD else N) + ldc_pad
         a.ldaux, a.cu_share, a.c_is_f32 = 2 * N, 2, int(sum_)
     tiles, ks = (C.c_int * len(group))(), (C.c_int * len(group))()
-    _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), ride_bytes, tiles, ks)
+    _riding_tiles((C.c_int * len(group))(*[g[0] for g in group]), args, len(group), tiles, ks)
     return list(zip(tiles, ks))
 
 
-def riding_tiles(group, ride_bytes=0.0, ldc_pad=0):
+def riding_tiles(group, ldc_pad=0):
     """Its tiles alone."""
-    return [tile for tile, _ in riding_plan(group, ride_bytes, ldc_pad)]
+    return [tile for tile, _ in riding_plan(group, ldc_pad)]
 
 
 SMALL_128X128, DUO_128X128, DUO_64X128, DUO_64X64 = 1000, 1024, 1025, 1026
