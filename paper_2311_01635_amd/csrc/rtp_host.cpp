@@ -246,6 +246,7 @@ struct rtp_ring {
     int base_idx = 0;    // weight buffer index at step 0 of the open pass
     int rotations = 0;   // rotate_step calls in the open pass
     int executed = 0;    // blocking mode: rotations already carried out
+    int64_t tokens = 0;  // of the ring's widest linear when the pass began (an expert layer's ring has none)
     bool may_carry = true; // (a schedule that moves the shards itself on the other streams says no before it begins)
     bool rode = false;   // what `carry` said in the pass that is open, or was last (rtp_ring_rides)
     bool carry = false;  // the open pass runs on the compute stream alone, its transfers riding in the GEMM launches
@@ -306,6 +307,8 @@ static rtp_status ensure_events(rtp_ring *r)
     return RTP_OK;
 }
 
+constexpr int64_t COPY_SHORT_TOKENS = 2048;
+
 // done: an event recorded on `s` behind the transfer; a copy kernel carries it as its completion signal (one host
 // call and one packet in the queue less than a record of its own).  A dry ring has no events.
 static rtp_status copy_async(rtp_ring *r, void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr)
@@ -321,8 +324,14 @@ static rtp_status copy_async(rtp_ring *r, void *dst, const void *src, size_t byt
         HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
         if (done) HIP_TRY(hipEventRecord(done, s));
     } else {
-        // (on the compute stream a copy runs between the kernels, on the stage stream beside them)
-        HIP_TRY((s == r->cs() ? launch_copy_alone : launch_copy)(dst, src, bytes, s, done));
+        // On the compute stream a copy runs between the kernels, on the stage stream beside them: in short pieces while the
+        // transfers bound the step, in long ones past 2048 tokens, where the GEMMs do.  us a training step, long -> short: 512
+        // tokens 5632 -> 16392 gated over 3 2700 -> 2532, large unit (2048 tokens) 8188 -> 8067, expert unit 16026 -> 15574;
+        // 3925 tokens 3520 -> 12928 gated over 8 3906 -> 4063, 4096 tokens 4544 -> 16608 over 6 4587 -> 4706 and 3520 -> 12608 over
+        // 8 3132 -> 3336, 5120 tokens 3136 -> 9360 over 6 2761 -> 2709.  41 steps of more than 2048 tokens: 0.8 % for the long
+        // ones on the mean, and none with them more than 1.1 % behind what it took before there were short ones (3.2 % with those).
+        const bool beside = s != r->cs();
+        HIP_TRY((!beside ? launch_copy_alone : r->tokens > COPY_SHORT_TOKENS ? launch_copy_long : launch_copy)(dst, src, bytes, s, done));
     }
     return RTP_OK;
 }
@@ -664,14 +673,19 @@ extern "C" int rtp_pass_rides(const rtp_ring_desc *d, int64_t T, rtp_pass pass)
     return d->w_bytes + d->g_bytes <= CARRY_BWD_BYTES && work <= CARRY_BWD_WORK;
 }
 
+static int64_t ring_tokens(const rtp_ring *r)
+{
+    int64_t T = 0;
+    for (const rtp_linear *l : r->linears) T = std::max(T, l->d.T);
+    return T;
+}
+
 static bool ring_carries(const rtp_ring *r, rtp_pass pass)
 {
     if (r->dry || r->linears.empty()) return false; // (no layers: no launch to ride in)
     // the test delays hold the other streams back: those passes run on them
     if (r->delay_stage_ticks > 0 || r->delay_aux_ticks > 0 || r->delay_compute_ticks > 0) return false;
-    int64_t T = 0;
-    for (const rtp_linear *l : r->linears) T = std::max(T, l->d.T);
-    return rtp_pass_rides(&r->d, T, pass) != 0;
+    return rtp_pass_rides(&r->d, ring_tokens(r), pass) != 0;
 }
 
 extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
@@ -687,6 +701,7 @@ extern "C" rtp_status rtp_ring_begin(rtp_ring *r, rtp_pass pass)
                     (rank + 1) % n, r->resident);
     RTP_TRY(refuse_capture(r, "rtp_ring_begin"));
     RTP_TRY(ensure_events(r));
+    r->tokens = ring_tokens(r);
     r->carry = may_carry && ring_carries(r, pass);
     r->pend.count = r->pend.sums = 0;
     RTP_TRY(begin_join(r));

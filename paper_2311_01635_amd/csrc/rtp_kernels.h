@@ -128,8 +128,9 @@ hipError_t launch_gemm_f32_riding(const int *layouts, const GemmArgs *a, int cou
 hipError_t launch_act_f32(int kind, const float *pre, int64_t ldpre, const float *in, int64_t ldin,
                           float *out, int64_t ldout, int rows, int cols, int half, hipStream_t s);
 
-// device-to-device staging copy with a bounded number of workgroups
+// device-to-device staging copy beside other kernels, in pieces of 32 KB a workgroup; _long: of 64 KB
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr);
+hipError_t launch_copy_long(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr);
 // the same where nothing else runs beside the copy
 hipError_t launch_copy_alone(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done = nullptr);
 // up to COPY_MAX_SEGS copies that do not overlap one another, as one launch (no order among them)

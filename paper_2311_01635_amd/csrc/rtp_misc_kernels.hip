@@ -330,16 +330,17 @@ hipError_t launch_act_f32(int kind, const float *pre, int64_t ldpre, const float
 }
 
 // ---- staging copy ---------------------------------------------------------------------
-// Each workgroup moves one 32 KB piece with 16-byte accesses and exits, so the
+// Each workgroup moves one piece of 32 or 64 KB with 16-byte accesses and exits, so the
 // copy slips into whatever wave slots the GEMM running beside it leaves free
 // instead of holding compute units for the whole transfer.  A whole piece is moved without a bounds test per unit:
 // behind one, the compiler waits ahead of every store for all stores before it (Llama-shaped unit's training step
-// against one reference on one box: 1.004 -> 1.027 x as fast).  Pieces of 64 KB -> 32 KB -> 16 KB beside the GEMMs, us a
-// training step: large unit 8122 -> 7953 -> 8032, expert unit 15973 -> 15792 -> 15709, Llama-shaped 3999 -> 3993 -> 3999;
-// alone, 541 MB 225 -> 183 -> 189.
+// against one reference on one box: 1.004 -> 1.027 x as fast).
+// Pieces of 32 KB go faster, those of 64 KB disturb the GEMMs less: short ones where the transfers bound the step, long ones
+// where many tokens do (copy_async has the line and what it measured).  Alone, 541 MB with pieces of 64, 32 and 16 KB 225, 183
+// and 189 us.
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 constexpr int COPY_THREADS = 256;
-constexpr int COPY_PER_THREAD = 8; // x 16 bytes
+constexpr int COPY_PER_THREAD = 8, COPY_LONG_PER_THREAD = 16; // x 16 bytes
 
 // the units of a thread from `base` on
 template <int PER>
@@ -369,6 +370,10 @@ __device__ __forceinline__ void copy_piece(u32x4 *__restrict__ dst, const u32x4 
 __global__ __launch_bounds__(COPY_THREADS) void copy_kernel(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, int64_t n16)
 {
     copy_piece<COPY_PER_THREAD>(dst, src, n16);
+}
+__global__ __launch_bounds__(COPY_THREADS) void copy_long_kernel(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, int64_t n16)
+{
+    copy_piece<COPY_LONG_PER_THREAD>(dst, src, n16);
 }
 
 // The same for a copy that nothing runs beside: pieces of 16 KB, so that some workgroups read while others write.  us alone,
@@ -401,6 +406,11 @@ static hipError_t launch_copy_pieces(void (*kernel)(u32x4 *, const u32x4 *, int6
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done)
 {
     return launch_copy_pieces(copy_kernel, COPY_PER_THREAD, dst, src, bytes, s, done);
+}
+
+hipError_t launch_copy_long(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done)
+{
+    return launch_copy_pieces(copy_long_kernel, COPY_LONG_PER_THREAD, dst, src, bytes, s, done);
 }
 
 hipError_t launch_copy_alone(void *dst, const void *src, size_t bytes, hipStream_t s, hipEvent_t done)
