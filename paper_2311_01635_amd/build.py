@@ -40,6 +40,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
                 # loops start on an instruction-cache line: left to chance, the same instructions ran up to 10 % slower
                 # (256-high tile, 2048 x 1792 x 8192 NN: 137 us starting 28 bytes into a line, 125 us on one)
                 cmd.insert(-4, "-falign-loops=64")
+                # ... which leaves out loops that are entered in their middle: their first block follows a jump.  (256-high tile of
+                # the TN kernel, 4096 x 1376 x 4096: 78.5 us where they fell on a line, 85.0 where the 128 x 128 tile's code had
+                # moved them, 80.4 so; 768 x 6144 x 8192 97.3, 103.0, 98.0)
+                cmd[-4:-4] = ["-mllvm", "-align-all-nofallthru-blocks=6"]
             if verbose:
                 print(" ".join(cmd), flush=True)
             res = subprocess.run(cmd, check=True, stderr=subprocess.PIPE, text=True)
