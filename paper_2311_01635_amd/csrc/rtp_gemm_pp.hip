@@ -307,6 +307,16 @@ static bool keeps_cuts(const GemmArgs &a, int ref_tile, int ref_ks, int tile, in
     return chunks == ref && (chunks == 1 || each * tile_bk(tile, lay) == ref_each * tile_bk(ref_tile, lay));
 }
 
+// The 128 x 128 tile in launches that it fills the machine with more than one and a half times, which the estimate above prices too low:
+// products alone, tall tiles -> 128 x 128: 1.8 to 2 times 0.83 to 1.1 times as fast, 2.8 to 3 times 0.76 to 0.85 (3480 x 3448 x
+// 5440 121 -> 150 us), 4.1 to 4.3 times 0.81 to 0.95 (four times exactly 1.1, the one exception); up to 1.3 times 0.98 to 1.6.  Training steps of
+// units with such shards, us: 6488 tokens 2816 -> 7488 over 8 2825 -> 3129, 6096 tokens 1152 -> 3456 over 3 578 -> 676; at 1.34 to
+// 1.5 times, forward, 992 tokens 6912 -> 21568 gated over 8 1748 -> 1561 and 2008 tokens 3008 -> 5440 over 8 500 -> 442.
+static bool crowded(const GemmArgs &a, int chunks)
+{
+    return 2L * tiles_m_of(a, SMALL_128X128) * tiles_n_of(a, SMALL_128X128) * chunks > 3L * compute_units();
+}
+
 // max_split (may be null): chunks of K each problem may be cut in; square: whether 128 x 128 tiles are considered
 static Plan plan_group(int layout, const GemmArgs *given, int count, const int *bm_override, int cu_share, const int *max_split = nullptr,
                        bool square = true)
@@ -371,6 +381,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
             for (int k = 0; k < (split_ok ? 6 : 1); ++k) {
                 if (splits[k] > cap[q]) break;
                 if (splits[k] > 1 && (a[q].K + 31) / 32 / splits[k] < (is_small(heights[h]) ? 8 : 4)) break; // keep at least four sub-tiles per chunk
+                if (forced == 0 && heights[h] == SMALL_128X128 && crowded(a[q], splits[k])) continue;
                 if (square && !keeps_cuts(a[q], ref.bm[q], ref.ks[q], heights[h], splits[k], layout)) continue;
                 obm[q][nopt[q]] = heights[h];
                 oks[q][nopt[q]] = splits[k];

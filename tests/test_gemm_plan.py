@@ -172,6 +172,21 @@ def test_which_kernel_a_riding_launch_runs_on():
         assert all(t in duo for t in G.riding_tiles([(B.LAYOUT_NN, 1024, 384, 768, last), (B.LAYOUT_TN, 768, 384, 1024, G.EPI_ACC_LAST)]))
 
 
+def test_square_tiles_do_not_crowd_the_machine():
+    """128 x 128 tiles are for problems that they fill the 256 compute units with one and a half times at most."""
+    for layout, M, N, K, epi in ((B.LAYOUT_NN, 1160, 9600, 6176, G.EPI_STORE), (B.LAYOUT_TN, 1192, 9512, 1760, G.EPI_ACC_ADD),
+                                 (B.LAYOUT_TN, 3480, 3448, 5440, G.EPI_STORE), (B.LAYOUT_NN, 6664, 1144, 2912, G.EPI_STORE)):
+        assert G.plan(layout, M, N, K, epi)[0] != SMALL_128X128, (layout, M, N, K)
+    assert G.plan(B.LAYOUT_TN, 1784, 1320, 2176)[0] == G.plan(B.LAYOUT_NT, 936, 4056, 1728)[0] == SMALL_128X128
+    assert SMALL_128X128 not in G.riding_tiles([(B.LAYOUT_NN, 6488, 936, 2816, G.EPI_GELU_ERF_BWD), (B.LAYOUT_TN, 2816, 936, 6488, G.EPI_ACC_LAST)])[:1]
+    rng = random.Random(29)
+    for _ in range(400):
+        M, N, K = 8 * rng.randint(8, 1000), 8 * rng.randint(8, 1200), 32 * rng.randint(2, 200)
+        for layout, epi in ((B.LAYOUT_NT, G.EPI_STORE), (B.LAYOUT_TN, G.EPI_ACC_ADD)):
+            tile, ks = G.plan(layout, M, N, K, epi)
+            assert tile != SMALL_128X128 or -(-M // 128) * -(-N // 128) * ks <= 384, (layout, M, N, K)
+
+
 def test_a_gated_prompt_keeps_a_compute_unit_to_a_tile():
     """Pairs of gate and up columns have no 64 x 64 tile: with the wider ones the forward pass of these units (tokens, inputs,
     units of a shard) takes up to a fifth longer, whatever rides in its launches."""
