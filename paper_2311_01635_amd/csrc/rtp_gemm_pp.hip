@@ -100,9 +100,9 @@ static double epilogue_steps(int epi, int c_is_f32)
     }
 }
 
-// The 64 x 128 tile: a fixed part and a part per 64 K (the 128 x 128 one half a unit more and 1.45 times; beside another GEMM 1.6
-// times, with 1.45 a step of three 4864-wide shards on the streams took 2 % longer).  Launches alone (us, launch included): one round 512 x 2752 x 4096
-// 21.0, two rounds 2048 x 1792 x 8192 75 and 992 x 4096 x 14336 139, three rounds 8192 x 768 x 2048 37.3 and
+// The 64 x 128 tile: a fixed part and a part per 64 K (the 128 x 128 one half a unit more and 1.45 times; beside another GEMM
+// 1.6 times, with 1.45 a step of three 4864-wide shards on the streams took 2 % longer).  Launches alone (us, launch
+// included): one round 512 x 2752 x 4096 21.0, two rounds 2048 x 1792 x 8192 75 and 992 x 4096 x 14336 139, three rounds 8192 x 768 x 2048 37.3 and
 // 8192 x 768 x 384 16.6 (the 128-high tile: 50.4, 91, 168, 31.6, 11.6) give 1.5 and 0.44.  Beside another GEMM both are
 // larger, as it fetches twice the bytes per flop: with 1.5 and 0.44 there too the ragged Llama-shaped step took 3.80 ms
 // and the expert layer's 17.15, with 3.0 and 0.5 3.73 and 17.00.
@@ -244,7 +244,7 @@ static double makespan(const GemmArgs *a, const int *bm, const int *ks, const in
 }
 
 // Heights, K splits and launch order (longest tiles first) of a group.  Every combination is tried
-// (4 tiles, and up to 6 split factors for a problem that may be split and is short of tiles);
+// (5 tiles, and up to 6 split factors for a problem that may be split and is short of tiles);
 // the estimate above picks.  Plans are remembered per shape.
 struct PlanKey {
     int layout, count, cu_share, square;
@@ -307,11 +307,11 @@ static bool keeps_cuts(const GemmArgs &a, int ref_tile, int ref_ks, int tile, in
     return chunks == ref && (chunks == 1 || each * tile_bk(tile, lay) == ref_each * tile_bk(ref_tile, lay));
 }
 
-// The 128 x 128 tile in launches that it fills the machine with more than one and a half times, which the estimate above prices too low:
-// products alone, tall tiles -> 128 x 128: 1.8 to 2 times 0.83 to 1.1 times as fast, 2.8 to 3 times 0.76 to 0.85 (3480 x 3448 x
-// 5440 121 -> 150 us), 4.1 to 4.3 times 0.81 to 0.95 (four times exactly 1.1, the one exception); up to 1.3 times 0.98 to 1.6.  Training steps of
-// units with such shards, us: 6488 tokens 2816 -> 7488 over 8 2825 -> 3129, 6096 tokens 1152 -> 3456 over 3 578 -> 676; at 1.34 to
-// 1.5 times, forward, 992 tokens 6912 -> 21568 gated over 8 1748 -> 1561 and 2008 tokens 3008 -> 5440 over 8 500 -> 442.
+// Whether 128 x 128 tiles would fill the machine more than one and a half times, where the estimate above prices them too low.
+// Products alone, the other tiles -> these: at 1.8 to 2 fillings 0.83 to 1.1 times as fast, at 2.8 to 3 0.76 to 0.85 (3480 x
+// 3448 x 5440 121 -> 150 us), at 4.1 to 4.3 0.81 to 0.95 (at just under four 1.1, given up); up to 1.3 0.98 to 1.6.  Units with such
+// shards, us: training, 6488 tokens 2816 -> 7488 over 8 2825 -> 3129, 6096 tokens 1152 -> 3456 over 3 578 -> 676; at 1.34 to 1.5,
+// forward, 992 tokens 6912 -> 21568 gated over 8 1748 -> 1561, 2008 tokens 3008 -> 5440 gated over 8 500 -> 442.
 static bool crowded(const GemmArgs &a, int chunks)
 {
     return 2L * tiles_m_of(a, SMALL_128X128) * tiles_n_of(a, SMALL_128X128) * chunks > 3L * compute_units();
@@ -431,9 +431,10 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
 // (16 to 8192 tokens, shards of 64 to 1536) and of 4096^3 products: within 7 (64 x 64) to 15 % (192 x 256).  A compute unit with
 // one workgroup of the duo kernel waits for its operands between the sub-tiles of the two wider tiles (per_unit: tiles a
 // unit).
-// Passes of 75 units and layers of all sizes, the tall and the 64 x 128 tile everywhere -> the duo kernel where this estimate
-// prefers it: 0.92 to 1.39 times as fast, geometric mean 1.097 (the duo kernel everywhere 1.075, the better one known
-// beforehand 1.11).  47 more, the 128 x 128 tile of gemm_pp_kernel beside those: 1.019, units of 1000 to 5000 tokens 1.03 to 1.17.
+// Passes, the tall and the 64 x 128 tile everywhere -> all of them where this estimate prefers them: 50 drawn units and layers
+// 0.95 to 1.38 times as fast, geometric mean 1.11; 80 forward passes of 96 to 4096 tokens 1.15, 36 of 16 to 256 tokens
+// with shards of 40 to 180 MB 1.06, one of them behind (68 tokens, 8192 -> 22272 over 3, 280 -> 304: 232 tiles of 64 x 64 that
+// read 122 MB of weights leave the transfers no compute unit).
 struct TileTime {
     double once, fixed, step, step_full;
 };

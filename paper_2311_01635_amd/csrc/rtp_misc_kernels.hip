@@ -524,8 +524,9 @@ hipError_t launch_riders(const Riders &r, hipStream_t s)
     return hipGetLastError();
 }
 
-// Bound: HBM writes.  A thread stores one unit, past the caches, and its workgroup of 4 KB is done.  us, 4096 workgroups that walk the buffer -> so: 16 MB 5.3 -> 4.5, 90 MB 15.1 ->
-// 14.5, 541 MB 122 -> 86, 1.9 GB 488 -> 296, 5.6 GB 1331 -> 879 (6.7 TB/s); 16 KB a workgroup 984, 64 KB 1040.
+// Bound: HBM writes.  A thread stores one unit, past the caches, and its workgroup of 4 KB is done.  us, 4096 workgroups that
+// walk the buffer -> so: 16 MB 5.3 -> 4.5, 90 MB 15.1 -> 14.5, 541 MB 122 -> 86, 1.9 GB 488 -> 296, 5.64 GB 1331 -> 879 (6.4
+// TB/s); 16 KB a workgroup 984, 64 KB 1040.
 __global__ __launch_bounds__(256) void fill_zero_kernel(u32x4 *dst, int64_t n16)
 {
     const u32x4 z = {0u, 0u, 0u, 0u};
