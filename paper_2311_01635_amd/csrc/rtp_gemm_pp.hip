@@ -432,7 +432,7 @@ static Plan plan_group(int layout, const GemmArgs *given, int count, const int *
 // one workgroup of the duo kernel waits for its operands between the sub-tiles of the two wider tiles (per_unit: tiles a
 // unit).
 // Passes, the tall and the 64 x 128 tile everywhere -> all of them where this estimate prefers them: 50 drawn units and layers
-// 0.95 to 1.38 times as fast, geometric mean 1.11; 80 forward passes of 96 to 4096 tokens 1.15, 36 of 16 to 256 tokens
+// 0.95 to 1.37 times as fast, geometric mean 1.09; 80 forward passes of 96 to 4096 tokens 1.17, 36 of 16 to 256 tokens
 // with shards of 40 to 180 MB 1.06, one of them behind (68 tokens, 8192 -> 22272 over 3, 280 -> 304: 232 tiles of 64 x 64 that
 // read 122 MB of weights leave the transfers no compute unit).
 struct TileTime {
